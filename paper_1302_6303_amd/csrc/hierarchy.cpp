@@ -67,11 +67,30 @@ inline int64_t intersect(const int32_t alo[3], const int32_t ahi[3],
 
 }  // namespace
 
-int32_t default_zchunk(const int32_t n[3], int32_t variant) {
-    // staged planes: long runs amortise the first plane's staging and its
-    // repeated z face; register-marching: short runs keep enough waves
-    // resident to hide load latency
-    if (variant == 3) return 16;
+int32_t default_zchunk(const Tables& t, int32_t b, int32_t variant) {
+    if (variant == 3) {
+        // Staged planes: a tile's planes are a serial chain of about 1.8 us
+        // each (stage, barrier, faces, barrier), while every tile stages its
+        // first plane and evaluates its lowest z face once more than a longer
+        // one would.  So the chunk is the shortest power of two that leaves
+        // the launch at most about ten workgroups per CU (256 CUs), up to 16.
+        // Measured residual and Jacobian action at the chunk chosen and at
+        // 16, us: 16^3 6 and 28, 32^3 6 and 29; 64^3 8 and 28; six ragged
+        // boxes of 0.75 M cells (2) 16 / 23 and 32 / 40; 128^3 (4) 35 / 53
+        // and 42 / 58; 160^3 (8) 72 / 110 and 77 / 111; 51 patches of 1.1 M
+        // cells (2) 47 / 76 and 65 / 93; 20 M cells (16) 291 / 366 against
+        // 311 / 418 at 4.
+        constexpr int64_t kMostTiles = 2700;
+        int64_t n = 0;
+        for (const PatchInfo& p : t.patches)
+            n += (int64_t)p.n[2] * ((p.n[0] * p.n[1] + kStageCells - 1) / kStageCells);
+        int32_t kc = 1;
+        while (kc < 16 && n > kMostTiles * kc) kc *= 2;
+        return kc;
+    }
+    // register-marching: short runs keep enough waves resident to hide load
+    // latency
+    const int32_t* n = t.patches[b].n;
     return n[0] * n[1] >= 4096 ? 4 : 8;
 }
 
@@ -547,7 +566,7 @@ nrd_status build_tables(const nrd_problem* probs, int32_t nprob,
     t.level_tile0[t.nlev] = (int32_t)t.tiles.size();
     {
         std::vector<int32_t> kc(nbox);
-        for (int b = 0; b < nbox; ++b) kc[b] = default_zchunk(t.patches[b].n, 1);
+        for (int b = 0; b < nbox; ++b) kc[b] = default_zchunk(t, b, 1);
         build_planes(t, kc, 256);   // default stencil variant: plane marching
     }
     t.prob_vtile0.assign(nprob + 1, 0);

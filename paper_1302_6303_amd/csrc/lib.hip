@@ -1679,19 +1679,24 @@ nrd_status nrd_hierarchy_create(const nrd_problem* probs, int32_t nprob, const n
         }
         if (h->opt.stencil >= 1 || h->opt.zchunk > 0) {
             std::vector<int32_t> kc(h->t.nbox);
-            for (int b = 0; b < h->t.nbox; ++b)
-                kc[b] = h->opt.zchunk > 0 ? h->opt.zchunk
-                                          : default_zchunk(h->t.patches[b].n, h->opt.stencil);
+            auto chunks = [&](int variant) {
+                if (h->opt.zchunk > 0) {
+                    std::fill(kc.begin(), kc.end(), h->opt.zchunk);
+                } else if (variant == 3) {
+                    std::fill(kc.begin(), kc.end(), default_zchunk(h->t, 0, variant));
+                } else {
+                    for (int b = 0; b < h->t.nbox; ++b) kc[b] = default_zchunk(h->t, b, variant);
+                }
+            };
             int st = h->opt.stencil;
+            chunks(st);
             bool ok = build_planes(h->t, kc, st == 2 ? 4 * 63 : (st == 3 ? kStageCells : 256),
                                    st == 3 ? kStageLen : 0);
             if (!ok && st == 3) {
                 // rows too wide for the staged slices (x extent above about
                 // 250): the plane-marching variant, same values, any width
                 st = h->opt.stencil = 1;
-                for (int b = 0; b < h->t.nbox; ++b)
-                    kc[b] = h->opt.zchunk > 0 ? h->opt.zchunk
-                                              : default_zchunk(h->t.patches[b].n, st);
+                chunks(st);
                 ok = build_planes(h->t, kc, 256, 0);
             }
             if (!ok) {
@@ -1993,7 +1998,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
     const int32_t run0 = var == 2 ? 4 * 63 : (var == 3 ? kStageCells : 256);
     std::vector<std::pair<int32_t, int32_t>> cand;           // (planes, run)
     if (var == 3) {
-        for (int kc : {4, 8, 16, 32}) cand.push_back({kc, kStageCells});
+        for (int kc : {1, 2, 4, 8, 16, 32}) cand.push_back({kc, kStageCells});
     } else {
         for (int kc : {2, 4, 8, 16}) cand.push_back({kc, run0});
     }
@@ -2031,10 +2036,12 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
     }
     // current shapes: cached choices, else the defaults
     std::vector<int32_t> kc(t.nbox), run(t.nbox);
+    const int32_t staged = default_zchunk(t, 0, 3);
     for (auto& kv : cls) {
         auto it = pick.find(kv.first);
         for (int b : kv.second) {
-            kc[b] = it != pick.end() ? it->second.first : default_zchunk(t.patches[b].n, var);
+            kc[b] = it != pick.end() ? it->second.first
+                                     : (var == 3 ? staged : default_zchunk(t, b, var));
             run[b] = it != pick.end() ? it->second.second : run0;
         }
     }

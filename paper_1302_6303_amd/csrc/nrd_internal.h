@@ -181,8 +181,9 @@ constexpr int32_t kBottomBand = 26;
 constexpr int32_t kStageCells = 256;
 constexpr int32_t kStageLen = 512;
 
-// Plane-marching tiles: planes per tile (z chunk) of each patch.
-int32_t default_zchunk(const int32_t n[3], int32_t variant);
+// Plane-marching tiles: planes per tile (z chunk) of patch b (staged planes:
+// the same for every patch of the hierarchy).
+int32_t default_zchunk(const Tables& t, int32_t b, int32_t variant);
 // Length of the ghosted-plane slice that covers cells [s0, s0 + cnt) of a
 // plane of patch p and their x / y neighbours.
 int32_t staged_len(const PatchInfo& p, int32_t s0, int32_t cnt);
