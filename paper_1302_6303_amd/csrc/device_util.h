@@ -40,4 +40,13 @@ __device__ __forceinline__ int native_index(const PatchInfo& p, int i, int j, in
     return p.off + (i + 1) + p.sy * (j + 1) + p.sz * (k + 1);
 }
 
+// D_T = kappa T_f^(5/2) of the face between cells of temperatures Ta, Tb
+// (symmetric in Ta, Tb); the sweeps over colour-split storage recompute it
+// from T with this same expression, so they see the snapshot's values.
+template <typename PT>
+__device__ __forceinline__ PT face_DT(PT Ta, PT Tb, PT kappa) {
+    const PT Tf = PT(0.5) * (Ta + Tb);
+    return kappa * Tf * Tf * sqrt(Tf);
+}
+
 }  // namespace nrd

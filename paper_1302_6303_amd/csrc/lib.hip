@@ -104,8 +104,7 @@ struct nrd_hierarchy final : public Clock {
         size_t patches, tiles, stiles, vtiles, prob_vtile0, gcopy, gcf, sib, sync[kMaxLev], rfaces,
             rcells, cfrows, cfsrc, ctype, shadows, shadow_src, coff, ps, active, amap;
         size_t mg_box[kMaxMG], mg_tiles[kMaxMG], mg_box_of[kMaxMG], mg_smooth[kMaxMG],
-            mg_bprobs[kMaxMG], mg_bboxes[kMaxMG], bot_probs, bot_boxes, bot_grid, bottom_off,
-            Lbuf, Xbuf, mg_l0map, ltiles;
+            tails, Xbuf, mg_l0map, ltiles;
         size_t z, z3, cur, prev, udot, bvec, x, F, s, w, tmp, tmp2, gzn, V, Z, pred;
         size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f, pc_shadow;
         size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG];
@@ -256,23 +255,17 @@ static void layout(nrd_hierarchy* h) {
         }
         o.mg_box_of[g] = b.take(sizeof(int32_t) * nprob);
         o.mg_smooth[g] = b.take(sizeof(Tile) * (t.tiles.size() + 1));
-        o.mg_bprobs[g] = b.take(sizeof(int32_t) * nprob);
-        o.mg_bboxes[g] = b.take(sizeof(int32_t) * nprob);
     }
     // per native cell of the first multigrid grid: the level-0 patch that
     // holds its eight children
     o.mg_l0map = b.take(sizeof(int32_t) * std::max<int64_t>(1, G >= 1 ? t.mg[1].len : 1));
-    o.bot_probs = b.take(sizeof(int32_t) * nprob);
-    o.bot_boxes = b.take(sizeof(int32_t) * nprob);
-    o.bot_grid = b.take(sizeof(int32_t) * nprob);
-    o.bottom_off = b.take(sizeof(int64_t) * nprob);
+    o.tails = b.take(sizeof(TailEntry) * nprob);
     int64_t bsum = 0;
     for (int p = 0; p < nprob; ++p) {
         int64_t nb = 1;
         for (int d = 0; d < 3; ++d) nb *= t.probs[p].base_n[d] >> t.prob_mgdepth[p];
         bsum += nb * nb;
     }
-    o.Lbuf = b.take(8);
     o.Xbuf = b.take(sizeof(double) * 2 * bsum);
     // state and work vectors (double)
     o.z = b.take(8 * nl);
@@ -428,25 +421,17 @@ static void wire_pc(nrd_hierarchy* h, PcArrays<PT>& pc) {
             pc.mg.box[g] = h->at<PatchInfo>(o.mg_box[g]);
             pc.mg.len[g] = t.mg[g].len;
             pc.mg.tiles[g] = h->at<Tile>(o.mg_tiles[g]);
-            pc.mg.ntiles[g] = (int)t.mg[g].tiles.size();
             pc.mg.Dg[g] = h->at<PT>(o.mg_D[g]);
             pc.mg.eg[g] = h->at<PT>(o.mg_e[g]);
             pc.mg.fg[g] = h->at<PT>(o.mg_f[g]);
         }
         pc.mg.box_of[g] = h->at<int32_t>(o.mg_box_of[g]);
         pc.mg.smooth_tiles[g] = h->at<Tile>(o.mg_smooth[g]);
-        pc.mg.bottom_probs[g] = h->at<int32_t>(o.mg_bprobs[g]);
-        pc.mg.bottom_boxes[g] = h->at<int32_t>(o.mg_bboxes[g]);
     }
     pc.mg.l0map = G >= 1 ? h->at<int32_t>(o.mg_l0map) : nullptr;
     pc.ltiles = h->at<Tile>(o.ltiles);
     pc.mg.multi0 = t.level_sib0[1] > t.level_sib0[0];
-    pc.mg.bottom_off = h->at<int64_t>(o.bottom_off);
-    pc.mg.bot_probs = h->at<int32_t>(o.bot_probs);
-    pc.mg.bot_boxes = h->at<int32_t>(o.bot_boxes);
-    pc.mg.bot_grid = h->at<int32_t>(o.bot_grid);
-    pc.mg.nbot_all = t.nprob;
-    pc.mg.Lbuf = h->at<double>(o.Lbuf);
+    pc.mg.tails = h->at<TailEntry>(o.tails);
     pc.mg.Xbuf = h->at<double>(o.Xbuf);
     pc.p2_mode = h->opt.p2_mode;
     pc.nu_pre = std::max(1, h->opt.mg_nu_pre);
@@ -493,33 +478,68 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     for (int p = 0; p < t.nprob; ++p) box_of[0][p] = t.level_patches[p][0][0];
     for (int g = 1; g <= G; ++g)
         for (size_t i = 0; i < t.mg[g].probs.size(); ++i) box_of[g][t.mg[g].probs[i]] = (int32_t)i;
-    std::vector<int32_t> nsmooth(G + 1, 0), nbottom(G + 1, 0);
-    for (int g = 0; g <= G; ++g) {
-        if (g >= 1) {
-            HIPCHK(up(s, h->ws + o.mg_box[g], t.mg[g].boxes));
-            HIPCHK(up(s, h->ws + o.mg_tiles[g], t.mg[g].tiles));
+    // tail grid of every problem that coarsens (see kTailCells)
+    std::vector<TailEntry> tails;
+    std::vector<int32_t> start(t.nprob, 0);
+    int32_t top = 0, nbase = 0;
+    for (int pass = 0; pass < 2; ++pass)
+        for (int p = 0; p < t.nprob; ++p) {
+            const int32_t depth = t.prob_mgdepth[p];
+            if ((depth > 0) != (pass == 1)) continue;
+            int32_t g = depth;
+            auto cells = [&](int32_t q) {
+                int64_t n = 1;
+                for (int d = 0; d < 3; ++d) n *= t.probs[p].base_n[d] >> q;
+                return n;
+            };
+            if (depth > 0)
+                while (g > 1 && cells(g - 1) <= kTailCells) --g;
+            start[p] = g;
+            top = std::max(top, g);
+            TailEntry te;
+            std::memset(&te, 0, sizeof(te));
+            te.prob = p;
+            te.start = g;
+            te.depth = depth;
+            te.boff = 2 * (int64_t)t.bottom_off[p];
+            for (int32_t q = g; q <= depth; ++q)
+                te.grid[q - g] = q == 0 ? t.patches[box_of[0][p]] : t.mg[q].boxes[box_of[q][p]];
+            tails.push_back(te);
+            nbase += depth == 0;
         }
+    HIPCHK(up(s, h->ws + o.tails, tails));
+    std::vector<int32_t> nsmooth(G + 1, 0), ntiles(G + 1, 0);
+    std::vector<std::vector<Tile>> lists;         // alive until the uploads are done
+    for (int g = 0; g <= G; ++g) {
         HIPCHK(up(s, h->ws + o.mg_box_of[g], box_of[g]));
-        std::vector<Tile> sm;
+        std::vector<Tile> sm, tl;
         if (g == 0) {
             for (int i = t.level_tile0[0]; i < t.level_tile0[1]; ++i)
-                if (t.prob_mgdepth[t.tiles[i].prob] > 0) sm.push_back(t.tiles[i]);
+                if (start[t.tiles[i].prob] > 0) sm.push_back(t.tiles[i]);
         } else {
-            for (const Tile& tl : t.mg[g].tiles)
-                if (t.prob_mgdepth[tl.prob] > g) sm.push_back(tl);
+            HIPCHK(up(s, h->ws + o.mg_box[g], t.mg[g].boxes));
+            for (const Tile& x : t.mg[g].tiles) {
+                if (start[x.prob] > g) sm.push_back(x);
+                if (start[x.prob] >= g) tl.push_back(x);
+            }
+            ntiles[g] = (int)tl.size();
+            HIPCHK(up(s, h->ws + o.mg_tiles[g], tl));
         }
         nsmooth[g] = (int)sm.size();
         HIPCHK(up(s, h->ws + o.mg_smooth[g], sm));
-        std::vector<int32_t> bp, bb;
-        for (int p = 0; p < t.nprob; ++p)
-            if (t.prob_mgdepth[p] == g) {
-                bp.push_back(p);
-                bb.push_back(box_of[g][p]);
-            }
-        nbottom[g] = (int)bp.size();
-        HIPCHK(up(s, h->ws + o.mg_bprobs[g], bp));
-        HIPCHK(up(s, h->ws + o.mg_bboxes[g], bb));
+        lists.push_back(std::move(sm));
+        lists.push_back(std::move(tl));
     }
+    // per-precision counts
+    auto counts = [&](auto& mg) {
+        for (int g = 0; g <= G; ++g) {
+            mg.nsmooth[g] = nsmooth[g];
+            mg.ntiles[g] = ntiles[g];
+        }
+        mg.top = top;
+        mg.nbase = nbase;
+        mg.ntail = t.nprob - nbase;
+    };
     {
         std::vector<Tile> lt;
         std::vector<int32_t> l0(t.nlev + 1, 0);
@@ -564,20 +584,6 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
         }
         HIPCHK(up(s, h->ws + o.mg_l0map, l0));
     }
-    std::vector<int64_t> boff(t.nprob);
-    for (int p = 0; p < t.nprob; ++p) boff[p] = t.bottom_off[p];
-    HIPCHK(up(s, h->ws + o.bottom_off, boff));
-    std::vector<int32_t> bpa, bba, bga;
-    for (int g = 0; g <= G; ++g)
-        for (int p = 0; p < t.nprob; ++p)
-            if (t.prob_mgdepth[p] == g) {
-                bpa.push_back(p);
-                bba.push_back(box_of[g][p]);
-                bga.push_back(g);
-            }
-    HIPCHK(up(s, h->ws + o.bot_probs, bpa));
-    HIPCHK(up(s, h->ws + o.bot_boxes, bba));
-    HIPCHK(up(s, h->ws + o.bot_grid, bga));
     // device views
     Dev& D = h->D;
     D.nl = t.nl;
@@ -659,16 +665,10 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     h->fdsum = h->at<double>(o.fdsum);
     if (h->mixed) {
         wire_pc(h, h->pcf);
-        for (int g = 0; g <= G; ++g) {
-            h->pcf.mg.nsmooth[g] = nsmooth[g];
-            h->pcf.mg.nbottom[g] = nbottom[g];
-        }
+        counts(h->pcf.mg);
     } else {
         wire_pc(h, h->pcd);
-        for (int g = 0; g <= G; ++g) {
-            h->pcd.mg.nsmooth[g] = nsmooth[g];
-            h->pcd.mg.nbottom[g] = nbottom[g];
-        }
+        counts(h->pcd.mg);
     }
     h->host_active.assign(t.nprob, 1);
     HIPCHK(up(s, h->active, h->host_active));

@@ -1,0 +1,560 @@
+// The small grids of the base multigrid: set-up of the coarsest grid's dense
+// inverse and the part of the V-cycle below a problem's tail grid, one
+// workgroup per (problem, field) each (paper Sec. 4.3).
+#include <hip/hip_runtime.h>
+
+#include "device_util.h"
+#include "kernels.h"
+#include "precond.h"
+
+namespace nrd {
+
+// ---------------------------------------------------------------------------
+// numbering of the coarsest grid's cells: the longest axis slowest, so that
+// neighbours lie within a half-band of N / n_max <= 25 (checked on the host)
+// ---------------------------------------------------------------------------
+
+struct BottomOrder {
+    int a[3];      // axes, fastest first
+    int st[3];     // stride of each (original) axis in the numbering
+};
+
+// (written with selects only, so that nothing is indexed at run time)
+__device__ __forceinline__ BottomOrder bottom_order(const PatchInfo& p) {
+    BottomOrder o;
+    const int n0 = p.n[0], n1 = p.n[1], n2 = p.n[2];
+    const int slow = (n2 > n0 && n2 > n1) ? 2 : ((n1 > n0) ? 1 : 0);
+    o.a[0] = slow == 0 ? 1 : 0;
+    o.a[1] = slow == 2 ? 1 : 2;
+    o.a[2] = slow;
+    const int na0 = slow == 0 ? n1 : n0;                  // extent of axis a[0]
+    const int na1 = slow == 2 ? n1 : n2;                  // extent of axis a[1]
+    o.st[0] = slow == 0 ? na0 * na1 : 1;
+    o.st[1] = slow == 1 ? na0 * na1 : (slow == 0 ? 1 : na0);
+    o.st[2] = slow == 2 ? na0 * na1 : na0;
+    return o;
+}
+
+__device__ __forceinline__ void bottom_coords(const PatchInfo& p, const BottomOrder& o, int lin,
+                                              int id[3]) {
+    const int n0 = p.n[0], n1 = p.n[1], n2 = p.n[2];
+    const int slow = o.a[2];
+    const int na0 = slow == 0 ? n1 : n0;
+    const int na1 = slow == 2 ? n1 : n2;
+    const int c0 = lin % na0;
+    const int r = lin / na0;
+    const int c1 = r % na1;
+    const int c2 = r / na1;
+    // axis a[0] gets c0, a[1] gets c1, a[2] (slow) gets c2
+    id[0] = slow == 0 ? c2 : c0;
+    id[1] = slow == 1 ? c2 : (slow == 0 ? c0 : c1);
+    id[2] = slow == 2 ? c2 : c1;
+}
+
+// floor(q / d) for 0 <= q < 2^20 and d < 2^12 from inv = 1 / d: the rounding
+// of (q + 1/2) inv stays below the distance 1 / (2 d) to the next integer
+// (q = 4095 and less here); an integer division costs five times as much
+__device__ __forceinline__ int quot(int q, float inv) { return (int)(((float)q + 0.5f) * inv); }
+
+// Coefficients of a coarse face (grid g of one field): the mean of the four
+// fine ones.  Boundary faces included.
+template <typename PT>
+__device__ __forceinline__ void coarsen_field(const PatchInfo& pc, const PatchInfo& pf,
+                                              const PT* Df, int64_t nlf, PT* Dc, int64_t nlc) {
+    const int stc[3] = {1, pc.sy, pc.sz};
+    const int stf[3] = {1, pf.sy, pf.sz};
+    const float inv_x = 1.0f / (float)pc.n[0], inv_y = 1.0f / (float)pc.n[1];
+    for (int lin = threadIdx.x; lin < pc.ncell; lin += blockDim.x) {
+        const int r = quot(lin, inv_x), k = quot(r, inv_y);
+        const int id[3] = {lin - r * pc.n[0], r - k * pc.n[1], k};
+        const int c = native_index(pc, id[0], id[1], id[2]);
+        const int f0 = native_index(pf, 2 * id[0], 2 * id[1], 2 * id[2]);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const int t1 = d == 0 ? 1 : 0;
+            const int t2 = d == 2 ? 1 : 2;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (s == 1 && id[d] != pc.n[d] - 1) continue;
+                const int fs = s ? f0 + 2 * stf[d] : f0;
+                const PT* src = Df + d * nlf;
+                const PT v = (src[fs] + src[fs + stf[t1]]) +
+                             (src[fs + stf[t2]] + src[fs + stf[t1] + stf[t2]]);
+                Dc[d * nlc + (s ? c + stc[d] : c)] = v * PT(0.25);
+            }
+        }
+    }
+}
+
+constexpr int kSetupThreads = 512;
+
+// Set-up below a problem's tail grid: the face coefficients of the grids
+// start + 1 .. depth, then the inverse X (float64, N x N, row major in the
+// numbering above) of the coarsest grid's operator.  The matrix is symmetric
+// and strictly diagonally dominant, so it is inverted without pivoting by N
+// symmetric sweeps (Gauss-Jordan: after the sweep of every index the matrix
+// holds -A^-1).  Up to 512 threads keep an 8 x 4 tile each in registers; a
+// sweep needs one column, which its owners put into LDS, so there is one
+// barrier per index and nothing else is serial.  What bounds it is that chain
+// of N barriers and LDS reads.  Measured, with the coefficients of the grids
+// below the tail: N = 64 (a 32^3 problem) 30 us, N = 125 (in an ensemble)
+// 69 us; a band Cholesky with two barriers per index and one triangular solve
+// per column took 62 and 137 us, after two launches for the coefficients.
+template <typename PT>
+__global__ __launch_bounds__(kSetupThreads) void k_tail_setup(
+    const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
+    const ProbScalars* __restrict__ ps, double* __restrict__ X) {
+    __shared__ double A[kBottomMax * kBottomBand];   // A(i, i - d) at [i kBottomBand + d]
+    __shared__ __align__(16) double col[2][kBottomMax];
+    const TailEntry& t = tails[blockIdx.x >> 1];
+    const int fld = blockIdx.x & 1;
+    if (act && !act[t.prob]) return;                 // uniform over the workgroup
+    for (int g = t.start + 1; g <= t.depth; ++g) {
+        const PatchInfo& pc = t.grid[g - t.start];
+        const PatchInfo& pf = t.grid[g - t.start - 1];
+        coarsen_field(pc, pf, G.D[g - 1] + fld * 3 * G.nl[g - 1], G.nl[g - 1],
+                      G.D[g] + fld * 3 * G.nl[g], G.nl[g]);
+        __threadfence_block();
+        __syncthreads();
+    }
+    const int g = t.depth;                           // the problem's coarsest grid
+    const PatchInfo& p = t.grid[g - t.start];
+    const PT* D = G.D[g] + fld * 3 * G.nl[g];
+    const int64_t nl = G.nl[g];
+    const double beta = ps[t.prob].beta;
+    // grid 0 without stored D_T: the T-field coefficients from T
+    const PT* __restrict__ T0 = (g == 0 && fld == 1) ? G.T0 : nullptr;
+    const PT kappa = (PT)ps[t.prob].kappa;
+    const int N = p.ncell;                           // <= kBottomMax (checked on the host)
+    const BottomOrder o = bottom_order(p);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < N * kBottomBand; i += kSetupThreads) A[i] = 0.0;
+    __syncthreads();
+    const int st[3] = {1, p.sy, p.sz};
+    for (int lin = tid; lin < N; lin += kSetupThreads) {
+        int id[3];
+        bottom_coords(p, o, lin, id);
+        const int c = native_index(p, id[0], id[1], id[2]);
+        double dg = 1.0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double bh2 = beta * p.ih[d] * p.ih[d];
+            const PT* Dd = D + d * nl;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (id[d] == (s ? p.n[d] - 1 : 0)) {        // grid covers the domain
+                    if (fld == 0 && ((p.robin >> (2 * d + s)) & 1)) {
+                        const double Dv = (double)Dd[s ? c + st[d] : c];
+                        dg += 2.0 * beta * Dv / ((4.0 * Dv + p.h[d]) * p.h[d]);
+                    }
+                    continue;
+                }
+                const int nb = s ? c + st[d] : c - st[d];
+                const double Dv = T0 ? (double)face_DT(T0[c], T0[nb], kappa)
+                                     : (double)Dd[s ? c + st[d] : c];
+                const double a = bh2 * Dv;
+                dg += a;
+                // the lower neighbour's entry; the upper one is that
+                // neighbour's lower entry (same face, same coefficient)
+                if (s == 0) A[lin * kBottomBand + o.st[d]] = -a;
+            }
+        }
+        A[lin * kBottomBand] = dg;
+    }
+    __syncthreads();
+    // tiles of 8 x 4 for as many threads as it takes; the other wavefronts
+    // end here, which shortens the barriers
+    const int ldc = (N + 3) >> 2, ldr = (N + 7) >> 3;
+    if ((tid & ~63) >= ldr * ldc) return;
+    const int tr = tid / ldc, tc = tid - tr * ldc;
+    const int r0 = 8 * tr, c0 = 4 * tc;
+    const bool on = tr < ldr;
+    double a[8][4];
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = r0 + i, c = c0 + j;
+            const int hi = r > c ? r : c, d = r > c ? r - c : c - r;
+            a[i][j] = (hi < N && d < kBottomBand) ? A[hi * kBottomBand + d] : 0.0;
+        }
+    // (rows and columns beyond N stay zero: their published values are zero)
+    for (int kq = 0; 8 * kq < N; ++kq) {
+#pragma unroll
+        for (int b = 0; b < 8; ++b) {
+            const int k = 8 * kq + b;
+            if (k >= N) break;                       // uniform
+            // double buffered: a buffer is rewritten two barriers after it was
+            // read
+            double* v = col[b & 1];
+            if (on && tc == 2 * kq + (b >> 2))
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[r0 + i] = a[i][b & 3];
+            __syncthreads();
+            if (!on) continue;
+            const double ip = rcp_nr(v[k]);
+            double vr[8], vc[4];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vr[i] = v[r0 + i];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) vc[j] = v[c0 + j] * ip;
+#pragma unroll
+            for (int i = 0; i < 8; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[i][j] -= vr[i] * vc[j];
+            if (tr == kq)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) a[b][j] = vc[j];
+            if (tc == 2 * kq + (b >> 2)) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) a[i][b & 3] = vr[i] * ip;
+                if (tr == kq) a[b][b & 3] = -ip;
+            }
+        }
+    }
+    double* Xi = X + t.boff + (int64_t)fld * N * N;
+    if (on)
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (r0 + i < N && c0 + j < N) Xi[(r0 + i) * N + c0 + j] = -a[i][j];
+}
+
+// ---------------------------------------------------------------------------
+// V-cycle below the tail grid
+// ---------------------------------------------------------------------------
+
+__device__ __forceinline__ float reciprocal(float x) { return 1.0f / x; }
+__device__ __forceinline__ double reciprocal(double x) { return rcp_nr(x); }
+
+// One grid of a tail, one field, held by the workgroup: every thread owns up
+// to C cells of each colour and keeps their level operator (beta D / h^2 of
+// the six faces, 0 on physical ones; the diagonal with its Marshak terms) and
+// right-hand side in registers; the iterate lives in LDS, x fastest, with
+// n0 n1 zeros before and after it so that no neighbour index leaves it.  Owned
+// cells q: lane q & 3 of the quad of coarse cell q >> 2 owns the child with
+// offsets (0,0,0), (1,1,0), (1,0,1), (0,1,1) (colour 0) and the child
+// mirrored in x (colour 1).
+template <typename PT, int C>
+struct TailGrid {
+    PT a[2][C][6], rdg[2][C], f[2][C];   // rdg: 1 / diagonal
+    PT ns0[C];                           // neighbour sums colour 0 was relaxed with
+    int c[2][C], nat[2][C];              // index into e (-1: no cell), native index
+    int n[3], cn[3];                     // extents, extents of the next grid
+    float inv_x, inv_y;                  // 1 / cn[0], 1 / cn[1]
+    PT* e;
+
+    // operator of every owned cell; e zeroed (its last reader is past a
+    // barrier)
+    __device__ __forceinline__ void load(const PatchInfo& p, const PT* D, int64_t nl,
+                                         double beta, int robin, PT* buf) {
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            n[d] = p.n[d];
+            cn[d] = p.n[d] >> 1;
+        }
+        inv_x = 1.0f / (float)cn[0];
+        inv_y = 1.0f / (float)cn[1];
+        const int pad = n[0] * n[1];
+        e = buf + pad;
+        for (int q = threadIdx.x; q < p.ncell + 2 * pad; q += kTailThreads) buf[q] = PT(0);
+        PT bh2[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) bh2[d] = (PT)(beta * p.ih[d] * p.ih[d]);
+        const int st[3] = {1, p.sy, p.sz};
+#pragma unroll
+        for (int w = 0; w < C; ++w) {
+            const int q = threadIdx.x + w * kTailThreads;
+            c[0][w] = c[1][w] = -1;
+            if (q >= (p.ncell >> 1)) continue;
+            int I, J, K;
+            quad_cell(q >> 2, I, J, K);
+            const int lane = q & 3;
+            const int child = lane == 0 ? 0 : (lane == 1 ? 3 : (lane == 2 ? 5 : 6));
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                const int id[3] = {2 * I + ((child ^ col) & 1), 2 * J + ((child >> 1) & 1),
+                                   2 * K + (child >> 2)};
+                c[col][w] = id[0] + n[0] * (id[1] + n[1] * id[2]);
+                const int cc = native_index(p, id[0], id[1], id[2]);
+                nat[col][w] = cc;
+                PT s = PT(1);
+#pragma unroll
+                for (int d = 0; d < 3; ++d)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h) {
+                        const bool edge = id[d] == (h ? n[d] - 1 : 0);
+                        const PT Df = D[d * nl + (h ? cc + st[d] : cc)];
+                        const PT v = edge ? PT(0) : bh2[d] * Df;
+                        a[col][w][2 * d + h] = v;
+                        s += v;
+                        if (edge && ((robin >> (2 * d + h)) & 1)) {
+                            const PT hd = (PT)p.h[d];
+                            s += PT(2) * (PT)beta * Df / ((PT(4) * Df + hd) * hd);
+                        }
+                    }
+                rdg[col][w] = reciprocal(s);
+            }
+        }
+    }
+    __device__ __forceinline__ void quad_cell(int q, int& I, int& J, int& K) const {
+        const int r = quot(q, inv_x);
+        I = q - r * cn[0];
+        K = quot(r, inv_y);
+        J = r - K * cn[1];
+    }
+    __device__ __forceinline__ PT neighbours(int col, int w) const {
+        const int i = c[col][w], sy = n[0], sz = n[0] * n[1];
+        PT ns = PT(0);
+        ns += a[col][w][0] * e[i - 1];
+        ns += a[col][w][1] * e[i + 1];
+        ns += a[col][w][2] * e[i - sy];
+        ns += a[col][w][3] * e[i + sy];
+        ns += a[col][w][4] * e[i - sz];
+        ns += a[col][w][5] * e[i + sz];
+        return ns;
+    }
+    // one colour of a red-black sweep (zero: from e = 0)
+    __device__ __forceinline__ void half(int col, bool zero) {
+#pragma unroll
+        for (int w = 0; w < C; ++w)
+            if (c[col][w] >= 0) {
+                const PT ns = zero ? PT(0) : neighbours(col, w);
+                e[c[col][w]] = (f[col][w] + ns) * rdg[col][w];
+                if (col == 0) ns0[w] = ns;
+            }
+        __syncthreads();
+    }
+    __device__ __forceinline__ void sweeps(int nu, bool zero) {
+        for (int it = 0; it < nu; ++it) {
+            half(0, zero && it == 0);
+            half(1, false);
+        }
+    }
+    // fc = mean over the children of the residual.  It is zero on colour 1,
+    // relaxed last; a colour-0 cell was relaxed to f + ns0 = dg e, so its
+    // residual f - (dg e - ns) is what its neighbour sum has changed by since.
+    __device__ __forceinline__ void restrict_to(PT* fc) const {
+#pragma unroll
+        for (int w = 0; w < C; ++w) {
+            const int i = c[0][w];
+            PT v = PT(0);
+            if (i >= 0) v = neighbours(0, w) - ns0[w];
+            v += __shfl_xor(v, 1);                   // quads are live or not as a whole
+            v += __shfl_xor(v, 2);
+            const int q = threadIdx.x + w * kTailThreads;
+            if (i >= 0 && (q & 3) == 0) fc[q >> 2] = v * PT(0.125);
+        }
+        __syncthreads();
+    }
+    // e += trilinear prolongation of the next grid's ec (copy rule at edges)
+    __device__ __forceinline__ void prolong(const PT* ec) {
+#pragma unroll
+        for (int w = 0; w < C; ++w) {
+            const int q = threadIdx.x + w * kTailThreads;
+            int I, J, K;
+            quad_cell(q >> 2, I, J, K);
+            const int lane = q & 3;
+            const int child = lane == 0 ? 0 : (lane == 1 ? 3 : (lane == 2 ? 5 : 6));
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                if (c[col][w] < 0) continue;
+                const int x = min(max(I + (((child ^ col) & 1) ? 1 : -1), 0), cn[0] - 1);
+                const int y = min(max(J + (((child >> 1) & 1) ? 1 : -1), 0), cn[1] - 1);
+                const int z = min(max(K + ((child >> 2) ? 1 : -1), 0), cn[2] - 1);
+                PT v = PT(0);
+#pragma unroll
+                for (int i = 0; i < 2; ++i)
+#pragma unroll
+                    for (int j = 0; j < 2; ++j)
+#pragma unroll
+                        for (int k = 0; k < 2; ++k) {
+                            const PT wt = (i ? PT(0.25) : PT(0.75)) * (j ? PT(0.25) : PT(0.75)) *
+                                          (k ? PT(0.25) : PT(0.75));
+                            v += wt * ec[(i ? x : I) +
+                                         cn[0] * ((j ? y : J) + cn[1] * (k ? z : K))];
+                        }
+                e[c[col][w]] += v;
+            }
+        }
+        __syncthreads();
+    }
+};
+
+// The V-cycle of one (problem, field) on its grids start .. depth, one
+// workgroup each: the right-hand side of grid `start` is read and its
+// correction written.  A grid of at most kTailCells cells is smaller than the
+// launch that sweeps it, so the whole of it runs between barriers, with the
+// operator in registers (loaded once, before anything waits for it) and the
+// iterates in LDS: a half-sweep is six LDS reads and a division per cell.
+// kTailCells is what 1024 threads hold at two cells of each colour.  The
+// smallest coarsening halves 6, so two grids are smoothed at most (4096 and
+// 512 cells) before the coarsest.  What bounds it is one CU's instruction
+// rate on the 16^3 grid and, on the smaller ones, the chain of barriers.
+// Measured (float): a tail of 16^3 14.4 us, of 64 problems at once 21.5 us,
+// where the 13 launches it replaces took about 58 and 75 us.
+template <typename PT>
+__global__ __launch_bounds__(kTailThreads) void k_mg_tail(
+    const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
+    const ProbScalars* __restrict__ ps, const double* __restrict__ X, int nu_pre, int nu_post) {
+    // iterates with their padding (n0 n1 <= n / 6 where a grid coarsens)
+    __shared__ PT eA[kTailCells + kTailCells / 3 + 8], eB[kTailCells / 8 + kTailCells / 24 + 8];
+    __shared__ PT fB[kTailCells / 8], fC[kBottomMax], eC[kBottomMax];
+    __shared__ double fv[kBottomMax];
+    const TailEntry& t = tails[blockIdx.x >> 1];
+    const int fld = blockIdx.x & 1;
+    if (act && !act[t.prob]) return;                 // uniform over the workgroup
+    const double beta = ps[t.prob].beta;
+    const int tid = threadIdx.x;
+    const int levels = t.depth - t.start;            // smoothed grids (0, 1 or 2)
+    const PatchInfo& pa = t.grid[0];
+    const PatchInfo& pb = t.grid[1];                 // (used where levels > 1)
+    const PatchInfo& pc = t.grid[levels];
+    const PT* fa = G.f[t.start] + fld * G.nl[t.start];
+    PT* out = G.e[t.start] + fld * G.nl[t.start];
+    TailGrid<PT, 2> A;
+    TailGrid<PT, 1> B;
+    const int N = pc.ncell;
+    const BottomOrder o = bottom_order(pc);
+    int id[3] = {0, 0, 0};
+    const int row = tid >> 3, part = tid & 7;        // eight lanes per row of X
+    if (row < N) bottom_coords(pc, o, row, id);
+    const int cell = id[0] + pc.n[0] * (id[1] + pc.n[1] * id[2]);
+    if (levels > 0) {
+        A.load(pa, G.D[t.start] + fld * 3 * G.nl[t.start], G.nl[t.start], beta,
+               fld == 0 ? pa.robin : 0, eA);
+#pragma unroll
+        for (int w = 0; w < 2; ++w)
+#pragma unroll
+            for (int col = 0; col < 2; ++col)
+                if (A.c[col][w] >= 0) A.f[col][w] = fa[A.nat[col][w]];
+    }
+    if (levels > 1)
+        B.load(pb, G.D[t.start + 1] + fld * 3 * G.nl[t.start + 1], G.nl[t.start + 1], beta,
+               fld == 0 ? pb.robin : 0, eB);
+    // the first 64 columns of the inverse, wanted only at the bottom (float:
+    // float64 coefficients leave no registers for them)
+    constexpr int kAhead = sizeof(PT) == 4 ? 8 : 0;
+    const double* __restrict__ Xi = X + t.boff + (int64_t)fld * N * N;
+    double xr[kAhead + 1];
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+        xr[j] = (row < N && part + 8 * j < N) ? Xi[row * N + part + 8 * j] : 0.0;
+    __syncthreads();
+    if (levels > 0) {
+        A.sweeps(nu_pre, true);
+        A.restrict_to(levels > 1 ? fB : fC);
+    }
+    if (levels > 1) {
+#pragma unroll
+        for (int col = 0; col < 2; ++col)
+            if (B.c[col][0] >= 0) B.f[col][0] = fB[B.c[col][0]];
+        B.sweeps(nu_pre, true);
+        B.restrict_to(fC);
+    }
+    // coarsest grid: e = X f in float64
+    if (row < N && part == 0)
+        fv[row] = (double)(levels > 0 ? fC[cell] : fa[native_index(pc, id[0], id[1], id[2])]);
+    __syncthreads();
+    double acc = 0.0;
+#pragma unroll
+    for (int j = 0; j < kAhead; ++j)
+        if (part + 8 * j < N) acc += xr[j] * fv[part + 8 * j];
+    if (row < N)
+        for (int j = part + 8 * kAhead; j < N; j += 8) acc += Xi[row * N + j] * fv[j];
+    acc += __shfl_xor(acc, 1, 64);
+    acc += __shfl_xor(acc, 2, 64);
+    acc += __shfl_xor(acc, 4, 64);
+    if (row < N && part == 0) {
+        if (levels > 0)
+            eC[cell] = (PT)acc;
+        else
+            out[native_index(pc, id[0], id[1], id[2])] = (PT)acc;
+    }
+    if (levels == 0) return;
+    __syncthreads();
+    if (levels > 1) {
+        B.prolong(eC);
+        B.sweeps(nu_post, false);
+    }
+    A.prolong(levels > 1 ? B.e : eC);
+    A.sweeps(nu_post, false);
+#pragma unroll
+    for (int w = 0; w < 2; ++w)
+#pragma unroll
+        for (int col = 0; col < 2; ++col) {
+            const int i = A.c[col][w];
+            if (i >= 0) out[A.nat[col][w]] = A.e[i];
+        }
+}
+
+// The solve of problems whose base grid does not coarsen, one workgroup per
+// (problem, field).
+template <typename PT>
+__global__ __launch_bounds__(kBlock) void k_bottom_apply(const int32_t* __restrict__ act,
+    const TailEntry* __restrict__ tails, const double* __restrict__ X, const PT* __restrict__ f, PT* __restrict__ e,
+    int64_t nl, int split) {
+    // split: e and f in colour-split storage
+    __shared__ double fv[kBottomMax];
+    const int fld = blockIdx.x & 1;
+    const TailEntry& t = tails[blockIdx.x >> 1];
+    if (act && !act[t.prob]) return;
+    const PatchInfo& p = t.grid[0];
+    const int N = p.ncell;
+    const BottomOrder o = bottom_order(p);
+    const double* Xi = X + t.boff + (int64_t)fld * N * N;
+    for (int j = threadIdx.x; j < N; j += blockDim.x) {
+        int id[3];
+        bottom_coords(p, o, j, id);
+        const int c = split ? split_index(p, id[0] + 1, id[1] + 1, id[2] + 1)
+                            : native_index(p, id[0], id[1], id[2]);
+        fv[j] = (double)f[fld * nl + c];
+    }
+    __syncthreads();
+    // X is symmetric: row i = column i, read with consecutive threads on
+    // consecutive addresses
+    for (int row = threadIdx.x; row < N; row += blockDim.x) {
+        double acc = 0.0;
+        for (int jj = 0; jj < N; ++jj) acc += Xi[(int64_t)jj * N + row] * fv[jj];
+        int id[3];
+        bottom_coords(p, o, row, id);
+        const int c = split ? split_index(p, id[0] + 1, id[1] + 1, id[2] + 1)
+                            : native_index(p, id[0], id[1], id[2]);
+        e[fld * nl + c] = (PT)acc;
+    }
+}
+
+template <typename PT>
+void bottom_apply(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
+                  const double* X, const PT* f, PT* e, int64_t nl, int split) {
+    if (n > 0) k_bottom_apply<PT><<<2 * n, kBlock, 0, s>>>(act, tails, X, f, e, nl, split);
+}
+
+template <typename PT>
+void tail_setup(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
+                const TailGrids<PT>& G, const ProbScalars* ps, double* X) {
+    if (n > 0) k_tail_setup<PT><<<2 * n, kSetupThreads, 0, s>>>(act, tails, G, ps, X);
+}
+
+template <typename PT>
+void tail_cycle(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
+                const TailGrids<PT>& G, const ProbScalars* ps, const double* X, int nu_pre,
+                int nu_post) {
+    if (n > 0)
+        k_mg_tail<PT><<<2 * n, kTailThreads, 0, s>>>(act, tails, G, ps, X, nu_pre, nu_post);
+}
+
+#define NRD_TAIL(PT)                                                                          \
+    template void tail_setup<PT>(hipStream_t, int, const int32_t*, const TailEntry*,          \
+                                 const TailGrids<PT>&, const ProbScalars*, double*);          \
+    template void bottom_apply<PT>(hipStream_t, int, const int32_t*, const TailEntry*,        \
+                                   const double*, const PT*, PT*, int64_t, int);              \
+    template void tail_cycle<PT>(hipStream_t, int, const int32_t*, const TailEntry*,          \
+                                 const TailGrids<PT>&, const ProbScalars*, const double*,     \
+                                 int, int);
+NRD_TAIL(float)
+NRD_TAIL(double)
+#undef NRD_TAIL
+
+}  // namespace nrd

@@ -48,15 +48,46 @@ __host__ __device__ inline void split_stencil(const PatchInfo& p, const int id[3
 // weight that damps the upper half of the 7-point Laplacian's spectrum best.
 constexpr double kJacobiOmega = 6.0 / 7.0;
 
-// Per multigrid grid: box table, face coefficients, field length (kernel
-// argument of the merged bottom-solve setup).
+// Coarsest grids hold at most kBottomMax cells.
+constexpr int kBottomMax = 128;
+
+// The small grids of the base multigrid (mgtail.hip).  A problem's tail
+// starts at its first grid >= 1 of at most kTailCells cells; one workgroup
+// per (problem, field) runs the V-cycle from there down, in LDS.
+constexpr int kTailThreads = 1024;
+constexpr int kTailCells = 4096;
+struct TailEntry {
+    int32_t prob, start, depth, pad;
+    int64_t boff;            // of the problem's inverses, in doubles
+    PatchInfo grid[3];       // grids start .. depth (at most three: each has an
+                             // eighth of the cells, and 6 cells per axis or more
+                             // where it coarsens)
+};
+
+// Per multigrid grid: face coefficients, vectors, field length
+// (kernel argument of the tail kernels).
 template <typename PT>
-struct BottomGrids {
-    const PatchInfo* P[kMaxMG] = {};
-    const PT* D[kMaxMG] = {};
+struct TailGrids {
+    PT* D[kMaxMG] = {};
+    const PT* f[kMaxMG] = {};
+    PT* e[kMaxMG] = {};
     int64_t nl[kMaxMG] = {};
     const PT* T0 = nullptr;     // grid 0's T in PT when its D_T arrays are not stored
 };
+
+// coefficients below the tail grid and the coarsest grid's inverse, n problems
+template <typename PT>
+void tail_setup(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
+                const TailGrids<PT>& G, const ProbScalars* ps, double* X);
+// e of grid 0 from its f for n problems whose base grid does not coarsen
+template <typename PT>
+void bottom_apply(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
+                  const double* X, const PT* f, PT* e, int64_t nl, int split);
+// e of the tail grids from f of the tail grids, n problems
+template <typename PT>
+void tail_cycle(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
+                const TailGrids<PT>& G, const ProbScalars* ps, const double* X, int nu_pre,
+                int nu_post);
 
 template <typename PT>
 struct PcArrays {
@@ -79,23 +110,19 @@ struct PcArrays {
         const Tile* tiles[kMaxMG] = {};
         int ntiles[kMaxMG] = {};
         const int32_t* box_of[kMaxMG] = {};
+        // tiles: of the problems whose grid g is their tail grid or above it;
+        // smooth_tiles: of those whose grid g is above it
         const Tile* smooth_tiles[kMaxMG] = {};
         int nsmooth[kMaxMG] = {};
-        const int32_t* bottom_probs[kMaxMG] = {};
-        const int32_t* bottom_boxes[kMaxMG] = {};
-        int nbottom[kMaxMG] = {};
-        const int64_t* bottom_off = nullptr;
-        double* Lbuf = nullptr;
+        int top = 0;                    // largest tail grid of any problem
+        // problems whose base grid does not coarsen, then the others
+        const TailEntry* tails = nullptr;
+        int nbase = 0, ntail = 0;
         double* Xbuf = nullptr;
         // first grid: per native cell, the level-0 patch of its children
         // (a base grid cut into several boxes); multi0: level 0 has siblings
         const int32_t* l0map = nullptr;
         bool multi0 = false;
-        // all problems with their coarsest grid (one setup launch)
-        const int32_t* bot_probs = nullptr;
-        const int32_t* bot_boxes = nullptr;
-        const int32_t* bot_grid = nullptr;
-        int nbot_all = 0;
         PT* Dg[kMaxMG] = {};
         PT* eg[kMaxMG] = {};
         PT* fg[kMaxMG] = {};
@@ -122,6 +149,7 @@ struct PcArrays {
     const PT* fac(hipStream_t s) const;     // returns u or e (one level)
     const PT* afacx(hipStream_t s) const;   // returns e
     const PT* p1(hipStream_t s) const;      // the configured cycle
+    TailGrids<PT> tail_grids() const;
     void vcycle(hipStream_t s) const;
     void composite_residual(hipStream_t s, int lev) const;
     void smooth_level(hipStream_t s, const PT* rhs, int lev, int sweeps) const;

@@ -16,6 +16,7 @@
 // otherwise.
 #include <hip/hip_runtime.h>
 
+#include "device_util.h"
 #include "kernels.h"
 #include "precond.h"
 
@@ -36,15 +37,6 @@ __device__ __forceinline__ int nat(const PatchInfo& p, int i, int j, int k) {
 // ---------------------------------------------------------------------------
 // snapshot: D_E, D_T on every face of every patch, sigma per cell
 // ---------------------------------------------------------------------------
-
-// D_T = kappa T_f^(5/2) of the face between cells of temperatures Ta, Tb
-// (symmetric in Ta, Tb); the sweeps over colour-split storage recompute it
-// from T with this same expression, so they see the snapshot's values.
-template <typename PT>
-__device__ __forceinline__ PT face_DT(PT Ta, PT Tb, PT kappa) {
-    const PT Tf = PT(0.5) * (Ta + Tb);
-    return kappa * Tf * Tf * sqrt(Tf);
-}
 
 // Face coefficients in the preconditioner's precision (the inputs are
 // rounded to PT first; in float64 mode this is the float64 formula).
@@ -846,210 +838,6 @@ __global__ __launch_bounds__(kBlock) void k_mg_prolong2(const int32_t* __restric
 }
 
 // ---------------------------------------------------------------------------
-// bottom solve (float64).  The coarsest grid's operator is SPD and banded:
-// setup factors it as L L^T (band Cholesky; cells numbered with the longest
-// axis slowest, so the half-bandwidth b = N / n_max <= N^(2/3) <= 25 for
-// N <= 128 cells) and forms the explicit inverse column by column with two
-// banded triangular solves (one thread per column); apply is then a dense
-// matrix-vector product with one thread per row.  One workgroup per
-// (problem, field).
-// ---------------------------------------------------------------------------
-
-constexpr int kBottomMax = 128;     // cells of the coarsest grid
-constexpr int kBandLd = kBottomBand; // band row stride in LDS (b + 1 <= 26)
-
-struct BottomOrder {
-    int a[3];      // axes, fastest first
-    int st[3];     // stride of each (original) axis in the band numbering
-    int b;         // half-bandwidth
-};
-
-// (written with selects only, so that nothing is indexed at run time)
-__device__ __forceinline__ BottomOrder bottom_order(const PatchInfo& p) {
-    BottomOrder o;
-    const int n0 = p.n[0], n1 = p.n[1], n2 = p.n[2];
-    const int slow = (n2 > n0 && n2 > n1) ? 2 : ((n1 > n0) ? 1 : 0);
-    o.a[0] = slow == 0 ? 1 : 0;
-    o.a[1] = slow == 2 ? 1 : 2;
-    o.a[2] = slow;
-    const int na0 = slow == 0 ? n1 : n0;                  // extent of axis a[0]
-    const int na1 = slow == 2 ? n1 : n2;                  // extent of axis a[1]
-    o.st[0] = slow == 0 ? na0 * na1 : 1;
-    o.st[1] = slow == 1 ? na0 * na1 : (slow == 0 ? 1 : na0);
-    o.st[2] = slow == 2 ? na0 * na1 : na0;
-    o.b = na0 * na1;
-    return o;
-}
-
-__device__ __forceinline__ void bottom_coords(const PatchInfo& p, const BottomOrder& o, int lin,
-                                              int id[3]) {
-    const int n0 = p.n[0], n1 = p.n[1], n2 = p.n[2];
-    const int slow = o.a[2];
-    const int na0 = slow == 0 ? n1 : n0;
-    const int na1 = slow == 2 ? n1 : n2;
-    const int c0 = lin % na0;
-    const int r = lin / na0;
-    const int c1 = r % na1;
-    const int c2 = r / na1;
-    // axis a[0] gets c0, a[1] gets c1, a[2] (slow) gets c2
-    id[0] = slow == 0 ? c2 : c0;
-    id[1] = slow == 1 ? c2 : (slow == 0 ? c0 : c1);
-    id[2] = slow == 2 ? c2 : c1;
-}
-
-// X block of (problem, field): the N x N inverse, row-major, in the band
-// numbering.
-constexpr int kBottomThreads = 4 * kBottomMax;   // four threads per inverse column
-
-template <typename PT>
-__global__ __launch_bounds__(kBottomThreads) void k_bottom_setup(const int32_t* __restrict__ act, 
-    const int32_t* __restrict__ probs, const int32_t* __restrict__ boxes,
-    const int32_t* __restrict__ grids, const BottomGrids<PT> G,
-    const ProbScalars* __restrict__ ps, const int64_t* __restrict__ boff,
-    double* __restrict__ X) {
-    __shared__ double A[kBottomMax * kBandLd];   // A(i, i - d) at [i kBandLd + d]
-    __shared__ double Li[kBottomMax];            // 1 / diagonal of L
-    __shared__ double W[kBottomMax * kBottomMax];   // column j of the inverse at [i N + j]
-    const int pi = blockIdx.x >> 1;
-    const int fld = blockIdx.x & 1;
-    const int prob = probs[pi];
-    if (act && !act[prob]) return;
-    const int g = grids[pi];                    // the problem's coarsest grid
-    const PatchInfo& p = G.P[g][boxes[pi]];
-    const PT* __restrict__ D = G.D[g];
-    const int64_t nl = G.nl[g];
-    const double beta = ps[prob].beta;
-    // grid 0 without stored D_T: the T-field coefficients from T
-    const PT* __restrict__ T0 = (g == 0 && fld == 1) ? G.T0 : nullptr;
-    const PT kappa = (PT)ps[prob].kappa;
-    const int N = p.ncell;                      // <= kBottomMax (checked on the host)
-    const BottomOrder o = bottom_order(p);
-    const int b = o.b;                          // < kBandLd (checked on the host)
-    const int tid = threadIdx.x;
-    for (int i = tid; i < N * kBandLd; i += blockDim.x) A[i] = 0.0;
-    __syncthreads();
-    const int st[3] = {1, p.sy, p.sz};
-    for (int lin = tid; lin < N; lin += blockDim.x) {
-        int id[3];
-        bottom_coords(p, o, lin, id);
-        const int c = nat(p, id[0], id[1], id[2]);
-        double dg = 1.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const double bh2 = beta * p.ih[d] * p.ih[d];
-            const PT* Dd = D + (fld * 3 + d) * nl;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                if (id[d] == (s ? p.n[d] - 1 : 0)) {        // grid covers the domain
-                    if (fld == 0 && ((p.robin >> (2 * d + s)) & 1)) {
-                        const double Dv = (double)Dd[s ? c + st[d] : c];
-                        dg += 2.0 * beta * Dv / ((4.0 * Dv + p.h[d]) * p.h[d]);
-                    }
-                    continue;
-                }
-                const int nb = s ? c + st[d] : c - st[d];
-                const double Dv = T0 ? (double)face_DT(T0[c], T0[nb], kappa)
-                                     : (double)Dd[s ? c + st[d] : c];
-                const double a = bh2 * Dv;
-                dg += a;
-                // the lower neighbour's entry; the upper one is that
-                // neighbour's lower entry (same face, same coefficient)
-                if (s == 0) A[lin * kBandLd + o.st[d]] = -a;
-            }
-        }
-        A[lin * kBandLd] = dg;
-    }
-    // this thread's (r, q) pair of the trailing-update triangle 1 <= q <= r <= b
-    // (b (b + 1) / 2 <= 325 < kBottomThreads)
-    int pr, pq;
-    {
-        int r = 1;
-        while (r * (r + 1) / 2 <= tid) ++r;
-        pr = (tid < b * (b + 1) / 2) ? r : kBottomMax;      // out of range: never used
-        pq = tid - r * (r - 1) / 2 + 1;
-    }
-    __syncthreads();
-    // right-looking band Cholesky: scale column k, update the trailing triangle
-    for (int k = 0; k < N; ++k) {
-        const double dkk = sqrt(A[k * kBandLd]);
-        const double inv = 1.0 / dkk;
-        const int m = min(b, N - 1 - k);
-        if (tid >= 1 && tid <= m) A[(k + tid) * kBandLd + tid] *= inv;
-        if (tid == 0) Li[k] = inv;
-        __syncthreads();
-        if (pr <= m)
-            A[(k + pr) * kBandLd + (pr - pq)] -= A[(k + pr) * kBandLd + pr] * A[(k + pq) * kBandLd + pq];
-        __syncthreads();
-    }
-    // inverse: the four threads 4j..4j+3 (one wavefront holds whole groups)
-    // solve L L^T x = e_j into column j of W; each sums every fourth band term
-    // and the group adds its partial sums with two cross-lane exchanges, so
-    // all four hold the row value and write it (same value, same address).
-    // Groups run different row counts: no workgroup barrier inside.
-    const int j = tid >> 2, q = tid & 3;
-    if (j < N) {
-        for (int i = q; i < j; i += 4) W[i * N + j] = 0.0;
-        for (int i = j; i < N; ++i) {               // L y = e_j
-            const int lmax = min(b, i - j);
-            double acc = 0.0;
-            for (int l = 1 + q; l <= lmax; l += 4) acc -= A[i * kBandLd + l] * W[(i - l) * N + j];
-            acc += __shfl_xor(acc, 1, 64);
-            acc += __shfl_xor(acc, 2, 64);
-            W[i * N + j] = (((i == j) ? 1.0 : 0.0) + acc) * Li[i];
-        }
-        for (int i = N - 1; i >= 0; --i) {          // L^T x = y
-            const int lmax = min(b, N - 1 - i);
-            double acc = 0.0;
-            for (int l = 1 + q; l <= lmax; l += 4)
-                acc -= A[(i + l) * kBandLd + l] * W[(i + l) * N + j];
-            acc += __shfl_xor(acc, 1, 64);
-            acc += __shfl_xor(acc, 2, 64);
-            W[i * N + j] = (W[i * N + j] + acc) * Li[i];
-        }
-    }
-    __syncthreads();
-    double* Xi = X + boff[prob] * 2 + (int64_t)fld * N * N;
-    for (int i = tid; i < N * N; i += blockDim.x) Xi[i] = W[i];
-}
-
-template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_bottom_apply(const int32_t* __restrict__ act, 
-    const int32_t* __restrict__ probs, const int32_t* __restrict__ boxes,
-    const PatchInfo* __restrict__ P, const int64_t* __restrict__ boff,
-    const double* __restrict__ X, const PT* __restrict__ f, PT* __restrict__ e,
-    int64_t nl, int split) {
-    // split: e and f in colour-split storage
-    __shared__ double fv[kBottomMax];
-    const int pi = blockIdx.x >> 1;
-    const int fld = blockIdx.x & 1;
-    const int prob = probs[pi];
-    if (act && !act[prob]) return;
-    const PatchInfo& p = P[boxes[pi]];
-    const int N = p.ncell;
-    const BottomOrder o = bottom_order(p);
-    const double* Xi = X + boff[prob] * 2 + (int64_t)fld * N * N;
-    for (int j = threadIdx.x; j < N; j += blockDim.x) {
-        int id[3];
-        bottom_coords(p, o, j, id);
-        const int c = split ? split_index(p, id[0] + 1, id[1] + 1, id[2] + 1)
-                            : nat(p, id[0], id[1], id[2]);
-        fv[j] = (double)f[fld * nl + c];
-    }
-    __syncthreads();
-    // X is symmetric: row i = column i, read with consecutive threads on
-    // consecutive addresses
-    for (int row = threadIdx.x; row < N; row += blockDim.x) {
-        double acc = 0.0;
-        for (int jj = 0; jj < N; ++jj) acc += Xi[(int64_t)jj * N + row] * fv[jj];
-        int id[3];
-        bottom_coords(p, o, row, id);
-        const int c = split ? split_index(p, id[0] + 1, id[1] + 1, id[2] + 1)
-                            : nat(p, id[0], id[1], id[2]);
-        e[fld * nl + c] = (PT)acc;
-    }
-}
-
-// ---------------------------------------------------------------------------
 // P2 and precision conversion
 // ---------------------------------------------------------------------------
 
@@ -1199,7 +987,7 @@ void PcArrays<PT>::setup(hipStream_t s, const double* u_state) const {
     k_snapshot<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, u_state, d.z3, Dface,
                                             sigma, d.nl, split0 ? Tp : nullptr);
     if (base_smooth) return;                   // no multigrid grids to set up
-    for (int g = 1; g <= mg.G; ++g) {
+    for (int g = 1; g <= mg.top; ++g) {
         const PT* Df = (g == 1) ? Dface : mg.Dg[g - 1];
         const int64_t nlf = (g == 1) ? d.nl : mg.len[g - 1];
         const PatchInfo* Pf = (g == 1) ? d.patches : mg.box[g - 1];
@@ -1210,18 +998,21 @@ void PcArrays<PT>::setup(hipStream_t s, const double* u_state) const {
                                                          (g == 1 && split0) ? Tp : nullptr,
                                                          d.ps);
     }
-    // every problem's coarsest grid in one launch
-    BottomGrids<PT> bg;
+    // below the tail grids: one launch
+    tail_setup<PT>(s, mg.nbase + mg.ntail, d.active, mg.tails, tail_grids(), d.ps, mg.Xbuf);
+}
+
+template <typename PT>
+TailGrids<PT> PcArrays<PT>::tail_grids() const {
+    TailGrids<PT> t;
     for (int g = 0; g <= mg.G; ++g) {
-        bg.P[g] = (g == 0) ? d.patches : mg.box[g];
-        bg.D[g] = (g == 0) ? Dface : mg.Dg[g];
-        bg.nl[g] = (g == 0) ? d.nl : mg.len[g];
-        bg.T0 = split0 ? Tp : nullptr;
+        t.D[g] = (g == 0) ? Dface : mg.Dg[g];
+        t.f[g] = (g == 0) ? f : mg.fg[g];
+        t.e[g] = (g == 0) ? e : mg.eg[g];
+        t.nl[g] = (g == 0) ? D->nl : mg.len[g];
     }
-    if (mg.nbot_all > 0)
-        k_bottom_setup<PT><<<2 * mg.nbot_all, kBottomThreads, 0, s>>>(
-            d.active, mg.bot_probs, mg.bot_boxes, mg.bot_grid, bg, d.ps, mg.bottom_off,
-            mg.Xbuf);
+    t.T0 = split0 ? Tp : nullptr;
+    return t;
 }
 
 template <typename PT>
@@ -1249,7 +1040,7 @@ void PcArrays<PT>::vcycle(hipStream_t s) const {
                                                      colour, nlg);
         }
     };
-    for (int g = 0; g <= mg.G; ++g) {
+    for (int g = 0; g <= mg.top; ++g) {
         const PatchInfo* Pg = (g == 0) ? d.patches : mg.box[g];
         const int64_t nlg = (g == 0) ? d.nl : mg.len[g];
         PT* eg = (g == 0) ? e : mg.eg[g];
@@ -1285,12 +1076,13 @@ void PcArrays<PT>::vcycle(hipStream_t s) const {
                     g == 0 ? mg.l0map : nullptr, d.ps, d.ctype, Dg, fg, eg, nlg, mg.fg[g + 1],
                     mg.len[g + 1]);
         }
-        if (mg.nbottom[g] > 0)
-            k_bottom_apply<PT><<<2 * mg.nbottom[g], kBlock, 0, s>>>(d.active, 
-                mg.bottom_probs[g], mg.bottom_boxes[g], Pg, mg.bottom_off, mg.Xbuf, fg, eg,
-                nlg, sp ? 1 : 0);
     }
-    for (int g = mg.G - 1; g >= 0; --g) {
+    // problems whose base grid does not coarsen, and the grids from every
+    // other problem's tail grid down
+    bottom_apply<PT>(s, mg.nbase, d.active, mg.tails, mg.Xbuf, f, e, d.nl, split0 ? 1 : 0);
+    tail_cycle<PT>(s, mg.ntail, d.active, mg.tails + mg.nbase, tail_grids(), d.ps, mg.Xbuf,
+                   nu_pre, nu_post);
+    for (int g = mg.top - 1; g >= 0; --g) {
         if (mg.nsmooth[g] == 0) continue;
         const PatchInfo* Pg = (g == 0) ? d.patches : mg.box[g];
         const int64_t nlg = (g == 0) ? d.nl : mg.len[g];

@@ -38,3 +38,27 @@ def test_plane_chunk_of_the_size_rule_keeps_every_value(ext):
         outs.append((compact_from_native(H, F), compact_from_native(H, Jv)))
     np.testing.assert_array_equal(outs[0][0], outs[1][0])
     np.testing.assert_array_equal(outs[0][1], outs[1][1])
+
+
+# the grid below which one workgroup runs the V-cycle (at most 4096 cells, the
+# first grid or a coarser one): exactly 4096 cells, 4032 of unequal sides, one
+# grid further down, the coarsest grid itself, 108 and 125 coarsest cells
+@pytest.mark.parametrize("precision,tol", [(0, 1e-10), (1, 1e-4)])
+@pytest.mark.parametrize("ext", [(32, 32, 32), (24, 24, 56), (40, 32, 32), (8, 8, 8),
+                                 (48, 48, 24), (40, 40, 40)])
+def test_precond_with_small_grids_in_one_workgroup(ext, precision, tol):
+    """Preconditioner against the oracle, each field normwise: operation
+    order and the dense inverse in float64 (as the repository's other
+    preconditioner tests), single precision of the whole cycle in mixed."""
+    w = _box(ext)
+    s = system(w)
+    H = make(w, precision=precision, gmres_restart=2)
+    H.begin_step([1e-3])
+    rng = np.random.default_rng(42)
+    u = state(s, w) * rng.uniform(0.9, 1.1, 2 * s.nc)
+    wv = rng.standard_normal(u.shape)
+    H.precond_setup(native_from_compact(H, u))
+    got = compact_from_native(H, H.precond_apply(native_from_compact(H, wv), H.native()))
+    ref = s.precond(u, 1e-3)[0](wv)
+    for f in (slice(0, s.nc), slice(s.nc, 2 * s.nc)):
+        assert rel_err(got[f], ref[f]) < tol
