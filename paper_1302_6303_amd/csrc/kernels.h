@@ -164,7 +164,7 @@ void combine_dot(const Dev& D, hipStream_t s, const double* X, int64_t xstride, 
 void combine_norm(const Dev& D, hipStream_t s, const double* X, int64_t xstride,
                   int nv, const double* coef, int cstride, double* y, double* partial,
                   double* out, const double* xsc = nullptr);
-// Newton update from a Krylov basis (nv <= 16): keep = x, x -= sum_v
+// Newton update from a Krylov basis: keep = x, x -= sum_v
 // coef[p][v] z_v on active problems, out[p] = min over composite cells of
 // both fields of the new x (-1 for NaN)
 void update_min(const Dev& D, hipStream_t s, const double* Z, int64_t zstride, int nv,

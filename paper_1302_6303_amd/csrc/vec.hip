@@ -429,6 +429,13 @@ __global__ __launch_bounds__(kBlock) void k_update_min(
                     s0 += cf[v] * Z[v * zs + c];
                     s1 += cf[v] * Z[v * zs + c + nl];
                 }
+            for (int v = NV; v < nv; ++v) {              // a basis of more than 16
+                const double cv = coef[t.prob * cs + v];
+                if (cv != 0.0) {
+                    s0 += cv * Z[v * zs + c];
+                    s1 += cv * Z[v * zs + c + nl];
+                }
+            }
             const double x0 = x[c], x1 = x[c + nl];
             keep[c] = x0;
             keep[c + nl] = x1;

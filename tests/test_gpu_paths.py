@@ -62,3 +62,17 @@ def test_precond_with_small_grids_in_one_workgroup(ext, precision, tol):
     ref = s.precond(u, 1e-3)[0](wv)
     for f in (slice(0, s.nc), slice(s.nc, 2 * s.nc)):
         assert rel_err(got[f], ref[f]) < tol
+
+
+def test_newton_update_from_more_than_16_basis_vectors():
+    """Steps whose Newton systems take more than 16 Krylov vectors in one
+    cycle: every vector enters the update, so the iteration counts follow
+    those of a basis of 16 with restarts (both solve each system to the same
+    forcing tolerance: at most one Newton iteration apart)."""
+    w = I.marshak_single(32, state="front")
+    st = []
+    for m in (64, 16):
+        H = make(w, gmres_restart=m, gmres_maxrestarts=60, bdf_max_order=1, fac_base=1)
+        st.append(H.implicit_step([6e-3])[1][0])
+    assert max(st[0]["krylov_per_newton"]) > 16
+    assert abs(st[0]["newton_iters"] - st[1]["newton_iters"]) <= 1
