@@ -11,6 +11,7 @@ namespace nrd {
 
 constexpr int kMaxLev = 12;
 constexpr int kBlock = 256;          // threads per workgroup (4 wave64)
+constexpr int kFusedTiles = 256;     // reduction tiles summed within one launch
 
 // Workgroups are dispatched round-robin over the 8 XCDs, each with its own
 // L2.  Tile lists are ordered so that neighbouring tiles share halo data;
@@ -67,6 +68,7 @@ struct Dev {
     const Tile* vtiles = nullptr;
     int32_t nvtiles = 0;
     const int32_t* prob_vtile0 = nullptr;    // device [nprob+1]
+    int32_t* count = nullptr;                // device [nprob], zero between launches
     const GhostCopy* gcopy = nullptr;
     int32_t ncopy = 0;
     const GhostCF* gcf = nullptr;
@@ -142,10 +144,12 @@ void vjp_full(const Dev& D, hipStream_t s, const double* u, double* lam, double*
 //   out[p * nv + v] = sum over composite cells of problem p of
 //                     vol * (x_v . y) (both fields), x_v = X + v * xstride
 //   (xsc: optional per-problem factor applied to every x_v as it is read,
-//   giving the values a scale_copy of X would hold; also for the next two)
+//   giving the values a scale_copy of X would hold)
+//   fuse: one launch where the hierarchy is small, with the counters D.count
+//   (not for calls that may overlap with others on this hierarchy)
 void multidot(const Dev& D, hipStream_t s, const double* X, int64_t xstride,
               int nv, const double* y, double* partial, double* out,
-              const double* xsc = nullptr);
+              const double* xsc = nullptr, bool fuse = false);
 // out[p] = min over composite cells of min(E + lam_p dE, T + lam_p dT)
 void min_positive(const Dev& D, hipStream_t s, const double* u, const double* du,
                   const double* lam, double* partial, double* out);
@@ -154,16 +158,28 @@ void min_positive(const Dev& D, hipStream_t s, const double* u, const double* du
 void combine(const Dev& D, hipStream_t s, const double* X, int64_t xstride,
              int nv, const double* coef, int cstride, double* y, int accumulate,
              double alpha);
-// y -= sum_v coef[p][v] x_v, then out[p * nv + v] = x_v . y (one pass for
-// nv <= 16; the values of combine followed by multidot)
-void combine_dot(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
-                 const double* coef, int cstride, double* y, double* partial, double* out,
-                 const double* xsc = nullptr);
+// Device arrays of the per-problem FGMRES scalars (H: [nprob][(m+1) * m],
+// column j at H[p][(m+1) j]; h1, h2: [nprob][j+1] of the current column).
+struct GmresScalars {
+    double *h1, *h2, *hn2, *H, *cs, *sn, *g, *rho, *vscale;
+};
+// Second Gram-Schmidt pass against nv <= 16 basis vectors, w untouched: h2 and
+// the norm of the twice corrected w, then column nv - 1 of every active problem
+void gs_again(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
+              const double* w, double* partial, int m, const GmresScalars& G,
+              const double* xsc = nullptr);
+// Basis vector nv (1 <= nv <= 16) of the active problems from w, h1, h2 and
+// vscale; with xsc (nv = 1) vector 0 is r scaled by it and is written too; f
+// (may be NULL): the new vector in PT, as the preconditioner's input
+template <typename PT>
+void gs_next(const Dev& D, hipStream_t s, double* X, int64_t xstride, int nv, const double* r,
+             const double* xsc, const double* h1, const double* h2, const double* w,
+             const double* vscale, PT* f, int split);
 // y -= sum_v coef[p][v] x_v, then out[p] = ||y||^2 (composite, volume
 // weighted) in the same pass over y
 void combine_norm(const Dev& D, hipStream_t s, const double* X, int64_t xstride,
                   int nv, const double* coef, int cstride, double* y, double* partial,
-                  double* out, const double* xsc = nullptr);
+                  double* out);
 // Newton update from a Krylov basis: keep = x, x -= sum_v
 // coef[p][v] z_v on active problems, out[p] = min over composite cells of
 // both fields of the new x (-1 for NaN)
@@ -232,12 +248,10 @@ void refine_level(const Dev& D, hipStream_t s, const ShadowPatch* shadows,
                   const int32_t* shadow_src, int lev, double* x, double* sh, int64_t slen,
                   int nf);
 
-// Givens / Hessenberg update of FGMRES for every active problem.
-//   hcol [nprob][m+1] holds the new column (CGS sums), hn2 [nprob] = ||w||^2
+// Givens / Hessenberg update of FGMRES for every active problem from h1, h2
+// and hn2 = ||w||^2.
 void gmres_column(hipStream_t s, int nprob, int m, int j, const int32_t* active,
-                  const double* h1, const double* h2, const double* hn2,
-                  double* H, double* cs, double* sn, double* g, double* rho,
-                  double* vscale);
+                  const GmresScalars& G);
 void gmres_backsolve(hipStream_t s, int nprob, int m, const int32_t* kdim,
                      const double* H, const double* g, double* y);
 

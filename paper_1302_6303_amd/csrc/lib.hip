@@ -108,7 +108,7 @@ struct nrd_hierarchy final : public Clock {
         size_t z, z3, cur, prev, udot, bvec, x, F, s, w, tmp, tmp2, gzn, V, Z, pred;
         size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f, pc_shadow;
         size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG];
-        size_t partial, dots, h1, h2, hn2, H, cs, sn, g, rho, vscale, y, kdim, coefA, coefB,
+        size_t partial, count, dots, h1, h2, hn2, H, cs, sn, g, rho, vscale, y, kdim, coefA, coefB,
             minout, flag, ckpt, fdF, fdw, fdsum;
     } o;
     int32_t adjoint_slots = 0;
@@ -311,7 +311,8 @@ static void layout(nrd_hierarchy* h) {
         o.mg_f[g] = b.take(es * 2 * n);
     }
     // reductions and per-problem scalars
-    o.partial = b.take(8 * 16 * std::max<size_t>(1, t.vtiles.size()));
+    o.partial = b.take(8 * 17 * std::max<size_t>(1, t.vtiles.size()));
+    o.count = b.take(4 * nprob);
     o.dots = b.take(8 * nprob * (m + 2));
     o.h1 = b.take(8 * nprob * (m + 1));
     o.h2 = b.take(8 * nprob * (m + 1));
@@ -599,6 +600,7 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     D.vtiles = h->at<Tile>(o.vtiles);
     D.nvtiles = (int32_t)t.vtiles.size();
     D.prob_vtile0 = h->at<int32_t>(o.prob_vtile0);
+    D.count = h->at<int32_t>(o.count);
     D.gcopy = h->at<GhostCopy>(o.gcopy);
     D.ncopy = (int32_t)t.gcopy.size();
     D.gcf = h->at<GhostCF>(o.gcf);
@@ -839,7 +841,7 @@ static nrd_status upload_active(nrd_hierarchy* h) {
 static nrd_status dot_host(nrd_hierarchy* h, const double* x, const double* y,
                            std::vector<double>& out, bool masked = false) {
     if (!masked) h->D.active = nullptr;
-    multidot(h->D, h->stream, x, 0, 1, y, h->partial, h->dots);
+    multidot(h->D, h->stream, x, 0, 1, y, h->partial, h->dots, nullptr, true);
     out.resize(h->t.nprob);
     HIPCHK(hipMemcpyAsync(out.data(), h->dots, 8 * h->t.nprob, hipMemcpyDeviceToHost,
                           h->stream));
@@ -949,7 +951,7 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
         if (cycle == 0 && b2_first) {
             b2 = *b2_first;
         } else {
-            multidot(h->D, s, r, 0, 1, r, h->partial, h->dots);
+            multidot(h->D, s, r, 0, 1, r, h->partial, h->dots, nullptr, true);
             b2.resize(np);
             HIPCHK(hipMemcpyAsync(b2.data(), h->dots, 8 * np, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
@@ -980,34 +982,57 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
         std::vector<int32_t> live = todo;
         for (int p = 0; p < np; ++p) kd[p] = 0;
         for (int j = 0; j < m; ++j) {
-            // one iteration: v_j = w / ||w|| (the previous iteration's w,
-            // scaled only now that another iteration is needed), z_j =
-            // P^-1 v_j, w = J z_j, CGS2 against v_0..v_j, Hessenberg column +
-            // Givens.  Everything it reads that changes between calls (active
-            // mask, scalars, the preconditioner snapshot) is device-resident,
-            // so it can be captured once per j and replayed.
+            // one iteration: v_j from the previous iteration's w (formed only
+            // now that another iteration is needed), z_j = P^-1 v_j, w = J z_j,
+            // CGS2 against v_0..v_j, Hessenberg column + Givens.  Everything
+            // it reads that changes between calls (active mask, scalars, the
+            // preconditioner snapshot) is device-resident, so it can be
+            // captured once per j and replayed.  Up to 16 basis vectors the
+            // passes keep w and its corrections in registers (gs_again,
+            // gs_next); beyond, w is corrected in place.
             auto iteration = [&]() {
                 double* Vj = h->V + j * NL;
                 double* Zj = h->Z + j * NL;
                 double* wv = h->w;
-                if (j > 0) scale_copy(h->D, s, wv, h->vscale, Vj);
-                if (j == 1 && v0_lazy) scale_copy(h->D, s, r, h->coefA, h->V);
+                const GmresScalars G{h->h1, h->h2, h->hn2, h->H,  h->cs,
+                                     h->sn, h->g,  h->rho, h->vscale};
+                // the previous iteration read r with 1/beta in place of v_0
+                const bool was_lazy = j == 1 && v0_lazy;
+                bool ready = false;      // the preconditioner's input is in place
+                if (j > 16) {
+                    scale_copy(h->D, s, wv, h->vscale, Vj);
+                } else if (j > 0) {
+                    const double* xsc = was_lazy ? h->coefA : nullptr;
+                    if (transpose)
+                        gs_next<double>(h->D, s, h->V, NL, j, r, xsc, h->h1, h->h2, wv, h->vscale,
+                                        nullptr, 0);
+                    else if (h->mixed)
+                        gs_next<float>(h->D, s, h->V, NL, j, r, xsc, h->h1, h->h2, wv, h->vscale,
+                                       h->pcf.f, h->pcf.split0);
+                    else
+                        gs_next<double>(h->D, s, h->V, NL, j, r, xsc, h->h1, h->h2, wv, h->vscale,
+                                        h->pcd.f, h->pcd.split0);
+                    ready = !transpose;
+                }
                 // the basis read by this iteration: v_0 .. v_j, or r with 1/beta
                 const double* Vb = (j == 0 && v0_lazy) ? r : h->V;
                 const double* vsc = (j == 0 && v0_lazy) ? h->coefA : nullptr;
                 if (!transpose) {
-                    pc_apply(h, (j == 0 && v0_lazy) ? r : Vj, Zj, vsc);
+                    pc_apply(h, ready ? nullptr : (j == 0 && v0_lazy) ? r : Vj, Zj, vsc);
                     op_jvp(h, u, Zj, wv, true);
                 } else {
                     pc_apply_t(h, Vj, Zj);
                     vjp_full(h->D, s, u, Zj, wv, h->gzn);
                 }
-                multidot(h->D, s, Vb, NL, j + 1, wv, h->partial, h->h1, vsc);
-                combine_dot(h->D, s, Vb, NL, j + 1, h->h1, j + 1, wv, h->partial, h->h2, vsc);
-                combine_norm(h->D, s, Vb, NL, j + 1, h->h2, j + 1, wv, h->partial, h->hn2,
-                             vsc);
-                gmres_column(s, np, m, j, h->active, h->h1, h->h2, h->hn2, h->H, h->cs, h->sn,
-                             h->g, h->rho, h->vscale);
+                multidot(h->D, s, Vb, NL, j + 1, wv, h->partial, h->h1, vsc, true);
+                if (j < 16) {
+                    gs_again(h->D, s, Vb, NL, j + 1, wv, h->partial, m, G, vsc);
+                } else {
+                    combine(h->D, s, Vb, NL, j + 1, h->h1, j + 1, wv, 1, -1.0);
+                    multidot(h->D, s, Vb, NL, j + 1, wv, h->partial, h->h2, nullptr, true);
+                    combine_norm(h->D, s, Vb, NL, j + 1, h->h2, j + 1, wv, h->partial, h->hn2);
+                    gmres_column(s, np, m, j, h->active, G);
+                }
             };
             if (h->opt.use_graph) {
                 hipGraphExec_t& ge = h->graphs[std::make_tuple(
@@ -1647,7 +1672,21 @@ nrd_status nrd_hierarchy_create(const nrd_problem* probs, int32_t nprob, const n
         h->adjoint_slots = std::max(0, h->opt.adjoint_slots);
         h->stream = static_cast<hipStream_t>(hip_stream);
         std::string msg;
-        nrd_status rc = build_tables(probs, nprob, boxes, nbox, kBlock, 8 * kBlock, h->t, msg);
+        // cells per reduction tile: 2048, or fewer where the grid is too small
+        // to give two workgroups to every CU that way (32^3: 16 workgroups of
+        // eight cells per thread took 6.5 us for an inner product, 128 of one
+        // cell 4.2 us)
+        int32_t vcells = 8 * kBlock;
+        if (boxes && nbox > 0) {
+            int64_t n = 0;
+            for (int32_t b = 0; b < nbox; ++b) {
+                int64_t c = 1;
+                for (int d = 0; d < 3; ++d) c *= std::max(0, boxes[b].hi[d] - boxes[b].lo[d]);
+                n += c;
+            }
+            while (vcells > kBlock && n < (int64_t)512 * vcells) vcells /= 2;
+        }
+        nrd_status rc = build_tables(probs, nprob, boxes, nbox, kBlock, vcells, h->t, msg);
         if (rc) {
             delete h;
             return fail(rc, msg);

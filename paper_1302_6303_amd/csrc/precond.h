@@ -144,6 +144,7 @@ struct PcArrays {
     void setup(hipStream_t s, const double* u_state) const;
     // y = P^-1 (wsc_p w); wsc (per problem, may be NULL) scales the input as
     // it is read
+    // w NULL: f already holds the input
     void apply(hipStream_t s, const double* w, double* y, const double* wsc = nullptr) const;
     void apply_transpose(hipStream_t s, const double* w, double* y) const;
     const PT* fac(hipStream_t s) const;     // returns u or e (one level)

@@ -1351,7 +1351,7 @@ void PcArrays<PT>::apply(hipStream_t s, const double* w, double* y, const double
     const int ntiles = d.level_tile0[d.nlev];
     // with split0 the cycle reads f and returns e in colour-split storage
     const int sp = split0 ? 1 : 0;
-    k_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, w, wsc, f, d.nl, sp);
+    if (w) k_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, w, wsc, f, d.nl, sp);
     const PT* x = p1(s);
     k_p2<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, sigma, d.z3, x, y,
                                        p2_mode, 0, d.nl, sp);

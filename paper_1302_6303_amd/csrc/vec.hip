@@ -9,6 +9,7 @@
 #include <cfloat>
 
 #include "kernels.h"
+#include "precond.h"
 
 namespace nrd {
 
@@ -60,21 +61,87 @@ __device__ __forceinline__ double block_max(double v, double* sh) {
     return r;
 }
 
-__device__ __forceinline__ int interior_index(const PatchInfo& p, int lin) {
-    const int i = lin % p.n[0];
+__device__ __forceinline__ int interior_cell(const PatchInfo& p, int lin, int& i, int& j,
+                                             int& k) {
+    i = lin % p.n[0];
     const int r = lin / p.n[0];
-    const int j = r % p.n[1];
-    const int k = r / p.n[1];
+    j = r % p.n[1];
+    k = r / p.n[1];
     return p.off + (i + 1) + p.sy * (j + 1) + p.sz * (k + 1);
 }
+__device__ __forceinline__ int interior_index(const PatchInfo& p, int lin) {
+    int i, j, k;
+    return interior_cell(p, lin, i, j, k);
+}
 
+// Sums over the workgroup of acc[0 .. nv): sum v in sh[0][v] after the closing
+// barrier, added as block_sum adds (one barrier for all of them).
+template <int NV>
+__device__ __forceinline__ void block_sums(double (&acc)[NV], int nv, double (*sh)[NV]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+        if (v < nv) {
+            const double s = wave_sum(acc[v]);
+            if (lane == 0) sh[w][v] = s;
+        }
+    __syncthreads();
+    if ((int)threadIdx.x < nv) {
+        const int v = threadIdx.x;
+        sh[0][v] = (sh[0][v] + sh[1][v]) + (sh[2][v] + sh[3][v]);
+    }
+    __syncthreads();
+}
+
+// Sums of the tile partials of problem p (tiles [a, b), nv values each) into
+// sh[0][v], the order of k_sum_partials.
+template <int NV>
+__device__ __forceinline__ void partial_sums(const double* partial, int a, int b, int nv,
+                                             double (*sh)[NV]) {
+    double acc[NV];
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+    for (int i = a + threadIdx.x; i < b; i += kBlock)
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (v < nv) acc[v] += partial[(int64_t)i * nv + v];
+    block_sums<NV>(acc, nv, sh);
+}
+
+// A tile's sums (sh[0][v], after block_sums) to its partials; true in the
+// workgroup that finishes its problem, to whom every partial of the problem is
+// then visible.  The count is left at zero for the next launch.  Fences and
+// counts are device wide (the eight XCDs have an L2 each); all stores of the
+// partials are the counting wavefront's own.
+__device__ __forceinline__ bool last_of_problem(const double* sums, int nv, double vol,
+                                                double* partial, int32_t* count, int ntiles) {
+    __shared__ int last;
+    if ((int)threadIdx.x < nv) partial[(int64_t)blockIdx.x * nv + threadIdx.x] = sums[threadIdx.x] * vol;
+    if (threadIdx.x < 64) {
+        __threadfence();
+        if (threadIdx.x == 0) {
+            const int n = atomicAdd(count, 1);
+            last = n == ntiles - 1;
+            if (last) __hip_atomic_store(count, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+    }
+    __syncthreads();
+    if (!last) return false;
+    __threadfence();
+    return true;
+}
+
+// cnt (may be NULL): one zeroed counter per problem; the last tile of a
+// problem then sums its partials itself and writes out[p * ostride + v]
+// (NULL: k_sum_partials follows).
 template <int NV>
 __global__ __launch_bounds__(kBlock) void k_multidot(
     const Tile* __restrict__ vt, const PatchInfo* __restrict__ P,
     const uint8_t* __restrict__ ctype, const int32_t* __restrict__ active,
     const double* __restrict__ X, int64_t xs, int nv, const double* __restrict__ xsc,
-    const double* __restrict__ y, double* __restrict__ partial, int64_t nl) {
-    __shared__ double sh[4];
+    const double* __restrict__ y, double* partial, int64_t nl, int32_t* cnt,
+    const int32_t* __restrict__ t0, double* out, int ostride) {
+    __shared__ double sh[4][NV];
     const Tile t = vt[blockIdx.x];
     double acc[NV];
 #pragma unroll
@@ -96,13 +163,16 @@ __global__ __launch_bounds__(kBlock) void k_multidot(
                 }
         }
     }
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        if (v < nv) {
-            const double s = block_sum(acc[v], sh);
-            if (threadIdx.x == 0) partial[(int64_t)blockIdx.x * nv + v] = s * p.vol;
-        }
+    block_sums<NV>(acc, nv, sh);
+    if (!cnt) {
+        if ((int)threadIdx.x < nv)
+            partial[(int64_t)blockIdx.x * nv + threadIdx.x] = sh[0][threadIdx.x] * p.vol;
+        return;
     }
+    const int a = t0[t.prob], b = t0[t.prob + 1];
+    if (!last_of_problem(sh[0], nv, p.vol, partial, cnt + t.prob, b - a)) return;
+    partial_sums<NV>(partial, a, b, nv, sh);
+    if ((int)threadIdx.x < nv) out[t.prob * ostride + threadIdx.x] = sh[0][threadIdx.x];
 }
 
 // out[p * ostride + v] = sum of the problem's tile partials (fixed order)
@@ -120,28 +190,37 @@ __global__ __launch_bounds__(kBlock) void k_sum_partials(
     }
 }
 
+// Launches K<NV>(args) with the smallest NV of 1, 2, 4, 8, 16 that holds nv.
+#define NRD_BY_NV(nv, K, grid, s, ...)                                        \
+    do {                                                                      \
+        if ((nv) <= 1)                                                        \
+            K<1><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+        else if ((nv) <= 2)                                                   \
+            K<2><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+        else if ((nv) <= 4)                                                   \
+            K<4><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+        else if ((nv) <= 8)                                                   \
+            K<8><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+        else                                                                  \
+            K<16><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                       \
+    } while (0)
+
+// Up to this many tiles the last workgroup of a problem sums its partials (one
+// launch, 7.7 us for an inner product at 32^3 against about 10.5 us for two);
+// the fence in every workgroup makes it lose beyond: 1024 tiles (128^3) 34 us
+// against 17.
+static int32_t* fused_count(const Dev& D) { return D.nvtiles <= kFusedTiles ? D.count : nullptr; }
+
 void multidot(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
-              const double* y, double* partial, double* out, const double* xsc) {
+              const double* y, double* partial, double* out, const double* xsc, bool fuse) {
+    int32_t* cnt = fuse ? fused_count(D) : nullptr;
     for (int v0 = 0; v0 < nv; v0 += 16) {
         const int c = std::min(16, nv - v0);
         const double* Xc = X + v0 * xstride;
-        if (c == 1)
-            k_multidot<1><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       Xc, xstride, c, xsc, y, partial, D.nl);
-        else if (c <= 2)
-            k_multidot<2><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       Xc, xstride, c, xsc, y, partial, D.nl);
-        else if (c <= 4)
-            k_multidot<4><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       Xc, xstride, c, xsc, y, partial, D.nl);
-        else if (c <= 8)
-            k_multidot<8><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       Xc, xstride, c, xsc, y, partial, D.nl);
-        else
-            k_multidot<16><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype,
-                                                        D.active, Xc, xstride, c, xsc, y,
-                                                        partial, D.nl);
-        k_sum_partials<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, partial, c, out + v0, nv);
+        NRD_BY_NV(c, k_multidot, D.nvtiles, s, D.vtiles, D.patches, D.ctype, D.active, Xc, xstride,
+                  c, xsc, y, partial, D.nl, cnt, D.prob_vtile0, out + v0, nv);
+        if (!cnt)
+            k_sum_partials<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, partial, c, out + v0, nv);
     }
 }
 
@@ -243,33 +322,90 @@ void combine(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int 
     }
 }
 
-// y -= sum_v coef[p][v] x_v (combine with alpha = -1, accumulating) and, in
-// the same pass, out[p][v] = x_v . y of the new y (multidot), nv <= 16: the
-// first Gram-Schmidt correction of FGMRES followed by the inner products of
-// the second, with the expressions of those two kernels.
+// The new Hessenberg column, its Givens rotations and the residual estimate
+// of one problem (one thread).
+__device__ __forceinline__ void gmres_column_one(int p, int m, int j, const double* h1,
+                                                 const double* h2, double hn2,
+                                                 const GmresScalars& G) {
+    double* col = G.H + (int64_t)p * (m + 1) * m + (int64_t)(m + 1) * j;
+    double* c = G.cs + p * m;
+    double* s = G.sn + p * m;
+    double* gg = G.g + p * (m + 1);
+    for (int i = 0; i <= j; ++i) col[i] = h1[i] + h2[i];
+    const double hn = sqrt(hn2);
+    col[j + 1] = hn;
+    for (int i = 0; i < j; ++i) {
+        const double tmp = c[i] * col[i] + s[i] * col[i + 1];
+        col[i + 1] = -s[i] * col[i] + c[i] * col[i + 1];
+        col[i] = tmp;
+    }
+    const double a = col[j], b = col[j + 1];
+    double cc, ss, r;
+    if (b == 0.0) {
+        cc = 1.0;
+        ss = 0.0;
+        r = a;
+    } else {
+        r = sqrt(a * a + b * b);
+        cc = a / r;
+        ss = b / r;
+    }
+    c[j] = cc;
+    s[j] = ss;
+    col[j] = r;
+    col[j + 1] = 0.0;
+    gg[j + 1] = -ss * gg[j];
+    gg[j] = cc * gg[j];
+    G.rho[p] = fabs(gg[j + 1]);
+    G.hn2[p] = hn2;
+    G.vscale[p] = hn > 0.0 ? 1.0 / hn : 0.0;
+}
+
+// End of the second Gram-Schmidt pass of one problem from its sums S = (h2_0
+// .. h2_j, ||w1||^2): the basis is orthonormal, so w2 = w1 - sum h2_v v_v has
+// ||w2||^2 = ||w1||^2 - sum h2_v^2.
+__device__ __forceinline__ void gs_finish(int p, int m, int j, const double* S,
+                                          const GmresScalars& G) {
+    double* h2 = G.h2 + (int64_t)p * (j + 1);
+    double n2 = S[j + 1];
+    for (int v = 0; v <= j; ++v) {
+        h2[v] = S[v];
+        n2 -= S[v] * S[v];
+    }
+    gmres_column_one(p, m, j, G.h1 + (int64_t)p * (j + 1), S, fmax(n2, 0.0), G);
+}
+
+// Second Gram-Schmidt pass of FGMRES without storing anything: w1 = w - sum_v
+// h1[p][v] v_v in registers, its inner products with the basis (h2) and its
+// norm.  The corrected vector is formed only if another iteration needs it
+// (k_gs_next).  Bound by reading the basis and w once, 16 (j + 2) B per cell:
+// 97 us for one basis vector on an ensemble of 20 M cells (6.6 TB/s), where
+// storing w1, then w2 with its norm took two passes of 155 and 187 us.
 template <int NV>
-__global__ __launch_bounds__(kBlock) void k_combine_dot(
+__global__ __launch_bounds__(kBlock) void k_gs_again(
     const Tile* __restrict__ vt, const PatchInfo* __restrict__ P,
     const uint8_t* __restrict__ ctype, const int32_t* __restrict__ active,
     const double* __restrict__ X, int64_t xs, int nv, const double* __restrict__ xsc,
-    const double* __restrict__ coef, int cs, double* __restrict__ y,
-    double* __restrict__ partial, int64_t nl) {
-    __shared__ double sh[4];
+    const double* __restrict__ w, double* partial, int64_t nl, int32_t* cnt,
+    const int32_t* __restrict__ t0, int m, GmresScalars G) {
+    __shared__ double sh[4][NV + 1];
     const Tile t = vt[blockIdx.x];
-    double acc[NV];
+    double acc[NV + 1];
 #pragma unroll
-    for (int v = 0; v < NV; ++v) acc[v] = 0.0;
+    for (int v = 0; v <= NV; ++v) acc[v] = 0.0;
+    double nrm = 0.0;
     const bool on = !active || active[t.prob];
     const PatchInfo& p = P[t.patch];
     if (on) {
         double cf[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v) cf[v] = (v < nv) ? -1.0 * coef[t.prob * cs + v] : 0.0;
+        for (int v = 0; v < NV; ++v) cf[v] = (v < nv) ? -G.h1[t.prob * nv + v] : 0.0;
         const bool cov = p.flags & PF_COVERED;
         const double sc = xsc ? xsc[t.prob] : 1.0;
         for (int lin = t.start + threadIdx.x; lin < t.start + t.count; lin += kBlock) {
             const int c = interior_index(p, lin);
-            double a0 = y[c], a1 = y[c + nl];
+            if (cov && (ctype[c] & CT_COVERED)) continue;
+            double a0 = w[c], a1 = w[c + nl];
             double x0[NV], x1[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
@@ -282,63 +418,154 @@ __global__ __launch_bounds__(kBlock) void k_combine_dot(
                     a0 += cf[v] * x0[v];
                     a1 += cf[v] * x1[v];
                 }
-            y[c] = a0;
-            y[c + nl] = a1;
-            if (cov && (ctype[c] & CT_COVERED)) continue;
 #pragma unroll
             for (int v = 0; v < NV; ++v)
                 if (v < nv) acc[v] += x0[v] * a0 + x1[v] * a1;
+            nrm += a0 * a0 + a1 * a1;
         }
     }
 #pragma unroll
+    for (int v = 1; v <= NV; ++v)
+        if (v == nv) acc[v] = nrm;
+    block_sums<NV + 1>(acc, nv + 1, sh);
+    if (!cnt) {
+        if ((int)threadIdx.x <= nv)
+            partial[(int64_t)blockIdx.x * (nv + 1) + threadIdx.x] = sh[0][threadIdx.x] * p.vol;
+        return;
+    }
+    const int a = t0[t.prob], b = t0[t.prob + 1];
+    if (!last_of_problem(sh[0], nv + 1, p.vol, partial, cnt + t.prob, b - a)) return;
+    partial_sums<NV + 1>(partial, a, b, nv + 1, sh);
+    if (threadIdx.x == 0 && on) gs_finish(t.prob, m, nv - 1, sh[0], G);
+    if (threadIdx.x == 0 && !on) G.vscale[t.prob] = 0.0;
+}
+
+// The sums and the new column of every problem (one workgroup each).
+__global__ __launch_bounds__(kBlock) void k_gs_finish(const int32_t* __restrict__ t0,
+                                                      const int32_t* __restrict__ active,
+                                                      const double* __restrict__ partial, int nv,
+                                                      int m, GmresScalars G) {
+    __shared__ double sh[4][17];
+    const int p = blockIdx.x;
+    if (active && !active[p]) {
+        if (threadIdx.x == 0) G.vscale[p] = 0.0;
+        return;
+    }
+    partial_sums<17>(partial, t0[p], t0[p + 1], nv + 1, sh);
+    if (threadIdx.x == 0) gs_finish(p, m, nv - 1, sh[0], G);
+}
+
+void gs_again(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
+              const double* w, double* partial, int m, const GmresScalars& G,
+              const double* xsc) {
+    int32_t* cnt = fused_count(D);
+    NRD_BY_NV(nv, k_gs_again, D.nvtiles, s, D.vtiles, D.patches, D.ctype, D.active, X, xstride, nv,
+              xsc, w, partial, D.nl, cnt, D.prob_vtile0, m, G);
+    if (!cnt)
+        k_gs_finish<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, D.active, partial, nv, m, G);
+}
+
+// The next basis vector from the pass before: v_next = vscale (w - sum h1 v -
+// sum h2 v), the corrections applied one after the other as they were found.
+// With xsc (a basis of one vector read through its scale) v_0 itself is
+// written too.  f (may be NULL): v_next rounded to PT, the preconditioner's
+// right-hand side (colour-split where split is set), which saves the pass that
+// would read v_next for it.
+template <int NV, typename PT>
+__global__ __launch_bounds__(kBlock) void k_gs_next(
+    const Tile* __restrict__ vt, const PatchInfo* __restrict__ P,
+    const int32_t* __restrict__ active, double* __restrict__ X, int64_t xs, int nv,
+    const double* __restrict__ r, const double* __restrict__ xsc,
+    const double* __restrict__ h1, const double* __restrict__ h2,
+    const double* __restrict__ w, const double* __restrict__ vscale, PT* __restrict__ f,
+    int split, int64_t nl) {
+    const Tile t = vt[blockIdx.x];
+    if (active && !active[t.prob]) return;
+    const PatchInfo& p = P[t.patch];
+    double c1[NV], c2[NV];
+#pragma unroll
     for (int v = 0; v < NV; ++v) {
-        if (v < nv) {
-            const double sv = block_sum(acc[v], sh);
-            if (threadIdx.x == 0) partial[(int64_t)blockIdx.x * nv + v] = sv * p.vol;
+        c1[v] = (v < nv) ? -h1[t.prob * nv + v] : 0.0;
+        c2[v] = (v < nv) ? -h2[t.prob * nv + v] : 0.0;
+    }
+    const double sc = xsc ? xsc[t.prob] : 1.0, vs = vscale[t.prob];
+    double* out = X + nv * xs;
+    for (int lin = t.start + threadIdx.x; lin < t.start + t.count; lin += kBlock) {
+        int i, j, k;
+        const int c = interior_cell(p, lin, i, j, k);
+        double a0 = w[c], a1 = w[c + nl];
+        double x0[NV], x1[NV];
+        if (xsc) {
+            x0[0] = sc * r[c];
+            x1[0] = sc * r[c + nl];
+            X[c] = x0[0];
+            X[c + nl] = x1[0];
+        } else {
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                x0[v] = (v < nv) ? X[v * xs + c] : 0.0;
+                x1[v] = (v < nv) ? X[v * xs + c + nl] : 0.0;
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (v < nv && c1[v] != 0.0) {
+                a0 += c1[v] * x0[v];
+                a1 += c1[v] * x1[v];
+            }
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (v < nv && c2[v] != 0.0) {
+                a0 += c2[v] * x0[v];
+                a1 += c2[v] * x1[v];
+            }
+        a0 *= vs;
+        a1 *= vs;
+        out[c] = a0;
+        out[c + nl] = a1;
+        if (f) {
+            const int cx = split ? split_index(p, i + 1, j + 1, k + 1) : c;
+            f[cx] = (PT)a0;
+            f[cx + nl] = (PT)a1;
         }
     }
 }
 
-void combine_dot(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
-                 const double* coef, int cstride, double* y, double* partial, double* out,
-                 const double* xsc) {
-    if (nv > 16) {            // (never with xsc: scaled bases have one vector)
-        combine(D, s, X, xstride, nv, coef, cstride, y, 1, -1.0);
-        multidot(D, s, X, xstride, nv, y, partial, out);
-        return;
-    }
+template <typename PT>
+void gs_next(const Dev& D, hipStream_t s, double* X, int64_t xstride, int nv, const double* r,
+             const double* xsc, const double* h1, const double* h2, const double* w,
+             const double* vscale, PT* f, int split) {
+#define NRD_NEXT(NV)                                                                            \
+    k_gs_next<NV, PT><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.active, X, xstride, nv, \
+                                                   r, xsc, h1, h2, w, vscale, f, split, D.nl)
     if (nv <= 1)
-        k_combine_dot<1><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active, X,
-                                                      xstride, nv, xsc, coef, cstride, y, partial,
-                                                      D.nl);
+        NRD_NEXT(1);
     else if (nv <= 2)
-        k_combine_dot<2><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active, X,
-                                                      xstride, nv, xsc, coef, cstride, y, partial,
-                                                      D.nl);
+        NRD_NEXT(2);
     else if (nv <= 4)
-        k_combine_dot<4><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active, X,
-                                                      xstride, nv, xsc, coef, cstride, y, partial,
-                                                      D.nl);
+        NRD_NEXT(4);
     else if (nv <= 8)
-        k_combine_dot<8><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active, X,
-                                                      xstride, nv, xsc, coef, cstride, y, partial,
-                                                      D.nl);
+        NRD_NEXT(8);
     else
-        k_combine_dot<16><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       X, xstride, nv, xsc, coef, cstride, y, partial,
-                                                       D.nl);
-    k_sum_partials<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, partial, nv, out, nv);
+        NRD_NEXT(16);
+#undef NRD_NEXT
 }
+template void gs_next<float>(const Dev&, hipStream_t, double*, int64_t, int, const double*,
+                             const double*, const double*, const double*, const double*,
+                             const double*, float*, int);
+template void gs_next<double>(const Dev&, hipStream_t, double*, int64_t, int, const double*,
+                              const double*, const double*, const double*, const double*,
+                              const double*, double*, int);
 
 // y -= sum_v coef[p][v] x_v (accumulating into y) and, in the same pass,
 // out[p] = ||y||^2 (volume weighted over composite cells; fixed-order
-// two-stage sum).  The second Gram-Schmidt pass of FGMRES ends with the
-// norm of the orthogonalised vector, so this saves one pass over it.
+// two-stage sum): the end of the second Gram-Schmidt pass of FGMRES with a
+// basis of more than 16 vectors.
 template <int NV>
 __global__ __launch_bounds__(kBlock) void k_combine_norm(
     const Tile* __restrict__ vt, const PatchInfo* __restrict__ P,
     const uint8_t* __restrict__ ctype, const int32_t* __restrict__ active,
-    const double* __restrict__ X, int64_t xs, int nv, const double* __restrict__ xsc,
+    const double* __restrict__ X, int64_t xs, int nv,
     const double* __restrict__ coef, int cs, double* __restrict__ y,
     double* __restrict__ partial, int64_t nl) {
     __shared__ double sh[4];
@@ -351,15 +578,14 @@ __global__ __launch_bounds__(kBlock) void k_combine_norm(
 #pragma unroll
         for (int v = 0; v < NV; ++v) cf[v] = (v < nv) ? -coef[t.prob * cs + v] : 0.0;
         const bool cov = p.flags & PF_COVERED;
-        const double sc = xsc ? xsc[t.prob] : 1.0;
         for (int lin = t.start + threadIdx.x; lin < t.start + t.count; lin += kBlock) {
             const int c = interior_index(p, lin);
             double a0 = y[c], a1 = y[c + nl];
 #pragma unroll
             for (int v = 0; v < NV; ++v)
                 if (v < nv && cf[v] != 0.0) {
-                    a0 += cf[v] * (sc * X[v * xs + c]);
-                    a1 += cf[v] * (sc * X[v * xs + c + nl]);
+                    a0 += cf[v] * X[v * xs + c];
+                    a1 += cf[v] * X[v * xs + c + nl];
                 }
             y[c] = a0;
             y[c + nl] = a1;
@@ -371,31 +597,14 @@ __global__ __launch_bounds__(kBlock) void k_combine_norm(
 }
 
 void combine_norm(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
-                  const double* coef, int cstride, double* y, double* partial, double* out,
-                  const double* xsc) {
-    // more than 16 basis vectors: plain combines first, the norm with the last 16
+                  const double* coef, int cstride, double* y, double* partial, double* out) {
+    // plain combines first, the norm with the last 16
     int v0 = 0;
     for (; nv - v0 > 16; v0 += 16)
         combine(D, s, X + v0 * xstride, xstride, 16, coef + v0, cstride, y, 1, -1.0);
     const int c = nv - v0;
-    const double* Xc = X + v0 * xstride;
-    const double* cc = coef + v0;
-    if (c <= 1)
-        k_combine_norm<1><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       Xc, xstride, c, xsc, cc, cstride, y, partial,
-                                                       D.nl);
-    else if (c <= 4)
-        k_combine_norm<4><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       Xc, xstride, c, xsc, cc, cstride, y, partial,
-                                                       D.nl);
-    else if (c <= 8)
-        k_combine_norm<8><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                       Xc, xstride, c, xsc, cc, cstride, y, partial,
-                                                       D.nl);
-    else
-        k_combine_norm<16><<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, D.active,
-                                                        Xc, xstride, c, xsc, cc, cstride, y, partial,
-                                                        D.nl);
+    NRD_BY_NV(c, k_combine_norm, D.nvtiles, s, D.vtiles, D.patches, D.ctype, D.active,
+              X + v0 * xstride, xstride, c, coef + v0, cstride, y, partial, D.nl);
     k_sum_partials<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, partial, 1, out, 1);
 }
 
@@ -819,55 +1028,19 @@ void fd_quotient(const Dev& D, hipStream_t s, const double* sums, const double* 
 // ---------------------------------------------------------------------------
 
 __global__ void k_gmres_column(int nprob, int m, int j, const int32_t* __restrict__ active,
-                               const double* __restrict__ h1, const double* __restrict__ h2,
-                               const double* __restrict__ hn2, double* __restrict__ H,
-                               double* __restrict__ cs, double* __restrict__ sn,
-                               double* __restrict__ g, double* __restrict__ rho,
-                               double* __restrict__ vscale) {
+                               GmresScalars G) {
     const int p = blockIdx.x * blockDim.x + threadIdx.x;
     if (p >= nprob) return;
     if (active && !active[p]) {
-        vscale[p] = 0.0;
+        G.vscale[p] = 0.0;
         return;
     }
-    double* col = H + (int64_t)p * (m + 1) * m + (int64_t)(m + 1) * j;
-    double* c = cs + p * m;
-    double* s = sn + p * m;
-    double* gg = g + p * (m + 1);
-    for (int i = 0; i <= j; ++i) col[i] = h1[p * (j + 1) + i] + h2[p * (j + 1) + i];
-    const double hn = sqrt(hn2[p]);
-    col[j + 1] = hn;
-    for (int i = 0; i < j; ++i) {
-        const double tmp = c[i] * col[i] + s[i] * col[i + 1];
-        col[i + 1] = -s[i] * col[i] + c[i] * col[i + 1];
-        col[i] = tmp;
-    }
-    const double a = col[j], b = col[j + 1];
-    double cc, ss, r;
-    if (b == 0.0) {
-        cc = 1.0;
-        ss = 0.0;
-        r = a;
-    } else {
-        r = sqrt(a * a + b * b);
-        cc = a / r;
-        ss = b / r;
-    }
-    c[j] = cc;
-    s[j] = ss;
-    col[j] = r;
-    col[j + 1] = 0.0;
-    gg[j + 1] = -ss * gg[j];
-    gg[j] = cc * gg[j];
-    rho[p] = fabs(gg[j + 1]);
-    vscale[p] = hn > 0.0 ? 1.0 / hn : 0.0;
+    gmres_column_one(p, m, j, G.h1 + (int64_t)p * (j + 1), G.h2 + (int64_t)p * (j + 1), G.hn2[p], G);
 }
 
 void gmres_column(hipStream_t s, int nprob, int m, int j, const int32_t* active,
-                  const double* h1, const double* h2, const double* hn2, double* H, double* cs,
-                  double* sn, double* g, double* rho, double* vscale) {
-    k_gmres_column<<<(nprob + 63) / 64, 64, 0, s>>>(nprob, m, j, active, h1, h2, hn2, H, cs,
-                                                    sn, g, rho, vscale);
+                  const GmresScalars& G) {
+    k_gmres_column<<<(nprob + 63) / 64, 64, 0, s>>>(nprob, m, j, active, G);
 }
 
 __global__ void k_gmres_backsolve(int nprob, int m, const int32_t* __restrict__ kdim,

@@ -64,6 +64,37 @@ def test_precond_with_small_grids_in_one_workgroup(ext, precision, tol):
         assert rel_err(got[f], ref[f]) < tol
 
 
+# reduction tiles: 256 cells each up to the size that gives 512 of them, then
+# 512, 1024 and 2048; up to 256 tiles one launch sums them.  A batch: one
+# counter per problem.
+@pytest.mark.parametrize("exts", [[(12, 12, 12)], [(40, 40, 40)], [(48, 48, 48), (8, 8, 8)],
+                                  [(64, 64, 64)], [(128, 128, 96)]])
+def test_inner_products_of_every_tile_size(exts):
+    """nrd_dot against exactly rounded sums (math.fsum): pairwise error of a
+    tile's and the tiles' sums, well below n eps |x| |y|; twice, the counters
+    of the first call reused."""
+    import math
+    parts = [_box(e, seed=7 + i) for i, e in enumerate(exts)]
+    boxes = [I.Box(i, 0, p.boxes[0].lo, p.boxes[0].hi) for i, p in enumerate(parts)]
+    w = I.Workload("dots", [p.problems[0] for p in parts], boxes, [p.z[0] for p in parts],
+                   [p.E[0] for p in parts], [p.T[0] for p in parts], np.full(len(parts), 1e-3))
+    H = make(w, gmres_restart=2)
+    rng = np.random.default_rng(9)
+    n = w.ncells()
+    x, y = rng.standard_normal(2 * n), rng.standard_normal(2 * n)
+    gx, gy = native_from_compact(H, x), native_from_compact(H, y)
+    first = H.dot(gx, gy)
+    assert H.dot(gx, gy) == first
+    off = 0
+    for p, (b, pr) in enumerate(zip(boxes, w.problems)):
+        idx = np.r_[off:off + b.ncells, n + off:n + off + b.ncells]
+        off += b.ncells
+        vol = float(np.prod(pr.h()))
+        prod = x[idx] * y[idx]
+        ref = math.fsum(prod) * vol
+        assert abs(first[p] - ref) < 1e-13 * np.abs(prod).sum() * vol
+
+
 def test_newton_update_from_more_than_16_basis_vectors():
     """Steps whose Newton systems take more than 16 Krylov vectors in one
     cycle: every vector enters the update, so the iteration counts follow
@@ -76,3 +107,17 @@ def test_newton_update_from_more_than_16_basis_vectors():
         st.append(H.implicit_step([6e-3])[1][0])
     assert max(st[0]["krylov_per_newton"]) > 16
     assert abs(st[0]["newton_iters"] - st[1]["newton_iters"]) <= 1
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_gradient_with_a_long_krylov_basis(precision):
+    """Transposed solves to 1e-12 with a weak preconditioner: a basis of 64
+    (more than 16 vectors take the in-place passes) and one of 16 with
+    restarts solve the same systems, which the gradient keeps to 1e-9."""
+    w = I.marshak_single(16, state="front")
+    out = []
+    for m in (64, 16):
+        H = make(w, precision=precision, gmres_restart=m, gmres_maxrestarts=60, bdf_max_order=1,
+                 adjoint_slots=6, fac_base=1)
+        out.append(to_host(H.adjoint_run([2e-3], 1, 1)))
+    assert rel_err(out[0], out[1]) < 1e-9
