@@ -159,9 +159,11 @@ void combine(const Dev& D, hipStream_t s, const double* X, int64_t xstride,
              int nv, const double* coef, int cstride, double* y, int accumulate,
              double alpha);
 // Device arrays of the per-problem FGMRES scalars (H: [nprob][(m+1) * m],
-// column j at H[p][(m+1) j]; h1, h2: [nprob][j+1] of the current column).
+// column j at H[p][(m+1) j]; h1, h2: [nprob][j+1] of the current column).  rho
+// and hn2_host, which the host reads after every iteration, are pinned host
+// memory.
 struct GmresScalars {
-    double *h1, *h2, *hn2, *H, *cs, *sn, *g, *rho, *vscale;
+    double *h1, *h2, *hn2, *H, *cs, *sn, *g, *vscale, *rho, *hn2_host;
 };
 // Second Gram-Schmidt pass against nv <= 16 basis vectors, w untouched: h2 and
 // the norm of the twice corrected w, then column nv - 1 of every active problem
@@ -205,6 +207,19 @@ void bdf2_predict(const Dev& D, hipStream_t s, const double* c, const double* u,
 void scale_copy(const Dev& D, hipStream_t s, const double* x, const double* sc,
                 double* y);
 void copy_interior(const Dev& D, hipStream_t s, const double* x, double* y);
+// Arrays of 4- or 8-byte values to the device in one launch: segment q holds
+// `words` 4-byte words of data from word `first`, pairs of words `stride` words
+// apart at the destination (2: contiguous)
+constexpr int kPutSegs = 6, kPutSmall = 48, kPutLarge = 832;
+struct PutSeg { uint32_t* dst; int32_t words, first, stride, pad; };
+template <int W>
+struct PutArgs {
+    int32_t count = 0, used = 0;
+    PutSeg seg[kPutSegs];
+    uint32_t data[W];
+};
+void put(hipStream_t s, const PutArgs<kPutSmall>& a);
+void put(hipStream_t s, const PutArgs<kPutLarge>& a);
 void fill_native(hipStream_t s, double* x, int64_t n, double v);
 void fill_native_f(hipStream_t s, float* x, int64_t n, float v);
 void pack(const Dev& D, hipStream_t s, const int64_t* coff, const double* native,

@@ -2,9 +2,11 @@
 //
 // The host drives one lock-step inexact Newton / FGMRES iteration over all
 // problems of the hierarchy; all vector arithmetic, reductions and small
-// per-problem FGMRES updates run on the device.  The host reads back one
-// small per-problem array per Krylov iteration (the residual estimates)
-// and a few per Newton iteration (norms, positivity minima).
+// per-problem FGMRES updates run on the device.  The host reads one small
+// per-problem array per Krylov iteration (the residual estimates) and a few
+// per Newton iteration (norms, positivity minima), which the kernels write to
+// pinned host memory, and sends small arrays as launch arguments: copies to
+// and from pageable memory were a third of a 32^3 step.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -108,7 +110,7 @@ struct nrd_hierarchy final : public Clock {
         size_t z, z3, cur, prev, udot, bvec, x, F, s, w, tmp, tmp2, gzn, V, Z, pred;
         size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f, pc_shadow;
         size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG];
-        size_t partial, count, dots, h1, h2, hn2, H, cs, sn, g, rho, vscale, y, kdim, coefA, coefB,
+        size_t partial, count, h1, h2, hn2, H, cs, sn, g, vscale, y, kdim, coefA, coefB,
             minout, flag, ckpt, fdF, fdw, fdsum;
     } o;
     int32_t adjoint_slots = 0;
@@ -126,12 +128,20 @@ struct nrd_hierarchy final : public Clock {
     // device pointers
     double *z, *z3, *cur, *prev, *udot, *bvec, *x, *F, *s, *w, *tmp, *tmp2, *gzn, *V, *Z, *pred;
     std::vector<double> err_prev;   // per problem: last error norm (-1: none)
-    double *partial, *dots, *h1, *h2, *hn2, *H, *cs, *sn, *g, *rho, *vscale, *y, *coefA, *coefB,
+    double *partial, *h1, *h2, *hn2, *H, *cs, *sn, *g, *vscale, *y, *coefA, *coefB,
         *minout, *ckpt, *fdF, *fdw, *fdsum;
     const double* fd_base = nullptr;   // F at the Newton iterate (Jacobian-free mode)
     int32_t *kdim, *flag, *active;
     int32_t* amap;                  // stencil tiles of the active problems
     std::vector<int32_t> host_amap;
+    std::vector<int32_t> dev_active;   // flags last sent (empty: none)
+    // results the host waits for, one value per problem each, in pinned host
+    // memory that the kernels write
+    double* mail = nullptr;
+    double* mail_rho() const { return mail; }
+    double* mail_hn2() const { return mail + t.nprob; }
+    double* mail_dot() const { return mail + 2 * (size_t)t.nprob; }
+    double* mail_min() const { return mail + 3 * (size_t)t.nprob; }
     ProbScalars* ps;
     double* scratch = nullptr;      // device address of the fixed partial-sum array
     // timers
@@ -313,7 +323,6 @@ static void layout(nrd_hierarchy* h) {
     // reductions and per-problem scalars
     o.partial = b.take(8 * 17 * std::max<size_t>(1, t.vtiles.size()));
     o.count = b.take(4 * nprob);
-    o.dots = b.take(8 * nprob * (m + 2));
     o.h1 = b.take(8 * nprob * (m + 1));
     o.h2 = b.take(8 * nprob * (m + 1));
     o.hn2 = b.take(8 * nprob);
@@ -321,7 +330,6 @@ static void layout(nrd_hierarchy* h) {
     o.cs = b.take(8 * nprob * m);
     o.sn = b.take(8 * nprob * m);
     o.g = b.take(8 * nprob * (m + 1));
-    o.rho = b.take(8 * nprob);
     o.vscale = b.take(8 * nprob);
     o.y = b.take(8 * nprob * m);
     o.kdim = b.take(4 * nprob);
@@ -452,6 +460,11 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     // the fixed partial-sum array of nrd_dot_noalloc, on the device of this
     // workspace (the current device)
     HIPCHK(scratch_ptr(&h->scratch));
+    if (!h->mail) {
+        void* m = nullptr;
+        HIPCHK(hipHostMalloc(&m, sizeof(double) * 4 * h->t.nprob, hipHostMallocDefault));
+        h->mail = static_cast<double*>(m);
+    }
     h->ws = static_cast<char*>(ptr);
     Tables& t = h->t;
     auto& o = h->o;
@@ -645,7 +658,6 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     h->pred = h->at<double>(o.pred);
     h->err_prev.assign(t.nprob, -1.0);
     h->partial = h->at<double>(o.partial);
-    h->dots = h->at<double>(o.dots);
     h->h1 = h->at<double>(o.h1);
     h->h2 = h->at<double>(o.h2);
     h->hn2 = h->at<double>(o.hn2);
@@ -653,7 +665,6 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     h->cs = h->at<double>(o.cs);
     h->sn = h->at<double>(o.sn);
     h->g = h->at<double>(o.g);
-    h->rho = h->at<double>(o.rho);
     h->vscale = h->at<double>(o.vscale);
     h->y = h->at<double>(o.y);
     h->kdim = h->at<int32_t>(o.kdim);
@@ -673,6 +684,7 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
         counts(h->pcd.mg);
     }
     h->host_active.assign(t.nprob, 1);
+    h->dev_active.clear();
     HIPCHK(up(s, h->active, h->host_active));
     // per-problem constants (valid before the first begin_step)
     h->ps_host.assign(t.nprob, ProbScalars());
@@ -809,13 +821,61 @@ static void pc_apply_t(nrd_hierarchy* h, const double* w, double* y) {
         h->pcd.apply_transpose(h->stream, w, y);
 }
 
-// Sends the active flags to the device together with the list of stencil
-// tiles of the flagged problems, so masked residual and Jacobian launches
-// have no workgroups for finished problems (captured graphs keep reading the
-// flags: their launch sizes are fixed).
-static nrd_status upload_active(nrd_hierarchy* h) {
-    HIPCHK(hipMemcpyAsync(h->active, h->host_active.data(), 4 * h->t.nprob,
-                          hipMemcpyHostToDevice, h->stream));
+// Small host arrays on their way to the device; go() launches them all.
+struct Send {
+    nrd_hierarchy* h;
+    PutArgs<kPutLarge> a;
+    struct Big { void* dst; std::vector<char> src; int32_t stride; };
+    std::vector<Big> big;            // what does not fit the arguments
+
+    explicit Send(nrd_hierarchy* h_) : h(h_) {}
+    // stride: distance of consecutive 8-byte values in words (2: contiguous)
+    template <typename T>
+    void add(void* dst, const std::vector<T>& v, int32_t stride = 2) {
+        const size_t bytes = sizeof(T) * v.size();
+        if (bytes == 0) return;
+        const size_t words = bytes / 4;
+        if (a.count == kPutSegs || a.used + words > (size_t)kPutLarge) {
+            const char* p = reinterpret_cast<const char*>(v.data());
+            big.push_back({dst, std::vector<char>(p, p + bytes), stride});
+            return;
+        }
+        a.seg[a.count++] = {static_cast<uint32_t*>(dst), (int32_t)words, a.used, stride, 0};
+        std::memcpy(a.data + a.used, v.data(), bytes);
+        a.used += (int32_t)words;
+    }
+    nrd_status go() {
+        hipStream_t s = h->stream;
+        if (a.count > 0 && a.used <= kPutSmall) {
+            PutArgs<kPutSmall> b;
+            b.count = a.count;
+            b.used = a.used;
+            std::copy(a.seg, a.seg + kPutSegs, b.seg);
+            std::copy(a.data, a.data + a.used, b.data);
+            put(s, b);
+        } else if (a.count > 0) {
+            put(s, a);
+        }
+        for (Big& x : big) {
+            if (x.stride == 2)
+                HIPCHK(hipMemcpyAsync(x.dst, x.src.data(), x.src.size(), hipMemcpyHostToDevice, s));
+            else
+                HIPCHK(hipMemcpy2DAsync(x.dst, 4 * (size_t)x.stride, x.src.data(), 8, 8,
+                                        x.src.size() / 8, hipMemcpyHostToDevice, s));
+        }
+        if (!big.empty()) HIPCHK(hipStreamSynchronize(s));     // the sources end here
+        return NRD_OK;
+    }
+};
+
+// Adds the active flags, if they differ from those the device has, together
+// with the list of stencil tiles of the flagged problems, so masked residual
+// and Jacobian launches have no workgroups for finished problems (captured
+// graphs keep reading the flags: their launch sizes are fixed).
+static nrd_status add_active(nrd_hierarchy* h, Send& S) {
+    if (h->dev_active == h->host_active) return NRD_OK;
+    S.add(h->active, h->host_active);
+    h->dev_active = h->host_active;
     h->D.amap = nullptr;
     h->D.namap = 0;
     if (h->opt.use_graph) return NRD_OK;
@@ -836,17 +896,25 @@ static nrd_status upload_active(nrd_hierarchy* h) {
     h->D.namap = (int32_t)m.size();
     return NRD_OK;
 }
+static nrd_status upload_active(nrd_hierarchy* h) {
+    Send S(h);
+    RCHK(add_active(h, S));
+    return S.go();
+}
+
+// The values of a pinned array once the stream has written them.
+static nrd_status mailed(nrd_hierarchy* h, const double* mail, std::vector<double>& out) {
+    HIPCHK(hipStreamSynchronize(h->stream));
+    out.assign(mail, mail + h->t.nprob);
+    return NRD_OK;
+}
 
 // masked: only the problems of the current active mask (0 for the others)
 static nrd_status dot_host(nrd_hierarchy* h, const double* x, const double* y,
                            std::vector<double>& out, bool masked = false) {
     if (!masked) h->D.active = nullptr;
-    multidot(h->D, h->stream, x, 0, 1, y, h->partial, h->dots, nullptr, true);
-    out.resize(h->t.nprob);
-    HIPCHK(hipMemcpyAsync(out.data(), h->dots, 8 * h->t.nprob, hipMemcpyDeviceToHost,
-                          h->stream));
-    HIPCHK(hipStreamSynchronize(h->stream));
-    return NRD_OK;
+    multidot(h->D, h->stream, x, 0, 1, y, h->partial, h->mail_dot(), nullptr, true);
+    return mailed(h, h->mail_dot(), out);
 }
 
 // ---------------------------------------------------------------------------
@@ -880,17 +948,14 @@ static nrd_status begin_step(nrd_hierarchy* h, const double* dt, bool bdf1_only 
         b[p] = first ? 0.0 : -al * al / (1.0 + al);
     }
     hipStream_t s = h->stream;
-    HIPCHK(up(s, h->ps, h->ps_host));
     // b = a u_n + b u_{n-1}
-    std::vector<double> coef(2 * np);
-    for (int p = 0; p < np; ++p) {
-        coef[p] = a[p];
-        coef[np + p] = b[p];
-    }
-    HIPCHK(up(s, h->coefA, coef));
+    Send S(h);
+    S.add(h->ps, h->ps_host);
+    S.add(h->coefA, a);
+    S.add(h->coefA + np, b);
+    RCHK(S.go());
     h->D.active = nullptr;
     lincomb2(h->D, s, h->coefA, h->cur, h->coefA + np, h->prev, h->bvec);
-    HIPCHK(hipStreamSynchronize(s));
     h->step_ready = true;
     return NRD_OK;
 }
@@ -921,7 +986,7 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
     hipStream_t s = h->stream;
     std::vector<int32_t> outer = h->host_active;           // problems asked to solve
     its.assign(np, 0);
-    std::vector<double> beta0(np), rho(np), inv(np);
+    std::vector<double> beta0(np), inv(np);
     std::vector<int32_t> kd(np);
     if (pending) pending->clear();
     bool sol_set = false;        // sol holds the corrections of earlier cycles
@@ -942,19 +1007,18 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
                 vjp_full(h->D, s, u, h->tmp2, h->tmp, h->gzn);
             }
             copy_interior(h->D, s, rhs, h->w);
-            std::vector<double> mone(np, -1.0), pone(np, 1.0);
-            HIPCHK(up(s, h->coefA, mone));
-            HIPCHK(up(s, h->coefB, pone));
+            Send S(h);
+            S.add(h->coefA, std::vector<double>(np, -1.0));
+            S.add(h->coefB, std::vector<double>(np, 1.0));
+            RCHK(S.go());
             axpby(h->D, s, h->coefA, h->tmp, h->coefB, h->w);
         }
         std::vector<double> b2;
         if (cycle == 0 && b2_first) {
             b2 = *b2_first;
         } else {
-            multidot(h->D, s, r, 0, 1, r, h->partial, h->dots, nullptr, true);
-            b2.resize(np);
-            HIPCHK(hipMemcpyAsync(b2.data(), h->dots, 8 * np, hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
+            multidot(h->D, s, r, 0, 1, r, h->partial, h->mail_dot(), nullptr, true);
+            RCHK(mailed(h, h->mail_dot(), b2));
         }
         bool any = false;
         for (int p = 0; p < np; ++p) {
@@ -969,16 +1033,16 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
         }
         if (!any) break;
         h->host_active = todo;
-        RCHK(upload_active(h));
-        HIPCHK(up(s, h->coefA, inv));
+        Send S(h);
+        RCHK(add_active(h, S));
+        S.add(h->coefA, inv);
+        S.add(h->g, beta0, 2 * (m + 1));        // the rest of g is written before it is read
+        RCHK(S.go());
         // v_0 = r / beta.  On a forward solve's first cycle r (the right-hand
         // side) stays untouched, so iteration 0 reads r scaled by 1/beta
         // (coefA) in place of v_0 and v_0 is formed only if iteration 1 runs.
         const bool v0_lazy = cycle == 0 && !transpose;
         if (!v0_lazy) scale_copy(h->D, s, r, h->coefA, h->V);
-        std::vector<double> g0((size_t)np * (m + 1), 0.0);
-        for (int p = 0; p < np; ++p) g0[(size_t)p * (m + 1)] = beta0[p];
-        HIPCHK(up(s, h->g, g0));
         std::vector<int32_t> live = todo;
         for (int p = 0; p < np; ++p) kd[p] = 0;
         for (int j = 0; j < m; ++j) {
@@ -994,8 +1058,8 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
                 double* Vj = h->V + j * NL;
                 double* Zj = h->Z + j * NL;
                 double* wv = h->w;
-                const GmresScalars G{h->h1, h->h2, h->hn2, h->H,  h->cs,
-                                     h->sn, h->g,  h->rho, h->vscale};
+                const GmresScalars G{h->h1, h->h2, h->hn2,    h->H,          h->cs,
+                                     h->sn, h->g,  h->vscale, h->mail_rho(), h->mail_hn2()};
                 // the previous iteration read r with 1/beta in place of v_0
                 const bool was_lazy = j == 1 && v0_lazy;
                 bool ready = false;      // the preconditioner's input is in place
@@ -1064,10 +1128,8 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
             } else {
                 iteration();
             }
-            std::vector<double> hn(np);
-            HIPCHK(hipMemcpyAsync(rho.data(), h->rho, 8 * np, hipMemcpyDeviceToHost, s));
-            HIPCHK(hipMemcpyAsync(hn.data(), h->hn2, 8 * np, hipMemcpyDeviceToHost, s));
             HIPCHK(hipStreamSynchronize(s));
+            const double *rho = h->mail_rho(), *hn = h->mail_hn2();
             bool left = false;
             for (int p = 0; p < np; ++p) {
                 if (!live[p]) continue;
@@ -1088,8 +1150,12 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
         std::vector<int32_t> did(np, 0);
         for (int p = 0; p < np; ++p) did[p] = kd[p] > 0;
         h->host_active = did;
-        RCHK(upload_active(h));
-        HIPCHK(up(s, h->kdim, kd));
+        {
+            Send S(h);
+            RCHK(add_active(h, S));
+            S.add(h->kdim, kd);
+            RCHK(S.go());
+        }
         gmres_backsolve(s, np, m, h->kdim, h->H, h->g, h->y);
         int kmax = *std::max_element(kd.begin(), kd.end());
         bool rem = false;
@@ -1132,9 +1198,7 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
         combine(h->D, s, nullptr, 0, 0, h->coefA, 0, sol, 0, 1.0);
     }
     h->host_active = outer;
-    RCHK(upload_active(h));
-    HIPCHK(hipStreamSynchronize(s));
-    return NRD_OK;
+    return upload_active(h);
 }
 
 // ---------------------------------------------------------------------------
@@ -1240,9 +1304,9 @@ static nrd_status newton(nrd_hierarchy* h, std::vector<nrd_step_stats>& st) {
             h->host_active = did;
             RCHK(upload_active(h));
             h->D.active = h->active;
-            update_min(h->D, s, h->Z, NL, kmax, h->y, m, h->x, h->tmp, h->partial, h->minout);
-            HIPCHK(hipMemcpyAsync(mn.data(), h->minout, 8 * np, hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
+            update_min(h->D, s, h->Z, NL, kmax, h->y, m, h->x, h->tmp, h->partial,
+                       h->mail_min());
+            RCHK(mailed(h, h->mail_min(), mn));
             bool any_bad = false;
             for (int p = 0; p < np; ++p) {
                 if (!act[p]) continue;
@@ -1272,13 +1336,14 @@ static nrd_status newton(nrd_hierarchy* h, std::vector<nrd_step_stats>& st) {
                 searching |= h->host_active[p] != 0;
             }
             if (!searching) break;
-            RCHK(upload_active(h));
             for (int p = 0; p < np; ++p) mlam[p] = -lam[p];      // step = -lam s
-            HIPCHK(up(s, h->coefA, mlam));
+            Send S(h);
+            RCHK(add_active(h, S));
+            S.add(h->coefA, mlam);
+            RCHK(S.go());
             h->D.active = h->active;
-            min_positive(h->D, s, h->x, h->s, h->coefA, h->partial, h->minout);
-            HIPCHK(hipMemcpyAsync(mn.data(), h->minout, 8 * np, hipMemcpyDeviceToHost, s));
-            HIPCHK(hipStreamSynchronize(s));
+            min_positive(h->D, s, h->x, h->s, h->coefA, h->partial, h->mail_min());
+            RCHK(mailed(h, h->mail_min(), mn));
             for (int p = 0; p < np; ++p) {
                 if (!h->host_active[p]) continue;
                 if (mn[p] > 0.0) {
@@ -1298,11 +1363,12 @@ static nrd_status newton(nrd_hierarchy* h, std::vector<nrd_step_stats>& st) {
             step |= h->host_active[p] != 0;
         }
         if (step) {
-            RCHK(upload_active(h));
-            std::vector<double> one(np, 1.0);
             for (int p = 0; p < np; ++p) mlam[p] = -lam[p];
-            HIPCHK(up(s, h->coefA, mlam));
-            HIPCHK(up(s, h->coefB, one));
+            Send S(h);
+            RCHK(add_active(h, S));
+            S.add(h->coefA, mlam);
+            S.add(h->coefB, std::vector<double>(np, 1.0));
+            RCHK(S.go());
             h->D.active = h->active;
             axpby(h->D, s, h->coefA, h->s, h->coefB, h->x);
         }
@@ -1358,17 +1424,18 @@ static nrd_status implicit_step(nrd_hierarchy* h, const double* dt, nrd_step_sta
             buf[np + p] = bdf2 ? a * a : 0.0;
             buf[2 * np + p] = bdf2 ? -a * a : 0.0;
         }
-        HIPCHK(up(s, h->coefA, buf));
+        Send S(h);
+        S.add(h->coefA, buf);
+        S.add(h->coefB, std::vector<double>(np, 0.0));
+        RCHK(S.go());
         // written straight into the Newton iterate, with its copy for the
         // error estimate
         bdf2_predict(h->D, s, h->coefA, h->cur, h->udot, h->prev, h->x,
                      h->opt.error_estimate ? h->pred : nullptr);
         // a BDF2 problem whose predictor is not positive starts from u_n
-        std::vector<double> zero(np, 0.0), mn(np);
-        HIPCHK(up(s, h->coefB, zero));
-        min_positive(h->D, s, h->x, h->x, h->coefB, h->partial, h->minout);
-        HIPCHK(hipMemcpyAsync(mn.data(), h->minout, 8 * np, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        std::vector<double> mn;
+        min_positive(h->D, s, h->x, h->x, h->coefB, h->partial, h->mail_min());
+        RCHK(mailed(h, h->mail_min(), mn));
         std::vector<int32_t> back(np);
         bool any_back = false;
         for (int p = 0; p < np; ++p) {
@@ -1399,14 +1466,15 @@ static nrd_status implicit_step(nrd_hierarchy* h, const double* dt, nrd_step_sta
             cf[p] = (a + 1.0) / (3.0 * a + 2.0);
             h->host_active[p] = a > 0.0;
         }
-        RCHK(upload_active(h));
-        HIPCHK(up(s, h->coefA, cf));
+        Send S(h);
+        RCHK(add_active(h, S));
+        S.add(h->coefA, cf);
+        RCHK(S.go());
         h->D.active = h->active;
         err_norm(h->D, s, h->x, h->pred, h->coefA, h->opt.err_eta_E, h->opt.err_eta_T,
-                 h->partial, h->minout);
+                 h->partial, h->mail_min());
         h->D.active = nullptr;
-        HIPCHK(hipMemcpyAsync(en.data(), h->minout, 8 * np, hipMemcpyDeviceToHost, s));
-        HIPCHK(hipStreamSynchronize(s));
+        RCHK(mailed(h, h->mail_min(), en));
         h->host_active.assign(np, 1);
         RCHK(upload_active(h));
         for (int p = 0; p < np; ++p)
@@ -1424,7 +1492,11 @@ static nrd_status implicit_step(nrd_hierarchy* h, const double* dt, nrd_step_sta
         buf[p] = h->c0[p] / dt[p];
         buf[np + p] = -1.0 / dt[p];
     }
-    HIPCHK(up(s, h->coefA, buf));
+    {
+        Send S(h);
+        S.add(h->coefA, buf);
+        RCHK(S.go());
+    }
     lincomb2(h->D, s, h->coefA, h->x, h->coefA + np, h->bvec, h->udot);
     std::swap(h->prev, h->cur);       // prev <- u_n
     std::swap(h->cur, h->x);          // cur <- u_{n+1}
@@ -1505,7 +1577,12 @@ static nrd_status adjoint_run(nrd_hierarchy* h, const double* dt, int nsteps, in
         h->ps_host[p].beta = dt[p];
         h->ps_host[p].alpha = 0.0;
     }
-    HIPCHK(up(s, h->ps, h->ps_host));
+    auto send_ps = [&]() {
+        Send S(h);
+        S.add(h->ps, h->ps_host);
+        return S.go();
+    };
+    RCHK(send_ps());
     for (int segi = nck - 1; segi >= 0; --segi) {
         const int n0 = segi * every;
         const int n1 = std::min(nsteps, n0 + every);
@@ -1523,7 +1600,7 @@ static nrd_status adjoint_run(nrd_hierarchy* h, const double* dt, int nsteps, in
             h->ps_host[p].c0 = 1.0;
             h->ps_host[p].beta = dt[p];
         }
-        HIPCHK(up(s, h->ps, h->ps_host));
+        RCHK(send_ps());
         for (int n = n1; n > n0; --n) {
             // the linearisation point goes to the Newton iterate's buffer,
             // which the recomputation no longer needs (and which captured
@@ -1546,9 +1623,10 @@ static nrd_status adjoint_run(nrd_hierarchy* h, const double* dt, int nsteps, in
             if (rc) return rc;
             // grad -= lam^T dF/dz ; next rhs = lam
             vjp_full(h->D, s, un, lam, h->w, h->gzn);
-            std::vector<double> mone(np, -1.0), one(np, 1.0);
-            HIPCHK(up(s, h->coefA, mone));
-            HIPCHK(up(s, h->coefB, one));
+            Send S(h);
+            S.add(h->coefA, std::vector<double>(np, -1.0));
+            S.add(h->coefB, std::vector<double>(np, 1.0));
+            RCHK(S.go());
             // gacc (field 0 only used) += -gz : use a 2-field axpby on (gz | scratch)
             {
                 // gz is a single field; place it in tmp field 0, zero field 1
@@ -1760,6 +1838,7 @@ nrd_status nrd_hierarchy_destroy(nrd_hierarchy* h) {
     if (!h) return NRD_OK;
     h->drop_graphs();
     if (h->cap_stream) (void)hipStreamDestroy(h->cap_stream);
+    if (h->mail) (void)hipHostFree(h->mail);
     for (hipEvent_t e : h->ev_pool) (void)hipEventDestroy(e);
     delete h;
     return NRD_OK;
@@ -2177,6 +2256,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
     HIPCHK(up(s, h->ws + h->o.stiles, t.stiles));
     for (int l = 0; l <= t.nlev; ++l) h->D.level_stile0[l] = t.level_stile0[l];
     h->drop_graphs();                               // captured launches used the old tiles
+    h->dev_active.clear();
     RCHK(upload_active(h));                         // tile map of the new list
     HIPCHK(hipStreamSynchronize(s));
     return NRD_OK;
@@ -2195,10 +2275,11 @@ static nrd_status set_udot(nrd_hierarchy* h, const double* x) {
         buf[p] = h->c0[p] / h->dt_cur[p];
         buf[np + p] = -1.0 / h->dt_cur[p];
     }
-    HIPCHK(up(s, h->coefA, buf));
+    Send S(h);
+    S.add(h->coefA, buf);
+    RCHK(S.go());
     h->D.active = nullptr;
     lincomb2(h->D, s, h->coefA, x, h->coefA + np, h->bvec, h->udot);
-    HIPCHK(hipStreamSynchronize(s));      // the host coefficient buffer ends here
     return NRD_OK;
 }
 
@@ -2369,7 +2450,11 @@ nrd_status nrd_resolve(nrd_hierarchy* h, nrd_step_stats* stats) {
     if (!h->resolve_ready) return NRD_OK;
     hipStream_t s = h->stream;
     h->D.active = nullptr;
-    HIPCHK(up(s, h->ps, h->ps_host));
+    {
+        Send S(h);
+        S.add(h->ps, h->ps_host);
+        RCHK(S.go());
+    }
     copy_interior(h->D, s, h->cur, h->x);
     std::vector<nrd_step_stats> st;
     const nrd_status rc = newton(h, st);

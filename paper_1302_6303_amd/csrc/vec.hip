@@ -356,8 +356,8 @@ __device__ __forceinline__ void gmres_column_one(int p, int m, int j, const doub
     col[j + 1] = 0.0;
     gg[j + 1] = -ss * gg[j];
     gg[j] = cc * gg[j];
-    G.rho[p] = fabs(gg[j + 1]);
-    G.hn2[p] = hn2;
+    G.rho[p] = fabs(gg[j + 1]);       // host memory, as is hn2_host
+    G.hn2_host[p] = hn2;
     G.vscale[p] = hn > 0.0 ? 1.0 / hn : 0.0;
 }
 
@@ -840,6 +840,20 @@ void copy_interior(const Dev& D, hipStream_t s, const double* x, double* y) {
     k_scale_copy<<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.active, x, nullptr, y,
                                               D.nl);
 }
+
+// Small host arrays to the device, carried in the launch's own arguments: a
+// copy from pageable memory costs the host about 15 us, this one a launch, and
+// all arrays that a step of the solver needs go in one.
+template <int W>
+__global__ __launch_bounds__(kBlock) void k_put(const PutArgs<W> a) {
+    for (int q = 0; q < a.count; ++q) {
+        const PutSeg g = a.seg[q];
+        for (int i = threadIdx.x; i < g.words; i += kBlock)
+            g.dst[(i >> 1) * (int64_t)g.stride + (i & 1)] = a.data[g.first + i];
+    }
+}
+void put(hipStream_t s, const PutArgs<kPutSmall>& a) { k_put<kPutSmall><<<1, kBlock, 0, s>>>(a); }
+void put(hipStream_t s, const PutArgs<kPutLarge>& a) { k_put<kPutLarge><<<1, kBlock, 0, s>>>(a); }
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_fill(T* __restrict__ x, int64_t n, T v) {
