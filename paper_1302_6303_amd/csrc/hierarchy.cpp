@@ -545,6 +545,18 @@ nrd_status build_tables(const nrd_problem* probs, int32_t nprob,
         rc.first = (int32_t)i;
         rc.count = (int32_t)(j - i);
         rc.prob = t.patches[t.rfaces[i].fpatch].prob;
+        {
+            // the patch whose block holds the cell (blocks lie in patch order)
+            const auto it = std::upper_bound(
+                t.patches.begin(), t.patches.end(), rc.c,
+                [](int32_t c, const PatchInfo& q) { return c < q.off; });
+            rc.patch = (int32_t)(it - t.patches.begin()) - 1;
+            const PatchInfo& op = t.patches[rc.patch];
+            const int32_t q = rc.c - op.off;
+            rc.id[0] = q % op.sy - 1;
+            rc.id[1] = q % op.sz / op.sy - 1;
+            rc.id[2] = q / op.sz - 1;
+        }
         t.rcells.push_back(rc);
         i = j;
     }

@@ -101,7 +101,7 @@ struct Dev {
 // ghosts of every patch (physical ghosts are never read).
 void ghost_fill_d(const Dev& D, hipStream_t s, double* x, int nf);
 void ghost_fill_f(const Dev& D, hipStream_t s, float* x, int nf);
-// covered cells <- mean of children, finest level first
+// covered cells <- mean of children, finest level first (levels lev_lo and up)
 void restrict_d(const Dev& D, hipStream_t s, double* x, int nf, int lev_lo = 0);
 void restrict_f(const Dev& D, hipStream_t s, float* x, int nf, int lev_lo = 0);
 // adjoint fill of a multiplier vector's two fields: sibling copies, 1/8 of

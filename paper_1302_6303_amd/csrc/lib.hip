@@ -108,7 +108,7 @@ struct nrd_hierarchy final : public Clock {
         size_t mg_box[kMaxMG], mg_tiles[kMaxMG], mg_box_of[kMaxMG], mg_smooth[kMaxMG],
             tails, Xbuf, mg_l0map, ltiles;
         size_t z, z3, cur, prev, udot, bvec, x, F, s, w, tmp, tmp2, gzn, V, Z, pred;
-        size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f, pc_shadow;
+        size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f;
         size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG];
         size_t partial, count, h1, h2, hn2, H, cs, sn, g, vscale, y, kdim, coefA, coefB,
             minout, flag, ckpt, fdF, fdw, fdsum;
@@ -313,7 +313,6 @@ static void layout(nrd_hierarchy* h) {
     o.pc_u = b.take(es * 2 * nl);
     o.pc_r = b.take(es * 2 * nl);
     o.pc_f = b.take(es * 2 * nl);
-    o.pc_shadow = b.take(es * 2 * std::max<int64_t>(1, t.shadow_len));
     for (int g = 1; g <= G; ++g) {
         const int64_t n = t.mg[g].len;
         o.mg_D[g] = b.take(es * 6 * n);
@@ -419,10 +418,8 @@ static void wire_pc(nrd_hierarchy* h, PcArrays<PT>& pc) {
     pc.u = h->at<PT>(o.pc_u);
     pc.r = h->at<PT>(o.pc_r);
     pc.f = h->at<PT>(o.pc_f);
-    pc.shadow = h->at<PT>(o.pc_shadow);
     pc.shadow_src = h->at<int32_t>(o.shadow_src);
     pc.shadows = h->at<ShadowPatch>(o.shadows);
-    pc.shadow_len = std::max<int64_t>(1, t.shadow_len);
     const int G = (int)t.mg.size() - 1;
     pc.mg.G = G;
     for (int g = 0; g <= G; ++g) {
@@ -804,13 +801,13 @@ static void pc_setup(nrd_hierarchy* h, double* u, bool prepared) {
         h->pcd.setup(h->stream, u);
 }
 
-static void pc_apply(nrd_hierarchy* h, const double* w, double* y,
-                     const double* wsc = nullptr) {
+static void pc_apply(nrd_hierarchy* h, const double* w, double* y, const double* wsc,
+                     bool covered) {
     auto tk = h->tic(NRD_TIMER_PRECOND);
     if (h->mixed)
-        h->pcf.apply(h->stream, w, y, wsc);
+        h->pcf.apply(h->stream, w, y, wsc, covered);
     else
-        h->pcd.apply(h->stream, w, y, wsc);
+        h->pcd.apply(h->stream, w, y, wsc, covered);
     h->toc(NRD_TIMER_PRECOND, tk);
 }
 
@@ -1072,17 +1069,18 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
                                         nullptr, 0);
                     else if (h->mixed)
                         gs_next<float>(h->D, s, h->V, NL, j, r, xsc, h->h1, h->h2, wv, h->vscale,
-                                       h->pcf.f, h->pcf.split0);
+                                       h->pcf.input(), h->pcf.split0);
                     else
                         gs_next<double>(h->D, s, h->V, NL, j, r, xsc, h->h1, h->h2, wv, h->vscale,
-                                        h->pcd.f, h->pcd.split0);
+                                        h->pcd.input(), h->pcd.split0);
                     ready = !transpose;
                 }
                 // the basis read by this iteration: v_0 .. v_j, or r with 1/beta
                 const double* Vb = (j == 0 && v0_lazy) ? r : h->V;
                 const double* vsc = (j == 0 && v0_lazy) ? h->coefA : nullptr;
                 if (!transpose) {
-                    pc_apply(h, ready ? nullptr : (j == 0 && v0_lazy) ? r : Vj, Zj, vsc);
+                    // (the Jacobian action restricts Zj, so its covered cells may be left)
+                    pc_apply(h, ready ? nullptr : (j == 0 && v0_lazy) ? r : Vj, Zj, vsc, false);
                     op_jvp(h, u, Zj, wv, true);
                 } else {
                     pc_apply_t(h, Vj, Zj);
@@ -1965,7 +1963,7 @@ nrd_status nrd_precond_apply(nrd_hierarchy* h, const double* w, double* y) {
     NEED_BOUND(h);
     if (!h->step_ready) return fail(NRD_ESTATE, "call nrd_begin_step first");
     h->D.active = nullptr;
-    pc_apply(h, w, y);
+    pc_apply(h, w, y, nullptr, true);
     HIPCHK(hipGetLastError());
     return NRD_OK;
 }

@@ -73,7 +73,7 @@ struct RefluxFace {
     int32_t fpatch;
 };
 // Coarse cells with refluxed faces, CSR into RefluxFace.
-struct RefluxCell { int32_t c, first, count, prob; };
+struct RefluxCell { int32_t c, first, count, prob, patch, id[3]; };
 // Transposed coarse-fine interpolation: the coarse cells that feed
 // coarse-fine ghosts, CSR into the ghosts they feed with the tangential
 // weight (9, 3, 3 or 1) of the bilinear stencil.

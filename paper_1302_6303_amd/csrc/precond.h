@@ -99,10 +99,9 @@ struct PcArrays {
     PT* u = nullptr;
     PT* r = nullptr;
     PT* f = nullptr;
-    PT* shadow = nullptr;       // 2 * shadow_len
+    // per refined patch: the map of the coarse cells its prolongation reads
     const int32_t* shadow_src = nullptr;
     const ShadowPatch* shadows = nullptr;
-    int64_t shadow_len = 0;
     struct MGArr {
         int G = 0;
         const PatchInfo* box[kMaxMG] = {};
@@ -140,21 +139,23 @@ struct PcArrays {
                                      // line smoother, AFACx coarse approximations
     Clock* clock = nullptr;     // times the base grid's sweeps
 
-    void zero(hipStream_t s) const;
     void setup(hipStream_t s, const double* u_state) const;
     // y = P^-1 (wsc_p w); wsc (per problem, may be NULL) scales the input as
     // it is read
-    // w NULL: f already holds the input
-    void apply(hipStream_t s, const double* w, double* y, const double* wsc = nullptr) const;
+    // w NULL: input() already holds it; covered: the covered cells of y take
+    // part (else they are left as the cycle leaves them)
+    void apply(hipStream_t s, const double* w, double* y, const double* wsc, bool covered) const;
+    // where the cycle reads its input, in PT (colour-split when split0)
+    PT* input() const { return fac_cycle == NRD_FAC_AFACX ? r : f; }
     void apply_transpose(hipStream_t s, const double* w, double* y) const;
-    const PT* fac(hipStream_t s) const;     // returns u or e (one level)
-    const PT* afacx(hipStream_t s) const;   // returns e
-    const PT* p1(hipStream_t s) const;      // the configured cycle
+    const PT* fac(hipStream_t s, bool covered) const;    // returns u or e (one level)
+    const PT* afacx(hipStream_t s, bool covered) const;  // returns e
+    const PT* p1(hipStream_t s, bool covered) const;     // the configured cycle
     TailGrids<PT> tail_grids() const;
     void vcycle(hipStream_t s) const;
     void composite_residual(hipStream_t s, int lev) const;
     void smooth_level(hipStream_t s, const PT* rhs, int lev, int sweeps) const;
-    void correct_level(hipStream_t s, int lev) const;
+    void correct_level(hipStream_t s, int lev, bool last) const;
     void fill_ghosts(hipStream_t s, PT* x) const;
     void restrict_(hipStream_t s, PT* x, int lev_lo) const;
     // sibling ghosts of levels lev .. lev_hi (lev_hi < 0: lev only)

@@ -465,31 +465,19 @@ __global__ __launch_bounds__(kBlock) void k_level_res(const int32_t* __restrict_
 // skipped here and supplied by k_comp_reflux.
 // ---------------------------------------------------------------------------
 
+// Both fields of one composite cell without the fluxes that flux matching
+// supplies (bit f + 1 of ct: face f).
 template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_comp_res(const int32_t* __restrict__ act, 
-    const Tile* __restrict__ tiles, const PatchInfo* __restrict__ P,
-    const ProbScalars* __restrict__ ps, const uint8_t* __restrict__ ctype,
-    const PT* __restrict__ D, const PT* __restrict__ f, const PT* __restrict__ u,
-    PT* __restrict__ r, int64_t nl) {
-    const Tile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
-    if (act && !act[t.prob]) return;           // problem not being solved
-    if ((int)threadIdx.x >= t.count) return;
-    const PatchInfo& p = P[t.patch];
-    int id[3];
-    coords(p, t.start + threadIdx.x, id[0], id[1], id[2]);
-    const int c = nat(p, id[0], id[1], id[2]);
-    const int ct = (p.flags & PF_CTYPE) ? ctype[c] : 0;
-    if (ct & CT_COVERED) {
-        r[c] = PT(0);
-        r[c + nl] = PT(0);
-        return;
-    }
-    const double beta = ps[t.prob].beta;
+__device__ __forceinline__ void comp_cell(const PatchInfo& p, const int id[3], int c, int ct,
+                                          double beta, const PT* __restrict__ D,
+                                          const PT* __restrict__ f, const PT* __restrict__ u,
+                                          int64_t nl, PT out[2]) {
     const int st[3] = {1, p.sy, p.sz};
     // faces classified with selects (operands loaded unconditionally; ghost
     // slots are finite): a physical face carries the Marshak flux of E or
     // nothing, a face whose flux comes from flux matching nothing, any other
     // face the flux D (u_b - u_a) / h
+#pragma unroll
     for (int fld = 0; fld < 2; ++fld) {
         const PT* uf = u + fld * nl;
         const PT uc = uf[c];
@@ -515,40 +503,75 @@ __global__ __launch_bounds__(kBlock) void k_comp_res(const int32_t* __restrict__
             }
             div += (hi - lo) * ih;
         }
-        r[fld * nl + c] = f[fld * nl + c] - (uc - (PT)beta * div);
+        out[fld] = f[fld * nl + c] - (uc - (PT)beta * div);
     }
 }
 
+// The first nt workgroups: the cells of the tiles that border no finer level
+// (covered cells 0).  The others: the coarse cells that do, four lanes each
+// (the quad shares the cell's loop bounds, lane q takes fine face q of every
+// matched face), levels lev and up.  One launch for both: the matched cells
+// used to be written by the first kind and read again by a launch of the
+// second (13 + 7 us on a hierarchy of 1 M cells, 17 now).
 template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_comp_reflux(
-    const RefluxCell* __restrict__ rc, int n, const RefluxFace* __restrict__ rf,
-    const PatchInfo* __restrict__ P, const ProbScalars* __restrict__ ps,
-    const PT* __restrict__ D, const PT* __restrict__ u, PT* __restrict__ r, int64_t nl) {
-    // four lanes per coarse cell (the quad shares the cell's loop bounds)
-    const int t = (blockIdx.x * blockDim.x + threadIdx.x) >> 2;
-    const int k = threadIdx.x & 3;
-    if (t >= n) return;
-    const RefluxCell cell = rc[t];
-    const double beta = ps[cell.prob].beta;
-    for (int fld = 0; fld < 2; ++fld) {
-        const PT* uf = u + fld * nl;
-        PT acc = PT(0);
-        for (int e = cell.first; e < cell.first + cell.count; ++e) {
-            const int face = rf[e].face;
-            const int d = face >> 1;
-            const bool hi = face & 1;
-            const PatchInfo& fp = P[rf[e].fpatch];
-            const PT* Dd = D + (fld * 3 + d) * nl;
-            const PT ih = (PT)fp.ih[d];
-            const int fi = rf[e].fine[k];
-            const int g = fi + rf[e].gofs;
-            // fine face: lower cell a, upper cell b; its D sits at b's slot
-            const int a = hi ? g : fi;
-            const int b = hi ? fi : g;
-            const PT sum = quad_sum(Dd[b] * (uf[b] - uf[a]) * ih);
-            acc += (hi ? PT(1) : PT(-1)) * PT(0.25) * sum * (PT(0.5) * ih);
+__global__ __launch_bounds__(kBlock) void k_comp_res(const int32_t* __restrict__ act,
+    const Tile* __restrict__ tiles, int nt, const PatchInfo* __restrict__ P,
+    const ProbScalars* __restrict__ ps, const uint8_t* __restrict__ ctype,
+    const RefluxCell* __restrict__ rc, int nrc, const RefluxFace* __restrict__ rf, int lev,
+    const PT* __restrict__ D, const PT* __restrict__ f, const PT* __restrict__ u,
+    PT* __restrict__ r, int64_t nl) {
+    if ((int)blockIdx.x < nt) {
+        const Tile t = tiles[xcd_tile(blockIdx.x, nt)];
+        if (act && !act[t.prob]) return;           // problem not being solved
+        if ((int)threadIdx.x >= t.count) return;
+        const PatchInfo& p = P[t.patch];
+        int id[3];
+        coords(p, t.start + threadIdx.x, id[0], id[1], id[2]);
+        const int c = nat(p, id[0], id[1], id[2]);
+        const int ct = (p.flags & PF_CTYPE) ? ctype[c] : 0;
+        if (ct & CT_COVERED) {
+            r[c] = PT(0);
+            r[c + nl] = PT(0);
+            return;
         }
-        if (k == 0) r[fld * nl + cell.c] += (PT)beta * acc;
+        if (ct) return;                            // matched faces: below
+        PT v[2];
+        comp_cell<PT>(p, id, c, 0, ps[t.prob].beta, D, f, u, nl, v);
+        r[c] = v[0];
+        r[c + nl] = v[1];
+        return;
+    }
+    const int t = ((blockIdx.x - nt) * kBlock + threadIdx.x) >> 2;
+    const int k = threadIdx.x & 3;
+    if (t >= nrc) return;
+    const RefluxCell cell = rc[t];
+    const PatchInfo& p = P[cell.patch];
+    if (p.level < lev || (act && !act[cell.prob])) return;
+    const double beta = ps[cell.prob].beta;
+    PT acc[2] = {PT(0), PT(0)};
+    for (int e = cell.first; e < cell.first + cell.count; ++e) {
+        const int face = rf[e].face;
+        const int d = face >> 1;
+        const bool hi = face & 1;
+        const PatchInfo& fp = P[rf[e].fpatch];
+        const PT ih = (PT)fp.ih[d];
+        const int fi = rf[e].fine[k];
+        const int g = fi + rf[e].gofs;
+        // fine face: lower cell a, upper cell b; its D sits at b's slot
+        const int a = hi ? g : fi;
+        const int b = hi ? fi : g;
+#pragma unroll
+        for (int fld = 0; fld < 2; ++fld) {
+            const PT* uf = u + fld * nl;
+            const PT sum = quad_sum(D[(fld * 3 + d) * nl + b] * (uf[b] - uf[a]) * ih);
+            acc[fld] += (hi ? PT(1) : PT(-1)) * PT(0.25) * sum * (PT(0.5) * ih);
+        }
+    }
+    if (k == 0) {
+        PT v[2];
+        comp_cell<PT>(p, cell.id, cell.c, ctype[cell.c], beta, D, f, u, nl, v);
+        r[cell.c] = v[0] + (PT)beta * acc[0];
+        r[nl + cell.c] = v[1] + (PT)beta * acc[1];
     }
 }
 
@@ -556,51 +579,48 @@ __global__ __launch_bounds__(kBlock) void k_comp_reflux(
 // transfers
 // ---------------------------------------------------------------------------
 
+// Trilinear prolongation (weights 3/4, 1/4 per axis) of x on the next coarser
+// level onto the cells of a patch, through the patch's map of the coarse cells
+// around it (its box coarsened and grown by one cell; beyond the domain the
+// nearest cell): e = P x, u += P x (either may be NULL).  Cells of level
+// add_lev instead add x: u += x.  Reading the coarse cells through the map
+// costs about as much as the copy of them that a launch before made, and the
+// sum of the correction's own level rides along.
 template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_gather(const int32_t* __restrict__ src, int n,
-                                                   const PT* __restrict__ x, int64_t nlx,
-                                                   PT* __restrict__ y, int64_t nly) {
-    const int t = blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= n) return;
-    const int s = src[t];
-    y[t] = x[s];
-    y[t + nly] = x[s + nlx];
-}
-
-// Trilinear prolongation (weights 3/4, 1/4 per axis) of the shadow block of
-// each level-m patch onto its cells: e = P e_coarse, u += e.
-template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_prolong_level(const int32_t* __restrict__ act, 
+__global__ __launch_bounds__(kBlock) void k_prolong_level(const int32_t* __restrict__ act,
     const Tile* __restrict__ tiles, const PatchInfo* __restrict__ P,
-    const ShadowPatch* __restrict__ SP, const PT* __restrict__ sh, int64_t nls,
-    PT* __restrict__ e, PT* __restrict__ u, int64_t nl) {
-    // e: the prolonged correction, kept as the source for the next finer
-    // level (NULL on the finest level, where only u is updated); u NULL:
-    // only e is written
+    const ShadowPatch* __restrict__ SP, const int32_t* __restrict__ map, const PT* x, PT* e,
+    PT* u, int add_lev, int64_t nl) {
     const Tile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     if (act && !act[t.prob]) return;           // problem not being solved
     if ((int)threadIdx.x >= t.count) return;
     const PatchInfo& p = P[t.patch];
-    const ShadowPatch sp = SP[t.patch];
     int id[3];
     coords(p, t.start + threadIdx.x, id[0], id[1], id[2]);
     const int c = nat(p, id[0], id[1], id[2]);
+    if (p.level == add_lev) {                  // uniform over the workgroup
+        u[c] += x[c];
+        u[nl + c] += x[nl + c];
+        return;
+    }
+    const ShadowPatch sp = SP[t.patch];
     int q[3], o[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
         const int g = p.lo[d] + id[d];
-        q[d] = (g >> 1) - (p.lo[d] >> 1) + 1;      // shadow has a one-cell halo
+        q[d] = (g >> 1) - (p.lo[d] >> 1) + 1;      // the map has a one-cell halo
         o[d] = (g & 1) ? 1 : -1;
     }
     const int sy = sp.m0, sz = sp.m0 * sp.m1;
-    const int base = sp.off + q[0] + sy * q[1] + sz * q[2];
+    const int32_t* m = map + sp.off + q[0] + sy * q[1] + sz * q[2];
     const int ox = o[0], oy = o[1] * sy, oz = o[2] * sz;
+    const int i0 = m[0], ix = m[ox], iy = m[oy], iz = m[oz], ixy = m[ox + oy], ixz = m[ox + oz],
+              iyz = m[oy + oz], ixyz = m[ox + oy + oz];
+#pragma unroll
     for (int fld = 0; fld < 2; ++fld) {
-        const PT* s = sh + fld * nls + base;
-        const PT v = PT(27.0 / 64) * s[0] +
-                     PT(9.0 / 64) * (s[ox] + s[oy] + s[oz]) +
-                     PT(3.0 / 64) * (s[ox + oy] + s[ox + oz] + s[oy + oz]) +
-                     PT(1.0 / 64) * s[ox + oy + oz];
+        const PT* s = x + fld * nl;
+        const PT v = PT(27.0 / 64) * s[i0] + PT(9.0 / 64) * (s[ix] + s[iy] + s[iz]) +
+                     PT(3.0 / 64) * (s[ixy] + s[ixz] + s[iyz]) + PT(1.0 / 64) * s[ixyz];
         if (e) e[fld * nl + c] = v;
         if (u) u[fld * nl + c] += v;
     }
@@ -623,11 +643,13 @@ __global__ __launch_bounds__(kBlock) void k_copy_level(const int32_t* __restrict
     y[c + nl] = x[c + nl];
 }
 
+// u = e on level lev, 0 on every other level (all tiles).
 template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_add_level(const int32_t* __restrict__ act, const Tile* __restrict__ tiles,
-                                                      const PatchInfo* __restrict__ P,
-                                                      const PT* __restrict__ e,
-                                                      PT* __restrict__ u, int64_t nl) {
+__global__ __launch_bounds__(kBlock) void k_start_level(const int32_t* __restrict__ act,
+                                                        const Tile* __restrict__ tiles,
+                                                        const PatchInfo* __restrict__ P, int lev,
+                                                        const PT* __restrict__ e,
+                                                        PT* __restrict__ u, int64_t nl) {
     const Tile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     if (act && !act[t.prob]) return;           // problem not being solved
     if ((int)threadIdx.x >= t.count) return;
@@ -635,8 +657,9 @@ __global__ __launch_bounds__(kBlock) void k_add_level(const int32_t* __restrict_
     int id[3];
     coords(p, t.start + threadIdx.x, id[0], id[1], id[2]);
     const int c = nat(p, id[0], id[1], id[2]);
-    u[c] += e[c];
-    u[c + nl] += e[c + nl];
+    const bool on = p.level == lev;
+    u[c] = on ? e[c] : PT(0);
+    u[nl + c] = on ? e[nl + c] : PT(0);
 }
 
 // multigrid: f_{g+1} = restriction (mean of 8) of the residual f - A e on
@@ -946,39 +969,9 @@ __global__ __launch_bounds__(kBlock) void k_out(const int32_t* __restrict__ act,
     y[c + nl] = (double)x[cx + nl];
 }
 
-template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_fill_t(PT* __restrict__ x, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = PT(0);
-}
-
-// plain copy (a kernel rather than a runtime copy, so that captured graphs
-// hold only kernel nodes)
-template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_copy_t(const PT* __restrict__ x,
-                                                   PT* __restrict__ y, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) y[i] = x[i];
-}
-
 // ---------------------------------------------------------------------------
 // drivers
 // ---------------------------------------------------------------------------
-
-template <typename PT>
-void PcArrays<PT>::zero(hipStream_t s) const {
-    k_fill_t<PT><<<nblocks(2 * D->nl), kBlock, 0, s>>>(e, 2 * D->nl);
-    k_fill_t<PT><<<nblocks(2 * D->nl), kBlock, 0, s>>>(u, 2 * D->nl);
-    k_fill_t<PT><<<nblocks(2 * D->nl), kBlock, 0, s>>>(r, 2 * D->nl);
-    k_fill_t<PT><<<nblocks(2 * D->nl), kBlock, 0, s>>>(f, 2 * D->nl);
-    k_fill_t<PT><<<nblocks(6 * D->nl), kBlock, 0, s>>>(Dface, 6 * D->nl);
-    for (int g = 1; g <= mg.G; ++g) {
-        const int64_t n = mg.len[g];
-        k_fill_t<PT><<<nblocks(6 * n), kBlock, 0, s>>>(mg.Dg[g], 6 * n);
-        k_fill_t<PT><<<nblocks(2 * n), kBlock, 0, s>>>(mg.eg[g], 2 * n);
-        k_fill_t<PT><<<nblocks(2 * n), kBlock, 0, s>>>(mg.fg[g], 2 * n);
-    }
-}
 
 template <typename PT>
 void PcArrays<PT>::setup(hipStream_t s, const double* u_state) const {
@@ -1144,11 +1137,9 @@ void PcArrays<PT>::composite_residual(hipStream_t s, int lev) const {
     const Dev& d = *D;
     fill_ghosts(s, u);
     const int t0 = d.level_tile0[lev], nt = d.level_tile0[d.nlev] - t0;
-    k_comp_res<PT><<<nt, kBlock, 0, s>>>(d.active, d.tiles + t0, d.patches, d.ps, d.ctype,
-                                         Dface, f, u, r, d.nl);
-    if (d.nrcells > 0)
-        k_comp_reflux<PT><<<nblocks(4 * (int64_t)d.nrcells), kBlock, 0, s>>>(
-            d.rcells, d.nrcells, d.rfaces, d.patches, d.ps, Dface, u, r, d.nl);
+    k_comp_res<PT><<<nt + nblocks(4 * (int64_t)d.nrcells), kBlock, 0, s>>>(
+        d.active, d.tiles + t0, nt, d.patches, d.ps, d.ctype, d.rcells, d.nrcells, d.rfaces, lev,
+        Dface, f, u, r, d.nl);
     restrict_(s, r, lev);
 }
 
@@ -1205,33 +1196,31 @@ void PcArrays<PT>::smooth_level(hipStream_t s, const PT* rhs, int lev, int sweep
 }
 
 template <typename PT>
-void PcArrays<PT>::correct_level(hipStream_t s, int lev) const {
+void PcArrays<PT>::correct_level(hipStream_t s, int lev, bool last) const {
     // u += e on level lev and, by trilinear prolongation level by level, on
-    // every finer level; then covered cells of u <- mean of their children
+    // every finer level; then (unless last) covered cells of u <- mean of
+    // their children
     const Dev& d = *D;
     const int L = d.nlev - 1;
-    const int t0 = d.level_tile0[lev], nt = d.level_tile0[lev + 1] - t0;
-    k_add_level<PT><<<nt, kBlock, 0, s>>>(d.active, d.tiles + t0, d.patches, e, u, d.nl);
-    for (int m = lev + 1; m <= L; ++m) {
-        const int a = d.level_shadow0[m], b = d.level_shadow0[m + 1];
-        k_gather<PT><<<nblocks(b - a), kBlock, 0, s>>>(shadow_src + a, b - a, e, d.nl,
-                                                       shadow + a, shadow_len);
-        const int m0 = d.level_tile0[m], mt = d.level_tile0[m + 1] - m0;
+    for (int m = std::min(lev + 1, L); m <= L; ++m) {
+        // the first launch covers level lev too (adjacent in the tile list)
+        const int m0 = d.level_tile0[m <= lev + 1 ? lev : m], mt = d.level_tile0[m + 1] - m0;
         k_prolong_level<PT><<<mt, kBlock, 0, s>>>(d.active, d.tiles + m0, d.patches, shadows,
-                                                  shadow, shadow_len, m < L ? e : nullptr, u,
-                                                  d.nl);
+                                                  shadow_src, e, m < L ? e : nullptr, u,
+                                                  m <= lev + 1 ? lev : -1, d.nl);
     }
-    restrict_(s, u, 0);
+    if (!last) restrict_(s, u, 0);
 }
 
 template <typename PT>
-const PT* PcArrays<PT>::fac(hipStream_t s) const {
+const PT* PcArrays<PT>::fac(hipStream_t s, bool covered) const {
     // One FAC V(m,n) cycle from u = 0 for A^c u = f (Alg. 1): m = fac_pre
     // sweeps per level on the down-sweep, the base multigrid V-cycle, n =
     // fac_post sweeps per level on the up-sweep with the composite residual
     // refreshed.  Returns the buffer holding the result: u, or e when there
     // is one level (u = 0 plus the base level's correction is that
-    // correction).
+    // correction).  covered: the covered cells of the result, too, hold the
+    // mean of their children.
     const Dev& d = *D;
     const int L = d.nlev - 1;
     if (L == 0) {
@@ -1241,16 +1230,12 @@ const PT* PcArrays<PT>::fac(hipStream_t s) const {
             vcycle(s);
         return e;
     }
-    k_fill_t<PT><<<nblocks(2 * d.nl), kBlock, 0, s>>>(u, 2 * d.nl);
     for (int lev = L; lev >= 0; --lev) {
-        if (lev == L) {
-            // u = 0: r = f (the finest level has no covered cells)
-            k_copy_t<PT><<<nblocks(2 * d.nl), kBlock, 0, s>>>(f, r, 2 * d.nl);
-        } else {
-            composite_residual(s, lev);     // u was restricted by the last correction
-        }
+        if (lev < L) composite_residual(s, lev);     // u was restricted by the last correction
+        // finest level, u = 0: r = f there (it has no covered cells)
+        const PT* rhs = lev < L ? r : f;
         if (lev > 0 || base_smooth) {
-            smooth_level(s, r, lev, fac_pre);
+            smooth_level(s, rhs, lev, fac_pre);
         } else {
             // base level: multigrid V-cycle with rhs f^0 = r on level 0 (the
             // V-cycle only reads its level-0 right-hand side)
@@ -1258,12 +1243,18 @@ const PT* PcArrays<PT>::fac(hipStream_t s) const {
             v.f = r;
             v.vcycle(s);
         }
-        correct_level(s, lev);
+        if (lev == L) {
+            k_start_level<PT><<<d.level_tile0[d.nlev], kBlock, 0, s>>>(d.active, d.tiles,
+                                                                       d.patches, L, e, u, d.nl);
+            restrict_(s, u, 0);
+        } else {
+            correct_level(s, lev, lev == 0 && fac_post == 0 && !covered);
+        }
     }
     for (int lev = 1; fac_post > 0 && lev <= L; ++lev) {
         composite_residual(s, lev);
         smooth_level(s, r, lev, fac_post);
-        correct_level(s, lev);
+        correct_level(s, lev, lev == L && !covered);
     }
     return u;
 }
@@ -1296,9 +1287,9 @@ void PcArrays<PT>::smooth_range(hipStream_t s, const PT* rhs, PT* x, int lo, int
 }
 
 template <typename PT>
-const PT* PcArrays<PT>::afacx(hipStream_t s) const {
-    // AFACx from u = 0 for A^c u = f: r = f with covered cells the mean of
-    // their children; the coarse approximations of every pair (l-1, l) at
+const PT* PcArrays<PT>::afacx(hipStream_t s, bool covered) const {
+    // AFACx from u = 0 for A^c u = r, r with covered cells the mean of
+    // their children (its input is written to r, not f); the coarse approximations of every pair (l-1, l) at
     // once in e2 (sweeps on the cells level l covers, the rest 0); their
     // trilinear interpolation s onto every refined level in e; the fine
     // right-hand sides r - A^l s; the fine corrections from zero, every
@@ -1306,16 +1297,12 @@ const PT* PcArrays<PT>::afacx(hipStream_t s) const {
     // correction; each level's correction carried to the finer levels.
     const Dev& d = *D;
     const int L = d.nlev - 1;
-    k_copy_t<PT><<<nblocks(2 * d.nl), kBlock, 0, s>>>(f, r, 2 * d.nl);
     restrict_(s, r, 0);
     if (L > 0) {
         smooth_range(s, r, e2, 0, L - 1, fac_pre, true);
-        const int a = d.level_shadow0[1], b = d.level_shadow0[L + 1];
-        k_gather<PT><<<nblocks(b - a), kBlock, 0, s>>>(shadow_src + a, b - a, e2, d.nl,
-                                                       shadow + a, shadow_len);
         const int t1 = d.level_tile0[1], nt1 = d.level_tile0[L + 1] - t1;
         k_prolong_level<PT><<<nt1, kBlock, 0, s>>>(d.active, d.tiles + t1, d.patches, shadows,
-                                                   shadow, shadow_len, e, nullptr, d.nl);
+                                                   shadow_src, e2, e, nullptr, -1, d.nl);
         siblings(s, e, 1, L);
         k_level_res<PT><<<nt1, kBlock, 0, s>>>(d.active, d.tiles + t1, d.patches, d.ps, d.ctype,
                                                Dface, e, r, d.nl);
@@ -1329,30 +1316,29 @@ const PT* PcArrays<PT>::afacx(hipStream_t s) const {
         v.vcycle(s);
     }
     for (int m = 1; m <= L; ++m) {
-        const int a = d.level_shadow0[m], b = d.level_shadow0[m + 1];
-        k_gather<PT><<<nblocks(b - a), kBlock, 0, s>>>(shadow_src + a, b - a, e, d.nl,
-                                                       shadow + a, shadow_len);
         const int m0 = d.level_tile0[m], mt = d.level_tile0[m + 1] - m0;
         k_prolong_level<PT><<<mt, kBlock, 0, s>>>(d.active, d.tiles + m0, d.patches, shadows,
-                                                  shadow, shadow_len, nullptr, e, d.nl);
+                                                  shadow_src, e, nullptr, e, -1, d.nl);
     }
-    restrict_(s, e, 0);
+    if (covered) restrict_(s, e, 0);
     return e;
 }
 
 template <typename PT>
-const PT* PcArrays<PT>::p1(hipStream_t s) const {
-    return fac_cycle == NRD_FAC_AFACX ? afacx(s) : fac(s);
+const PT* PcArrays<PT>::p1(hipStream_t s, bool covered) const {
+    return fac_cycle == NRD_FAC_AFACX ? afacx(s, covered) : fac(s, covered);
 }
 
 template <typename PT>
-void PcArrays<PT>::apply(hipStream_t s, const double* w, double* y, const double* wsc) const {
+void PcArrays<PT>::apply(hipStream_t s, const double* w, double* y, const double* wsc,
+                         bool covered) const {
     const Dev& d = *D;
     const int ntiles = d.level_tile0[d.nlev];
     // with split0 the cycle reads f and returns e in colour-split storage
     const int sp = split0 ? 1 : 0;
-    if (w) k_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, w, wsc, f, d.nl, sp);
-    const PT* x = p1(s);
+    if (w)
+        k_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, w, wsc, input(), d.nl, sp);
+    const PT* x = p1(s, covered);
     k_p2<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, sigma, d.z3, x, y,
                                        p2_mode, 0, d.nl, sp);
 }
@@ -1362,9 +1348,9 @@ void PcArrays<PT>::apply_transpose(hipStream_t s, const double* w, double* y) co
     const Dev& d = *D;
     const int ntiles = d.level_tile0[d.nlev];
     const int sp = split0 ? 1 : 0;
-    k_p2t_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, sigma, d.z3, w, f,
-                                           p2_mode, d.nl, sp);
-    const PT* x = p1(s);
+    k_p2t_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, sigma, d.z3, w,
+                                           input(), p2_mode, d.nl, sp);
+    const PT* x = p1(s, false);
     k_out<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, x, y, d.nl, sp);
 }
 
