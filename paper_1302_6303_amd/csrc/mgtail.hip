@@ -3,7 +3,7 @@
 // workgroup per (problem, field) each (paper Sec. 4.3).
 #include <hip/hip_runtime.h>
 
-#include "device_util.h"
+#include "pc_device.h"
 #include "kernels.h"
 #include "precond.h"
 
@@ -348,8 +348,9 @@ struct TailGrid {
         }
         __syncthreads();
     }
-    // e += trilinear prolongation of the next grid's ec (copy rule at edges)
-    __device__ __forceinline__ void prolong(const PT* ec) {
+    // e += trilinear prolongation of the next grid's ec (copy rule at edges);
+    // only colour 1 unless both (the sweep that follows overwrites colour 0)
+    __device__ __forceinline__ void prolong(const PT* ec, bool both) {
 #pragma unroll
         for (int w = 0; w < C; ++w) {
             const int q = threadIdx.x + w * kTailThreads;
@@ -359,23 +360,20 @@ struct TailGrid {
             const int child = lane == 0 ? 0 : (lane == 1 ? 3 : (lane == 2 ? 5 : 6));
 #pragma unroll
             for (int col = 0; col < 2; ++col) {
-                if (c[col][w] < 0) continue;
+                if (c[col][w] < 0 || (col == 0 && !both)) continue;
                 const int x = min(max(I + (((child ^ col) & 1) ? 1 : -1), 0), cn[0] - 1);
                 const int y = min(max(J + (((child >> 1) & 1) ? 1 : -1), 0), cn[1] - 1);
                 const int z = min(max(K + ((child >> 2) ? 1 : -1), 0), cn[2] - 1);
-                PT v = PT(0);
+                PT v[2][2][2];
 #pragma unroll
                 for (int i = 0; i < 2; ++i)
 #pragma unroll
                     for (int j = 0; j < 2; ++j)
 #pragma unroll
-                        for (int k = 0; k < 2; ++k) {
-                            const PT wt = (i ? PT(0.25) : PT(0.75)) * (j ? PT(0.25) : PT(0.75)) *
-                                          (k ? PT(0.25) : PT(0.75));
-                            v += wt * ec[(i ? x : I) +
-                                         cn[0] * ((j ? y : J) + cn[1] * (k ? z : K))];
-                        }
-                e[c[col][w]] += v;
+                        for (int k = 0; k < 2; ++k)
+                            v[i][j][k] =
+                                ec[(i ? x : I) + cn[0] * ((j ? y : J) + cn[1] * (k ? z : K))];
+                e[c[col][w]] += trilinear<PT>(v);
             }
         }
         __syncthreads();
@@ -475,10 +473,10 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
     if (levels == 0) return;
     __syncthreads();
     if (levels > 1) {
-        B.prolong(eC);
+        B.prolong(eC, nu_post == 0);
         B.sweeps(nu_post, false);
     }
-    A.prolong(levels > 1 ? B.e : eC);
+    A.prolong(levels > 1 ? B.e : eC, nu_post == 0);
     A.sweeps(nu_post, false);
 #pragma unroll
     for (int w = 0; w < 2; ++w)

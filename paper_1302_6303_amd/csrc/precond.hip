@@ -16,7 +16,7 @@
 // otherwise.
 #include <hip/hip_runtime.h>
 
-#include "device_util.h"
+#include "pc_device.h"
 #include "kernels.h"
 #include "precond.h"
 
@@ -183,6 +183,7 @@ __device__ __forceinline__ void level_terms(const PatchInfo& p, const int id[3],
                                             const int* enb = nullptr,
                                             const PT* __restrict__ Tp = nullptr,
                                             PT kappa = PT(0)) {
+#pragma clang fp contract(off)
     const int st[3] = {1, p.sy, p.sz};
     PT bh2[3];
     bool ph[6], cf[6];
@@ -217,7 +218,7 @@ __device__ __forceinline__ void level_terms(const PatchInfo& p, const int id[3],
                                    : ef[SPLIT ? enb[fc] : (s ? c + st[d] : c - st[d])];
                 const bool open = !(ph[fc] || cf[fc]);
                 dg += open ? a : (cf[fc] ? PT(2.0 / 3.0) * a : PT(0));
-                ns += open ? a * en : PT(0);
+                ns = fma_t(open ? a : PT(0), en, ns);
             }
         }
         if (fld == 0 && any_robin) {
@@ -228,8 +229,7 @@ __device__ __forceinline__ void level_terms(const PatchInfo& p, const int id[3],
                     const int fc = 2 * d + s;
                     if (ph[fc] && ((p.robin >> fc) & 1)) {
                         const PT Db = D[d * nl + (s ? c + st[d] : c)];
-                        const PT h = (PT)p.h[d];
-                        dg += PT(2) * (PT)beta * Db / ((PT(4) * Db + h) * h);
+                        dg += robin_diag<PT>((PT)beta, Db, (PT)p.h[d]);
                     }
                 }
         }
@@ -253,7 +253,7 @@ __device__ __forceinline__ void level_update(const PatchInfo& p, const int id[3]
 #pragma unroll
     for (int fld = 0; fld < 2; ++fld) {
         const int64_t cfi = fld * nl + own;
-        e[cfi] = (f[cfi] + ns[fld]) / dg[fld];
+        e[cfi] = relax(f[cfi], ns[fld], dg[fld]);
     }
 }
 
@@ -667,23 +667,25 @@ __global__ __launch_bounds__(kBlock) void k_start_level(const int32_t* __restric
 // colour 1.  Relaxing a cell solves its own equation with its neighbours
 // (all of the other colour) held, so the residual of every colour-1 cell is
 // zero and only the four colour-0 children of each coarse cell are
-// evaluated; the residual is never stored.  Four lanes per coarse cell, one
-// child each, summed across the lanes in a fixed order.
-// fmap: as in k_mg_coarsen.  The children of a coarse cell start at an even
+// evaluated; the residual is never stored.  ONCE: that sweep was the only one
+// and started from zero, so colour 0 was relaxed to dg e = f and its residual
+// f - (dg e - ns) is its neighbour sum ns alone: neither f, e nor the diagonal
+// is read (first grid of the 20 M cell ensemble 154 -> 119 us).  Four
+// lanes per coarse cell, one child each, summed across the lanes in a fixed
+// order.
+// The children of a coarse cell start at an even
 // level index, so its colour-0 children are those with an even offset sum.
-template <typename PT, bool SPLIT = false>   // SPLIT: fine grid's e, f colour-split
+template <typename PT, bool ONCE>
 __global__ __launch_bounds__(kBlock) void k_mg_res_restrict(const int32_t* __restrict__ act,
     const Tile* __restrict__ tiles, const PatchInfo* __restrict__ Pc,
     const PatchInfo* __restrict__ Pf, const int32_t* __restrict__ fbox,
-    const int32_t* __restrict__ fmap,
     const ProbScalars* __restrict__ ps, const uint8_t* __restrict__ ctype,
     const PT* __restrict__ D, const PT* __restrict__ f, const PT* __restrict__ e, int64_t nlf,
-    PT* __restrict__ fc, int64_t nlc, const PT* __restrict__ Tp = nullptr) {
+    PT* __restrict__ fc, int64_t nlc) {
     const Tile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     if (act && !act[t.prob]) return;           // uniform over the workgroup
     const PatchInfo& pc = Pc[t.patch];
     const double beta = ps[t.prob].beta;
-    const PT kappa = (PT)ps[t.prob].kappa;
     // colour-0 children (bit 0: x, 1: y, 2: z offset)
     const int lane = threadIdx.x & 3;
     const int child = lane == 0 ? 0 : (lane == 1 ? 3 : (lane == 2 ? 5 : 6));
@@ -694,18 +696,15 @@ __global__ __launch_bounds__(kBlock) void k_mg_res_restrict(const int32_t* __res
         if (live) coords(pc, t.start + q, id[0], id[1], id[2]);
         PT v0 = PT(0), v1 = PT(0);
         if (live) {
-            const PatchInfo& pf = Pf[fmap ? fmap[nat(pc, id[0], id[1], id[2])] : fbox[t.prob]];
+            const PatchInfo& pf = Pf[fbox[t.prob]];
             const int fid[3] = {2 * id[0] + (child & 1) - pf.lo[0],
                                 2 * id[1] + ((child >> 1) & 1) - pf.lo[1],
                                 2 * id[2] + (child >> 2) - pf.lo[2]};
             const int c = nat(pf, fid[0], fid[1], fid[2]);
-            int own = c, enb[6];
-            if (SPLIT) split_stencil(pf, fid, own, enb);
             PT dg[2], ns[2];
-            level_terms<PT, false, SPLIT>(pf, fid, c, beta, ctype, D, e, nlf, dg, ns, enb, Tp,
-                                          kappa);
-            v0 = f[own] - (dg[0] * e[own] - ns[0]);
-            v1 = f[nlf + own] - (dg[1] * e[nlf + own] - ns[1]);
+            level_terms<PT, false>(pf, fid, c, beta, ctype, D, e, nlf, dg, ns);
+            v0 = ONCE ? ns[0] : cell_residual(f[c], ns[0], dg[0], e[c]);
+            v1 = ONCE ? ns[1] : cell_residual(f[nlf + c], ns[1], dg[1], e[nlf + c]);
         }
         v0 += __shfl_xor(v0, 1);
         v1 += __shfl_xor(v1, 1);
@@ -721,7 +720,7 @@ __global__ __launch_bounds__(kBlock) void k_mg_res_restrict(const int32_t* __res
 // The same with one thread per coarse cell (the first grid, where the
 // coarse grid is large): the four children's residuals summed in the
 // order of the lane reduction above, (r_0 + r_3) + (r_5 + r_6).
-template <typename PT, bool SPLIT = false>
+template <typename PT, bool ONCE, bool SPLIT = false>   // SPLIT: fine e, f colour-split
 __global__ __launch_bounds__(kBlock) void k_mg_res_restrict1(const int32_t* __restrict__ act,
     const Tile* __restrict__ tiles, const PatchInfo* __restrict__ Pc,
     const PatchInfo* __restrict__ Pf, const int32_t* __restrict__ fbox,
@@ -752,65 +751,25 @@ __global__ __launch_bounds__(kBlock) void k_mg_res_restrict1(const int32_t* __re
         PT dg[2], ns[2];
         level_terms<PT, false, SPLIT>(pf, fid, c, beta, ctype, D, e, nlf, dg, ns, enb, Tp,
                                       kappa);
-        r0[k] = f[own] - (dg[0] * e[own] - ns[0]);
-        r1[k] = f[nlf + own] - (dg[1] * e[nlf + own] - ns[1]);
+        r0[k] = ONCE ? ns[0] : cell_residual(f[own], ns[0], dg[0], e[own]);
+        r1[k] = ONCE ? ns[1] : cell_residual(f[nlf + own], ns[1], dg[1], e[nlf + own]);
     }
     fc[cc] = ((r0[0] + r0[1]) + (r0[2] + r0[3])) * PT(0.125);
     fc[nlc + cc] = ((r1[0] + r1[1]) + (r1[2] + r1[3])) * PT(0.125);
 }
 
-// multigrid: e_g += trilinear prolongation of e_{g+1} (copy rule at edges)
+// multigrid: e_g += trilinear prolongation of e_{g+1} (copy rule at edges),
+// kBlock / 2 threads per tile: thread q takes the cells (2q, 2q + 1) of a row
+// (even x extents, boxes at even level indices), which share their coarse x
+// cell.  Only colour 1 unless `both`: a sweep that follows relaxes colour 0
+// first, from its neighbours alone, so what colour 0 held is not read.
+// split: ef in colour-split storage.
 template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_mg_prolong(const int32_t* __restrict__ act, 
+__global__ __launch_bounds__(kBlock) void k_mg_prolong(const int32_t* __restrict__ act,
     const Tile* __restrict__ tiles, const PatchInfo* __restrict__ Pf,
     const PatchInfo* __restrict__ Pc, const int32_t* __restrict__ cbox,
-    const PT* __restrict__ ec, int64_t nlc, PT* __restrict__ ef, int64_t nlf, int split) {
-    // split: ef in colour-split storage
-    const Tile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
-    if (act && !act[t.prob]) return;           // problem not being solved
-    if ((int)threadIdx.x >= t.count) return;
-    const PatchInfo& pf = Pf[t.patch];
-    const PatchInfo& pc = Pc[cbox[t.prob]];
-    int id[3];
-    coords(pf, t.start + threadIdx.x, id[0], id[1], id[2]);
-    const int c = split ? split_index(pf, id[0] + 1, id[1] + 1, id[2] + 1)
-                        : nat(pf, id[0], id[1], id[2]);
-    int q[3], nbq[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) {
-        const int I = pf.lo[d] + id[d];            // fine level index (coarse box at 0)
-        q[d] = I >> 1;
-        const int o = (I & 1) ? 1 : -1;
-        nbq[d] = min(max(q[d] + o, 0), pc.n[d] - 1);
-    }
-    for (int fld = 0; fld < 2; ++fld) {
-        const PT* s = ec + fld * nlc;
-        PT v = PT(0);
-#pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-                for (int cc = 0; cc < 2; ++cc) {
-                    const PT w = (a ? PT(0.25) : PT(0.75)) * (b ? PT(0.25) : PT(0.75)) *
-                                 (cc ? PT(0.25) : PT(0.75));
-                    v += w * s[nat(pc, a ? nbq[0] : q[0], b ? nbq[1] : q[1],
-                                   cc ? nbq[2] : q[2])];
-                }
-        ef[fld * nlf + c] += v;
-    }
-}
-
-// The same on the colour-split base grid (even x extents, boxes at even
-// level indices), kBlock / 2 threads per tile: thread q takes the cell pair
-// (2q, 2q + 1) of a row, which shares its coarse x cell, reads the twelve
-// coarse values the two cells use once and updates both cells, each with
-// the weights and summation order above.
-template <typename PT>
-__global__ __launch_bounds__(kBlock) void k_mg_prolong2(const int32_t* __restrict__ act,
-    const Tile* __restrict__ tiles, const PatchInfo* __restrict__ Pf,
-    const PatchInfo* __restrict__ Pc, const int32_t* __restrict__ cbox,
-    const PT* __restrict__ ec, int64_t nlc, PT* __restrict__ ef, int64_t nlf) {
+    const PT* __restrict__ ec, int64_t nlc, PT* __restrict__ ef, int64_t nlf, int split,
+    int both) {
     const Tile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     if (act && !act[t.prob]) return;           // problem not being solved
     const int a0 = 2 * (int)threadIdx.x;       // tile starts are even
@@ -819,6 +778,8 @@ __global__ __launch_bounds__(kBlock) void k_mg_prolong2(const int32_t* __restric
     const PatchInfo& pc = Pc[cbox[t.prob]];
     int id[3];
     coords(pf, t.start + a0, id[0], id[1], id[2]);    // id[0] even
+    // x offset of colour 1 within the pair
+    const int one = (1 + id[1] + id[2] + pf.lo[0] + pf.lo[1] + pf.lo[2]) & 1;
     int q[3], nbq[3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -827,35 +788,24 @@ __global__ __launch_bounds__(kBlock) void k_mg_prolong2(const int32_t* __restric
         const int o = (I & 1) ? 1 : -1;
         nbq[d] = min(max(q[d] + o, 0), pc.n[d] - 1);
     }
-    const int xm = max(q[0] - 1, 0), xp = min(q[0] + 1, pc.n[0] - 1);
-    const int c0 = split_index(pf, id[0] + 1, id[1] + 1, id[2] + 1);
-    const int c1 = split_index(pf, id[0] + 2, id[1] + 1, id[2] + 1);
-    for (int fld = 0; fld < 2; ++fld) {
-        const PT* s = ec + fld * nlc;
-        PT R[3][2][2];                         // x: q - 1, q, q + 1; y, z: q, neighbour
+    for (int k = both ? 0 : 1; k < 2; ++k) {
+        const int x = k ? one : 1 - one;
+        const int nbx = min(max(q[0] + (x ? 1 : -1), 0), pc.n[0] - 1);
+        const int c = split ? split_index(pf, id[0] + x + 1, id[1] + 1, id[2] + 1)
+                            : nat(pf, id[0] + x, id[1], id[2]);
 #pragma unroll
-        for (int b = 0; b < 2; ++b)
-#pragma unroll
-            for (int cc = 0; cc < 2; ++cc) {
-                const int y = b ? nbq[1] : q[1], z = cc ? nbq[2] : q[2];
-                R[0][b][cc] = s[nat(pc, xm, y, z)];
-                R[1][b][cc] = s[nat(pc, q[0], y, z)];
-                R[2][b][cc] = s[nat(pc, xp, y, z)];
-            }
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {          // k = 0: even fine x (neighbour q - 1)
-            PT v = PT(0);
+        for (int fld = 0; fld < 2; ++fld) {
+            const PT* s = ec + fld * nlc;
+            PT v[2][2][2];
 #pragma unroll
             for (int a = 0; a < 2; ++a)
 #pragma unroll
                 for (int b = 0; b < 2; ++b)
 #pragma unroll
-                    for (int cc = 0; cc < 2; ++cc) {
-                        const PT w = (a ? PT(0.25) : PT(0.75)) * (b ? PT(0.25) : PT(0.75)) *
-                                     (cc ? PT(0.25) : PT(0.75));
-                        v += w * R[a ? (k ? 2 : 0) : 1][b][cc];
-                    }
-            ef[fld * nlf + (k ? c1 : c0)] += v;
+                    for (int cc = 0; cc < 2; ++cc)
+                        v[a][b][cc] = s[nat(pc, a ? nbx : q[0], b ? nbq[1] : q[1],
+                                            cc ? nbq[2] : q[2])];
+            ef[fld * nlf + c] += trilinear<PT>(v);
         }
     }
 }
@@ -872,7 +822,7 @@ __global__ __launch_bounds__(kBlock) void k_p2(const int32_t* __restrict__ act, 
                                                const double* __restrict__ z3,
                                                const PT* __restrict__ e,
                                                double* __restrict__ y, int mode,
-                                               int transpose, int64_t nl, int split) {
+                                               int64_t nl, int split) {
     // split: e in colour-split storage
     const Tile t = tiles[xcd_tile(blockIdx.x, gridDim.x)];
     if (act && !act[t.prob]) return;           // problem not being solved
@@ -881,22 +831,12 @@ __global__ __launch_bounds__(kBlock) void k_p2(const int32_t* __restrict__ act, 
     int id[3];
     coords(p, t.start + threadIdx.x, id[0], id[1], id[2]);
     const int c = nat(p, id[0], id[1], id[2]);
-    const double beta = ps[t.prob].beta;
-    const double sg = (double)sigma[c];
-    const double z = z3[c];
-    const double k = mode ? 4.0 : 1.0;
-    // [[1 + sigma beta, -k beta z^3], [-sigma beta, 1 + k beta z^3]]  (sigma T^3 = z^3)
-    const double a = 1.0 + sg * beta, b = -k * beta * z, cc = -sg * beta, d = 1.0 + k * beta * z;
-    const double det = a * d - b * cc;
     const int ce = split ? split_index(p, id[0] + 1, id[1] + 1, id[2] + 1) : c;
-    const double eE = (double)e[ce], eT = (double)e[ce + nl];
-    if (!transpose) {
-        y[c] = (d * eE - b * eT) / det;
-        y[c + nl] = (a * eT - cc * eE) / det;
-    } else {
-        y[c] = (d * eE - cc * eT) / det;
-        y[c + nl] = (a * eT - b * eE) / det;
-    }
+    double yE, yT;
+    p2_cell((double)sigma[c], z3[c], ps[t.prob].beta, mode, 0, (double)e[ce], (double)e[ce + nl],
+            yE, yT);
+    y[c] = yE;
+    y[c + nl] = yT;
 }
 
 // P2^-T applied first (transposed preconditioner): double in, PT out
@@ -917,16 +857,11 @@ __global__ __launch_bounds__(kBlock) void k_p2t_in(const int32_t* __restrict__ a
     int id[3];
     coords(p, t.start + threadIdx.x, id[0], id[1], id[2]);
     const int c = nat(p, id[0], id[1], id[2]);
-    const double beta = ps[t.prob].beta;
-    const double sg = (double)sigma[c];
-    const double z = z3[c];
-    const double k = mode ? 4.0 : 1.0;
-    const double a = 1.0 + sg * beta, b = -k * beta * z, cc = -sg * beta, d = 1.0 + k * beta * z;
-    const double det = a * d - b * cc;
-    const double eE = w[c], eT = w[c + nl];
+    double xE, xT;
+    p2_cell((double)sigma[c], z3[c], ps[t.prob].beta, mode, 1, w[c], w[c + nl], xE, xT);
     const int cx = split ? split_index(p, id[0] + 1, id[1] + 1, id[2] + 1) : c;
-    x[cx] = (PT)((d * eE - cc * eT) / det);
-    x[cx + nl] = (PT)((a * eT - b * eE) / det);
+    x[cx] = (PT)xE;
+    x[cx + nl] = (PT)xT;
 }
 
 template <typename PT>
@@ -1055,19 +990,28 @@ void PcArrays<PT>::vcycle(hipStream_t s) const {
                 if (g == 0 && clock) clock->toc(which, tk);
             }
             if (sib) siblings(s, eg, 0);
+            // the mean of the residual, from neighbour sums alone after a
+            // single sweep
+            auto restrict1 = [&](auto kernel) {
+                kernel<<<mg.ntiles[g + 1], kBlock, 0, s>>>(
+                    d.active, mg.tiles[g + 1], mg.box[g + 1], Pg, mg.box_of[g], mg.l0map, d.ps,
+                    d.ctype, Dg, fg, eg, nlg, mg.fg[g + 1], mg.len[g + 1], Tp);
+            };
+            auto restrict4 = [&](auto kernel) {
+                kernel<<<mg.ntiles[g + 1], kBlock, 0, s>>>(
+                    d.active, mg.tiles[g + 1], mg.box[g + 1], Pg, mg.box_of[g], d.ps, d.ctype, Dg,
+                    fg, eg, nlg, mg.fg[g + 1], mg.len[g + 1]);
+            };
+            const bool once = nu_pre == 1;
             if (sp)
-                k_mg_res_restrict1<PT, true><<<mg.ntiles[g + 1], kBlock, 0, s>>>(d.active,
-                    mg.tiles[g + 1], mg.box[g + 1], Pg, mg.box_of[g], mg.l0map, d.ps, d.ctype,
-                    Dg, fg, eg, nlg, mg.fg[g + 1], mg.len[g + 1], Tp);
+                once ? restrict1(k_mg_res_restrict1<PT, true, true>)
+                     : restrict1(k_mg_res_restrict1<PT, false, true>);
             else if (g == 0)
-                k_mg_res_restrict1<PT><<<mg.ntiles[g + 1], kBlock, 0, s>>>(d.active,
-                    mg.tiles[g + 1], mg.box[g + 1], Pg, mg.box_of[g], mg.l0map, d.ps, d.ctype,
-                    Dg, fg, eg, nlg, mg.fg[g + 1], mg.len[g + 1]);
+                once ? restrict1(k_mg_res_restrict1<PT, true>)
+                     : restrict1(k_mg_res_restrict1<PT, false>);
             else
-                k_mg_res_restrict<PT><<<mg.ntiles[g + 1], kBlock, 0, s>>>(d.active,
-                    mg.tiles[g + 1], mg.box[g + 1], Pg, mg.box_of[g],
-                    g == 0 ? mg.l0map : nullptr, d.ps, d.ctype, Dg, fg, eg, nlg, mg.fg[g + 1],
-                    mg.len[g + 1]);
+                once ? restrict4(k_mg_res_restrict<PT, true>)
+                     : restrict4(k_mg_res_restrict<PT, false>);
         }
     }
     // problems whose base grid does not coarsen, and the grids from every
@@ -1084,13 +1028,9 @@ void PcArrays<PT>::vcycle(hipStream_t s) const {
         const PT* Dg = (g == 0) ? Dface : mg.Dg[g];
         const Tile* tl = mg.smooth_tiles[g];
         const int nt = mg.nsmooth[g];
-        if (g == 0 && split0)
-            k_mg_prolong2<PT><<<nt, kBlock / 2, 0, s>>>(d.active, tl, Pg, mg.box[1], mg.box_of[1],
-                                                        mg.eg[1], mg.len[1], eg, nlg);
-        else
-            k_mg_prolong<PT><<<nt, kBlock, 0, s>>>(d.active, tl, Pg, mg.box[g + 1],
-                                                  mg.box_of[g + 1], mg.eg[g + 1], mg.len[g + 1],
-                                                  eg, nlg, 0);
+        k_mg_prolong<PT><<<nt, kBlock / 2, 0, s>>>(d.active, tl, Pg, mg.box[g + 1],
+                                                   mg.box_of[g + 1], mg.eg[g + 1], mg.len[g + 1],
+                                                   eg, nlg, g == 0 && split0, nu_post == 0);
         const bool sib = g == 0 && mg.multi0;
         for (int it = 0; it < nu_post; ++it) {
             std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
@@ -1340,7 +1280,7 @@ void PcArrays<PT>::apply(hipStream_t s, const double* w, double* y, const double
         k_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, w, wsc, input(), d.nl, sp);
     const PT* x = p1(s, covered);
     k_p2<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, sigma, d.z3, x, y,
-                                       p2_mode, 0, d.nl, sp);
+                                       p2_mode, d.nl, sp);
 }
 
 template <typename PT>
