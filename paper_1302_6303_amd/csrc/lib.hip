@@ -100,13 +100,14 @@ struct nrd_hierarchy final : public Clock {
     bool mixed = false;
     bool cf_built = false;          // transposed coarse-fine table uploaded
     std::vector<int32_t> patch_tile0;
+    std::vector<SweepTile> sweep[2];   // fused base sweeps: pre, post (empty: not fused)
 
     // workspace offsets
     struct Off {
         size_t patches, tiles, stiles, vtiles, prob_vtile0, gcopy, gcf, sib, sync[kMaxLev], rfaces,
             rcells, cfrows, cfsrc, ctype, shadows, shadow_src, coff, ps, active, amap;
         size_t mg_box[kMaxMG], mg_tiles[kMaxMG], mg_box_of[kMaxMG], mg_smooth[kMaxMG],
-            tails, Xbuf, mg_l0map, ltiles;
+            tails, Xbuf, mg_l0map, ltiles, sweep[2];
         size_t z, z3, cur, prev, udot, bvec, x, F, s, w, tmp, tmp2, gzn, V, Z, pred;
         size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f;
         size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG];
@@ -217,6 +218,61 @@ struct nrd_hierarchy final : public Clock {
     }
 };
 
+// Colour-split storage of the level-0 V-cycle vectors (split0): problems
+// of one level and one level-0 box, even x extents, a multigrid base.  The
+// index map is checked here for every box shape: a bijection of the ghosted
+// block onto itself, and each interior cell's stencil indices those of its
+// neighbours' positions.
+static bool split0_ok(const Tables& t, bool base_smooth) {
+    if (base_smooth || t.nlev != 1 || t.level_sib0[1] != t.level_sib0[0]) return false;
+    std::map<std::tuple<int, int, int, int, int, int>, bool> shapes;
+    for (const PatchInfo& p : t.patches) {
+        if ((p.n[0] & 1) || (p.sy & 1) || p.sy != p.n[0] + 2) return false;
+        shapes[std::make_tuple(p.n[0], p.n[1], p.n[2], p.sy, p.sz,
+                               (p.lo[0] + p.lo[1] + p.lo[2]) & 1)] = true;
+    }
+    // shapes already checked in this process (hierarchies are often rebuilt
+    // with the same boxes)
+    static std::mutex checked_mu;
+    static std::map<std::tuple<int, int, int, int, int, int>, bool> checked;
+    for (const auto& kv : shapes) {
+        {
+            std::lock_guard<std::mutex> lk(checked_mu);
+            if (checked.count(kv.first)) continue;
+        }
+        PatchInfo q;
+        std::memset(&q, 0, sizeof(q));
+        std::tie(q.n[0], q.n[1], q.n[2], q.sy, q.sz, q.lo[0]) = kv.first;
+        const int64_t vol = (int64_t)q.sz * (q.n[2] + 2);
+        std::vector<char> seen(vol, 0);
+        for (int z = 0; z < q.n[2] + 2; ++z)
+            for (int y = 0; y < q.n[1] + 2; ++y)
+                for (int x = 0; x < q.sy; ++x) {
+                    const int i = split_index(q, x, y, z);
+                    if (i < 0 || i >= vol || seen[i]) return false;
+                    seen[i] = 1;
+                }
+        for (int k = 0; k < q.n[2]; ++k)
+            for (int j = 0; j < q.n[1]; ++j)
+                for (int i = 0; i < q.n[0]; ++i) {
+                    const int id[3] = {i, j, k};
+                    int own, nb[6];
+                    split_stencil(q, id, own, nb);
+                    const int x = i + 1, y = j + 1, z = k + 1;
+                    if (own != split_index(q, x, y, z) || nb[0] != split_index(q, x - 1, y, z) ||
+                        nb[1] != split_index(q, x + 1, y, z) ||
+                        nb[2] != split_index(q, x, y - 1, z) ||
+                        nb[3] != split_index(q, x, y + 1, z) ||
+                        nb[4] != split_index(q, x, y, z - 1) ||
+                        nb[5] != split_index(q, x, y, z + 1))
+                        return false;
+                }
+        std::lock_guard<std::mutex> lk(checked_mu);
+        checked[kv.first] = true;
+    }
+    return true;
+}
+
 // ---------------------------------------------------------------------------
 // layout
 // ---------------------------------------------------------------------------
@@ -277,6 +333,26 @@ static void layout(nrd_hierarchy* h) {
         bsum += nb * nb;
     }
     o.Xbuf = b.take(sizeof(double) * 2 * bsum);
+    // Fused sweeps of the base grid (pre, post): float, colour-split storage,
+    // V(1,1) on problems that coarsen, and vectors beyond the last-level
+    // cache.  Preconditioner with half-sweeps against fused, us: 128^3 231 /
+    // 241, 192^3 (7 M cells) 590 / 627, 8 x 96^3 (7 M) 562 / 576, 32 x 64^3
+    // (8 M) 660 / 601, 96 x 48^3 (11 M) 885 / 735, 256^3 (17 M) 1358 / 1227,
+    // 64 x 64^3 (17 M) 1350 / 1062, 32 x 96^3 (28 M) 2160 / 1798.
+    // Their byte offsets have 32 bits.
+    {
+        const nrd_options& O = h->opt;
+        bool fuse = h->mixed && nl >= kSweepLen && nl < ((int64_t)1 << 30) &&
+                    O.mg_nu_pre <= 1 && O.mg_nu_post == 1 && O.fac_cycle == NRD_FAC_MULT &&
+                    split0_ok(t, O.fac_base == NRD_BASE_SMOOTH);
+        for (int p = 0; p < nprob; ++p)
+            fuse = fuse && t.prob_mgdepth[p] > 0;
+        for (int q = 0; q < 2; ++q) {
+            h->sweep[q].clear();
+            if (fuse) sweep_tiles(t, q + 1, h->sweep[q]);
+            o.sweep[q] = b.take(sizeof(SweepTile) * std::max<size_t>(1, h->sweep[q].size()));
+        }
+    }
     // state and work vectors (double)
     o.z = b.take(8 * nl);
     o.z3 = b.take(8 * nl);
@@ -350,61 +426,6 @@ static hipError_t up(hipStream_t s, void* dst, const std::vector<T>& v) {
     return hipMemcpyAsync(dst, v.data(), sizeof(T) * v.size(), hipMemcpyHostToDevice, s);
 }
 
-// Colour-split storage of the level-0 V-cycle vectors (split0): problems
-// of one level and one level-0 box, even x extents, a multigrid base.  The
-// index map is checked here for every box shape: a bijection of the ghosted
-// block onto itself, and each interior cell's stencil indices those of its
-// neighbours' positions.
-static bool split0_ok(const Tables& t, bool base_smooth) {
-    if (base_smooth || t.nlev != 1 || t.level_sib0[1] != t.level_sib0[0]) return false;
-    std::map<std::tuple<int, int, int, int, int, int>, bool> shapes;
-    for (const PatchInfo& p : t.patches) {
-        if ((p.n[0] & 1) || (p.sy & 1) || p.sy != p.n[0] + 2) return false;
-        shapes[std::make_tuple(p.n[0], p.n[1], p.n[2], p.sy, p.sz,
-                               (p.lo[0] + p.lo[1] + p.lo[2]) & 1)] = true;
-    }
-    // shapes already checked in this process (hierarchies are often rebuilt
-    // with the same boxes)
-    static std::mutex checked_mu;
-    static std::map<std::tuple<int, int, int, int, int, int>, bool> checked;
-    for (const auto& kv : shapes) {
-        {
-            std::lock_guard<std::mutex> lk(checked_mu);
-            if (checked.count(kv.first)) continue;
-        }
-        PatchInfo q;
-        std::memset(&q, 0, sizeof(q));
-        std::tie(q.n[0], q.n[1], q.n[2], q.sy, q.sz, q.lo[0]) = kv.first;
-        const int64_t vol = (int64_t)q.sz * (q.n[2] + 2);
-        std::vector<char> seen(vol, 0);
-        for (int z = 0; z < q.n[2] + 2; ++z)
-            for (int y = 0; y < q.n[1] + 2; ++y)
-                for (int x = 0; x < q.sy; ++x) {
-                    const int i = split_index(q, x, y, z);
-                    if (i < 0 || i >= vol || seen[i]) return false;
-                    seen[i] = 1;
-                }
-        for (int k = 0; k < q.n[2]; ++k)
-            for (int j = 0; j < q.n[1]; ++j)
-                for (int i = 0; i < q.n[0]; ++i) {
-                    const int id[3] = {i, j, k};
-                    int own, nb[6];
-                    split_stencil(q, id, own, nb);
-                    const int x = i + 1, y = j + 1, z = k + 1;
-                    if (own != split_index(q, x, y, z) || nb[0] != split_index(q, x - 1, y, z) ||
-                        nb[1] != split_index(q, x + 1, y, z) ||
-                        nb[2] != split_index(q, x, y - 1, z) ||
-                        nb[3] != split_index(q, x, y + 1, z) ||
-                        nb[4] != split_index(q, x, y, z - 1) ||
-                        nb[5] != split_index(q, x, y, z + 1))
-                        return false;
-                }
-        std::lock_guard<std::mutex> lk(checked_mu);
-        checked[kv.first] = true;
-    }
-    return true;
-}
-
 template <typename PT>
 static void wire_pc(nrd_hierarchy* h, PcArrays<PT>& pc) {
     auto& o = h->o;
@@ -448,6 +469,11 @@ static void wire_pc(nrd_hierarchy* h, PcArrays<PT>& pc) {
     pc.base_smooth = h->opt.fac_base == NRD_BASE_SMOOTH;
     pc.split0 = split0_ok(t, pc.base_smooth);
     pc.fac_cycle = h->opt.fac_cycle;
+    pc.fuse0 = pc.split0 && !h->sweep[0].empty();
+    pc.pre = h->at<SweepTile>(o.sweep[0]);
+    pc.post = h->at<SweepTile>(o.sweep[1]);
+    pc.npre = (int)h->sweep[0].size();
+    pc.npost = (int)h->sweep[1].size();
     pc.clock = h;
 }
 
@@ -519,6 +545,7 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
             nbase += depth == 0;
         }
     HIPCHK(up(s, h->ws + o.tails, tails));
+    for (int q = 0; q < 2; ++q) HIPCHK(up(s, h->ws + o.sweep[q], h->sweep[q]));
     std::vector<int32_t> nsmooth(G + 1, 0), ntiles(G + 1, 0);
     std::vector<std::vector<Tile>> lists;         // alive until the uploads are done
     for (int g = 0; g <= G; ++g) {

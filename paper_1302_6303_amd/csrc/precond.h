@@ -64,6 +64,26 @@ struct TailEntry {
                              // where it coarsens)
 };
 
+// Both colours of the base grid's sweeps in one launch (sweep.hip): a tile of
+// x-pairs [q0, q0 + w) and rows [r0, r0 + nr), one pair per thread, for the
+// planes [k0, k1); its core [cq0, cq1) x [cr0, cr1) is written.
+constexpr int kSweepThreads = 512;
+constexpr int64_t kSweepLen = 8 << 20;       // least field length, ghosts included
+struct SweepTile {
+    int32_t patch, prob, q0, w, r0, nr, cq0, cq1, cr0, cr1, k0, k1;
+};
+// tiles of a hierarchy with one level-0 box per problem, even x extents, for a
+// sweep whose core needs `rim` rows around it
+void sweep_tiles(const Tables& t, int rim, std::vector<SweepTile>& out);
+// colour 1 of e after a sweep from zero
+void sweep_pre(const Dev& D, hipStream_t s, const SweepTile* tiles, int nt, const float* Dface,
+               const float* T, const float* f, float* e);
+// y = (p2: P2^-1 of) the sweep from e (its colour 1) plus the prolonged ec
+void sweep_post(const Dev& D, hipStream_t s, const SweepTile* tiles, int nt, const PatchInfo* Pc,
+                const int32_t* cbox, const float* Dface, const float* T, const float* f,
+                const float* e, const float* ec, int64_t nlc, const float* sigma, int mode,
+                bool p2, double* y);
+
 // Per multigrid grid: face coefficients, vectors, field length
 // (kernel argument of the tail kernels).
 template <typename PT>
@@ -134,6 +154,10 @@ struct PcArrays {
     int32_t level_line0[kMaxLev + 1] = {};
     bool base_smooth = false;        // base level: level sweeps instead of multigrid
     bool split0 = false;             // level-0 e and f in colour-split storage
+    // sweep_pre / sweep_post in place of grid 0's half-sweeps
+    bool fuse0 = false;
+    const SweepTile *pre = nullptr, *post = nullptr;
+    int npre = 0, npost = 0;
     int fac_cycle = 0;               // NRD_FAC_MULT (Alg. 1) or NRD_FAC_AFACX
     PT* e2 = nullptr;                // 2 * nl: damped Jacobi with several sweeps,
                                      // line smoother, AFACx coarse approximations
@@ -152,7 +176,8 @@ struct PcArrays {
     const PT* afacx(hipStream_t s, bool covered) const;  // returns e
     const PT* p1(hipStream_t s, bool covered) const;     // the configured cycle
     TailGrids<PT> tail_grids() const;
-    void vcycle(hipStream_t s) const;
+    // y (fuse0): the cycle's result goes there, through P2^-1 if p2
+    void vcycle(hipStream_t s, double* y = nullptr, bool p2 = true) const;
     void composite_residual(hipStream_t s, int lev) const;
     void smooth_level(hipStream_t s, const PT* rhs, int lev, int sweeps) const;
     void correct_level(hipStream_t s, int lev, bool last) const;

@@ -944,9 +944,9 @@ TailGrids<PT> PcArrays<PT>::tail_grids() const {
 }
 
 template <typename PT>
-void PcArrays<PT>::vcycle(hipStream_t s) const {
+void PcArrays<PT>::vcycle(hipStream_t s, double* y, bool p2) const {
     // grid 0 = the level-0 patches: rhs in f, result in e (colour-split
-    // storage when split0, native otherwise)
+    // storage when split0, native otherwise), or in y
     const Dev& d = *D;
     // one colour of a red-black sweep of grid g (zero: from e = 0)
     auto half_sweep = [&](int g, const PatchInfo* Pg, const PT* Dg, const PT* fg, PT* eg,
@@ -979,7 +979,14 @@ void PcArrays<PT>::vcycle(hipStream_t s) const {
             // a base grid cut into several boxes: sibling ghosts refreshed
             // after every half-sweep that the next one reads
             const bool sib = g == 0 && mg.multi0;
-            for (int it = 0; it < nu_pre; ++it) {
+            if (g == 0 && y) {
+                std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
+                if (clock) tk = clock->tic(NRD_TIMER_SMOOTH_ZERO);
+                if constexpr (std::is_same_v<PT, float>)
+                    sweep_pre(d, s, pre, npre, Dface, Tp, f, e);
+                if (clock) clock->toc(NRD_TIMER_SMOOTH_ZERO, tk);
+            }
+            for (int it = 0; it < nu_pre && !(g == 0 && y); ++it) {
                 const int which = it == 0 ? NRD_TIMER_SMOOTH_ZERO : NRD_TIMER_SMOOTH;
                 std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
                 if (g == 0 && clock) tk = clock->tic(which);
@@ -1021,6 +1028,15 @@ void PcArrays<PT>::vcycle(hipStream_t s) const {
                    nu_pre, nu_post);
     for (int g = mg.top - 1; g >= 0; --g) {
         if (mg.nsmooth[g] == 0) continue;
+        if (g == 0 && y) {
+            std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
+            if (clock) tk = clock->tic(NRD_TIMER_SMOOTH);
+            if constexpr (std::is_same_v<PT, float>)
+                sweep_post(d, s, post, npost, mg.box[1], mg.box_of[1], Dface, Tp, f, e, mg.eg[1],
+                           mg.len[1], sigma, p2_mode, p2, y);
+            if (clock) clock->toc(NRD_TIMER_SMOOTH, tk);
+            break;
+        }
         const PatchInfo* Pg = (g == 0) ? d.patches : mg.box[g];
         const int64_t nlg = (g == 0) ? d.nl : mg.len[g];
         PT* eg = (g == 0) ? e : mg.eg[g];
@@ -1278,6 +1294,10 @@ void PcArrays<PT>::apply(hipStream_t s, const double* w, double* y, const double
     const int sp = split0 ? 1 : 0;
     if (w)
         k_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, w, wsc, input(), d.nl, sp);
+    if (fuse0) {
+        vcycle(s, y, true);
+        return;
+    }
     const PT* x = p1(s, covered);
     k_p2<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, sigma, d.z3, x, y,
                                        p2_mode, d.nl, sp);
@@ -1290,6 +1310,10 @@ void PcArrays<PT>::apply_transpose(hipStream_t s, const double* w, double* y) co
     const int sp = split0 ? 1 : 0;
     k_p2t_in<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, d.ps, sigma, d.z3, w,
                                            input(), p2_mode, d.nl, sp);
+    if (fuse0) {
+        vcycle(s, y, false);
+        return;
+    }
     const PT* x = p1(s, false);
     k_out<PT><<<ntiles, kBlock, 0, s>>>(d.active, d.tiles, d.patches, x, y, d.nl, sp);
 }

@@ -121,3 +121,62 @@ def test_gradient_with_a_long_krylov_basis(precision):
                  adjoint_slots=6, fac_base=1)
         out.append(to_host(H.adjoint_run([2e-3], 1, 1)))
     assert rel_err(out[0], out[1]) < 1e-9
+
+
+# one launch per base-grid sweep from 8 M cells on: the first (a filler)
+# brings the hierarchy above; pairs and rows cut or not, three pairs only,
+# fewer planes than a run of 16, runs with a remainder
+SWEEP_EXTS = [(256, 256, 192), (10, 14, 6), (6, 8, 10), (128, 64, 64), (48, 80, 48),
+              (20, 12, 20), (192, 96, 96), (14, 6, 10), (80, 80, 80)]
+
+
+def _sweep_batch():
+    """The problems of SWEEP_EXTS, Marshak faces in turn on every side, and
+    one hierarchy of them all."""
+    ws = [_box(e, seed=30 + i) for i, e in enumerate(SWEEP_EXTS)]
+    for p, w in enumerate(ws):
+        w.problems[0].bc_E = tuple(int((f + p) % 3 == 0) for f in range(6))
+        w.dt = np.array([2e-5 / (1 + p)])
+    boxes = [I.Box(p, 0, (0, 0, 0), e) for p, e in enumerate(SWEEP_EXTS)]
+    return ws, I.Workload("several", [x.problems[0] for x in ws], boxes, [x.z[0] for x in ws],
+                          [x.E[0] for x in ws], [x.T[0] for x in ws],
+                          np.concatenate([x.dt for x in ws]))
+
+
+def test_base_sweeps_in_one_launch_keep_every_value():
+    """Each problem's preconditioner beside the others, and alone in a small
+    hierarchy (a launch per colour): bit for bit the same, as both form every
+    value by the same operations."""
+    ws, w = _sweep_batch()
+    n = [x.ncells() for x in ws]
+    us = [np.concatenate([x.compact(x.E), x.compact(x.T)]) for x in ws]
+    vs = [np.random.default_rng(60 + p).standard_normal(2 * n[p]) for p in range(len(ws))]
+
+    def apply(w, u, v):
+        H = make(w, precision=1, gmres_restart=2)
+        H.begin_step([float(x) for x in w.dt])
+        H.precond_setup(native_from_compact(H, u))
+        return compact_from_native(H, H.precond_apply(native_from_compact(H, v), H.native()))
+
+    def join(xs):                        # every E field, then every T field
+        return np.concatenate([x[:k] for x, k in zip(xs, n)] + [x[k:] for x, k in zip(xs, n)])
+
+    got = apply(w, join(us), join(vs))
+    at = np.concatenate([[0], np.cumsum(n)])
+    for p in range(1, len(ws)):
+        want = apply(ws[p], us[p], vs[p])
+        mine = np.concatenate([got[f + at[p]:f + at[p + 1]] for f in (0, at[-1])])
+        np.testing.assert_array_equal(mine, want, err_msg=str(SWEEP_EXTS[p]))
+
+
+def test_gradient_through_the_base_sweeps_in_one_launch():
+    """The transposed cycle (no coupling solve in its last launch): gradient
+    of each problem beside the others and alone.  The systems are the same
+    and solved to 1e-12; inner products are summed in other groups."""
+    ws, w = _sweep_batch()
+    opt = dict(precision=1, gmres_restart=16, bdf_max_order=1, adjoint_slots=6)
+    got = to_host(make(w, **opt).adjoint_run([float(x) for x in w.dt], 1, 1))
+    at = np.concatenate([[0], np.cumsum([x.ncells() for x in ws])])
+    for p in range(1, len(ws)):
+        want = to_host(make(ws[p], **opt).adjoint_run([float(ws[p].dt[0])], 1, 1))
+        assert rel_err(got[at[p]:at[p + 1]], want) < 1e-9, SWEEP_EXTS[p]
