@@ -128,10 +128,10 @@ typedef struct {
                                1 plane-marching tiles (each face once, LDS),
                                2 wave runs (x faces shared across lanes),
                                3 staged planes (each plane slice read once
-                               into LDS, 256-cell runs; a hierarchy with a
-                               patch wider than about 250 cells in x runs
-                               variant 1 instead)                            */
-    int32_t zchunk;         /* planes per tile of variants 1, 2 (0: default)  */
+                               into LDS, 256-cell runs; a hierarchy whose
+                               vectors stay in the last-level cache or whose
+                               rows are wide runs variant 2's kernel instead)*/
+    int32_t zchunk;         /* planes per tile of variants 1 to 3 (0: default)*/
     int32_t bdf_max_order;  /* 2 (default): BDF2 after the first step; 1: BDF1
                                throughout (the adjoint assumes BDF1)         */
     int32_t error_estimate; /* 1: every BDF2 step keeps its leapfrog predictor

@@ -67,6 +67,38 @@ inline int64_t intersect(const int32_t alo[3], const int32_t ahi[3],
 
 }  // namespace
 
+// one-plane tiles of staged planes
+static int64_t plane_runs(const Tables& t) {
+    int64_t n = 0;
+    for (const PatchInfo& p : t.patches)
+        n += (int64_t)p.n[2] * ((p.n[0] * p.n[1] + kStageCells - 1) / kStageCells);
+    return n;
+}
+
+int32_t plane_variant(const Tables& t, int32_t variant) {
+    if (variant != 3) return variant;
+    // Staged planes read each value of a plane once per tile, but wait at two
+    // barriers per plane, and shorten their runs where a slice of kStageCells
+    // cells and its two rows of neighbours exceeds kStageLen (rows of more
+    // than 120 cells).  Wave runs read neighbours again from the caches.  So
+    // wave runs where the vectors stay in the last-level cache or most cells
+    // are in rows that wide.  Staged / wave runs, residual
+    // and Jacobian action, us: 40^3 6.4 / 6.4 and 7.3 / 6.4; three levels,
+    // 58 k cells 19.9 / 17.7 and 30.1 / 27.4; 80^3 13.4 / 11.4 and 18.9 /
+    // 16.1; 128^3 37 / 31 and 60 / 44; 160^3 82 / 53 and 125 / 85; 192^3 204
+    // / 114 and 294 / 151; 256^3 332 / 274 and 397 / 343 (one thread per
+    // column, which staged planes gave way to there); batches of boxes up to
+    // 96 wide: 8 boxes, 1.6 M cells 28.6 / 25.3 and 40.7 / 37.5, 16, 5.2 M 78
+    // / 87 and 122 / 121, 64, 20 M 305 / 334 and 367 / 410.  Below about 200
+    // tiles both take their launch: 32^3 6.0 / 6.2 and 6.4 / 6.8.
+    constexpr int64_t kFewTiles = 200, kManyTiles = 12000;
+    const int64_t n = plane_runs(t);
+    int64_t wide = 0;
+    for (const PatchInfo& p : t.patches)
+        if (p.n[0] > 120) wide += p.ncell;
+    return 2 * wide > t.ncells || (n >= kFewTiles && n <= kManyTiles) ? 2 : 3;
+}
+
 int32_t default_zchunk(const Tables& t, int32_t b, int32_t variant) {
     if (variant == 3) {
         // Staged planes: a tile's planes are a serial chain of about 1.8 us
@@ -81,12 +113,21 @@ int32_t default_zchunk(const Tables& t, int32_t b, int32_t variant) {
         // cells (2) 47 / 76 and 65 / 93; 20 M cells (16) 291 / 366 against
         // 311 / 418 at 4.
         constexpr int64_t kMostTiles = 2700;
-        int64_t n = 0;
-        for (const PatchInfo& p : t.patches)
-            n += (int64_t)p.n[2] * ((p.n[0] * p.n[1] + kStageCells - 1) / kStageCells);
+        const int64_t n = plane_runs(t);
         int32_t kc = 1;
         while (kc < 16 && n > kMostTiles * kc) kc *= 2;
         return kc;
+    }
+    if (variant == 2) {
+        // Wave runs: the same trade with a shorter chain (0.5 us a plane, no
+        // barrier), so up to four planes.  Residual / Jacobian action at 1, 2
+        // and 4 planes, us: 64^3 7.8 / 10.2, 7.8 / 10.7, 9.3 / 12.1; 80^3 (2)
+        // 11.5 / 15.9, 11.4 / 16.1, 12.5 / 17.0; 96^3 (4) 17.4 / 24.1, 15.7 /
+        // 22.4, 15.9 / 22.3; 128^3 (4) 35 / 52, 32 / 46, 31 / 44; 160^3 (4)
+        // 66 / 104, 57 / 89, 53 / 85, at 8 planes 55 / 85.
+        constexpr int64_t kMostTiles = 1500;
+        const int64_t n = plane_runs(t);
+        return n <= kMostTiles ? 1 : (n <= 2 * kMostTiles ? 2 : 4);
     }
     // register-marching: short runs keep enough waves resident to hide load
     // latency
@@ -101,12 +142,18 @@ int32_t staged_len(const PatchInfo& p, int32_t s0, int32_t cnt) {
     return (lb % nx + 1) + sy * (lb / nx + 2) - g0 + 1;
 }
 
-bool patch_planes(const PatchInfo& p, int32_t b, int32_t kc, int32_t run, int32_t max_span,
+int32_t default_run(int32_t variant) {
+    return variant == 2 ? kWaveRun : (variant == 3 ? kStageCells : 256);
+}
+
+bool patch_planes(const PatchInfo& p, int32_t b, int32_t kc, int32_t run, int32_t variant,
                   std::vector<STile>& out) {
-    const int32_t plane = p.n[0] * p.n[1];
+    const int32_t max_span = variant == 3 ? kStageLen : 0;
+    const int32_t plane = variant == 2 ? (p.n[0] + 1) * ((p.n[1] + kWaveRows - 1) / kWaveRows)
+                                       : p.n[0] * p.n[1];
     const int32_t ch = std::max(1, kc);
     // a tile's cells are owned one per thread of a 256-thread workgroup
-    if (run <= 0 || run > kStageCells) return false;
+    if (run <= 0 || run > default_run(variant)) return false;
     int32_t r = run;
     if (max_span > 0) {
         // shorten the runs of this patch until every staged slice fits
@@ -125,18 +172,14 @@ bool patch_planes(const PatchInfo& p, int32_t b, int32_t kc, int32_t run, int32_
     return true;
 }
 
-bool build_planes(Tables& t, const std::vector<int32_t>& kc, int32_t run, int32_t max_span) {
-    return build_planes(t, kc, std::vector<int32_t>(t.nbox, run), max_span);
-}
-
 bool build_planes(Tables& t, const std::vector<int32_t>& kc, const std::vector<int32_t>& run,
-                  int32_t max_span) {
+                  int32_t variant) {
     t.stiles.clear();
     t.level_stile0.assign(t.nlev + 1, 0);
     t.patch_stile0.assign(t.nbox + 1, 0);
     std::vector<std::vector<STile>> per(t.nbox);
     for (int b = 0; b < t.nbox; ++b)
-        if (!patch_planes(t.patches[b], b, kc[b], run[b], max_span, per[b])) return false;
+        if (!patch_planes(t.patches[b], b, kc[b], run[b], variant, per[b])) return false;
     for (int l = 0; l < t.nlev; ++l) {
         t.level_stile0[l] = (int32_t)t.stiles.size();
         for (int b = 0; b < t.nbox; ++b) {
@@ -579,7 +622,7 @@ nrd_status build_tables(const nrd_problem* probs, int32_t nprob,
     {
         std::vector<int32_t> kc(nbox);
         for (int b = 0; b < nbox; ++b) kc[b] = default_zchunk(t, b, 1);
-        build_planes(t, kc, 256);   // default stencil variant: plane marching
+        build_planes(t, kc, std::vector<int32_t>(nbox, 256), 1);   // default stencil variant: plane marching
     }
     t.prob_vtile0.assign(nprob + 1, 0);
     for (int p = 0; p < nprob; ++p) {

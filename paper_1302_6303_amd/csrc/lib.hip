@@ -100,6 +100,7 @@ struct nrd_hierarchy final : public Clock {
     bool mixed = false;
     bool cf_built = false;          // transposed coarse-fine table uploaded
     std::vector<int32_t> patch_tile0;
+    int32_t variant = 0;            // stencil kernel that runs (plane_variant)
     std::vector<SweepTile> sweep[2];   // fused base sweeps: pre, post (empty: not fused)
 
     // workspace offsets
@@ -632,7 +633,7 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     D.tiles = h->at<Tile>(o.tiles);
     for (int l = 0; l <= t.nlev; ++l) D.level_tile0[l] = t.level_tile0[l];
     D.stiles = h->at<STile>(o.stiles);
-    D.bricks = h->opt.stencil;
+    D.bricks = h->variant;
     for (int l = 0; l <= t.nlev; ++l) D.level_stile0[l] = t.level_stile0[l];
     D.vtiles = h->at<Tile>(o.vtiles);
     D.nvtiles = (int32_t)t.vtiles.size();
@@ -1819,27 +1820,30 @@ nrd_status nrd_hierarchy_create(const nrd_problem* probs, int32_t nprob, const n
                 if (first[h->t.tiles[i].patch] < 0) first[h->t.tiles[i].patch] = (int32_t)i;
             h->patch_tile0 = first;
         }
+        h->variant = plane_variant(h->t, h->opt.stencil);
         if (h->opt.stencil >= 1 || h->opt.zchunk > 0) {
             std::vector<int32_t> kc(h->t.nbox);
             auto chunks = [&](int variant) {
                 if (h->opt.zchunk > 0) {
                     std::fill(kc.begin(), kc.end(), h->opt.zchunk);
-                } else if (variant == 3) {
+                } else if (variant >= 2) {
                     std::fill(kc.begin(), kc.end(), default_zchunk(h->t, 0, variant));
                 } else {
                     for (int b = 0; b < h->t.nbox; ++b) kc[b] = default_zchunk(h->t, b, variant);
                 }
             };
-            int st = h->opt.stencil;
-            chunks(st);
-            bool ok = build_planes(h->t, kc, st == 2 ? 4 * 63 : (st == 3 ? kStageCells : 256),
-                                   st == 3 ? kStageLen : 0);
-            if (!ok && st == 3) {
-                // rows too wide for the staged slices (x extent above about
-                // 250): the plane-marching variant, same values, any width
-                st = h->opt.stencil = 1;
-                chunks(st);
-                ok = build_planes(h->t, kc, 256, 0);
+            auto build = [&] {
+                chunks(h->variant);
+                return build_planes(h->t, kc,
+                                    std::vector<int32_t>(h->t.nbox, default_run(h->variant)),
+                                    h->variant);
+            };
+            bool ok = build();
+            if (!ok && h->variant == 3) {
+                // some rows too wide for the staged slices (x extent above
+                // about 250): wave runs, any width
+                h->variant = 2;
+                ok = build();
             }
             if (!ok) {
                 delete h;
@@ -2120,11 +2124,11 @@ extern "C" {
 // Tiles of every patch with the given per-patch shapes, in launch order
 // (level by level); false if some patch has no shape that fits.
 static bool plane_list(const Tables& t, const std::vector<int32_t>& kc,
-                       const std::vector<int32_t>& run, int32_t span, std::vector<STile>& out) {
+                       const std::vector<int32_t>& run, int32_t variant, std::vector<STile>& out) {
     out.clear();
     for (int l = 0; l < t.nlev; ++l)
         for (int b = 0; b < t.nbox; ++b)
-            if (t.boxes[b].level == l && !patch_planes(t.patches[b], b, kc[b], run[b], span, out))
+            if (t.boxes[b].level == l && !patch_planes(t.patches[b], b, kc[b], run[b], variant, out))
                 return false;
     return true;
 }
@@ -2132,16 +2136,15 @@ static bool plane_list(const Tables& t, const std::vector<int32_t>& kc,
 nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed_classes) {
     NEED_BOUND(h);
     if (timed_classes) *timed_classes = 0;
-    const int var = h->opt.stencil;
+    const int var = h->variant;
     if (var == 0) return NRD_OK;                 // one-cell tiles: nothing to choose
     if (!h->fields_set) return fail(NRD_ESTATE, "nrd_autotune needs nrd_set_fields first");
     Tables& t = h->t;
     hipStream_t s = h->stream;
-    const int32_t span = var == 3 ? kStageLen : 0;
-    const int32_t run0 = var == 2 ? 4 * 63 : (var == 3 ? kStageCells : 256);
+    const int32_t run0 = default_run(var);
     std::vector<std::pair<int32_t, int32_t>> cand;           // (planes, run)
-    if (var == 3) {
-        for (int kc : {1, 2, 4, 8, 16, 32}) cand.push_back({kc, kStageCells});
+    if (var >= 2) {
+        for (int kc : {1, 2, 4, 8, 16, 32}) cand.push_back({kc, run0});
     } else {
         for (int kc : {2, 4, 8, 16}) cand.push_back({kc, run0});
     }
@@ -2152,6 +2155,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
         cls[k].push_back(b);
     }
     const std::string arch = device_arch();
+    const std::string tag = "v" + std::to_string(h->opt.stencil);
     // cache format tag: the tile constants the cached shapes were chosen with
     const std::string cache_fmt =
         "f" + std::to_string(kStageCells) + "x" + std::to_string(kStageLen) + "b" +
@@ -2166,25 +2170,27 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
             int32_t kc = 0, run = 0;
             if (!(ls >> a >> v >> fmt >> dims >> kc >> run)) continue;
             ClassKey k;
-            if (a != arch || v != "v" + std::to_string(var) || fmt != cache_fmt ||
+            if (a != arch || v != tag || fmt != cache_fmt ||
                 std::sscanf(dims.c_str(), "%dx%dx%d", &k.n[0], &k.n[1], &k.n[2]) != 3)
                 continue;
             // only shapes this build would itself try: a stale or edited line
             // can never give a tile more cells than a workgroup holds
+            // (planes chosen for staged planes or for wave runs serve both)
             bool known = false;
-            for (auto [ckc, crun] : cand) known |= (ckc == kc && crun == run);
+            for (auto [ckc, crun] : cand)
+                known |= ckc == kc && (crun == run || (h->opt.stencil == 3 &&
+                                                       (run == kStageCells || run == kWaveRun)));
             if (!known) continue;
-            pick[k] = {kc, run};
+            pick[k] = {kc, run0};
         }
     }
     // current shapes: cached choices, else the defaults
     std::vector<int32_t> kc(t.nbox), run(t.nbox);
-    const int32_t staged = default_zchunk(t, 0, 3);
     for (auto& kv : cls) {
         auto it = pick.find(kv.first);
         for (int b : kv.second) {
             kc[b] = it != pick.end() ? it->second.first
-                                     : (var == 3 ? staged : default_zchunk(t, b, var));
+                                     : default_zchunk(t, b, var);
             run[b] = it != pick.end() ? it->second.second : run0;
         }
     }
@@ -2226,7 +2232,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
     std::ofstream out;
     if (cache_path) out.open(cache_path, std::ios::app);
     double cur_ms = 1e300;
-    if (plane_list(t, kc, run, span, tl)) (void)time_list(cur_ms);
+    if (plane_list(t, kc, run, var, tl)) (void)time_list(cur_ms);
     for (auto& kv : cls) {
         if (rc) break;
         if (pick.count(kv.first)) continue;
@@ -2240,7 +2246,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
                 run2[b] = crun;
             }
             double ms = 0.0;
-            if (!plane_list(t, kc2, run2, span, tl) || !time_list(ms)) {
+            if (!plane_list(t, kc2, run2, var, tl) || !time_list(ms)) {
                 if (rc) break;
                 continue;
             }
@@ -2258,7 +2264,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
         pick[kv.first] = choice;
         if (timed_classes) ++*timed_classes;
         if (out)
-            out << arch << " v" << var << " " << cache_fmt << " " << kv.first.n[0] << "x"
+            out << arch << " " << tag << " " << cache_fmt << " " << kv.first.n[0] << "x"
                 << kv.first.n[1] << "x"
                 << kv.first.n[2] << " " << choice.first << " " << choice.second << " "
                 << best * 1e3 << "\n";
@@ -2273,7 +2279,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
     trial.nbox = t.nbox;
     trial.patches = t.patches;
     trial.boxes = t.boxes;
-    if (!build_planes(trial, kc, run, span) || trial.stiles.size() > h->stile_cap)
+    if (!build_planes(trial, kc, run, var) || trial.stiles.size() > h->stile_cap)
         return fail(NRD_EINVAL, "tuned tile shapes do not fit");
     t.stiles.swap(trial.stiles);
     t.level_stile0.swap(trial.level_stile0);

@@ -180,22 +180,28 @@ constexpr int32_t kBottomBand = 26;
 // kStageLen values.
 constexpr int32_t kStageCells = 256;
 constexpr int32_t kStageLen = 512;
+// Wave-run stencil tiles: entries of a plane (a row's cells and the ghost
+// after them, kWaveRows rows each) per tile, 63 of each wavefront.
+constexpr int32_t kWaveRun = 4 * 63;
+constexpr int32_t kWaveRows = 1;
 
-// Plane-marching tiles: planes per tile (z chunk) of patch b (staged planes:
+// The kernel that runs the configured stencil variant (staged planes give way
+// to wave runs by a rule on sizes).
+int32_t plane_variant(const Tables& t, int32_t variant);
+// Plane-marching tiles: planes per tile (z chunk) of patch b (variants 2 and 3:
 // the same for every patch of the hierarchy).
 int32_t default_zchunk(const Tables& t, int32_t b, int32_t variant);
 // Length of the ghosted-plane slice that covers cells [s0, s0 + cnt) of a
 // plane of patch p and their x / y neighbours.
 int32_t staged_len(const PatchInfo& p, int32_t s0, int32_t cnt);
-// run: cells of a plane per tile (256 for the plane kernel, 4 x 63 for
-// wave runs, kStageCells for staged planes); max_span > 0 shortens a
-// patch's runs until every staged slice fits.  False if none fits.
-bool build_planes(Tables& t, const std::vector<int32_t>& kc, int32_t run,
-                  int32_t max_span = 0);
-// Per-patch runs; patch_planes appends one patch's tiles (false: no run fits).
+// run: places of a plane per tile (256 cells for the plane kernel, kWaveRun
+// entries for wave runs, kStageCells cells for staged planes, whose runs are
+// shortened until every slice fits).  False if none fits.
+int32_t default_run(int32_t variant);
 bool build_planes(Tables& t, const std::vector<int32_t>& kc, const std::vector<int32_t>& run,
-                  int32_t max_span);
-bool patch_planes(const PatchInfo& p, int32_t b, int32_t kc, int32_t run, int32_t max_span,
+                  int32_t variant);
+// appends one patch's tiles (false: no run fits)
+bool patch_planes(const PatchInfo& p, int32_t b, int32_t kc, int32_t run, int32_t variant,
                   std::vector<STile>& out);
 
 // Berger-Rigoutsos clustering of tags into new boxes (cluster.cpp).

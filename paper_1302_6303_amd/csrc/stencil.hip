@@ -259,20 +259,26 @@ __global__ __launch_bounds__(kBlock) void k_stencil_z(
     }
 }
 
-// Wave-run variant.  Each wavefront of the workgroup owns a run of 63
-// consecutive cells of the (x fastest) linear index of a z-plane and walks
-// the planes k0 <= k < k1.  Lane l evaluates the low x face of its cell; the
-// high x face of lane l < 63 is lane l+1's low face (cross-lane shuffle, no
-// barrier), lane 63 only helps.  The y faces are evaluated per cell and the
-// z face is carried in registers to the next plane.
-template <int MODE>
-__global__ __launch_bounds__(kBlock) void k_stencil_w(
+// Wave-run variant.  A tile is a run of entries of one z-plane and a range of
+// planes.  An entry is a place on a row's nx cells and the ghost after them (x
+// fastest), and R rows of it: lane l evaluates its low x faces, the high ones
+// are lane l + 1's (cross-lane shuffle; the ghost's entry only serves the last
+// cell, lane 63 only lane 62: a wavefront owns 63 entries).  Between the R rows
+// a y face serves both; the z face is carried to the next plane.  No barrier,
+// nothing staged: a wavefront waits for one round of loads per plane, all of
+// them issued before the first face.  Bound by instruction issue in the cache
+// (128^3 Jacobian action 45 us, 68% of the issue slots; staged planes 54 us) and by the second
+// reads of neighbours beyond it.  R = 2 evaluates 3.5 faces per cell instead
+// of 4 but halves the wavefronts: 128^3 52 us, 160^3 the same 85.
+template <int MODE, int R>
+__global__ __launch_bounds__(kBlock, R == 1 ? 4 : 1) void k_stencil_w(
     const STile* __restrict__ tiles, int t0, const int32_t* __restrict__ map,
     const PatchInfo* __restrict__ P,
     const ProbScalars* __restrict__ ps, const int32_t* __restrict__ active,
     const uint8_t* __restrict__ ctype, const double* __restrict__ u,
     const double* __restrict__ v, const double* __restrict__ z3,
     const double* __restrict__ b, double* __restrict__ out, int64_t nl) {
+    constexpr int NA = MODE ? 5 : 3;                       // E, T, z^3 (, vE, vT)
     const STile t = tiles[tile_index(map, t0)];
     if (active && !active[t.prob]) return;
     const PatchInfo& p = P[t.patch];
@@ -281,96 +287,155 @@ __global__ __launch_bounds__(kBlock) void k_stencil_w(
     const int lane = threadIdx.x & 63;
     const int pos = (threadIdx.x >> 6) * 63 + lane;        // within the tile's run
     const int nx = p.n[0], ny = p.n[1], nz = p.n[2];
-    const int lin = t.s0 + pos;
-    const bool exists = pos <= t.cnt && lin < nx * ny;     // helper lanes included
-    const bool owned = lane < 63 && pos < t.cnt;
-    const int i = lin % nx, j = lin / nx;
+    const int last = (nx + 1) * ((ny + R - 1) / R) - 1;    // entries beyond repeat it
+    const int lin = min(t.s0 + pos, last);
+    const int i = lin % (nx + 1), j = (lin / (nx + 1)) * R;
+    const bool mine = lane < 63 && pos < t.cnt && i < nx;
     const int sy = p.sy, sz = p.sz;
     const bool use_ct = p.flags & PF_CTYPE;
     const double hx = p.h[0], hy = p.h[1], hz = p.h[2];
     const double ihx = p.ih[0], ihy = p.ih[1], ihz = p.ih[2];
     const bool xlo_p = (p.phys & 1) && i == 0, xhi_p = ((p.phys >> 1) & 1) && i == nx - 1;
-    const bool ylo_p = ((p.phys >> 2) & 1) && j == 0, yhi_p = ((p.phys >> 3) & 1) && j == ny - 1;
+    const bool ylo_p = ((p.phys >> 2) & 1) && j == 0;
     const bool zlo_p = (p.phys >> 4) & 1, zhi_p = (p.phys >> 5) & 1;
-    int c = p.off + (i + 1) + sy * (j + 1) + sz * (t.k0 + 1);
-    double czE = 0.0, czT = 0.0;
-    if (owned && !(t.k0 == 0 && zlo_p))
-        face_any<MODE>(u, v, z3, c - sz, c, nl, hz, ihz, kappa, lam, czE, czT);
-    for (int k = t.k0; k < t.k1; ++k, c += sz) {
-        double E = 0.0, T = 1.0, z = 1.0, dE = 0.0, dT = 0.0;
-        double lxE = 0.0, lxT = 0.0;
-        if (exists) {
-            E = u[c];
-            T = u[c + nl];
-            z = z3[c];
-            if (MODE) {
-                dE = v[c];
-                dT = v[c + nl];
+    const double* src[NA];
+    src[0] = u;
+    src[1] = u + nl;
+    src[2] = z3;
+    if (MODE) {
+        src[NA - 2] = v;
+        src[NA - 1] = v + nl;
+    }
+    // value o entries beyond offset e (inside a plane) of the plane at x: a
+    // uniform address plus a 32-bit byte offset
+    auto ld = [](const double* x, int64_t o, uint32_t e) {
+        return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(x + o) + e * 8u);
+    };
+    // plane offsets of the rows j - 1 .. j + R (a last odd row's group repeats
+    // the ghost row)
+    uint32_t row[R + 2];
+#pragma unroll
+    for (int r = 0; r < R + 2; ++r) row[r] = (i + 1) + sy * min(j + r, ny + 1);
+    auto face = [&](const double* a, const double* c, double h, double ih, double& fe,
+                    double& ft) {
+        if constexpr (MODE == 0)
+            face_flux(a[0], c[0], a[1], c[1], a[2], c[2], h, ih, kappa, lam, fe, ft);
+        else
+            face_flux_tan(a[0], c[0], a[1], c[1], a[2], c[2], a[NA - 2], c[NA - 2], a[NA - 1],
+                          c[NA - 1], h, ih, kappa, lam, fe, ft);
+    };
+    auto robin = [&](const double* c, int f, double h) {
+        return robin_any<MODE>(c[0], c[1], c[2], q.R[f], h, MODE ? c[NA - 2] : 0.0,
+                               MODE ? c[NA - 1] : 0.0);
+    };
+    int64_t base = p.off + (int64_t)sz * (t.k0 + 1);       // the plane's first entry
+    double own[R][NA];                                     // the entry's cells, plane k
+    double czE[R], czT[R];                                 // their low z fluxes
+    {
+        double below[R][NA];
+#pragma unroll
+        for (int r = 0; r < R; ++r)
+#pragma unroll
+            for (int a = 0; a < NA; ++a) {
+                own[r][a] = ld(src[a], base, row[r + 1]);
+                below[r][a] = ld(src[a], base - sz, row[r + 1]);
+            }
+        const bool edge = t.k0 == 0 && zlo_p;              // uniform
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            czE[r] = czT[r] = 0.0;
+            if (!edge)
+                face(below[r], own[r], hz, ihz, czE[r], czT[r]);
+            else if ((p.robin >> 4) & 1)
+                czE[r] = -robin(own[r], 4, hz);
+        }
+    }
+    for (int k = t.k0; k < t.k1; ++k, base += sz) {
+        // every load of the plane first
+        double next[R][NA], west[R][NA], south[NA], north[NA], bE[R] = {}, bT[R] = {};
+        int ct[R] = {};
+#pragma unroll
+        for (int a = 0; a < NA; ++a) {
+            south[a] = ld(src[a], base, row[0]);
+            north[a] = ld(src[a], base, row[R + 1]);
+#pragma unroll
+            for (int r = 0; r < R; ++r) {
+                west[r][a] = ld(src[a], base - 1, row[r + 1]);
+                next[r][a] = ld(src[a], base + sz, row[r + 1]);
+            }
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (MODE == 0) {
+                bE[r] = ld(b, base, row[r + 1]);
+                bT[r] = ld(b + nl, base, row[r + 1]);
+            }
+            if (use_ct) ct[r] = ctype[base + row[r + 1]];
+        }
+        // y faces: low one of the first row, between rows, high one of the last
+        double yE[R + 1], yT[R + 1];
+        face(south, own[0], hy, ihy, yE[0], yT[0]);
+#pragma unroll
+        for (int r = 1; r < R; ++r) face(own[r - 1], own[r], hy, ihy, yE[r], yT[r]);
+        face(own[R - 1], north, hy, ihy, yE[R], yT[R]);
+        if (ylo_p) {
+            yE[0] = yT[0] = 0.0;
+            if ((p.robin >> 2) & 1) yE[0] = -robin(own[0], 2, hy);
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool yhi_p = ((p.phys >> 3) & 1) && j + r == ny - 1;
+            double lxE, lxT, hzE = 0.0, hzT = 0.0;
+            face(west[r], own[r], hx, ihx, lxE, lxT);
+            if (k == nz - 1 && zhi_p) {                    // uniform
+                if ((p.robin >> 5) & 1) hzE = robin(own[r], 5, hz);
+            } else {
+                face(own[r], next[r], hz, ihz, hzE, hzT);
             }
             if (xlo_p) {
-                if (p.robin & 1) lxE = -robin_any<MODE>(E, T, z, q.R[0], hx, dE, dT);
-            } else {
-                face_any<MODE>(u, v, z3, c - 1, c, nl, hx, ihx, kappa, lam, lxE, lxT);
+                lxE = lxT = 0.0;
+                if (p.robin & 1) lxE = -robin(own[r], 0, hx);
             }
-        }
-        // high x face of lane l = low x face of lane l + 1
-        double hxE = __shfl_down(lxE, 1, 64);
-        double hxT = __shfl_down(lxT, 1, 64);
-        if (!owned) continue;
-        if (i == nx - 1) {
-            hxE = hxT = 0.0;
+            // high x face of lane l = low x face of lane l + 1
+            double hxE = __shfl_down(lxE, 1, 64);
+            double hxT = __shfl_down(lxT, 1, 64);
             if (xhi_p) {
-                if ((p.robin >> 1) & 1) hxE = robin_any<MODE>(E, T, z, q.R[1], hx, dE, dT);
-            } else {
-                face_any<MODE>(u, v, z3, c, c + 1, nl, hx, ihx, kappa, lam, hxE, hxT);
+                hxE = hxT = 0.0;
+                if ((p.robin >> 1) & 1) hxE = robin(own[r], 1, hx);
             }
+            double lyE = yE[r], lyT = yT[r], hyE = yE[r + 1], hyT = yT[r + 1];
+            if (yhi_p) {
+                hyE = hyT = 0.0;
+                if ((p.robin >> 3) & 1) hyE = robin(own[r], 3, hy);
+            }
+            double lzE = czE[r], lzT = czT[r];
+            czE[r] = hzE;
+            czT[r] = hzT;
+            if (use_ct) {                                  // uniform
+                if (ct[r] & (1 << 1)) lxE = lxT = 0.0;
+                if (ct[r] & (1 << 2)) hxE = hxT = 0.0;
+                if (ct[r] & (1 << 3)) lyE = lyT = 0.0;
+                if (ct[r] & (1 << 4)) hyE = hyT = 0.0;
+                if (ct[r] & (1 << 5)) lzE = lzT = 0.0;
+                if (ct[r] & (1 << 6)) hzE = hzT = 0.0;
+            }
+            const double divE = (hxE - lxE) * ihx + (hyE - lyE) * ihy + (hzE - lzE) * ihz;
+            const double divT = (hxT - lxT) * ihx + (hyT - lyT) * ihy + (hzT - lzT) * ihz;
+            double oE, oT;
+            if (MODE == 0)
+                cell_out0(q, own[r][0], own[r][1], own[r][2], bE[r], bT[r], divE, divT, oE, oT);
+            else
+                cell_out1(q, own[r][0], own[r][1], own[r][2], own[r][NA - 2], own[r][NA - 1],
+                          divE, divT, oE, oT);
+            if (mine && j + r < ny) {
+                const int64_t c = base + row[r + 1];
+                const bool covered = ct[r] & CT_COVERED;
+                out[c] = covered ? 0.0 : oE;
+                out[c + nl] = covered ? 0.0 : oT;
+            }
+#pragma unroll
+            for (int a = 0; a < NA; ++a) own[r][a] = next[r][a];
         }
-        double lyE = 0.0, lyT = 0.0, hyE = 0.0, hyT = 0.0, hzE = 0.0, hzT = 0.0;
-        double lzE = 0.0, lzT = 0.0;
-        if (ylo_p) {
-            if ((p.robin >> 2) & 1) lyE = -robin_any<MODE>(E, T, z, q.R[2], hy, dE, dT);
-        } else {
-            face_any<MODE>(u, v, z3, c - sy, c, nl, hy, ihy, kappa, lam, lyE, lyT);
-        }
-        if (yhi_p) {
-            if ((p.robin >> 3) & 1) hyE = robin_any<MODE>(E, T, z, q.R[3], hy, dE, dT);
-        } else {
-            face_any<MODE>(u, v, z3, c, c + sy, nl, hy, ihy, kappa, lam, hyE, hyT);
-        }
-        if (k == nz - 1 && zhi_p) {
-            if ((p.robin >> 5) & 1) hzE = robin_any<MODE>(E, T, z, q.R[5], hz, dE, dT);
-        } else {
-            face_any<MODE>(u, v, z3, c, c + sz, nl, hz, ihz, kappa, lam, hzE, hzT);
-        }
-        if (k == 0 && zlo_p) {
-            if ((p.robin >> 4) & 1) lzE = -robin_any<MODE>(E, T, z, q.R[4], hz, dE, dT);
-        } else {
-            lzE = czE;
-            lzT = czT;
-        }
-        czE = hzE;
-        czT = hzT;
-        const int ct = use_ct ? ctype[c] : 0;
-        if (ct & CT_COVERED) {
-            out[c] = 0.0;
-            out[c + nl] = 0.0;
-            continue;
-        }
-        if (ct & (1 << 1)) lxE = lxT = 0.0;
-        if (ct & (1 << 2)) hxE = hxT = 0.0;
-        if (ct & (1 << 3)) lyE = lyT = 0.0;
-        if (ct & (1 << 4)) hyE = hyT = 0.0;
-        if (ct & (1 << 5)) lzE = lzT = 0.0;
-        if (ct & (1 << 6)) hzE = hzT = 0.0;
-        const double divE = (hxE - lxE) * ihx + (hyE - lyE) * ihy + (hzE - lzE) * ihz;
-        const double divT = (hxT - lxT) * ihx + (hyT - lyT) * ihy + (hzT - lzT) * ihz;
-        double oE, oT;
-        if (MODE == 0)
-            cell_out0(q, E, T, z, b[c], b[c + nl], divE, divT, oE, oT);
-        else
-            cell_out1(q, E, T, z, dE, dT, divE, divT, oE, oT);
-        out[c] = oE;
-        out[c + nl] = oT;
     }
 }
 
@@ -754,7 +819,7 @@ static void residual_launch(const Dev& D, hipStream_t s, int t0, int nt, const i
         k_stencil_z<0><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, nullptr, D.z3, b, F, D.nl);
     else if (D.bricks == 2)
-        k_stencil_w<0><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
+        k_stencil_w<0, kWaveRows><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, nullptr, D.z3, b, F, D.nl);
     else
         k_stencil_flat<0><<<nt, kBlock, 0, s>>>(D.tiles, t0, map, D.patches, D.ps, D.active,
@@ -770,7 +835,7 @@ static void jvp_launch(const Dev& D, hipStream_t s, int t0, int nt, const int32_
         k_stencil_z<1><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, v, D.z3, nullptr, Jv, D.nl);
     else if (D.bricks == 2)
-        k_stencil_w<1><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
+        k_stencil_w<1, kWaveRows><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, v, D.z3, nullptr, Jv, D.nl);
     else
         k_stencil_flat<1><<<nt, kBlock, 0, s>>>(D.tiles, t0, map, D.patches, D.ps, D.active,

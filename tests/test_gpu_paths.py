@@ -180,3 +180,49 @@ def test_gradient_through_the_base_sweeps_in_one_launch():
     for p in range(1, len(ws)):
         want = to_host(make(ws[p], **opt).adjoint_run([float(ws[p].dt[0])], 1, 1))
         assert rel_err(got[at[p]:at[p + 1]], want) < 1e-9, SWEEP_EXTS[p]
+
+
+def _grid(base, fine):
+    """Problems of the given base extents (equal ones share their fields) and
+    refined boxes (lo, hi) of the first."""
+    rng = np.random.default_rng(I.SEED_BASE + 70)
+    problems, boxes = [], []
+    for p, e in enumerate(base):
+        problems.append(I.Problem(base_n=tuple(e), bc_E=(1, 0, 1, 1, 0, 1)))
+        boxes.append(I.Box(p, 0, (0, 0, 0), tuple(e)))
+    boxes += [I.Box(0, 1, lo, hi) for lo, hi in fine]
+    z = I.eval_on_boxes(I.box_field(I.sample_material_boxes(rng, 2)), problems, boxes)
+    E, T = I.front_state(problems, boxes, rng)
+    return I.Workload("grid", problems, boxes, z, E, T, np.full(len(base), 1e-3))
+
+
+# staged planes / wave runs: one-plane tiles 8 and 192 | 200, 12000 | 12008;
+# rows of 20 and 8 cells (with their ghost a whole share of a wavefront's 63
+# entries); wide rows; refined boxes of 60, 62, 126, 128 and 256 cells in x
+FINE = [((0, 0, 0), (126, 10, 40)), ((0, 20, 0), (62, 30, 40)), ((64, 20, 2), (124, 32, 42)),
+        ((0, 40, 60), (128, 46, 90))]
+
+
+@pytest.mark.parametrize("base,fine", [
+    ([(8, 8, 8)], []), ([(8, 8, 8)] * 24, []), ([(8, 8, 8)] * 25, []), ([(80, 80, 80)] * 6, []),
+    ([(80, 80, 80)] * 6 + [(8, 8, 8)], []), ([(20, 12, 20)] * 12, []), ([(128, 64, 64)], []),
+    ([(64, 64, 64)], FINE), ([(128, 64, 64)], [((0, 0, 0), (256, 8, 24))])])
+def test_stencil_kernel_of_the_size_rule(base, fine):
+    """Residual and Jacobian action by the default kernel against one thread
+    per cell: the same formulas of every face and cell, fused differently
+    kernel by kernel.  Rounding of a face's chain of about twenty operations,
+    of seven faces and terms: a few hundred ulp of the largest at most."""
+    w = _grid(base, fine)
+    rng = np.random.default_rng(5)
+    n = w.ncells()
+    v = rng.standard_normal(2 * n)
+    u = np.concatenate([w.compact(w.E), w.compact(w.T)]) * rng.uniform(0.9, 1.1, 2 * n)
+    outs = []
+    for st in (3, 0):
+        H = make(w, stencil=st, gmres_restart=2)
+        H.begin_step([float(x) for x in w.dt])
+        F = H.residual(native_from_compact(H, u), H.native())
+        Jv = H.jvp(native_from_compact(H, u), native_from_compact(H, v), H.native())
+        outs.append((compact_from_native(H, F), compact_from_native(H, Jv)))
+    for got, ref in zip(*outs):
+        assert rel_err(got, ref) < 1e-13
