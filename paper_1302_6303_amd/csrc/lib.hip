@@ -102,16 +102,17 @@ struct nrd_hierarchy final : public Clock {
     std::vector<int32_t> patch_tile0;
     int32_t variant = 0;            // stencil kernel that runs (plane_variant)
     std::vector<SweepTile> sweep[2];   // fused base sweeps: pre, post (empty: not fused)
+    std::vector<GridBlock> blocks[kMaxMG];     // grids whose legs run in blocks
 
     // workspace offsets
     struct Off {
         size_t patches, tiles, stiles, vtiles, prob_vtile0, gcopy, gcf, sib, sync[kMaxLev], rfaces,
             rcells, cfrows, cfsrc, ctype, shadows, shadow_src, coff, ps, active, amap;
         size_t mg_box[kMaxMG], mg_tiles[kMaxMG], mg_box_of[kMaxMG], mg_smooth[kMaxMG],
-            tails, Xbuf, mg_l0map, ltiles, sweep[2];
+            tails, Xbuf, mg_l0map, ltiles, sweep[2], mg_blocks[kMaxMG];
         size_t z, z3, cur, prev, udot, bvec, x, F, s, w, tmp, tmp2, gzn, V, Z, pred;
         size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f;
-        size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG];
+        size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG], mg_o[kMaxMG];
         size_t partial, count, h1, h2, hn2, H, cs, sn, g, vscale, y, kdim, coefA, coefB,
             minout, flag, ckpt, fdF, fdw, fdsum;
     } o;
@@ -274,6 +275,19 @@ static bool split0_ok(const Tables& t, bool base_smooth) {
     return true;
 }
 
+// cells of grid g of problem p
+static int64_t grid_cells(const Tables& t, int p, int g) {
+    int64_t n = 1;
+    for (int d = 0; d < 3; ++d) n *= t.probs[p].base_n[d] >> g;
+    return n;
+}
+// the grid from which on one workgroup runs the cycle (0: does not coarsen)
+static int32_t tail_grid(const Tables& t, int p) {
+    int32_t g = t.prob_mgdepth[p];
+    while (g > 1 && grid_cells(t, p, g - 1) <= kTailCells) --g;
+    return g;
+}
+
 // ---------------------------------------------------------------------------
 // layout
 // ---------------------------------------------------------------------------
@@ -354,6 +368,43 @@ static void layout(nrd_hierarchy* h) {
             o.sweep[q] = b.take(sizeof(SweepTile) * std::max<size_t>(1, h->sweep[q].size()));
         }
     }
+    // Grids above a problem's tail grid whose legs run in blocks: where a
+    // launch is bound by its latency.  Blocks relax 1.9 times as many cells,
+    // and the base grid recomputes D_T for each of them.  Preconditioner
+    // (set-up and application) without / with, us, coarse grids: 48^3 95 / 85,
+    // 96^3 162 / 138 (float64 205 / 178), 128^3 231 / 222 (342 / 314), 192^3
+    // 592 / 580 (1058 / 965); largest grid in blocks of 2 M cells: 256^3 1181
+    // / 1234, 64 x 64^3 in float64 2133 / 2190.  Base grid as well: 20^3 114 /
+    // 106, 32^3 77 / 72, 48^3 85 / 77 (94 / 90), 64^3 102 / 101 (125 / 129),
+    // 96^3 138 / 157.
+    {
+        const nrd_options& O = h->opt;
+        const bool v11 = O.mg_nu_pre <= 1 && O.mg_nu_post == 1;
+        const bool base = h->sweep[0].empty() && O.fac_cycle == NRD_FAC_MULT &&
+                          split0_ok(t, O.fac_base == NRD_BASE_SMOOTH);
+        for (int g = 0; g <= G; ++g) {
+            h->blocks[g].clear();
+            int64_t cells = 0;
+            for (int p = 0; p < nprob; ++p)
+                if (tail_grid(t, p) > g) cells += grid_cells(t, p, g);
+            if (v11 && (g > 0 ? cells <= kBlockCells : base && cells <= kBlockBase)) {
+                if (g == 0) {
+                    for (int p = 0; p < nprob; ++p)
+                        if (tail_grid(t, p) > 0) {
+                            const int32_t b0 = t.level_patches[p][0][0];
+                            grid_blocks(t.patches[b0], b0, p, h->blocks[0]);
+                        }
+                } else {
+                    for (size_t i = 0; i < t.mg[g].boxes.size(); ++i)
+                        if (tail_grid(t, t.mg[g].probs[i]) > g)
+                            grid_blocks(t.mg[g].boxes[i], (int32_t)i, t.mg[g].probs[i],
+                                        h->blocks[g]);
+                }
+            }
+            o.mg_blocks[g] =
+                b.take(sizeof(GridBlock) * std::max<size_t>(1, h->blocks[g].size()));
+        }
+    }
     // state and work vectors (double)
     o.z = b.take(8 * nl);
     o.z3 = b.take(8 * nl);
@@ -395,6 +446,7 @@ static void layout(nrd_hierarchy* h) {
         o.mg_D[g] = b.take(es * 6 * n);
         o.mg_e[g] = b.take(es * 2 * n);
         o.mg_f[g] = b.take(es * 2 * n);
+        o.mg_o[g] = b.take(h->blocks[g].empty() ? 0 : es * 2 * n);
     }
     // reductions and per-problem scalars
     o.partial = b.take(8 * 17 * std::max<size_t>(1, t.vtiles.size()));
@@ -444,6 +496,7 @@ static void wire_pc(nrd_hierarchy* h, PcArrays<PT>& pc) {
     pc.shadows = h->at<ShadowPatch>(o.shadows);
     const int G = (int)t.mg.size() - 1;
     pc.mg.G = G;
+    pc.mg.eg[0] = pc.e;
     for (int g = 0; g <= G; ++g) {
         if (g >= 1) {
             pc.mg.box[g] = h->at<PatchInfo>(o.mg_box[g]);
@@ -453,6 +506,9 @@ static void wire_pc(nrd_hierarchy* h, PcArrays<PT>& pc) {
             pc.mg.eg[g] = h->at<PT>(o.mg_e[g]);
             pc.mg.fg[g] = h->at<PT>(o.mg_f[g]);
         }
+        pc.mg.blocks[g] = h->at<GridBlock>(o.mg_blocks[g]);
+        pc.mg.nblocks[g] = (int)h->blocks[g].size();
+        pc.mg.eo[g] = g == 0 ? pc.u : h->at<PT>(o.mg_o[g]);
         pc.mg.box_of[g] = h->at<int32_t>(o.mg_box_of[g]);
         pc.mg.smooth_tiles[g] = h->at<Tile>(o.mg_smooth[g]);
     }
@@ -524,14 +580,7 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
         for (int p = 0; p < t.nprob; ++p) {
             const int32_t depth = t.prob_mgdepth[p];
             if ((depth > 0) != (pass == 1)) continue;
-            int32_t g = depth;
-            auto cells = [&](int32_t q) {
-                int64_t n = 1;
-                for (int d = 0; d < 3; ++d) n *= t.probs[p].base_n[d] >> q;
-                return n;
-            };
-            if (depth > 0)
-                while (g > 1 && cells(g - 1) <= kTailCells) --g;
+            const int32_t g = tail_grid(t, p);
             start[p] = g;
             top = std::max(top, g);
             TailEntry te;
@@ -547,6 +596,7 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
         }
     HIPCHK(up(s, h->ws + o.tails, tails));
     for (int q = 0; q < 2; ++q) HIPCHK(up(s, h->ws + o.sweep[q], h->sweep[q]));
+    for (int g = 0; g <= G; ++g) HIPCHK(up(s, h->ws + o.mg_blocks[g], h->blocks[g]));
     std::vector<int32_t> nsmooth(G + 1, 0), ntiles(G + 1, 0);
     std::vector<std::vector<Tile>> lists;         // alive until the uploads are done
     for (int g = 0; g <= G; ++g) {

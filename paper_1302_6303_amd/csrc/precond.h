@@ -84,6 +84,29 @@ void sweep_post(const Dev& D, hipStream_t s, const SweepTile* tiles, int nt, con
                 const float* e, const float* ec, int64_t nlc, const float* sigma, int mode,
                 bool p2, double* y);
 
+// Both legs of the cycle at one grid, a launch each (mgblock.hip): blocks of a
+// box that covers its problem's domain, both fields.
+struct GridBlock {
+    int32_t patch, prob, x0, y0, z0, pad[3];
+};
+constexpr int64_t kBlockCells = 1 << 20;      // largest grid in blocks, all problems
+constexpr int64_t kBlockBase = 128 << 10;     // largest base grid
+// a box's blocks
+void grid_blocks(const PatchInfo& p, int32_t patch, int32_t prob, std::vector<GridBlock>& out);
+// colour 1 of e after a sweep from zero and the coarser grid's fc (T: split
+// storage of e and f, D_T from T)
+template <typename PT>
+void block_down(hipStream_t s, int n, const int32_t* act, const GridBlock* blocks,
+                const PatchInfo* P, const PatchInfo* Pc, const int32_t* cbox,
+                const ProbScalars* ps, const PT* D, const PT* T, const PT* f, PT* e, int64_t nl,
+                PT* fc, int64_t nlc);
+// out = the sweep from e (its colour 1) plus the prolonged ec
+template <typename PT>
+void block_up(hipStream_t s, int n, const int32_t* act, const GridBlock* blocks,
+              const PatchInfo* P, const PatchInfo* Pc, const int32_t* cbox,
+              const ProbScalars* ps, const PT* D, const PT* T, const PT* f, const PT* e,
+              int64_t nl, const PT* ec, int64_t nlc, PT* out);
+
 // Per multigrid grid: face coefficients, vectors, field length
 // (kernel argument of the tail kernels).
 template <typename PT>
@@ -145,6 +168,12 @@ struct PcArrays {
         PT* Dg[kMaxMG] = {};
         PT* eg[kMaxMG] = {};
         PT* fg[kMaxMG] = {};
+        // grids whose legs run in blocks (nblocks > 0), their corrections in eo
+        const GridBlock* blocks[kMaxMG] = {};
+        int nblocks[kMaxMG] = {};
+        PT* eo[kMaxMG] = {};
+        // where the correction of grid g ends up (g = 0: level 0)
+        PT* result(int g) const { return nblocks[g] > 0 ? eo[g] : eg[g]; }
     } mg;
     int p2_mode = 0;
     int nu_pre = 1, nu_post = 1;

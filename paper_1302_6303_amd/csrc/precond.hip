@@ -936,7 +936,7 @@ TailGrids<PT> PcArrays<PT>::tail_grids() const {
     for (int g = 0; g <= mg.G; ++g) {
         t.D[g] = (g == 0) ? Dface : mg.Dg[g];
         t.f[g] = (g == 0) ? f : mg.fg[g];
-        t.e[g] = (g == 0) ? e : mg.eg[g];
+        t.e[g] = mg.result(g);
         t.nl[g] = (g == 0) ? D->nl : mg.len[g];
     }
     t.T0 = split0 ? Tp : nullptr;
@@ -975,7 +975,14 @@ void PcArrays<PT>::vcycle(hipStream_t s, double* y, bool p2) const {
         PT* fg = (g == 0) ? f : mg.fg[g];
         const PT* Dg = (g == 0) ? Dface : mg.Dg[g];
         const bool sp = g == 0 && split0;
-        if (mg.nsmooth[g] > 0) {
+        if (mg.nblocks[g] > 0) {
+            std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
+            if (g == 0 && clock) tk = clock->tic(NRD_TIMER_SMOOTH_ZERO);
+            block_down<PT>(s, mg.nblocks[g], d.active, mg.blocks[g], Pg, mg.box[g + 1],
+                           mg.box_of[g + 1], d.ps, Dg, sp ? Tp : nullptr, fg, eg, nlg,
+                           mg.fg[g + 1], mg.len[g + 1]);
+            if (g == 0 && clock) clock->toc(NRD_TIMER_SMOOTH_ZERO, tk);
+        } else if (mg.nsmooth[g] > 0) {
             // a base grid cut into several boxes: sibling ghosts refreshed
             // after every half-sweep that the next one reads
             const bool sib = g == 0 && mg.multi0;
@@ -1023,7 +1030,8 @@ void PcArrays<PT>::vcycle(hipStream_t s, double* y, bool p2) const {
     }
     // problems whose base grid does not coarsen, and the grids from every
     // other problem's tail grid down
-    bottom_apply<PT>(s, mg.nbase, d.active, mg.tails, mg.Xbuf, f, e, d.nl, split0 ? 1 : 0);
+    bottom_apply<PT>(s, mg.nbase, d.active, mg.tails, mg.Xbuf, f, mg.result(0),
+                     d.nl, split0 ? 1 : 0);
     tail_cycle<PT>(s, mg.ntail, d.active, mg.tails + mg.nbase, tail_grids(), d.ps, mg.Xbuf,
                    nu_pre, nu_post);
     for (int g = mg.top - 1; g >= 0; --g) {
@@ -1032,8 +1040,8 @@ void PcArrays<PT>::vcycle(hipStream_t s, double* y, bool p2) const {
             std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
             if (clock) tk = clock->tic(NRD_TIMER_SMOOTH);
             if constexpr (std::is_same_v<PT, float>)
-                sweep_post(d, s, post, npost, mg.box[1], mg.box_of[1], Dface, Tp, f, e, mg.eg[1],
-                           mg.len[1], sigma, p2_mode, p2, y);
+                sweep_post(d, s, post, npost, mg.box[1], mg.box_of[1], Dface, Tp, f, e,
+                           mg.result(1), mg.len[1], sigma, p2_mode, p2, y);
             if (clock) clock->toc(NRD_TIMER_SMOOTH, tk);
             break;
         }
@@ -1042,11 +1050,20 @@ void PcArrays<PT>::vcycle(hipStream_t s, double* y, bool p2) const {
         PT* eg = (g == 0) ? e : mg.eg[g];
         PT* fg = (g == 0) ? f : mg.fg[g];
         const PT* Dg = (g == 0) ? Dface : mg.Dg[g];
+        if (mg.nblocks[g] > 0) {
+            std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
+            if (g == 0 && clock) tk = clock->tic(NRD_TIMER_SMOOTH);
+            block_up<PT>(s, mg.nblocks[g], d.active, mg.blocks[g], Pg, mg.box[g + 1],
+                         mg.box_of[g + 1], d.ps, Dg, g == 0 && split0 ? Tp : nullptr, fg, eg, nlg,
+                         mg.result(g + 1), mg.len[g + 1], mg.eo[g]);
+            if (g == 0 && clock) clock->toc(NRD_TIMER_SMOOTH, tk);
+            continue;
+        }
         const Tile* tl = mg.smooth_tiles[g];
         const int nt = mg.nsmooth[g];
         k_mg_prolong<PT><<<nt, kBlock / 2, 0, s>>>(d.active, tl, Pg, mg.box[g + 1],
-                                                   mg.box_of[g + 1], mg.eg[g + 1], mg.len[g + 1],
-                                                   eg, nlg, g == 0 && split0, nu_post == 0);
+                                                   mg.box_of[g + 1], mg.result(g + 1),
+                                                   mg.len[g + 1], eg, nlg, g == 0 && split0, nu_post == 0);
         const bool sib = g == 0 && mg.multi0;
         for (int it = 0; it < nu_post; ++it) {
             std::pair<hipEvent_t, hipEvent_t> tk{nullptr, nullptr};
@@ -1184,7 +1201,7 @@ const PT* PcArrays<PT>::fac(hipStream_t s, bool covered) const {
             smooth_level(s, f, 0, fac_pre);
         else
             vcycle(s);
-        return e;
+        return mg.result(0);
     }
     for (int lev = L; lev >= 0; --lev) {
         if (lev < L) composite_residual(s, lev);     // u was restricted by the last correction

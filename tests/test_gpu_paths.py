@@ -226,3 +226,45 @@ def test_stencil_kernel_of_the_size_rule(base, fine):
         outs.append((compact_from_native(H, F), compact_from_native(H, Jv)))
     for got, ref in zip(*outs):
         assert rel_err(got, ref) < 1e-13
+
+
+# grids whose legs of the cycle run in blocks of 16 x 8 x 8 cells: base grid 6
+# cells wide (one clipped block), whole blocks, remainders in every direction,
+# 110 592 cells (the largest cube), 184 320 (the base grid in half-sweeps, the
+# next in blocks)
+BLOCK_EXTS = [(6, 8, 10), (10, 14, 6), (20, 12, 20), (32, 32, 32), (40, 40, 40), (24, 24, 40),
+              (24, 40, 40), (40, 24, 24), (48, 48, 48), (48, 80, 48)]
+
+
+@pytest.mark.parametrize("precision", [1, 0])
+def test_cycle_legs_in_blocks_keep_every_value(precision):
+    """Each problem's preconditioner alone (blocks where the grid is small)
+    and beside a filler that brings its first two grids above the rule (other
+    kernels): bit for bit the same."""
+    fill = (192, 256, 192)
+    ws = [_box(e, seed=80 + i) for i, e in enumerate([fill] + BLOCK_EXTS)]
+    for p, w in enumerate(ws):
+        w.problems[0].bc_E = tuple(int((f + p) % 3 == 0) for f in range(6))
+    w = I.Workload("several", [x.problems[0] for x in ws],
+                   [I.Box(p, 0, (0, 0, 0), e) for p, e in enumerate([fill] + BLOCK_EXTS)],
+                   [x.z[0] for x in ws], [x.E[0] for x in ws], [x.T[0] for x in ws],
+                   np.array([2e-5 / (1 + p) for p in range(len(ws))]))
+    n = [x.ncells() for x in ws]
+    us = [np.concatenate([x.compact(x.E), x.compact(x.T)]) for x in ws]
+    vs = [np.random.default_rng(90 + p).standard_normal(2 * n[p]) for p in range(len(ws))]
+
+    def apply(w, dt, u, v):
+        H = make(w, precision=precision, gmres_restart=2)
+        H.begin_step(dt)
+        H.precond_setup(native_from_compact(H, u))
+        return compact_from_native(H, H.precond_apply(native_from_compact(H, v), H.native()))
+
+    def join(xs):
+        return np.concatenate([x[:k] for x, k in zip(xs, n)] + [x[k:] for x, k in zip(xs, n)])
+
+    got = apply(w, [float(x) for x in w.dt], join(us), join(vs))
+    at = np.concatenate([[0], np.cumsum(n)])
+    for p in range(1, len(ws)):
+        want = apply(ws[p], [float(w.dt[p])], us[p], vs[p])
+        mine = np.concatenate([got[f + at[p]:f + at[p + 1]] for f in (0, at[-1])])
+        np.testing.assert_array_equal(mine, want, err_msg=str(BLOCK_EXTS[p - 1]))
