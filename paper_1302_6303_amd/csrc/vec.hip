@@ -74,38 +74,78 @@ __device__ __forceinline__ int interior_index(const PatchInfo& p, int lin) {
     return interior_cell(p, lin, i, j, k);
 }
 
-// Sums over the workgroup of acc[0 .. nv): sum v in sh[0][v] after the closing
-// barrier, added as block_sum adds (one barrier for all of them).
+// Sums over a wavefront of NV values (a power of two): value v on the lanes of
+// v * (64 / NV) ..  Each step halves the values a lane holds by trading the
+// other half with its partner, so 16 values take 17 exchanges rather than 96;
+// every sum adds the same pairs in the same order as wave_sum.
 template <int NV>
-__device__ __forceinline__ void block_sums(double (&acc)[NV], int nv, double (*sh)[NV]) {
-    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+__device__ __forceinline__ double wave_sums(const double* acc) {
+    static_assert((NV & (NV - 1)) == 0 && NV <= 16, "power of two");
+    const int lane = threadIdx.x & 63;
+    double t[NV];
 #pragma unroll
-    for (int v = 0; v < NV; ++v)
-        if (v < nv) {
-            const double s = wave_sum(acc[v]);
-            if (lane == 0) sh[w][v] = s;
+    for (int v = 0; v < NV; ++v) t[v] = acc[v];
+    int o = 32;
+#pragma unroll
+    for (int h = NV / 2; h > 0; h /= 2, o /= 2) {
+        const bool upper = lane & o;
+#pragma unroll
+        for (int v = 0; v < h; ++v) {
+            const double keep = upper ? t[v + h] : t[v], send = upper ? t[v] : t[v + h];
+            t[v] = keep + __shfl_xor(send, o, 64);
         }
+    }
+#pragma unroll
+    for (int r = 32 / NV; r > 0; r /= 2) t[0] += __shfl_xor(t[0], r, 64);
+    return t[0];
+}
+
+// Sums over a workgroup of W wavefronts of acc[0 .. nv): sum v in sh[0][v]
+// after the closing barrier (one for all of them).  NV: a power of two, or one
+// more.
+template <int NV, int W = 4>
+__device__ __forceinline__ void block_sums(double (&acc)[NV], int nv, double (*sh)[NV]) {
+    constexpr int N = (NV & (NV - 1)) == 0 ? NV : NV - 1;
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const double s = wave_sums<N>(acc);
+    if (lane % (64 / N) == 0) sh[w][lane / (64 / N)] = s;
+    if (N < NV) {
+        const double more = wave_sum(acc[NV - 1]);
+        if (lane == 0) sh[w][NV - 1] = more;
+    }
     __syncthreads();
     if ((int)threadIdx.x < nv) {
         const int v = threadIdx.x;
-        sh[0][v] = (sh[0][v] + sh[1][v]) + (sh[2][v] + sh[3][v]);
+        double r[W];
+#pragma unroll
+        for (int k = 0; k < W; ++k) r[k] = sh[k][v];
+#pragma unroll
+        for (int n = W; n > 1; n /= 2)
+#pragma unroll
+            for (int k = 0; k < n / 2; ++k) r[k] = r[2 * k] + r[2 * k + 1];
+        sh[0][v] = r[0];
     }
     __syncthreads();
 }
 
 // Sums of the tile partials of problem p (tiles [a, b), nv values each) into
-// sh[0][v], the order of k_sum_partials.
-template <int NV>
+// sh[0][v].  The loads of a step are unconditional (values beyond nv repeat the
+// last one and are dropped): with a branch around each the sums waited for one
+// after the other.
+template <int NV, int W = 4>
 __device__ __forceinline__ void partial_sums(const double* partial, int a, int b, int nv,
                                              double (*sh)[NV]) {
     double acc[NV];
 #pragma unroll
     for (int v = 0; v < NV; ++v) acc[v] = 0.0;
-    for (int i = a + threadIdx.x; i < b; i += kBlock)
+    for (int i = a + threadIdx.x; i < b; i += 64 * W) {
+        double x[NV];
 #pragma unroll
-        for (int v = 0; v < NV; ++v)
-            if (v < nv) acc[v] += partial[(int64_t)i * nv + v];
-    block_sums<NV>(acc, nv, sh);
+        for (int v = 0; v < NV; ++v) x[v] = partial[(int64_t)i * nv + min(v, nv - 1)];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] += x[v];
+    }
+    block_sums<NV, W>(acc, nv, sh);
 }
 
 // A tile's sums (sh[0][v], after block_sums) to its partials; true in the
@@ -155,12 +195,14 @@ __global__ __launch_bounds__(kBlock) void k_multidot(
             const int c = interior_index(p, lin);
             if (cov && (ctype[c] & CT_COVERED)) continue;
             const double y0 = y[c], y1 = y[c + nl];
+            double x0[NV], x1[NV];                   // all loads in flight at once
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-                if (v < nv) {
-                    const double x0 = sc * X[v * xs + c], x1 = sc * X[v * xs + c + nl];
-                    acc[v] += x0 * y0 + x1 * y1;
-                }
+            for (int v = 0; v < NV; ++v) {
+                x0[v] = X[min(v, nv - 1) * xs + c];
+                x1[v] = X[min(v, nv - 1) * xs + c + nl];
+            }
+#pragma unroll
+            for (int v = 0; v < NV; ++v) acc[v] += sc * x0[v] * y0 + sc * x1[v] * y1;
         }
     }
     block_sums<NV>(acc, nv, sh);
@@ -176,34 +218,43 @@ __global__ __launch_bounds__(kBlock) void k_multidot(
 }
 
 // out[p * ostride + v] = sum of the problem's tile partials (fixed order)
-__global__ __launch_bounds__(kBlock) void k_sum_partials(
+constexpr int kSumWaves = 16;
+template <int NV>
+__global__ __launch_bounds__(64 * kSumWaves) void k_sum_partials(
     const int32_t* __restrict__ t0, const double* __restrict__ partial, int nv,
     double* __restrict__ out, int ostride) {
-    __shared__ double sh[4];
+    __shared__ double sh[kSumWaves][NV];
     const int p = blockIdx.x;
-    const int a = t0[p], b = t0[p + 1];
-    for (int v = 0; v < nv; ++v) {
-        double acc = 0.0;
-        for (int i = a + threadIdx.x; i < b; i += kBlock) acc += partial[(int64_t)i * nv + v];
-        const double s = block_sum(acc, sh);
-        if (threadIdx.x == 0) out[p * ostride + v] = s;
-    }
+    partial_sums<NV, kSumWaves>(partial, t0[p], t0[p + 1], nv, sh);
+    if ((int)threadIdx.x < nv) out[p * ostride + threadIdx.x] = sh[0][threadIdx.x];
+}
+static void sum_partials(const Dev& D, hipStream_t s, const double* partial, int nv, double* out,
+                         int ostride) {
+    auto go = [&](auto kernel) {
+        kernel<<<D.nprob, 64 * kSumWaves, 0, s>>>(D.prob_vtile0, partial, nv, out, ostride);
+    };
+    if (nv <= 1) go(k_sum_partials<1>);
+    else if (nv <= 2) go(k_sum_partials<2>);
+    else if (nv <= 4) go(k_sum_partials<4>);
+    else if (nv <= 8) go(k_sum_partials<8>);
+    else go(k_sum_partials<16>);
 }
 
 // Launches K<NV>(args) with the smallest NV of 1, 2, 4, 8, 16 that holds nv.
-#define NRD_BY_NV(nv, K, grid, s, ...)                                        \
+#define NRD_BY_NV_T(nv, K, grid, threads, s, ...)                             \
     do {                                                                      \
         if ((nv) <= 1)                                                        \
-            K<1><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+            K<1><<<grid, threads, 0, s>>>(__VA_ARGS__);                       \
         else if ((nv) <= 2)                                                   \
-            K<2><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+            K<2><<<grid, threads, 0, s>>>(__VA_ARGS__);                       \
         else if ((nv) <= 4)                                                   \
-            K<4><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+            K<4><<<grid, threads, 0, s>>>(__VA_ARGS__);                       \
         else if ((nv) <= 8)                                                   \
-            K<8><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                        \
+            K<8><<<grid, threads, 0, s>>>(__VA_ARGS__);                       \
         else                                                                  \
-            K<16><<<grid, kBlock, 0, s>>>(__VA_ARGS__);                       \
+            K<16><<<grid, threads, 0, s>>>(__VA_ARGS__);                      \
     } while (0)
+#define NRD_BY_NV(nv, K, grid, s, ...) NRD_BY_NV_T(nv, K, grid, kBlock, s, __VA_ARGS__)
 
 // Up to this many tiles the last workgroup of a problem sums its partials (one
 // launch, 7.7 us for an inner product at 32^3 against about 10.5 us for two);
@@ -220,7 +271,7 @@ void multidot(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int
         NRD_BY_NV(c, k_multidot, D.nvtiles, s, D.vtiles, D.patches, D.ctype, D.active, Xc, xstride,
                   c, xsc, y, partial, D.nl, cnt, D.prob_vtile0, out + v0, nv);
         if (!cnt)
-            k_sum_partials<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, partial, c, out + v0, nv);
+            sum_partials(D, s, partial, c, out + v0, nv);
     }
 }
 
@@ -284,12 +335,18 @@ __global__ __launch_bounds__(kBlock) void k_combine(
         const int c = interior_index(p, lin);
         double a0 = accumulate ? y[c] : 0.0;
         double a1 = accumulate ? y[c + nl] : 0.0;
+        double x0[NV], x1[NV];                // all loads in flight at once
 #pragma unroll
-        for (int v = 0; v < NV; ++v)
-            if (v < nv && cf[v] != 0.0) {     // unused basis vectors may be stale
-                a0 += cf[v] * X[v * xs + c];
-                a1 += cf[v] * X[v * xs + c + nl];
-            }
+        for (int v = 0; v < NV; ++v) {
+            const bool use = v < nv && cf[v] != 0.0;     // others may be stale
+            x0[v] = use ? X[v * xs + c] : 0.0;
+            x1[v] = use ? X[v * xs + c + nl] : 0.0;
+        }
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            a0 += cf[v] * x0[v];
+            a1 += cf[v] * x1[v];
+        }
         y[c] = a0;
         y[c + nl] = a1;
     }
@@ -323,7 +380,9 @@ void combine(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int 
 }
 
 // The new Hessenberg column, its Givens rotations and the residual estimate
-// of one problem (one thread).
+// of one problem, by one wavefront: entry i and the rotation of row i on lane i
+// (j < m <= 64), the chain of rotations in registers.  (One thread that read
+// and wrote them in memory waited for each: 16 columns 10 us.)
 __device__ __forceinline__ void gmres_column_one(int p, int m, int j, const double* h1,
                                                  const double* h2, double hn2,
                                                  const GmresScalars& G) {
@@ -331,15 +390,18 @@ __device__ __forceinline__ void gmres_column_one(int p, int m, int j, const doub
     double* c = G.cs + p * m;
     double* s = G.sn + p * m;
     double* gg = G.g + p * (m + 1);
-    for (int i = 0; i <= j; ++i) col[i] = h1[i] + h2[i];
-    const double hn = sqrt(hn2);
-    col[j + 1] = hn;
+    const int lane = threadIdx.x & 63;
+    const double h = lane <= j ? h1[lane] + h2[lane] : 0.0;
+    const double ci = lane < j ? c[lane] : 1.0, si = lane < j ? s[lane] : 0.0;
+    const double g = gg[j];
+    double x = __shfl(h, 0, 64), mine = 0.0;
     for (int i = 0; i < j; ++i) {
-        const double tmp = c[i] * col[i] + s[i] * col[i + 1];
-        col[i + 1] = -s[i] * col[i] + c[i] * col[i + 1];
-        col[i] = tmp;
+        const double a = __shfl(ci, i, 64), b = __shfl(si, i, 64), next = __shfl(h, i + 1, 64);
+        if (lane == i) mine = a * x + b * next;
+        x = -b * x + a * next;
     }
-    const double a = col[j], b = col[j + 1];
+    const double hn = sqrt(hn2);
+    const double a = x, b = hn;
     double cc, ss, r;
     if (b == 0.0) {
         cc = 1.0;
@@ -350,28 +412,28 @@ __device__ __forceinline__ void gmres_column_one(int p, int m, int j, const doub
         cc = a / r;
         ss = b / r;
     }
-    c[j] = cc;
-    s[j] = ss;
-    col[j] = r;
-    col[j + 1] = 0.0;
-    gg[j + 1] = -ss * gg[j];
-    gg[j] = cc * gg[j];
-    G.rho[p] = fabs(gg[j + 1]);       // host memory, as is hn2_host
-    G.hn2_host[p] = hn2;
-    G.vscale[p] = hn > 0.0 ? 1.0 / hn : 0.0;
+    if (lane <= j) col[lane] = lane < j ? mine : r;
+    if (lane == 0) {
+        c[j] = cc;
+        s[j] = ss;
+        col[j + 1] = 0.0;
+        gg[j + 1] = -ss * g;
+        gg[j] = cc * g;
+        G.rho[p] = fabs(-ss * g);         // host memory, as is hn2_host
+        G.hn2_host[p] = hn2;
+        G.vscale[p] = hn > 0.0 ? 1.0 / hn : 0.0;
+    }
 }
 
 // End of the second Gram-Schmidt pass of one problem from its sums S = (h2_0
-// .. h2_j, ||w1||^2): the basis is orthonormal, so w2 = w1 - sum h2_v v_v has
-// ||w2||^2 = ||w1||^2 - sum h2_v^2.
+// .. h2_j, ||w1||^2), by one wavefront: the basis is orthonormal, so w2 = w1 -
+// sum h2_v v_v has ||w2||^2 = ||w1||^2 - sum h2_v^2.
 __device__ __forceinline__ void gs_finish(int p, int m, int j, const double* S,
                                           const GmresScalars& G) {
-    double* h2 = G.h2 + (int64_t)p * (j + 1);
+    const int lane = threadIdx.x & 63;
     double n2 = S[j + 1];
-    for (int v = 0; v <= j; ++v) {
-        h2[v] = S[v];
-        n2 -= S[v] * S[v];
-    }
+    for (int v = 0; v <= j; ++v) n2 -= S[v] * S[v];
+    if (lane <= j) G.h2[(int64_t)p * (j + 1) + lane] = S[lane];
     gmres_column_one(p, m, j, G.h1 + (int64_t)p * (j + 1), S, fmax(n2, 0.0), G);
 }
 
@@ -380,7 +442,9 @@ __device__ __forceinline__ void gs_finish(int p, int m, int j, const double* S,
 // norm.  The corrected vector is formed only if another iteration needs it
 // (k_gs_next).  Bound by reading the basis and w once, 16 (j + 2) B per cell:
 // 97 us for one basis vector on an ensemble of 20 M cells (6.6 TB/s), where
-// storing w1, then w2 with its norm took two passes of 155 and 187 us.
+// storing w1, then w2 with its norm took two passes of 155 and 187 us; 16 on 5
+// M cells 196 us (338 with a branch around each vector's loads), at 32^3, where
+// the sums and the new column are what takes time, 15 us (26).
 template <int NV>
 __global__ __launch_bounds__(kBlock) void k_gs_again(
     const Tile* __restrict__ vt, const PatchInfo* __restrict__ P,
@@ -409,18 +473,16 @@ __global__ __launch_bounds__(kBlock) void k_gs_again(
             double x0[NV], x1[NV];
 #pragma unroll
             for (int v = 0; v < NV; ++v) {
-                x0[v] = (v < nv) ? sc * X[v * xs + c] : 0.0;
-                x1[v] = (v < nv) ? sc * X[v * xs + c + nl] : 0.0;
+                x0[v] = sc * X[min(v, nv - 1) * xs + c];
+                x1[v] = sc * X[min(v, nv - 1) * xs + c + nl];
             }
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-                if (v < nv && cf[v] != 0.0) {
-                    a0 += cf[v] * x0[v];
-                    a1 += cf[v] * x1[v];
-                }
+            for (int v = 0; v < NV; ++v) {           // cf = 0 from nv on
+                a0 += cf[v] * x0[v];
+                a1 += cf[v] * x1[v];
+            }
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-                if (v < nv) acc[v] += x0[v] * a0 + x1[v] * a1;
+            for (int v = 0; v < NV; ++v) acc[v] += x0[v] * a0 + x1[v] * a1;
             nrm += a0 * a0 + a1 * a1;
         }
     }
@@ -436,23 +498,23 @@ __global__ __launch_bounds__(kBlock) void k_gs_again(
     const int a = t0[t.prob], b = t0[t.prob + 1];
     if (!last_of_problem(sh[0], nv + 1, p.vol, partial, cnt + t.prob, b - a)) return;
     partial_sums<NV + 1>(partial, a, b, nv + 1, sh);
-    if (threadIdx.x == 0 && on) gs_finish(t.prob, m, nv - 1, sh[0], G);
+    if (threadIdx.x < 64 && on) gs_finish(t.prob, m, nv - 1, sh[0], G);
     if (threadIdx.x == 0 && !on) G.vscale[t.prob] = 0.0;
 }
 
 // The sums and the new column of every problem (one workgroup each).
-__global__ __launch_bounds__(kBlock) void k_gs_finish(const int32_t* __restrict__ t0,
-                                                      const int32_t* __restrict__ active,
-                                                      const double* __restrict__ partial, int nv,
-                                                      int m, GmresScalars G) {
-    __shared__ double sh[4][17];
+template <int NV>
+__global__ __launch_bounds__(64 * kSumWaves) void k_gs_finish(
+    const int32_t* __restrict__ t0, const int32_t* __restrict__ active,
+    const double* __restrict__ partial, int nv, int m, GmresScalars G) {
+    __shared__ double sh[kSumWaves][NV + 1];
     const int p = blockIdx.x;
     if (active && !active[p]) {
         if (threadIdx.x == 0) G.vscale[p] = 0.0;
         return;
     }
-    partial_sums<17>(partial, t0[p], t0[p + 1], nv + 1, sh);
-    if (threadIdx.x == 0) gs_finish(p, m, nv - 1, sh[0], G);
+    partial_sums<NV + 1, kSumWaves>(partial, t0[p], t0[p + 1], nv + 1, sh);
+    if (threadIdx.x < 64) gs_finish(p, m, nv - 1, sh[0], G);
 }
 
 void gs_again(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
@@ -462,7 +524,8 @@ void gs_again(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int
     NRD_BY_NV(nv, k_gs_again, D.nvtiles, s, D.vtiles, D.patches, D.ctype, D.active, X, xstride, nv,
               xsc, w, partial, D.nl, cnt, D.prob_vtile0, m, G);
     if (!cnt)
-        k_gs_finish<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, D.active, partial, nv, m, G);
+        NRD_BY_NV_T(nv, k_gs_finish, D.nprob, 64 * kSumWaves, s, D.prob_vtile0, D.active, partial,
+                    nv, m, G);
 }
 
 // The next basis vector from the pass before: v_next = vscale (w - sum h1 v -
@@ -581,12 +644,18 @@ __global__ __launch_bounds__(kBlock) void k_combine_norm(
         for (int lin = t.start + threadIdx.x; lin < t.start + t.count; lin += kBlock) {
             const int c = interior_index(p, lin);
             double a0 = y[c], a1 = y[c + nl];
+            double x0[NV], x1[NV];            // all loads in flight at once
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-                if (v < nv && cf[v] != 0.0) {
-                    a0 += cf[v] * X[v * xs + c];
-                    a1 += cf[v] * X[v * xs + c + nl];
-                }
+            for (int v = 0; v < NV; ++v) {
+                const bool use = v < nv && cf[v] != 0.0;
+                x0[v] = use ? X[v * xs + c] : 0.0;
+                x1[v] = use ? X[v * xs + c + nl] : 0.0;
+            }
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                a0 += cf[v] * x0[v];
+                a1 += cf[v] * x1[v];
+            }
             y[c] = a0;
             y[c + nl] = a1;
             if (!(cov && (ctype[c] & CT_COVERED))) acc += a0 * a0 + a1 * a1;
@@ -605,7 +674,7 @@ void combine_norm(const Dev& D, hipStream_t s, const double* X, int64_t xstride,
     const int c = nv - v0;
     NRD_BY_NV(c, k_combine_norm, D.nvtiles, s, D.vtiles, D.patches, D.ctype, D.active,
               X + v0 * xstride, xstride, c, coef + v0, cstride, y, partial, D.nl);
-    k_sum_partials<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, partial, 1, out, 1);
+    sum_partials(D, s, partial, 1, out, 1);
 }
 
 // Newton update from the Krylov basis in one pass: for every active
@@ -632,12 +701,19 @@ __global__ __launch_bounds__(kBlock) void k_update_min(
         for (int lin = t.start + threadIdx.x; lin < t.start + t.count; lin += kBlock) {
             const int c = interior_index(p, lin);
             double s0 = 0.0, s1 = 0.0;
+            double z0[NV], z1[NV];            // all loads in flight at once
 #pragma unroll
-            for (int v = 0; v < NV; ++v)
-                if (v < nv && cf[v] != 0.0) {
-                    s0 += cf[v] * Z[v * zs + c];
-                    s1 += cf[v] * Z[v * zs + c + nl];
-                }
+            for (int v = 0; v < NV; ++v) {
+                const bool use = v < nv && cf[v] != 0.0;
+                z0[v] = use ? Z[v * zs + c] : 0.0;
+                z1[v] = use ? Z[v * zs + c + nl] : 0.0;
+            }
+            const double x0 = x[c], x1 = x[c + nl];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                s0 += cf[v] * z0[v];
+                s1 += cf[v] * z1[v];
+            }
             for (int v = NV; v < nv; ++v) {              // a basis of more than 16
                 const double cv = coef[t.prob * cs + v];
                 if (cv != 0.0) {
@@ -645,7 +721,6 @@ __global__ __launch_bounds__(kBlock) void k_update_min(
                     s1 += cv * Z[v * zs + c + nl];
                 }
             }
-            const double x0 = x[c], x1 = x[c + nl];
             keep[c] = x0;
             keep[c + nl] = x1;
             const double e = -1.0 * s0 + 1.0 * x0;
@@ -1025,7 +1100,7 @@ __global__ __launch_bounds__(kBlock) void k_fd_quotient(
 void fd_sums(const Dev& D, hipStream_t s, const double* u, const double* v, double* partial,
              double* sums) {
     k_fd_sums<<<D.nvtiles, kBlock, 0, s>>>(D.vtiles, D.patches, D.ctype, u, v, partial, D.nl);
-    k_sum_partials<<<D.nprob, kBlock, 0, s>>>(D.prob_vtile0, partial, 3, sums, 3);
+    sum_partials(D, s, partial, 3, sums, 3);
 }
 void fd_shift(const Dev& D, hipStream_t s, const double* sums, const double* u,
               const double* v, double* w) {
@@ -1037,16 +1112,16 @@ void fd_quotient(const Dev& D, hipStream_t s, const double* sums, const double* 
 }
 
 // ---------------------------------------------------------------------------
-// FGMRES per-problem scalars (one thread per problem)
+// FGMRES per-problem scalars (one wavefront per problem)
 //   H: [nprob][(m+1) * m], column j at H[p][(m+1) j]
 // ---------------------------------------------------------------------------
 
-__global__ void k_gmres_column(int nprob, int m, int j, const int32_t* __restrict__ active,
-                               GmresScalars G) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nprob) return;
+__global__ __launch_bounds__(64) void k_gmres_column(int m, int j,
+                                                     const int32_t* __restrict__ active,
+                                                     GmresScalars G) {
+    const int p = blockIdx.x;
     if (active && !active[p]) {
-        G.vscale[p] = 0.0;
+        if (threadIdx.x == 0) G.vscale[p] = 0.0;
         return;
     }
     gmres_column_one(p, m, j, G.h1 + (int64_t)p * (j + 1), G.h2 + (int64_t)p * (j + 1), G.hn2[p], G);
@@ -1054,29 +1129,41 @@ __global__ void k_gmres_column(int nprob, int m, int j, const int32_t* __restric
 
 void gmres_column(hipStream_t s, int nprob, int m, int j, const int32_t* active,
                   const GmresScalars& G) {
-    k_gmres_column<<<(nprob + 63) / 64, 64, 0, s>>>(nprob, m, j, active, G);
+    k_gmres_column<<<nprob, 64, 0, s>>>(m, j, active, G);
 }
 
-__global__ void k_gmres_backsolve(int nprob, int m, const int32_t* __restrict__ kdim,
-                                  const double* __restrict__ H, const double* __restrict__ g,
-                                  double* __restrict__ y) {
-    const int p = blockIdx.x * blockDim.x + threadIdx.x;
-    if (p >= nprob) return;
+// Back substitution by columns, row i on lane i (k <= m <= 64); eight columns
+// are read at once.
+__global__ __launch_bounds__(64) void k_gmres_backsolve(int m, const int32_t* __restrict__ kdim,
+                                                        const double* __restrict__ H,
+                                                        const double* __restrict__ g,
+                                                        double* __restrict__ y) {
+    const int p = blockIdx.x, lane = threadIdx.x;
     const int k = kdim[p];
     const double* Hp = H + (int64_t)p * (m + 1) * m;
-    const double* gp = g + p * (m + 1);
-    double* yp = y + p * m;
-    for (int i = k; i < m; ++i) yp[i] = 0.0;
-    for (int i = k - 1; i >= 0; --i) {
-        double acc = gp[i];
-        for (int l = i + 1; l < k; ++l) acc -= Hp[(m + 1) * l + i] * yp[l];
-        yp[i] = acc / Hp[(m + 1) * i + i];
+    double acc = lane < k ? g[(int64_t)p * (m + 1) + lane] : 0.0, mine = 0.0;
+    for (int l0 = k - 1; l0 >= 0; l0 -= 8) {
+        double hc[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int l = max(l0 - q, 0);
+            hc[q] = lane <= l ? Hp[(m + 1) * l + lane] : 0.0;
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int l = l0 - q;
+            if (l < 0) break;                        // uniform
+            const double yl = __shfl(acc, l, 64) / __shfl(hc[q], l, 64);
+            if (lane == l) mine = yl;
+            if (lane < l) acc -= hc[q] * yl;
+        }
     }
+    if (lane < m) y[(int64_t)p * m + lane] = mine;
 }
 
 void gmres_backsolve(hipStream_t s, int nprob, int m, const int32_t* kdim, const double* H,
                      const double* g, double* y) {
-    k_gmres_backsolve<<<(nprob + 63) / 64, 64, 0, s>>>(nprob, m, kdim, H, g, y);
+    k_gmres_backsolve<<<nprob, 64, 0, s>>>(m, kdim, H, g, y);
 }
 
 }  // namespace nrd

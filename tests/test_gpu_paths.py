@@ -268,3 +268,20 @@ def test_cycle_legs_in_blocks_keep_every_value(precision):
         want = apply(ws[p], [float(w.dt[p])], us[p], vs[p])
         mine = np.concatenate([got[f + at[p]:f + at[p + 1]] for f in (0, at[-1])])
         np.testing.assert_array_equal(mine, want, err_msg=str(BLOCK_EXTS[p - 1]))
+
+
+@pytest.mark.parametrize("m", [1, 5, 8, 9, 33])
+def test_gradient_with_a_basis_of_any_size(m):
+    """Columns, rotations and back substitution of 1 to 33 vectors (whole and
+    partly used groups of 1, 2, 4, 8 and 16).  The transposed systems are
+    solved to 1e-12 and the step they belong to to 1e-12 of its first
+    residual (the default 1e-8 leaves states 1e-10 and gradients 6e-9 apart),
+    which the gradient keeps to 1e-9.  One vector: with the multigrid
+    preconditioner, which needs few."""
+    w = I.marshak_single(16, state="front")
+    out = []
+    for k in (64, m):
+        H = make(w, precision=0, gmres_restart=k, gmres_maxrestarts=400, bdf_max_order=1,
+                 adjoint_slots=6, newton_rtol=1e-12, fac_base=int(m > 1))
+        out.append(to_host(H.adjoint_run([2e-3], 1, 1)))
+    assert rel_err(out[0], out[1]) < 1e-9
