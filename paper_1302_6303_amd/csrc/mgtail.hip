@@ -69,43 +69,137 @@ __device__ __forceinline__ void coarsen_field(const PatchInfo& pc, const PatchIn
         const int id[3] = {lin - r * pc.n[0], r - k * pc.n[1], k};
         const int c = native_index(pc, id[0], id[1], id[2]);
         const int f0 = native_index(pf, 2 * id[0], 2 * id[1], 2 * id[2]);
+        // (all loads of the low faces in flight at once; few cells have others)
+        PT v[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             const int t1 = d == 0 ? 1 : 0;
             const int t2 = d == 2 ? 1 : 2;
+            const PT* src = Df + d * nlf + f0;
+            v[d] = (src[0] + src[stf[t1]]) + (src[stf[t2]] + src[stf[t1] + stf[t2]]);
+        }
 #pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                if (s == 1 && id[d] != pc.n[d] - 1) continue;
-                const int fs = s ? f0 + 2 * stf[d] : f0;
-                const PT* src = Df + d * nlf;
-                const PT v = (src[fs] + src[fs + stf[t1]]) +
-                             (src[fs + stf[t2]] + src[fs + stf[t1] + stf[t2]]);
-                Dc[d * nlc + (s ? c + stc[d] : c)] = v * PT(0.25);
+        for (int d = 0; d < 3; ++d) {
+            Dc[d * nlc + c] = v[d] * PT(0.25);
+            if (id[d] == pc.n[d] - 1) {
+                const int t1 = d == 0 ? 1 : 0;
+                const int t2 = d == 2 ? 1 : 2;
+                const PT* src = Df + d * nlf + f0 + 2 * stf[d];
+                const PT w = (src[0] + src[stf[t1]]) + (src[stf[t2]] + src[stf[t1] + stf[t2]]);
+                Dc[d * nlc + c + stc[d]] = w * PT(0.25);
             }
         }
     }
 }
 
-constexpr int kSetupThreads = 512;
+constexpr int kSetupThreads = 1024;
+
+// The inverse of the banded N x N matrix A (A(i, i - d) at [i kBottomBand + d],
+// symmetric, strictly diagonally dominant) by N / 2 symmetric sweeps of two
+// indices each (Gauss-Jordan, no pivoting: after the sweep of every index the
+// matrix holds -A^-1).  Tiles of 4 x 4 in registers for as many threads as it
+// takes; a sweep needs two columns, which their owners put into LDS, so there
+// is one barrier per pair of indices and nothing else is serial.  What bounds
+// it is that chain (barrier, LDS, two reciprocals) for N = 64 and the LDS reads
+// for N = 125.  Cycles for N = 27, 64, 125: 14.5 k, 36.5 k, 152 k; one index at
+// a time on tiles of 8 x 4, which leaves two SIMDs idle at N = 64, 23 k, 51 k,
+// 146 k; pairs on 8 x 4 17 k, 39 k, 150 k.
+__device__ __forceinline__ void invert(const double* A, double (*col)[2][kBottomMax], int N,
+                                       double* Xi) {
+    const int ld = (N + 3) >> 2, tid = threadIdx.x;
+    if ((tid & ~63) >= ld * ld) return;              // wavefronts without a tile
+    const int tr = tid / ld, tc = tid - tr * ld;
+    const int r0 = 4 * tr, c0 = 4 * tc;
+    const bool on = tr < ld;
+    double a[4][4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = r0 + i, c = c0 + j;
+            const int hi = r > c ? r : c, d = r > c ? r - c : c - r;
+            a[i][j] = (hi < N && d < kBottomBand) ? A[hi * kBottomBand + d] : 0.0;
+        }
+    // (rows and columns beyond N stay zero: their published values are zero)
+    for (int kq = 0; 4 * kq < N; ++kq) {
+#pragma unroll
+        for (int b = 0; b < 4; b += 2) {
+            const int k = 4 * kq + b;
+            if (k >= N) break;                       // uniform
+            // double buffered: a buffer is rewritten two barriers after it was
+            // read
+            double *v0 = col[b >> 1][0], *v1 = col[b >> 1][1];
+            if (on && tc == kq)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    v0[r0 + i] = a[i][b];
+                    v1[r0 + i] = a[i][b + 1];
+                }
+            __syncthreads();
+            if (!on) continue;
+            // the inverse of the pair's 2 x 2 block (k + 1 = N: of k alone)
+            const double p0 = v0[k], p1 = v0[k + 1], p2 = k + 1 < N ? v1[k + 1] : 1.0;
+            double x0[4], x1[4], u0[4], u1[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                x0[i] = v0[r0 + i];
+                x1[i] = v1[r0 + i];
+                u0[i] = v0[c0 + i];
+                u1[i] = v1[c0 + i];
+            }
+            const double i0 = rcp_nr(p0), m = p1 * i0;
+            const double P11 = rcp_nr(fma(-p1, m, p2)), P01 = -m * P11, P00 = fma(-m, P01, i0);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const double w0 = u0[j], w1 = u1[j];
+                u0[j] = fma(P00, w0, P01 * w1);
+                u1[j] = fma(P01, w0, P11 * w1);
+            }
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j)
+                    a[i][j] = fma(-x0[i], u0[j], fma(-x1[i], u1[j], a[i][j]));
+            if (tr == kq)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    a[b][j] = u0[j];
+                    a[b + 1][j] = u1[j];
+                }
+            if (tc == kq) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    a[i][b] = fma(P00, x0[i], P01 * x1[i]);
+                    a[i][b + 1] = fma(P01, x0[i], P11 * x1[i]);
+                }
+                if (tr == kq) {
+                    a[b][b] = -P00;
+                    a[b][b + 1] = a[b + 1][b] = -P01;
+                    a[b + 1][b + 1] = -P11;
+                }
+            }
+        }
+    }
+    if (on)
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (r0 + i < N && c0 + j < N) Xi[(r0 + i) * N + c0 + j] = -a[i][j];
+}
 
 // Set-up below a problem's tail grid: the face coefficients of the grids
 // start + 1 .. depth, then the inverse X (float64, N x N, row major in the
-// numbering above) of the coarsest grid's operator.  The matrix is symmetric
-// and strictly diagonally dominant, so it is inverted without pivoting by N
-// symmetric sweeps (Gauss-Jordan: after the sweep of every index the matrix
-// holds -A^-1).  Up to 512 threads keep an 8 x 4 tile each in registers; a
-// sweep needs one column, which its owners put into LDS, so there is one
-// barrier per index and nothing else is serial.  What bounds it is that chain
-// of N barriers and LDS reads.  Measured, with the coefficients of the grids
-// below the tail: N = 64 (a 32^3 problem) 30 us, N = 125 (in an ensemble)
-// 69 us; a band Cholesky with two barriers per index and one triangular solve
-// per column took 62 and 137 us, after two launches for the coefficients.
+// numbering above) of the coarsest grid's operator.  Measured, with the
+// coefficients: N = 64 (a 32^3 problem) 22.7 us, N = 125 (in an ensemble) 70
+// us; a band Cholesky with two barriers per index and one triangular solve per
+// column took 62 and 137 us, after two launches for the coefficients.
 template <typename PT>
 __global__ __launch_bounds__(kSetupThreads) void k_tail_setup(
     const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
     const ProbScalars* __restrict__ ps, double* __restrict__ X) {
     __shared__ double A[kBottomMax * kBottomBand];   // A(i, i - d) at [i kBottomBand + d]
-    __shared__ __align__(16) double col[2][kBottomMax];
+    __shared__ __align__(16) double col[2][2][kBottomMax];
     const TailEntry& t = tails[blockIdx.x >> 1];
     const int fld = blockIdx.x & 1;
     if (act && !act[t.prob]) return;                 // uniform over the workgroup
@@ -162,63 +256,8 @@ __global__ __launch_bounds__(kSetupThreads) void k_tail_setup(
         A[lin * kBottomBand] = dg;
     }
     __syncthreads();
-    // tiles of 8 x 4 for as many threads as it takes; the other wavefronts
-    // end here, which shortens the barriers
-    const int ldc = (N + 3) >> 2, ldr = (N + 7) >> 3;
-    if ((tid & ~63) >= ldr * ldc) return;
-    const int tr = tid / ldc, tc = tid - tr * ldc;
-    const int r0 = 8 * tr, c0 = 4 * tc;
-    const bool on = tr < ldr;
-    double a[8][4];
-#pragma unroll
-    for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int r = r0 + i, c = c0 + j;
-            const int hi = r > c ? r : c, d = r > c ? r - c : c - r;
-            a[i][j] = (hi < N && d < kBottomBand) ? A[hi * kBottomBand + d] : 0.0;
-        }
-    // (rows and columns beyond N stay zero: their published values are zero)
-    for (int kq = 0; 8 * kq < N; ++kq) {
-#pragma unroll
-        for (int b = 0; b < 8; ++b) {
-            const int k = 8 * kq + b;
-            if (k >= N) break;                       // uniform
-            // double buffered: a buffer is rewritten two barriers after it was
-            // read
-            double* v = col[b & 1];
-            if (on && tc == 2 * kq + (b >> 2))
-#pragma unroll
-                for (int i = 0; i < 8; ++i) v[r0 + i] = a[i][b & 3];
-            __syncthreads();
-            if (!on) continue;
-            const double ip = rcp_nr(v[k]);
-            double vr[8], vc[4];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) vr[i] = v[r0 + i];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) vc[j] = v[c0 + j] * ip;
-#pragma unroll
-            for (int i = 0; i < 8; ++i)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[i][j] -= vr[i] * vc[j];
-            if (tr == kq)
-#pragma unroll
-                for (int j = 0; j < 4; ++j) a[b][j] = vc[j];
-            if (tc == 2 * kq + (b >> 2)) {
-#pragma unroll
-                for (int i = 0; i < 8; ++i) a[i][b & 3] = vr[i] * ip;
-                if (tr == kq) a[b][b & 3] = -ip;
-            }
-        }
-    }
     double* Xi = X + t.boff + (int64_t)fld * N * N;
-    if (on)
-#pragma unroll
-        for (int i = 0; i < 8; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (r0 + i < N && c0 + j < N) Xi[(r0 + i) * N + c0 + j] = -a[i][j];
+    invert(A, col, N, Xi);
 }
 
 // ---------------------------------------------------------------------------
@@ -245,10 +284,12 @@ struct TailGrid {
     float inv_x, inv_y;                  // 1 / cn[0], 1 / cn[1]
     PT* e;
 
-    // operator of every owned cell; e zeroed (its last reader is past a
-    // barrier)
-    __device__ __forceinline__ void load(const PatchInfo& p, const PT* D, int64_t nl,
-                                         double beta, int robin, PT* buf) {
+    // Owned cells, their coefficients and, from grid `ff` (may be NULL), their
+    // right-hand sides: loads only, so that they are all in flight, other
+    // grids' too, before the first is waited for (with the Marshak branch among
+    // them each waited for the one before: 24 in a row).
+    __device__ __forceinline__ void fetch(const PatchInfo& p, const PT* D, const PT* ff,
+                                          int64_t nl) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             n[d] = p.n[d];
@@ -256,12 +297,6 @@ struct TailGrid {
         }
         inv_x = 1.0f / (float)cn[0];
         inv_y = 1.0f / (float)cn[1];
-        const int pad = n[0] * n[1];
-        e = buf + pad;
-        for (int q = threadIdx.x; q < p.ncell + 2 * pad; q += kTailThreads) buf[q] = PT(0);
-        PT bh2[3];
-#pragma unroll
-        for (int d = 0; d < 3; ++d) bh2[d] = (PT)(beta * p.ih[d] * p.ih[d]);
         const int st[3] = {1, p.sy, p.sz};
 #pragma unroll
         for (int w = 0; w < C; ++w) {
@@ -279,24 +314,48 @@ struct TailGrid {
                 c[col][w] = id[0] + n[0] * (id[1] + n[1] * id[2]);
                 const int cc = native_index(p, id[0], id[1], id[2]);
                 nat[col][w] = cc;
-                PT s = PT(1);
 #pragma unroll
                 for (int d = 0; d < 3; ++d)
 #pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const bool edge = id[d] == (h ? n[d] - 1 : 0);
-                        const PT Df = D[d * nl + (h ? cc + st[d] : cc)];
-                        const PT v = edge ? PT(0) : bh2[d] * Df;
-                        a[col][w][2 * d + h] = v;
-                        s += v;
-                        if (edge && ((robin >> (2 * d + h)) & 1)) {
-                            const PT hd = (PT)p.h[d];
-                            s += PT(2) * (PT)beta * Df / ((PT(4) * Df + hd) * hd);
-                        }
-                    }
-                rdg[col][w] = reciprocal(s);
+                    for (int h = 0; h < 2; ++h)
+                        a[col][w][2 * d + h] = D[d * nl + (h ? cc + st[d] : cc)];
+                if (ff) f[col][w] = ff[cc];
             }
         }
+    }
+    // the level operator from them; e zeroed (its last reader is past a
+    // barrier)
+    __device__ __forceinline__ void form(const PatchInfo& p, double beta, int robin, PT* buf) {
+        const int pad = n[0] * n[1];
+        const float inv_n = 1.0f / (float)n[0], inv_m = 1.0f / (float)n[1];
+        e = buf + pad;
+        for (int q = threadIdx.x; q < p.ncell + 2 * pad; q += kTailThreads) buf[q] = PT(0);
+        PT bh2[3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) bh2[d] = (PT)(beta * p.ih[d] * p.ih[d]);
+#pragma unroll
+        for (int w = 0; w < C; ++w)
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+                if (c[col][w] < 0) continue;
+                const int r = quot(c[col][w], inv_n), k = quot(r, inv_m);
+                const int id[3] = {c[col][w] - r * n[0], r - k * n[1], k};
+                PT s = PT(1);
+#pragma unroll
+                for (int f = 0; f < 6; ++f) {
+                    const int d = f >> 1;
+                    const bool edge = id[d] == ((f & 1) ? n[d] - 1 : 0);
+                    const PT Df = a[col][w][f], v = edge ? PT(0) : bh2[d] * Df;
+                    a[col][w][f] = v;
+                    s += v;
+                    if ((robin >> f) & 1) {          // uniform
+                        const PT hd = (PT)p.h[d];
+                        const PT more = PT(2) * (PT)beta * Df / ((PT(4) * Df + hd) * hd);
+                        s += edge ? more : PT(0);
+                    }
+                }
+                rdg[col][w] = reciprocal(s);
+            }
     }
     __device__ __forceinline__ void quad_cell(int q, int& I, int& J, int& K) const {
         const int r = quot(q, inv_x);
@@ -389,9 +448,12 @@ struct TailGrid {
 // kTailCells is what 1024 threads hold at two cells of each colour.  The
 // smallest coarsening halves 6, so two grids are smoothed at most (4096 and
 // 512 cells) before the coarsest.  What bounds it is one CU's instruction
-// rate on the 16^3 grid and, on the smaller ones, the chain of barriers.
-// Measured (float): a tail of 16^3 14.4 us, of 64 problems at once 21.5 us,
-// where the 13 launches it replaces took about 58 and 75 us.
+// rate: of a tail of 16^3 half the cycles go into loading and forming the
+// operator (17 of 32 k in float, 25 of 46 k in double; with a wait per face 20
+// to 25 k and 31 to 43 k), then the chain of barriers.
+// Measured: a tail of 16^3 13.2 us in float, 19.3 in double (23.1), of the 64
+// problems of an ensemble 16.3 us, where the 13 launches it replaces took about
+// 58 and 75 us in float.
 template <typename PT>
 __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
     const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
@@ -419,18 +481,9 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
     const int row = tid >> 3, part = tid & 7;        // eight lanes per row of X
     if (row < N) bottom_coords(pc, o, row, id);
     const int cell = id[0] + pc.n[0] * (id[1] + pc.n[1] * id[2]);
-    if (levels > 0) {
-        A.load(pa, G.D[t.start] + fld * 3 * G.nl[t.start], G.nl[t.start], beta,
-               fld == 0 ? pa.robin : 0, eA);
-#pragma unroll
-        for (int w = 0; w < 2; ++w)
-#pragma unroll
-            for (int col = 0; col < 2; ++col)
-                if (A.c[col][w] >= 0) A.f[col][w] = fa[A.nat[col][w]];
-    }
+    if (levels > 0) A.fetch(pa, G.D[t.start] + fld * 3 * G.nl[t.start], fa, G.nl[t.start]);
     if (levels > 1)
-        B.load(pb, G.D[t.start + 1] + fld * 3 * G.nl[t.start + 1], G.nl[t.start + 1], beta,
-               fld == 0 ? pb.robin : 0, eB);
+        B.fetch(pb, G.D[t.start + 1] + fld * 3 * G.nl[t.start + 1], nullptr, G.nl[t.start + 1]);
     // the first 64 columns of the inverse, wanted only at the bottom (float:
     // float64 coefficients leave no registers for them)
     constexpr int kAhead = sizeof(PT) == 4 ? 8 : 0;
@@ -439,6 +492,8 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
 #pragma unroll
     for (int j = 0; j < kAhead; ++j)
         xr[j] = (row < N && part + 8 * j < N) ? Xi[row * N + part + 8 * j] : 0.0;
+    if (levels > 0) A.form(pa, beta, fld == 0 ? pa.robin : 0, eA);
+    if (levels > 1) B.form(pb, beta, fld == 0 ? pb.robin : 0, eB);
     __syncthreads();
     if (levels > 0) {
         A.sweeps(nu_pre, true);

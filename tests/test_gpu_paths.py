@@ -285,3 +285,12 @@ def test_gradient_with_a_basis_of_any_size(m):
                  adjoint_slots=6, newton_rtol=1e-12, fac_base=int(m > 1))
         out.append(to_host(H.adjoint_run([2e-3], 1, 1)))
     assert rel_err(out[0], out[1]) < 1e-9
+
+
+@pytest.mark.parametrize("ext", [(3, 1, 1), (2, 2, 1), (5, 3, 2), (12, 12, 12), (10, 14, 6), (6, 8, 10),
+                                 (5, 5, 5)])
+def test_coarsest_grids_of_any_size(ext):
+    """The dense inverse of 3, 4, 30 and 125 cells (base grids that do not
+    coarsen) and of 27, 105 and 60: odd counts end on a single index, tiles
+    of four on a remainder of each size.  Tolerance as above."""
+    test_precond_with_small_grids_in_one_workgroup(ext, 0, 1e-10)
