@@ -109,7 +109,7 @@ struct nrd_hierarchy final : public Clock {
         size_t patches, tiles, stiles, vtiles, prob_vtile0, gcopy, gcf, sib, sync[kMaxLev], rfaces,
             rcells, cfrows, cfsrc, ctype, shadows, shadow_src, coff, ps, active, amap;
         size_t mg_box[kMaxMG], mg_tiles[kMaxMG], mg_box_of[kMaxMG], mg_smooth[kMaxMG],
-            tails, Xbuf, mg_l0map, ltiles, sweep[2], mg_blocks[kMaxMG];
+            tails, Xbuf, tail_op, mg_l0map, ltiles, sweep[2], mg_blocks[kMaxMG];
         size_t z, z3, cur, prev, udot, bvec, x, F, s, w, tmp, tmp2, gzn, V, Z, pred;
         size_t pc_D, pc_sigma, pc_T, pc_e, pc_e2, pc_u, pc_r, pc_f;
         size_t mg_D[kMaxMG], mg_e[kMaxMG], mg_f[kMaxMG], mg_o[kMaxMG];
@@ -288,6 +288,14 @@ static int32_t tail_grid(const Tables& t, int p) {
     return g;
 }
 
+// values of the operators of its smoothed grids: six weights and a reciprocal
+// per cell and field
+static int64_t tail_values(const Tables& t, int p) {
+    int64_t n = 0;
+    for (int32_t g = tail_grid(t, p); g < t.prob_mgdepth[p]; ++g) n += 14 * grid_cells(t, p, g);
+    return n;
+}
+
 // ---------------------------------------------------------------------------
 // layout
 // ---------------------------------------------------------------------------
@@ -348,6 +356,9 @@ static void layout(nrd_hierarchy* h) {
         bsum += nb * nb;
     }
     o.Xbuf = b.take(sizeof(double) * 2 * bsum);
+    int64_t osum = 0;
+    for (int p = 0; p < nprob; ++p) osum += tail_values(t, p);
+    o.tail_op = b.take((h->mixed ? sizeof(float) : sizeof(double)) * osum);
     // Fused sweeps of the base grid (pre, post): float, colour-split storage,
     // V(1,1) on problems that coarsen, and vectors beyond the last-level
     // cache.  Preconditioner with half-sweeps against fused, us: 128^3 231 /
@@ -517,6 +528,7 @@ static void wire_pc(nrd_hierarchy* h, PcArrays<PT>& pc) {
     pc.mg.multi0 = t.level_sib0[1] > t.level_sib0[0];
     pc.mg.tails = h->at<TailEntry>(o.tails);
     pc.mg.Xbuf = h->at<double>(o.Xbuf);
+    pc.mg.tail_op = h->at<PT>(o.tail_op);
     pc.p2_mode = h->opt.p2_mode;
     pc.nu_pre = std::max(1, h->opt.mg_nu_pre);
     pc.nu_post = std::max(0, h->opt.mg_nu_post);
@@ -576,6 +588,7 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
     std::vector<TailEntry> tails;
     std::vector<int32_t> start(t.nprob, 0);
     int32_t top = 0, nbase = 0;
+    int64_t aoff = 0;
     for (int pass = 0; pass < 2; ++pass)
         for (int p = 0; p < t.nprob; ++p) {
             const int32_t depth = t.prob_mgdepth[p];
@@ -589,6 +602,8 @@ static nrd_status bind(nrd_hierarchy* h, void* ptr, size_t bytes) {
             te.start = g;
             te.depth = depth;
             te.boff = 2 * (int64_t)t.bottom_off[p];
+            te.aoff = aoff;
+            aoff += tail_values(t, p);
             for (int32_t q = g; q <= depth; ++q)
                 te.grid[q - g] = q == 0 ? t.patches[box_of[0][p]] : t.mg[q].boxes[box_of[q][p]];
             tails.push_back(te);

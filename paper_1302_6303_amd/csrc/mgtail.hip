@@ -93,6 +93,7 @@ __device__ __forceinline__ void coarsen_field(const PatchInfo& pc, const PatchIn
 }
 
 constexpr int kSetupThreads = 1024;
+static_assert(kSetupThreads == kTailThreads, "owners of the cells are the same threads");
 
 // The inverse of the banded N x N matrix A (A(i, i - d) at [i kBottomBand + d],
 // symmetric, strictly diagonally dominant) by N / 2 symmetric sweeps of two
@@ -188,82 +189,6 @@ __device__ __forceinline__ void invert(const double* A, double (*col)[2][kBottom
                 if (r0 + i < N && c0 + j < N) Xi[(r0 + i) * N + c0 + j] = -a[i][j];
 }
 
-// Set-up below a problem's tail grid: the face coefficients of the grids
-// start + 1 .. depth, then the inverse X (float64, N x N, row major in the
-// numbering above) of the coarsest grid's operator.  Measured, with the
-// coefficients: N = 64 (a 32^3 problem) 22.7 us, N = 125 (in an ensemble) 70
-// us; a band Cholesky with two barriers per index and one triangular solve per
-// column took 62 and 137 us, after two launches for the coefficients.
-template <typename PT>
-__global__ __launch_bounds__(kSetupThreads) void k_tail_setup(
-    const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
-    const ProbScalars* __restrict__ ps, double* __restrict__ X) {
-    __shared__ double A[kBottomMax * kBottomBand];   // A(i, i - d) at [i kBottomBand + d]
-    __shared__ __align__(16) double col[2][2][kBottomMax];
-    const TailEntry& t = tails[blockIdx.x >> 1];
-    const int fld = blockIdx.x & 1;
-    if (act && !act[t.prob]) return;                 // uniform over the workgroup
-    for (int g = t.start + 1; g <= t.depth; ++g) {
-        const PatchInfo& pc = t.grid[g - t.start];
-        const PatchInfo& pf = t.grid[g - t.start - 1];
-        coarsen_field(pc, pf, G.D[g - 1] + fld * 3 * G.nl[g - 1], G.nl[g - 1],
-                      G.D[g] + fld * 3 * G.nl[g], G.nl[g]);
-        __threadfence_block();
-        __syncthreads();
-    }
-    const int g = t.depth;                           // the problem's coarsest grid
-    const PatchInfo& p = t.grid[g - t.start];
-    const PT* D = G.D[g] + fld * 3 * G.nl[g];
-    const int64_t nl = G.nl[g];
-    const double beta = ps[t.prob].beta;
-    // grid 0 without stored D_T: the T-field coefficients from T
-    const PT* __restrict__ T0 = (g == 0 && fld == 1) ? G.T0 : nullptr;
-    const PT kappa = (PT)ps[t.prob].kappa;
-    const int N = p.ncell;                           // <= kBottomMax (checked on the host)
-    const BottomOrder o = bottom_order(p);
-    const int tid = threadIdx.x;
-    for (int i = tid; i < N * kBottomBand; i += kSetupThreads) A[i] = 0.0;
-    __syncthreads();
-    const int st[3] = {1, p.sy, p.sz};
-    for (int lin = tid; lin < N; lin += kSetupThreads) {
-        int id[3];
-        bottom_coords(p, o, lin, id);
-        const int c = native_index(p, id[0], id[1], id[2]);
-        double dg = 1.0;
-#pragma unroll
-        for (int d = 0; d < 3; ++d) {
-            const double bh2 = beta * p.ih[d] * p.ih[d];
-            const PT* Dd = D + d * nl;
-#pragma unroll
-            for (int s = 0; s < 2; ++s) {
-                if (id[d] == (s ? p.n[d] - 1 : 0)) {        // grid covers the domain
-                    if (fld == 0 && ((p.robin >> (2 * d + s)) & 1)) {
-                        const double Dv = (double)Dd[s ? c + st[d] : c];
-                        dg += 2.0 * beta * Dv / ((4.0 * Dv + p.h[d]) * p.h[d]);
-                    }
-                    continue;
-                }
-                const int nb = s ? c + st[d] : c - st[d];
-                const double Dv = T0 ? (double)face_DT(T0[c], T0[nb], kappa)
-                                     : (double)Dd[s ? c + st[d] : c];
-                const double a = bh2 * Dv;
-                dg += a;
-                // the lower neighbour's entry; the upper one is that
-                // neighbour's lower entry (same face, same coefficient)
-                if (s == 0) A[lin * kBottomBand + o.st[d]] = -a;
-            }
-        }
-        A[lin * kBottomBand] = dg;
-    }
-    __syncthreads();
-    double* Xi = X + t.boff + (int64_t)fld * N * N;
-    invert(A, col, N, Xi);
-}
-
-// ---------------------------------------------------------------------------
-// V-cycle below the tail grid
-// ---------------------------------------------------------------------------
-
 __device__ __forceinline__ float reciprocal(float x) { return 1.0f / x; }
 __device__ __forceinline__ double reciprocal(double x) { return rcp_nr(x); }
 
@@ -284,12 +209,7 @@ struct TailGrid {
     float inv_x, inv_y;                  // 1 / cn[0], 1 / cn[1]
     PT* e;
 
-    // Owned cells, their coefficients and, from grid `ff` (may be NULL), their
-    // right-hand sides: loads only, so that they are all in flight, other
-    // grids' too, before the first is waited for (with the Marshak branch among
-    // them each waited for the one before: 24 in a row).
-    __device__ __forceinline__ void fetch(const PatchInfo& p, const PT* D, const PT* ff,
-                                          int64_t nl) {
+    __device__ __forceinline__ void extents(const PatchInfo& p) {
 #pragma unroll
         for (int d = 0; d < 3; ++d) {
             n[d] = p.n[d];
@@ -297,65 +217,90 @@ struct TailGrid {
         }
         inv_x = 1.0f / (float)cn[0];
         inv_y = 1.0f / (float)cn[1];
-        const int st[3] = {1, p.sy, p.sz};
-#pragma unroll
-        for (int w = 0; w < C; ++w) {
-            const int q = threadIdx.x + w * kTailThreads;
-            c[0][w] = c[1][w] = -1;
-            if (q >= (p.ncell >> 1)) continue;
-            int I, J, K;
-            quad_cell(q >> 2, I, J, K);
-            const int lane = q & 3;
-            const int child = lane == 0 ? 0 : (lane == 1 ? 3 : (lane == 2 ? 5 : 6));
-#pragma unroll
-            for (int col = 0; col < 2; ++col) {
-                const int id[3] = {2 * I + ((child ^ col) & 1), 2 * J + ((child >> 1) & 1),
-                                   2 * K + (child >> 2)};
-                c[col][w] = id[0] + n[0] * (id[1] + n[1] * id[2]);
-                const int cc = native_index(p, id[0], id[1], id[2]);
-                nat[col][w] = cc;
-#pragma unroll
-                for (int d = 0; d < 3; ++d)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        a[col][w][2 * d + h] = D[d * nl + (h ? cc + st[d] : cc)];
-                if (ff) f[col][w] = ff[cc];
-            }
-        }
     }
-    // the level operator from them; e zeroed (its last reader is past a
-    // barrier)
-    __device__ __forceinline__ void form(const PatchInfo& p, double beta, int robin, PT* buf) {
-        const int pad = n[0] * n[1];
-        const float inv_n = 1.0f / (float)n[0], inv_m = 1.0f / (float)n[1];
-        e = buf + pad;
-        for (int q = threadIdx.x; q < p.ncell + 2 * pad; q += kTailThreads) buf[q] = PT(0);
+    // interior coordinates of owned cell w of colour col
+    __device__ __forceinline__ void place(int col, int w, int id[3]) const {
+        const int q = threadIdx.x + w * kTailThreads;
+        int I, J, K;
+        quad_cell(q >> 2, I, J, K);
+        const int lane = q & 3;
+        const int child = lane == 0 ? 0 : (lane == 1 ? 3 : (lane == 2 ? 5 : 6));
+        id[0] = 2 * I + ((child ^ col) & 1);
+        id[1] = 2 * J + ((child >> 1) & 1);
+        id[2] = 2 * K + (child >> 2);
+    }
+    // Set-up: the level operator of the owned cells to op, value k of colour
+    // col of all cells in the order of their owners.  (Every coefficient is
+    // loaded before the Marshak branch, which made each wait for the one
+    // before.)
+    template <typename F>
+    __device__ __forceinline__ void form(const PatchInfo& p, const F& coef, double beta,
+                                         int robin, PT* op) {
+        extents(p);
+        const int half = p.ncell >> 1;
         PT bh2[3];
 #pragma unroll
         for (int d = 0; d < 3; ++d) bh2[d] = (PT)(beta * p.ih[d] * p.ih[d]);
 #pragma unroll
-        for (int w = 0; w < C; ++w)
+        for (int w = 0; w < C; ++w) {
+            const int q = threadIdx.x + w * kTailThreads;
+            if (q >= half) continue;
 #pragma unroll
             for (int col = 0; col < 2; ++col) {
-                if (c[col][w] < 0) continue;
-                const int r = quot(c[col][w], inv_n), k = quot(r, inv_m);
-                const int id[3] = {c[col][w] - r * n[0], r - k * n[1], k};
+                int id[3];
+                place(col, w, id);
+                PT v[6];
+#pragma unroll
+                for (int f = 0; f < 6; ++f) v[f] = coef(id, f);
                 PT s = PT(1);
 #pragma unroll
                 for (int f = 0; f < 6; ++f) {
                     const int d = f >> 1;
                     const bool edge = id[d] == ((f & 1) ? n[d] - 1 : 0);
-                    const PT Df = a[col][w][f], v = edge ? PT(0) : bh2[d] * Df;
-                    a[col][w][f] = v;
-                    s += v;
+                    const PT Df = v[f];
+                    v[f] = edge ? PT(0) : bh2[d] * Df;
+                    s += v[f];
                     if ((robin >> f) & 1) {          // uniform
                         const PT hd = (PT)p.h[d];
                         const PT more = PT(2) * (PT)beta * Df / ((PT(4) * Df + hd) * hd);
                         s += edge ? more : PT(0);
                     }
                 }
-                rdg[col][w] = reciprocal(s);
+#pragma unroll
+                for (int f = 0; f < 6; ++f) op[(col * 7 + f) * half + q] = v[f];
+                op[(col * 7 + 6) * half + q] = reciprocal(s);
             }
+        }
+    }
+    // the operator back into registers, and right-hand sides from ff (unless
+    // NULL): loads only, in flight together with other grids'
+    __device__ __forceinline__ void load(const PatchInfo& p, const PT* op,
+                                         const PT* ff = nullptr) {
+        extents(p);
+        const int half = p.ncell >> 1;
+#pragma unroll
+        for (int w = 0; w < C; ++w) {
+            const int q = threadIdx.x + w * kTailThreads;
+            c[0][w] = c[1][w] = -1;
+            if (q >= half) continue;
+#pragma unroll
+            for (int col = 0; col < 2; ++col) {
+#pragma unroll
+                for (int f = 0; f < 6; ++f) a[col][w][f] = op[(col * 7 + f) * half + q];
+                rdg[col][w] = op[(col * 7 + 6) * half + q];
+                int id[3];
+                place(col, w, id);
+                c[col][w] = id[0] + n[0] * (id[1] + n[1] * id[2]);
+                nat[col][w] = native_index(p, id[0], id[1], id[2]);
+                if (ff) f[col][w] = ff[nat[col][w]];
+            }
+        }
+    }
+    // e = 0 (its last reader is past a barrier)
+    __device__ __forceinline__ void clear(PT* buf) {
+        const int pad = n[0] * n[1];
+        e = buf + pad;
+        for (int q = threadIdx.x; q < n[2] * pad + 2 * pad; q += kTailThreads) buf[q] = PT(0);
     }
     __device__ __forceinline__ void quad_cell(int q, int& I, int& J, int& K) const {
         const int r = quot(q, inv_x);
@@ -439,25 +384,136 @@ struct TailGrid {
     }
 };
 
+// Set-up below a problem's tail grid: the face coefficients of the grids
+// start + 1 .. depth, then the inverse X (float64, N x N, row major in the
+// numbering above) of the coarsest grid's operator; in workgroups of their own
+// the operators of the grids that k_mg_tail smooths.  Measured, with the
+// coefficients: N = 64 (a 32^3 problem) 22.7 us, N = 125 (in an ensemble) 70
+// us; a band Cholesky with two barriers per index and one triangular solve per
+// column took 62 and 137 us, after two launches for the coefficients.
+template <typename PT>
+__global__ __launch_bounds__(kSetupThreads) void k_tail_setup(
+    const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
+    const ProbScalars* __restrict__ ps, double* __restrict__ X) {
+    __shared__ double A[kBottomMax * kBottomBand];   // A(i, i - d) at [i kBottomBand + d]
+    __shared__ __align__(16) double col[2][2][kBottomMax];
+    const bool first = blockIdx.x >= (gridDim.x >> 1);      // the tail grid's own operator
+    const int b = first ? blockIdx.x - (gridDim.x >> 1) : blockIdx.x;
+    const TailEntry& t = tails[b >> 1];
+    const int fld = b & 1;
+    if (act && !act[t.prob]) return;                 // uniform over the workgroup
+    const int levels = t.depth - t.start;
+    const int64_t na = t.grid[0].ncell, nb = levels > 1 ? t.grid[1].ncell : 0;
+    PT* op = G.op + t.aoff + fld * 7 * (na + nb);
+    if (first) {
+        // (the second grid's coefficients as the mean of the tail grid's, the
+        // expression that the other workgroup stores)
+        const PatchInfo& p = t.grid[0];
+        const PT* D = G.D[t.start] + fld * 3 * G.nl[t.start];
+        const int64_t nl = G.nl[t.start];
+        const int st[3] = {1, p.sy, p.sz};
+        if (levels > 0) {
+            TailGrid<PT, 2> T;
+            T.form(p,
+                   [&](const int id[3], int f) {
+                       const int c = native_index(p, id[0], id[1], id[2]);
+                       return D[(f >> 1) * nl + ((f & 1) ? c + st[f >> 1] : c)];
+                   },
+                   ps[t.prob].beta, fld == 0 ? p.robin : 0, op);
+        }
+        if (levels > 1) {
+            TailGrid<PT, 1> T;
+            T.form(t.grid[1],
+                   [&](const int id[3], int f) {
+                       const int d = f >> 1, t1 = st[d == 0 ? 1 : 0], t2 = st[d == 2 ? 1 : 2];
+                       const PT* src = D + d * nl + native_index(p, 2 * id[0], 2 * id[1], 2 * id[2]) +
+                                       ((f & 1) ? 2 * st[d] : 0);
+                       return ((src[0] + src[t1]) + (src[t2] + src[t1 + t2])) * PT(0.25);
+                   },
+                   ps[t.prob].beta, fld == 0 ? t.grid[1].robin : 0, op + 7 * na);
+        }
+        return;
+    }
+    for (int g = t.start + 1; g <= t.depth; ++g) {
+        const PatchInfo& pc = t.grid[g - t.start];
+        const PatchInfo& pf = t.grid[g - t.start - 1];
+        coarsen_field(pc, pf, G.D[g - 1] + fld * 3 * G.nl[g - 1], G.nl[g - 1],
+                      G.D[g] + fld * 3 * G.nl[g], G.nl[g]);
+        __threadfence_block();
+        __syncthreads();
+    }
+    const int g = t.depth;                           // the problem's coarsest grid
+    const PatchInfo& p = t.grid[g - t.start];
+    const PT* D = G.D[g] + fld * 3 * G.nl[g];
+    const int64_t nl = G.nl[g];
+    const double beta = ps[t.prob].beta;
+    // grid 0 without stored D_T: the T-field coefficients from T
+    const PT* __restrict__ T0 = (g == 0 && fld == 1) ? G.T0 : nullptr;
+    const PT kappa = (PT)ps[t.prob].kappa;
+    const int N = p.ncell;                           // <= kBottomMax (checked on the host)
+    const BottomOrder o = bottom_order(p);
+    const int tid = threadIdx.x;
+    for (int i = tid; i < N * kBottomBand; i += kSetupThreads) A[i] = 0.0;
+    __syncthreads();
+    const int st[3] = {1, p.sy, p.sz};
+    for (int lin = tid; lin < N; lin += kSetupThreads) {
+        int id[3];
+        bottom_coords(p, o, lin, id);
+        const int c = native_index(p, id[0], id[1], id[2]);
+        double dg = 1.0;
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+            const double bh2 = beta * p.ih[d] * p.ih[d];
+            const PT* Dd = D + d * nl;
+#pragma unroll
+            for (int s = 0; s < 2; ++s) {
+                if (id[d] == (s ? p.n[d] - 1 : 0)) {        // grid covers the domain
+                    if (fld == 0 && ((p.robin >> (2 * d + s)) & 1)) {
+                        const double Dv = (double)Dd[s ? c + st[d] : c];
+                        dg += 2.0 * beta * Dv / ((4.0 * Dv + p.h[d]) * p.h[d]);
+                    }
+                    continue;
+                }
+                const int nb = s ? c + st[d] : c - st[d];
+                const double Dv = T0 ? (double)face_DT(T0[c], T0[nb], kappa)
+                                     : (double)Dd[s ? c + st[d] : c];
+                const double a = bh2 * Dv;
+                dg += a;
+                // the lower neighbour's entry; the upper one is that
+                // neighbour's lower entry (same face, same coefficient)
+                if (s == 0) A[lin * kBottomBand + o.st[d]] = -a;
+            }
+        }
+        A[lin * kBottomBand] = dg;
+    }
+    __syncthreads();
+    double* Xi = X + t.boff + (int64_t)fld * N * N;
+    invert(A, col, N, Xi);
+}
+
+// ---------------------------------------------------------------------------
+// V-cycle below the tail grid
+// ---------------------------------------------------------------------------
+
 // The V-cycle of one (problem, field) on its grids start .. depth, one
 // workgroup each: the right-hand side of grid `start` is read and its
 // correction written.  A grid of at most kTailCells cells is smaller than the
 // launch that sweeps it, so the whole of it runs between barriers, with the
-// operator in registers (loaded once, before anything waits for it) and the
-// iterates in LDS: a half-sweep is six LDS reads and a division per cell.
-// kTailCells is what 1024 threads hold at two cells of each colour.  The
+// operator in registers (as the set-up left it, in the order of its owners)
+// and the iterates in LDS: a half-sweep is six LDS reads and a product per
+// cell.  kTailCells is what 1024 threads hold at two cells of each colour.  The
 // smallest coarsening halves 6, so two grids are smoothed at most (4096 and
-// 512 cells) before the coarsest.  What bounds it is one CU's instruction
-// rate: of a tail of 16^3 half the cycles go into loading and forming the
-// operator (17 of 32 k in float, 25 of 46 k in double; with a wait per face 20
-// to 25 k and 31 to 43 k), then the chain of barriers.
-// Measured: a tail of 16^3 13.2 us in float, 19.3 in double (23.1), of the 64
-// problems of an ensemble 16.3 us, where the 13 launches it replaces took about
-// 58 and 75 us in float.
+// 512 cells) before the coarsest.  What bounds it is one CU's instruction rate
+// and the chain of barriers; in double the registers as well (64 B per thread
+// spilled).  Measured: a tail of 16^3 10.2 us in float and 18.2 in double (13.2
+// and 19.3 when every cycle formed the operator from the coefficients anew, 13.9
+// and 23.1 when it also waited for each of them), of the 64 problems of an
+// ensemble 14.3 us, where the 13 launches it replaces took about 58 and 75 us
+// in float.
 template <typename PT>
 __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
     const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
-    const ProbScalars* __restrict__ ps, const double* __restrict__ X, int nu_pre, int nu_post) {
+    const double* __restrict__ X, int nu_pre, int nu_post) {
     // iterates with their padding (n0 n1 <= n / 6 where a grid coarsens)
     __shared__ PT eA[kTailCells + kTailCells / 3 + 8], eB[kTailCells / 8 + kTailCells / 24 + 8];
     __shared__ PT fB[kTailCells / 8], fC[kBottomMax], eC[kBottomMax];
@@ -465,7 +521,6 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
     const TailEntry& t = tails[blockIdx.x >> 1];
     const int fld = blockIdx.x & 1;
     if (act && !act[t.prob]) return;                 // uniform over the workgroup
-    const double beta = ps[t.prob].beta;
     const int tid = threadIdx.x;
     const int levels = t.depth - t.start;            // smoothed grids (0, 1 or 2)
     const PatchInfo& pa = t.grid[0];
@@ -481,9 +536,15 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
     const int row = tid >> 3, part = tid & 7;        // eight lanes per row of X
     if (row < N) bottom_coords(pc, o, row, id);
     const int cell = id[0] + pc.n[0] * (id[1] + pc.n[1] * id[2]);
-    if (levels > 0) A.fetch(pa, G.D[t.start] + fld * 3 * G.nl[t.start], fa, G.nl[t.start]);
-    if (levels > 1)
-        B.fetch(pb, G.D[t.start + 1] + fld * 3 * G.nl[t.start + 1], nullptr, G.nl[t.start + 1]);
+    const PT* op = G.op + t.aoff + (int64_t)fld * 7 * (pa.ncell + (levels > 1 ? pb.ncell : 0));
+    if (levels > 0) A.load(pa, op, fa);
+    // (float64: registers for one grid's operator at a time)
+    constexpr bool kBoth = sizeof(PT) == 4;
+    const PT* opB = op + 7 * (int64_t)pa.ncell;
+    if (levels > 1) {
+        if (kBoth) B.load(pb, opB);
+        else B.extents(pb);
+    }
     // the first 64 columns of the inverse, wanted only at the bottom (float:
     // float64 coefficients leave no registers for them)
     constexpr int kAhead = sizeof(PT) == 4 ? 8 : 0;
@@ -492,14 +553,15 @@ __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
 #pragma unroll
     for (int j = 0; j < kAhead; ++j)
         xr[j] = (row < N && part + 8 * j < N) ? Xi[row * N + part + 8 * j] : 0.0;
-    if (levels > 0) A.form(pa, beta, fld == 0 ? pa.robin : 0, eA);
-    if (levels > 1) B.form(pb, beta, fld == 0 ? pb.robin : 0, eB);
+    if (levels > 0) A.clear(eA);
+    if (levels > 1) B.clear(eB);
     __syncthreads();
     if (levels > 0) {
         A.sweeps(nu_pre, true);
         A.restrict_to(levels > 1 ? fB : fC);
     }
     if (levels > 1) {
+        if (!kBoth) B.load(pb, opB);
 #pragma unroll
         for (int col = 0; col < 2; ++col)
             if (B.c[col][0] >= 0) B.f[col][0] = fB[B.c[col][0]];
@@ -587,15 +649,14 @@ void bottom_apply(hipStream_t s, int n, const int32_t* act, const TailEntry* tai
 template <typename PT>
 void tail_setup(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
                 const TailGrids<PT>& G, const ProbScalars* ps, double* X) {
-    if (n > 0) k_tail_setup<PT><<<2 * n, kSetupThreads, 0, s>>>(act, tails, G, ps, X);
+    if (n > 0) k_tail_setup<PT><<<4 * n, kSetupThreads, 0, s>>>(act, tails, G, ps, X);
 }
 
 template <typename PT>
 void tail_cycle(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
-                const TailGrids<PT>& G, const ProbScalars* ps, const double* X, int nu_pre,
-                int nu_post) {
+                const TailGrids<PT>& G, const double* X, int nu_pre, int nu_post) {
     if (n > 0)
-        k_mg_tail<PT><<<2 * n, kTailThreads, 0, s>>>(act, tails, G, ps, X, nu_pre, nu_post);
+        k_mg_tail<PT><<<2 * n, kTailThreads, 0, s>>>(act, tails, G, X, nu_pre, nu_post);
 }
 
 #define NRD_TAIL(PT)                                                                          \
@@ -604,8 +665,7 @@ void tail_cycle(hipStream_t s, int n, const int32_t* act, const TailEntry* tails
     template void bottom_apply<PT>(hipStream_t, int, const int32_t*, const TailEntry*,        \
                                    const double*, const PT*, PT*, int64_t, int);              \
     template void tail_cycle<PT>(hipStream_t, int, const int32_t*, const TailEntry*,          \
-                                 const TailGrids<PT>&, const ProbScalars*, const double*,     \
-                                 int, int);
+                                 const TailGrids<PT>&, const double*, int, int);
 NRD_TAIL(float)
 NRD_TAIL(double)
 #undef NRD_TAIL

@@ -59,6 +59,7 @@ constexpr int kTailCells = 4096;
 struct TailEntry {
     int32_t prob, start, depth, pad;
     int64_t boff;            // of the problem's inverses, in doubles
+    int64_t aoff;            // of the smoothed grids' operators, in values
     PatchInfo grid[3];       // grids start .. depth (at most three: each has an
                              // eighth of the cells, and 6 cells per axis or more
                              // where it coarsens)
@@ -115,6 +116,7 @@ struct TailGrids {
     const PT* f[kMaxMG] = {};
     PT* e[kMaxMG] = {};
     int64_t nl[kMaxMG] = {};
+    PT* op = nullptr;           // operators of the smoothed grids below
     const PT* T0 = nullptr;     // grid 0's T in PT when its D_T arrays are not stored
 };
 
@@ -129,8 +131,7 @@ void bottom_apply(hipStream_t s, int n, const int32_t* act, const TailEntry* tai
 // e of the tail grids from f of the tail grids, n problems
 template <typename PT>
 void tail_cycle(hipStream_t s, int n, const int32_t* act, const TailEntry* tails,
-                const TailGrids<PT>& G, const ProbScalars* ps, const double* X, int nu_pre,
-                int nu_post);
+                const TailGrids<PT>& G, const double* X, int nu_pre, int nu_post);
 
 template <typename PT>
 struct PcArrays {
@@ -161,6 +162,7 @@ struct PcArrays {
         const TailEntry* tails = nullptr;
         int nbase = 0, ntail = 0;
         double* Xbuf = nullptr;
+        PT* tail_op = nullptr;          // see TailGrids::op
         // first grid: per native cell, the level-0 patch of its children
         // (a base grid cut into several boxes); multi0: level 0 has siblings
         const int32_t* l0map = nullptr;

@@ -970,6 +970,7 @@ TailGrids<PT> PcArrays<PT>::tail_grids() const {
         t.e[g] = mg.result(g);
         t.nl[g] = (g == 0) ? D->nl : mg.len[g];
     }
+    t.op = mg.tail_op;
     t.T0 = split0 ? Tp : nullptr;
     return t;
 }
@@ -1063,8 +1064,8 @@ void PcArrays<PT>::vcycle(hipStream_t s, double* y, bool p2) const {
     // other problem's tail grid down
     bottom_apply<PT>(s, mg.nbase, d.active, mg.tails, mg.Xbuf, f, mg.result(0),
                      d.nl, split0 ? 1 : 0);
-    tail_cycle<PT>(s, mg.ntail, d.active, mg.tails + mg.nbase, tail_grids(), d.ps, mg.Xbuf,
-                   nu_pre, nu_post);
+    tail_cycle<PT>(s, mg.ntail, d.active, mg.tails + mg.nbase, tail_grids(), mg.Xbuf, nu_pre,
+                   nu_post);
     for (int g = mg.top - 1; g >= 0; --g) {
         if (mg.nsmooth[g] == 0) continue;
         if (g == 0 && y) {
