@@ -58,11 +58,16 @@ sys.path.insert(0, ROOT)
 
 BYTES_PER_CELL_RESIDUAL = 56      # read E, T, z^3, b_E, b_T; write F_E, F_T (f64)
 BYTES_PER_CELL_JVP = 56           # read E, T, z^3, v_E, v_T; write 2 (f64)
-# red-black sweep in float: read the right-hand side (2), the frozen state
-# E, T, z^3 (3) and the iterate (2), write the iterate (2); the first sweep
-# of a V-cycle starts from zero and does not read the iterate
+# red-black sweep in float, a launch per colour: read the right-hand side (2),
+# the frozen state E, T, z^3 (3) and the iterate (2), write the iterate (2);
+# the first sweep of a V-cycle starts from zero and does not read the iterate
 BYTES_PER_CELL_SWEEP = 36
 BYTES_PER_CELL_SWEEP_ZERO = 28
+# one launch for the whole sweep (base grids beyond the last-level cache): from
+# zero D_E (12), T (4), f (8), colour 1 of the iterate (4); the other one also
+# prolongs (1) and applies the coupling solve (sigma 4, z^3 8, float64 out 16)
+BYTES_PER_CELL_SWEEP_FUSED = 57
+FUSED_SWEEP_LEN = 8 << 20         # least field length, ghosts included
 HBM_PEAK_GBS = 8000.0
 
 # HBM bytes per composite cell of the residual on the ensemble workload from
@@ -1080,6 +1085,13 @@ def main():
         traffic = round(MEASURED_TRAFFIC["bytes_per_cell"] * res_cells)
     jvp_s = mixed["jvp_ms_avg"] / 1e3
     base_cells = sum(b.ncells for b in w.boxes if b.level == 0)
+    # sweeps in one launch (default smoother options; one level, even x extents)
+    fused = (all(b.level == 0 and b.shape[0] % 2 == 0 for b in w.boxes)
+             and len(w.boxes) == len(w.problems) and tuple(a.mg_nu) == (1, 1)
+             and a.fac_cycle != "afacx" and a.fac_base != "smooth"
+             and sum((b.shape[0] + 2) * (b.shape[1] + 2) * (b.shape[2] + 2)
+                     for b in w.boxes) >= FUSED_SWEEP_LEN)
+    sweep_bytes = BYTES_PER_CELL_SWEEP_FUSED if fused else BYTES_PER_CELL_SWEEP
     def gbs(nbytes, ms):
         return round(nbytes / ms / 1e6, 1) if ms > 0 else None
 
@@ -1133,13 +1145,16 @@ def main():
                          "frac": round(BYTES_PER_CELL_JVP * ncomp / jvp_s / 1e9 / HBM_PEAK_GBS, 4),
                          "avg_launch_ms": round(mixed["jvp_ms_avg"], 4)},
         "smoother_roofline": {
-            "kernel": "k_level<float> (red-black sweep of the base grid, one launch per colour, "
-                      "colour-split iterate and right-hand side, T-field face coefficients "
-                      "recomputed from T)",
-            "cells": base_cells, "bytes_per_cell": BYTES_PER_CELL_SWEEP,
-            "achieved": gbs(BYTES_PER_CELL_SWEEP * base_cells, mixed["sweep_ms_avg"]),
+            "kernel": "k_sweep_post (red-black sweep of the base grid, both colours, with the "
+                      "prolongation before and the coupling solve after it in one launch; from "
+                      "zero k_sweep_pre; T-field face coefficients recomputed from T)"
+                      if fused else
+                      "k_level<float> (red-black sweep of the base grid, one launch per colour; "
+                      "small grids: k_block_up and k_block_down, a leg of the cycle per launch)",
+            "cells": base_cells, "bytes_per_cell": sweep_bytes,
+            "achieved": gbs(sweep_bytes * base_cells, mixed["sweep_ms_avg"]),
             "unit": "GB/s",
-            "frac": frac(BYTES_PER_CELL_SWEEP * base_cells, mixed["sweep_ms_avg"]),
+            "frac": frac(sweep_bytes * base_cells, mixed["sweep_ms_avg"]),
             "avg_sweep_ms": round(mixed["sweep_ms_avg"], 4),
             "zero_start": {
                 "bytes_per_cell": BYTES_PER_CELL_SWEEP_ZERO,

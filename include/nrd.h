@@ -464,7 +464,10 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path,
  * one preconditioner application; SMOOTH: one red-black sweep (both colour
  * launches) on the base level's multigrid grid starting from a nonzero
  * iterate; SMOOTH_ZERO: the first such sweep of a V-cycle, from a zero
- * iterate.  NRD_EINVAL for an unknown timer.  Synchronises. */
+ * iterate.  Where a launch holds more than the sweep (large and small base
+ * grids under V(1,1)) its time is the launch's: SMOOTH with the prolongation
+ * and, on large ones, the coupling solve, SMOOTH_ZERO on small ones with the
+ * restriction.  NRD_EINVAL for an unknown timer.  Synchronises. */
 nrd_status nrd_timer_read(nrd_hierarchy* h, int32_t which, double* ms_total,
                           int32_t* count);
 enum { NRD_TIMER_RESIDUAL = 0, NRD_TIMER_JVP = 1, NRD_TIMER_PRECOND = 2,

@@ -170,7 +170,7 @@ struct Tables {
                                              // cells^2 doubles
 };
 
-// Band storage per row of the coarsest-grid Cholesky factor (b + 1).
+// Band storage per row of the coarsest grid's operator (b + 1).
 constexpr int32_t kBottomBand = 26;
 
 // Staged-plane stencil tiles: at most kStageCells cells of a plane per tile

@@ -496,7 +496,7 @@ __global__ __launch_bounds__(kBlock) void k_level_res(const int32_t* __restrict_
 // ---------------------------------------------------------------------------
 // composite operator residual r = f - A^c u on composite cells (covered -> 0)
 // with flux form on every face; coarse faces bordering a finer level are
-// skipped here and supplied by k_comp_reflux.
+// skipped here and supplied by the flux matching of k_comp_res.
 // ---------------------------------------------------------------------------
 
 // Both fields of one composite cell without the fluxes that flux matching

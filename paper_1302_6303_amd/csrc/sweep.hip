@@ -265,7 +265,7 @@ __global__ __launch_bounds__(kSweepThreads) void k_sweep_pre(
 
 // Prolongation of colour 1 (the correction of grid 1, ec), the post-sweep and,
 // cell by cell, P2^-1 into y (P2: otherwise the sweep's result itself): e is
-// only read.  53 B per cell are read and written (D_E 12, T 4, f 8, e 4, ec 1,
+// only read.  57 B per cell are read and written (D_E 12, T 4, f 8, e 4, ec 1,
 // sigma 4, z^3 8, y 16, less rims).
 template <bool P2>
 __global__ __launch_bounds__(kSweepThreads) void k_sweep_post(
