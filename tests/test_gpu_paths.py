@@ -294,3 +294,25 @@ def test_coarsest_grids_of_any_size(ext):
     coarsen) and of 27, 105 and 60: odd counts end on a single index, tiles
     of four on a remainder of each size.  Tolerance as above."""
     test_precond_with_small_grids_in_one_workgroup(ext, 0, 1e-10)
+
+
+def test_gathers_of_the_transpose_take_any_row_length():
+    """Coarse sources of a transposed product gather their ghosts' values four
+    at a time: <lam, J v> = <J^T lam, v> on a hierarchy of three levels whose
+    sources feed 1 to many ghosts, to the rounding of sums of n products."""
+    w = I.static_amr(base=16, nlevels=3, side=(4, 12), seed_k=12, state="front")
+    H = make(w, gmres_restart=2)
+    H.begin_step([1e-3])
+    rng = np.random.default_rng(3)
+    n = w.ncells()
+    u = np.concatenate([w.compact(w.E), w.compact(w.T)]) * rng.uniform(0.9, 1.1, 2 * n)
+    un = native_from_compact(H, u)
+    v, lam = (rng.standard_normal(2 * n) for _ in range(2))
+    # (both arguments on composite cells alone: the product's first step makes
+    # covered ones the mean of their children)
+    Jv = compact_from_native(H, H.jvp(un, native_from_compact(H, v), H.native()))
+    lam[Jv == 0.0] = 0.0
+    v0 = v.copy()
+    Jt = compact_from_native(H, H.vjp(un, native_from_compact(H, lam), H.native())[0])
+    a, b = float(lam @ Jv), float(Jt @ v0)
+    assert abs(a - b) < 1e-12 * float(np.abs(lam) @ np.abs(Jv) + np.abs(Jt) @ np.abs(v0))
