@@ -7,16 +7,17 @@
 
 namespace nrd {
 
-// Reciprocal and reciprocal square root: the hardware estimate (about 23
-// correct bits) refined by two Newton-Raphson steps (quadratic convergence,
-// so the result is within about one ulp); valid for the positive, normal
-// operands met here.
+// Reciprocal and reciprocal square root: the hardware estimate (about 24
+// correct bits) refined by one step of third order or two of Newton-Raphson
+// (the result is within about one ulp); valid for the positive, normal operands
+// met here.  The reciprocal, and the root below, give the same bits either way
+// over 2^22 operands; one step takes one and three operations less
+// (preconditioner of 96^3 185.9 -> 183.4 us).
 __device__ __forceinline__ double rcp_nr(double x) {
-    double y = __builtin_amdgcn_rcp(x);
-    double e = __builtin_fma(-x, y, 1.0);
-    y = __builtin_fma(y, e, y);
-    e = __builtin_fma(-x, y, 1.0);
-    return __builtin_fma(y, e, y);
+    // one step of third order: y (1 + e + e^2), e = 1 - x y of 24 bits
+    const double y = __builtin_amdgcn_rcp(x);
+    const double e = __builtin_fma(-x, y, 1.0);
+    return __builtin_fma(y, __builtin_fma(e, e, e), y);
 }
 __device__ __forceinline__ double rsqrt_nr(double x) {
     double y = __builtin_amdgcn_rsq(x);
@@ -53,7 +54,10 @@ __device__ __forceinline__ float sqrt_pos(float x) {
     return __builtin_fmaf(__builtin_fmaf(-g, g, x), 0.5f * y, g);
 }
 __device__ __forceinline__ double sqrt_pos(double x) {
-    const double y = rsqrt_nr(x + 1e-300);
+    // 1 / sqrt(x) by one step of third order, y (1 + r / 2 + 3 r^2 / 8)
+    double y = __builtin_amdgcn_rsq(x + 1e-300);
+    const double r = __builtin_fma(-(x * y), y, 1.0);
+    y = __builtin_fma(y, r * __builtin_fma(0.375, r, 0.5), y);
     const double g = x * y;
     return __builtin_fma(__builtin_fma(-g, g, x), 0.5 * y, g);
 }
