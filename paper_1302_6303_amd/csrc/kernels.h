@@ -167,6 +167,7 @@ struct GmresScalars {
 };
 // Second Gram-Schmidt pass against nv <= 16 basis vectors, w untouched: h2 and
 // the norm of the twice corrected w, then column nv - 1 of every active problem
+// (hn2_host = -1 and no column where that norm has to be formed from the vector)
 void gs_again(const Dev& D, hipStream_t s, const double* X, int64_t xstride, int nv,
               const double* w, double* partial, int m, const GmresScalars& G,
               const double* xsc = nullptr);

@@ -145,6 +145,9 @@ struct nrd_hierarchy final : public Clock {
     double* mail_hn2() const { return mail + t.nprob; }
     double* mail_dot() const { return mail + 2 * (size_t)t.nprob; }
     double* mail_min() const { return mail + 3 * (size_t)t.nprob; }
+    GmresScalars gmres_scalars() const {
+        return {h1, h2, hn2, H, cs, sn, g, vscale, mail_rho(), mail_hn2()};
+    }
     ProbScalars* ps;
     double* scratch = nullptr;      // device address of the fixed partial-sum array
     // timers
@@ -1148,8 +1151,7 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
                 double* Vj = h->V + j * NL;
                 double* Zj = h->Z + j * NL;
                 double* wv = h->w;
-                const GmresScalars G{h->h1, h->h2, h->hn2,    h->H,          h->cs,
-                                     h->sn, h->g,  h->vscale, h->mail_rho(), h->mail_hn2()};
+                const GmresScalars G = h->gmres_scalars();
                 // the previous iteration read r with 1/beta in place of v_0
                 const bool was_lazy = j == 1 && v0_lazy;
                 bool ready = false;      // the preconditioner's input is in place
@@ -1221,6 +1223,20 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
             }
             HIPCHK(hipStreamSynchronize(s));
             const double *rho = h->mail_rho(), *hn = h->mail_hn2();
+            // problems whose norm of w2 gs_again left to a direct sum
+            bool direct = false;
+            for (int p = 0; j < 16 && p < np; ++p) direct |= live[p] && hn[p] < 0.0;
+            if (direct) {
+                for (int p = 0; p < np; ++p) h->host_active[p] = live[p] && hn[p] < 0.0;
+                RCHK(upload_active(h));
+                const GmresScalars G = h->gmres_scalars();
+                if (j == 0 && v0_lazy) scale_copy(h->D, s, r, h->coefA, h->V);
+                copy_interior(h->D, s, h->w, h->tmp2);
+                combine(h->D, s, h->V, NL, j + 1, h->h1, j + 1, h->tmp2, 1, -1.0);
+                combine_norm(h->D, s, h->V, NL, j + 1, h->h2, j + 1, h->tmp2, h->partial, h->hn2);
+                gmres_column(s, np, m, j, h->active, G);
+                HIPCHK(hipStreamSynchronize(s));
+            }
             bool left = false;
             for (int p = 0; p < np; ++p) {
                 if (!live[p]) continue;

@@ -427,14 +427,21 @@ __device__ __forceinline__ void gmres_column_one(int p, int m, int j, const doub
 
 // End of the second Gram-Schmidt pass of one problem from its sums S = (h2_0
 // .. h2_j, ||w1||^2), by one wavefront: the basis is orthonormal, so w2 = w1 -
-// sum h2_v v_v has ||w2||^2 = ||w1||^2 - sum h2_v^2.
+// sum h2_v v_v has ||w2||^2 = ||w1||^2 - sum h2_v^2.  Unless the second pass
+// took half of it or more (w lies in the span of the basis to rounding, or is
+// NaN): there the difference has lost its digits, and the column is left to the
+// caller, who forms w2 and its norm (hn2_host < 0 asks for that).
 __device__ __forceinline__ void gs_finish(int p, int m, int j, const double* S,
                                           const GmresScalars& G) {
     const int lane = threadIdx.x & 63;
     double n2 = S[j + 1];
     for (int v = 0; v <= j; ++v) n2 -= S[v] * S[v];
     if (lane <= j) G.h2[(int64_t)p * (j + 1) + lane] = S[lane];
-    gmres_column_one(p, m, j, G.h1 + (int64_t)p * (j + 1), S, fmax(n2, 0.0), G);
+    if (!(n2 >= 0.5 * S[j + 1])) {                   // uniform; NaN too
+        if (lane == 0) G.hn2_host[p] = -1.0;
+        return;
+    }
+    gmres_column_one(p, m, j, G.h1 + (int64_t)p * (j + 1), S, n2, G);
 }
 
 // Second Gram-Schmidt pass of FGMRES without storing anything: w1 = w - sum_v
@@ -1120,10 +1127,7 @@ __global__ __launch_bounds__(64) void k_gmres_column(int m, int j,
                                                      const int32_t* __restrict__ active,
                                                      GmresScalars G) {
     const int p = blockIdx.x;
-    if (active && !active[p]) {
-        if (threadIdx.x == 0) G.vscale[p] = 0.0;
-        return;
-    }
+    if (active && !active[p]) return;
     gmres_column_one(p, m, j, G.h1 + (int64_t)p * (j + 1), G.h2 + (int64_t)p * (j + 1), G.hn2[p], G);
 }
 
