@@ -41,13 +41,17 @@ __device__ __forceinline__ int native_index(const PatchInfo& p, int i, int j, in
     return p.off + (i + 1) + p.sy * (j + 1) + p.sz * (k + 1);
 }
 
-// Square root of x >= 0 and quotient by a normal d > 0: the hardware estimate
-// refined until the last correction is below an ulp.  Over 2^24 float and 2^22
-// double operands none differed from the correctly rounded result; the
-// library's forms take three times the instructions, to scale subnormal and
-// huge operands too.  The sweeps of the base grid are bound by instruction
-// issue: 96^3 in double 248 -> 226 us per preconditioner, 128^3 in float 14.5
-// -> 13.8 ms per two steps.
+// Quotient by d > 0, infinite and NaN operands included, and square root of a
+// finite x >= 0: the hardware estimate refined until the last correction is
+// below an ulp; the library's forms take up to three times the instructions.
+// Over 2^22 operands of each type no quotient differed from the correctly
+// rounded one for divisors from 1 to the largest finite one (subnormal ones: by
+// an ulp, rarely), nor a root from 1e-33 (double: 1e-296) on.  A smaller root is
+// off, but face_DT, its caller, multiplies it by kappa x^2: no product differed
+// over 2^22 pairs of x and kappa, subnormal ones included.  The sweeps of the
+// base grid are bound by instruction issue: 96^3 in double 248 -> 226 us per
+// preconditioner, 128^3 in float 14.5 -> 13.8 ms per four steps (divisors beyond
+// 2^126 and infinities among them at no cost: 182.4 us and 12.7 ms either way).
 __device__ __forceinline__ float sqrt_pos(float x) {
     const float y = __builtin_amdgcn_rsqf(x + 1e-37f);   // finite at 0
     const float g = x * y;
@@ -62,15 +66,17 @@ __device__ __forceinline__ double sqrt_pos(double x) {
     return __builtin_fma(__builtin_fma(-g, g, x), 0.5 * y, g);
 }
 __device__ __forceinline__ float div_pos(float n, float d) {
-    float y = __builtin_amdgcn_rcpf(d);
-    y = __builtin_fmaf(__builtin_fmaf(-d, y, 1.0f), y, y);
+    // (the estimate of d / 4: that of d itself is flushed to 0 beyond 2^126)
+    const float d4 = 0.25f * d;
+    float y = __builtin_amdgcn_rcpf(d4);
+    y = 0.25f * __builtin_fmaf(__builtin_fmaf(-d4, y, 1.0f), y, y);
     const float q = n * y;
-    return __builtin_fmaf(__builtin_fmaf(-d, q, n), y, q);
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-d, q, n), y, q), d, n);
 }
 __device__ __forceinline__ double div_pos(double n, double d) {
     const double y = rcp_nr(d);
     const double q = n * y;
-    return __builtin_fma(__builtin_fma(-d, q, n), y, q);
+    return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-d, q, n), y, q), d, n);
 }
 
 // D_T = kappa T_f^(5/2) of the face between cells of temperatures Ta, Tb

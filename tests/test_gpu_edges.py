@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 
 from paper_1302_6303_amd import inputs as I
-from tests.gpu_helpers import make
+from tests.gpu_helpers import compact_from_native, make, native_from_compact, rel_err
+from tests.helpers import state, system
 from tests.test_gpu_paths import _box
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,26 @@ def test_norms_formed_from_the_vector_leave_other_problems_alone(precision, grap
     assert st[2]["krylov_per_newton"] == alone["krylov_per_newton"]
     assert st[2]["newton_iters"] == alone["newton_iters"]
     assert set(st[1]["krylov_per_newton"]) <= {0, 1}
+
+
+@pytest.mark.parametrize("kappa", [1e36, 4e36])
+def test_sweeps_divide_by_diagonals_of_floats_whole_range(kappa):
+    """Level sweeps (base level smoothed) whose diagonals lie between 2^126
+    and float's largest value (3 to 6 faces of 3.2e37), and beyond it (each
+    face 1.3e38): quotients to single precision of four operations, and 0."""
+    w = _uniform((8, 8, 8), kappa)
+    s = system(w, fac_base="smooth")
+    H = make(w, precision=1, fac_base=1, gmres_restart=2)
+    dt = 0.5                               # beta / h^2 = 32
+    H.begin_step([dt])
+    u = state(s, w)
+    wv = np.concatenate([np.zeros(s.nc),
+                         1e30 * np.random.default_rng(4).uniform(1.0, 2.0, s.nc)])
+    H.precond_setup(native_from_compact(H, u))
+    got = compact_from_native(H, H.precond_apply(native_from_compact(H, wv), H.native()))
+    if kappa > 1e36:
+        np.testing.assert_array_equal(got, 0.0)
+        return
+    ref = s.precond(u, dt)[0](wv)
+    for f in (slice(0, s.nc), slice(s.nc, 2 * s.nc)):
+        assert rel_err(got[f], ref[f]) < 1e-6
