@@ -448,8 +448,9 @@ nrd_status nrd_dot_noalloc(nrd_hierarchy* h, const double* dev_x,
  * choices, one line "arch v<variant> <fmt> <nx>x<ny>x<nz> <planes> <run> <us>"
  * per class (<fmt> names the tile constants of the build that wrote it);
  * classes found for this device architecture, variant and format whose shape
- * is one this build would try are not timed again (other lines are ignored),
- * newly timed ones are appended.  *timed_classes (may be NULL)
+ * is one this build would try are not timed again (other lines are ignored;
+ * the two kernels that variant 3 may run have runs of their own, and each its
+ * own lines), newly timed ones are appended.  *timed_classes (may be NULL)
  * returns how many classes were timed.  Needs a bound workspace and
  * nrd_set_fields (NRD_ESTATE otherwise); synchronises the stream; drops
  * captured graphs.  Variant 0 has nothing to tune (returns NRD_OK). */

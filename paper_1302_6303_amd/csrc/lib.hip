@@ -2254,15 +2254,14 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
             if (a != arch || v != tag || fmt != cache_fmt ||
                 std::sscanf(dims.c_str(), "%dx%dx%d", &k.n[0], &k.n[1], &k.n[2]) != 3)
                 continue;
-            // only shapes this build would itself try: a stale or edited line
-            // can never give a tile more cells than a workgroup holds
-            // (planes chosen for staged planes or for wave runs serve both)
+            // only shapes this build would itself try, by the kernel that runs
+            // (its run length is its own; one box shape may be tuned for
+            // several): a stale or edited line can never give a tile more
+            // cells than a workgroup holds
             bool known = false;
-            for (auto [ckc, crun] : cand)
-                known |= ckc == kc && (crun == run || (h->opt.stencil == 3 &&
-                                                       (run == kStageCells || run == kWaveRun)));
+            for (auto [ckc, crun] : cand) known |= ckc == kc && crun == run;
             if (!known) continue;
-            pick[k] = {kc, run0};
+            pick[k] = {kc, run};
         }
     }
     // current shapes: cached choices, else the defaults

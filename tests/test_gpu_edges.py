@@ -6,7 +6,7 @@ import pytest
 from paper_1302_6303_amd import inputs as I
 from tests.gpu_helpers import compact_from_native, make, native_from_compact, rel_err
 from tests.helpers import state, system
-from tests.test_gpu_paths import _box
+from tests.test_gpu_paths import _box, _grid
 
 pytestmark = pytest.mark.gpu
 
@@ -75,3 +75,12 @@ def test_sweeps_divide_by_diagonals_of_floats_whole_range(kappa):
     ref = s.precond(u, dt)[0](wv)
     for f in (slice(0, s.nc), slice(s.nc, 2 * s.nc)):
         assert rel_err(got[f], ref[f]) < 1e-6
+
+
+def test_tuned_shapes_are_kept_per_kernel(tmp_path):
+    """One box shape alone (16 plane runs: staged planes) and 13 of it (208:
+    wave runs) under one cache file: each kernel's choice is timed by itself
+    and found again."""
+    cache = str(tmp_path / "tiles.txt")
+    few, many = _grid([(16, 16, 16)], []), _grid([(16, 16, 16)] * 13, [])
+    assert [make(w).autotune(cache) for w in (few, many, few, many)] == [1, 1, 0, 0]
