@@ -136,7 +136,7 @@ struct nrd_hierarchy final : public Clock {
     const double* fd_base = nullptr;   // F at the Newton iterate (Jacobian-free mode)
     int32_t *kdim, *flag, *active;
     int32_t* amap;                  // stencil tiles of the active problems
-    std::vector<int32_t> host_amap;
+    std::vector<std::vector<int32_t>> amap_sent;   // copies that may be under way
     std::vector<int32_t> dev_active;   // flags last sent (empty: none)
     // results the host waits for, one value per problem each, in pinned host
     // memory that the kernels write
@@ -914,9 +914,17 @@ static void pc_apply_t(nrd_hierarchy* h, const double* w, double* y) {
         h->pcd.apply_transpose(h->stream, w, y);
 }
 
+// Waits for the stream; nothing sent to the device is read from the host then.
+static nrd_status settle(nrd_hierarchy* h) {
+    HIPCHK(hipStreamSynchronize(h->stream));
+    h->amap_sent.clear();
+    return NRD_OK;
+}
+
 // Small host arrays on their way to the device; go() launches them all.
 struct Send {
     nrd_hierarchy* h;
+    bool flags = false;              // the active flags are among them
     PutArgs<kPutLarge> a;
     struct Big { void* dst; std::vector<char> src; int32_t stride; };
     std::vector<Big> big;            // what does not fit the arguments
@@ -956,7 +964,8 @@ struct Send {
                 HIPCHK(hipMemcpy2DAsync(x.dst, 4 * (size_t)x.stride, x.src.data(), 8, 8,
                                         x.src.size() / 8, hipMemcpyHostToDevice, s));
         }
-        if (!big.empty()) HIPCHK(hipStreamSynchronize(s));     // the sources end here
+        if (!big.empty()) RCHK(settle(h));                     // the sources end here
+        if (flags) h->dev_active = h->host_active;
         return NRD_OK;
     }
 };
@@ -968,13 +977,13 @@ struct Send {
 static nrd_status add_active(nrd_hierarchy* h, Send& S) {
     if (h->dev_active == h->host_active) return NRD_OK;
     S.add(h->active, h->host_active);
-    h->dev_active = h->host_active;
+    S.flags = true;
+    h->dev_active.clear();
     h->D.amap = nullptr;
     h->D.namap = 0;
     if (h->opt.use_graph) return NRD_OK;
     const Tables& t = h->t;
-    auto& m = h->host_amap;
-    m.clear();
+    std::vector<int32_t> m;
     if (h->D.bricks) {
         for (int32_t i = 0; i < (int32_t)t.stiles.size(); ++i)
             if (h->host_active[t.stiles[i].prob]) m.push_back(i);
@@ -987,6 +996,7 @@ static nrd_status add_active(nrd_hierarchy* h, Send& S) {
                               h->stream));
     h->D.amap = h->amap;
     h->D.namap = (int32_t)m.size();
+    h->amap_sent.push_back(std::move(m));
     return NRD_OK;
 }
 static nrd_status upload_active(nrd_hierarchy* h) {
@@ -997,7 +1007,7 @@ static nrd_status upload_active(nrd_hierarchy* h) {
 
 // The values of a pinned array once the stream has written them.
 static nrd_status mailed(nrd_hierarchy* h, const double* mail, std::vector<double>& out) {
-    HIPCHK(hipStreamSynchronize(h->stream));
+    RCHK(settle(h));
     out.assign(mail, mail + h->t.nprob);
     return NRD_OK;
 }
@@ -1221,7 +1231,7 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
             } else {
                 iteration();
             }
-            HIPCHK(hipStreamSynchronize(s));
+            RCHK(settle(h));
             const double *rho = h->mail_rho(), *hn = h->mail_hn2();
             // problems whose norm of w2 gs_again left to a direct sum
             bool direct = false;
@@ -1235,7 +1245,7 @@ static nrd_status fgmres(nrd_hierarchy* h, double* u, const double* rhs, double*
                 combine(h->D, s, h->V, NL, j + 1, h->h1, j + 1, h->tmp2, 1, -1.0);
                 combine_norm(h->D, s, h->V, NL, j + 1, h->h2, j + 1, h->tmp2, h->partial, h->hn2);
                 gmres_column(s, np, m, j, h->active, G);
-                HIPCHK(hipStreamSynchronize(s));
+                RCHK(settle(h));
             }
             bool left = false;
             for (int p = 0; p < np; ++p) {

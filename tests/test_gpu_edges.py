@@ -4,7 +4,8 @@ import numpy as np
 import pytest
 
 from paper_1302_6303_amd import inputs as I
-from tests.gpu_helpers import compact_from_native, make, native_from_compact, rel_err
+from tests.gpu_helpers import (compact_from_native, make, native_from_compact, problem_slices,
+                               rel_err)
 from tests.helpers import state, system
 from tests.test_gpu_paths import _box, _grid
 
@@ -84,3 +85,32 @@ def test_tuned_shapes_are_kept_per_kernel(tmp_path):
     cache = str(tmp_path / "tiles.txt")
     few, many = _grid([(16, 16, 16)], []), _grid([(16, 16, 16)] * 13, [])
     assert [make(w).autotune(cache) for w in (few, many, few, many)] == [1, 1, 0, 0]
+
+
+def test_steps_of_hundreds_of_problems():
+    """300 problems at once, whose arrays do not fit one launch's arguments,
+    against batches of 60, which do: the same systems to the same relative
+    tolerances, so the states agree to the steps' own (1e-11 of the first
+    residual; inner products are summed in other groups)."""
+    exts = [(6, 6, 6), (8, 6, 6), (6, 8, 10)]
+    ws = [_box(exts[p % 3], seed=200 + p) for p in range(300)]
+    dts = [2e-4 * (1 + p % 7) for p in range(300)]
+
+    def run(ps):
+        w = I.Workload("many", [ws[p].problems[0] for p in ps],
+                       [I.Box(i, 0, (0, 0, 0), exts[p % 3]) for i, p in enumerate(ps)],
+                       [ws[p].z[0] for p in ps], [ws[p].E[0] for p in ps],
+                       [ws[p].T[0] for p in ps], np.array([dts[p] for p in ps]))
+        H = make(w, newton_rtol=1e-11, newton_atol=1e-18)
+        its = [[st["newton_iters"] for st in H.implicit_step([dts[p] for p in ps])[1]]
+               for _ in range(2)]
+        E, T = H.get_fields()
+        u = np.concatenate([E.cpu().numpy(), T.cpu().numpy()])
+        return [u[i] for i in problem_slices(w)], its
+
+    got, its = run(range(300))
+    assert len(set(its[0])) > 1            # the mask of active problems changes
+    for a in range(0, 300, 60):
+        want, _ = run(range(a, a + 60))
+        for p in range(60):
+            assert rel_err(got[a + p], want[p]) < 1e-9
