@@ -1870,16 +1870,19 @@ nrd_status nrd_hierarchy_create(const nrd_problem* probs, int32_t nprob, const n
         // cells per reduction tile: 2048, or fewer where the grid is too small
         // to give two workgroups to every CU that way (32^3: 16 workgroups of
         // eight cells per thread took 6.5 us for an inner product, 128 of one
-        // cell 4.2 us)
+        // cell 4.2 us) and nrd_dot_noalloc's array has room for the tiles
         int32_t vcells = 8 * kBlock;
         if (boxes && nbox > 0) {
-            int64_t n = 0;
+            double n = 0;                        // (extents are checked later)
             for (int32_t b = 0; b < nbox; ++b) {
-                int64_t c = 1;
-                for (int d = 0; d < 3; ++d) c *= std::max(0, boxes[b].hi[d] - boxes[b].lo[d]);
+                double c = 1;
+                for (int d = 0; d < 3; ++d)
+                    c *= std::max(0.0, (double)boxes[b].hi[d] - boxes[b].lo[d]);
                 n += c;
             }
-            while (vcells > kBlock && n < (int64_t)512 * vcells) vcells /= 2;
+            while (vcells > kBlock && n < 512.0 * vcells &&
+                   nbox + n / (vcells / 2) <= kScratchTiles)
+                vcells /= 2;
         }
         nrd_status rc = build_tables(probs, nprob, boxes, nbox, kBlock, vcells, h->t, msg);
         if (rc) {
