@@ -114,3 +114,38 @@ def test_steps_of_hundreds_of_problems():
         want, _ = run(range(a, a + 60))
         for p in range(60):
             assert rel_err(got[a + p], want[p]) < 1e-9
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_ghosts_of_large_tables(precision):
+    """Twelve problems refined on half their domain by 4^3 boxes (2.2 M ghosts,
+    siblings and coarse-fine: a thread takes both fields) against one of them
+    alone (a field per block): residual, Jacobian action by one kernel, and
+    preconditioner, bit for bit the same."""
+    nprob, fine = 12, [(x, y, z) for z in range(0, 64, 4) for y in range(0, 64, 4)
+                       for x in range(0, 32, 4)]
+    one = _grid([(32, 32, 32)], [(f, tuple(c + 4 for c in f)) for f in fine])
+    many = I.Workload("many", one.problems * nprob,
+                      [I.Box(p, b.level, b.lo, b.hi) for p in range(nprob) for b in one.boxes],
+                      one.z * nprob, one.E * nprob, one.T * nprob, np.full(nprob, 1e-3))
+    rng = np.random.default_rng(5)
+    n = one.ncells()
+    v0 = rng.standard_normal(2 * n)
+    u0 = np.concatenate([one.compact(one.E), one.compact(one.T)]) * rng.uniform(0.9, 1.1, 2 * n)
+
+    def outputs(w, batch):
+        H = make(w, precision=precision, stencil=0, gmres_restart=2)
+        H.begin_step([1e-3] * len(w.problems))
+        u = native_from_compact(H, batch(u0))
+        v = batch(v0)
+        out = [compact_from_native(H, H.residual(u, H.native())),
+               compact_from_native(H, H.jvp(u, native_from_compact(H, v), H.native()))]
+        H.precond_setup(u)
+        return out + [compact_from_native(H, H.precond_apply(native_from_compact(H, v),
+                                                             H.native()))]
+
+    want = outputs(one, lambda x: x)
+    got = outputs(many, lambda x: np.concatenate([np.tile(x[:n], nprob), np.tile(x[n:], nprob)]))
+    for a, b in zip(got, want):
+        for p in (0, nprob - 1):
+            np.testing.assert_array_equal(a.reshape(2, nprob, n)[:, p].ravel(), b)
