@@ -83,23 +83,28 @@ int32_t plane_variant(const Tables& t, int32_t variant) {
     // than 120 cells).  Wave runs read neighbours again from the caches.  So
     // wave runs where the vectors stay in the last-level cache, where most
     // cells are in rows that wide, and for patches of several levels, small
-    // enough for their neighbours to stay in the L2.  Staged / wave runs,
-    // residual and Jacobian action, us: 40^3 6.4 / 6.4 and 7.3 / 6.4; 80^3
-    // 13.4 / 11.4 and 18.9 / 16.1; 128^3 37 / 31 and 60 / 44; 160^3 82 / 53
-    // and 125 / 85; 192^3 204 / 114 and 294 / 151; 256^3 332 / 274 and 397 /
-    // 343 (one thread per column, which staged planes gave way to there).
-    // Batches of boxes up to 96 wide: 8 boxes, 1.6 M cells 28.6 / 25.3 and
-    // 40.7 / 37.5, 16, 5.2 M 78 / 87 and 122 / 121, 64, 20 M 305 / 334 and
-    // 367 / 410.  Several levels, with their ghosts: 58 k cells 19.9 / 17.7
-    // and 30.1 / 27.4; 5.3 M 202 / 200 and 316 / 307; 9.6 M 329 / 330 and 511
-    // / 498.  Below about 200 tiles both take their launch: 32^3 6.0 / 6.2 and
-    // 6.4 / 6.8.
-    constexpr int64_t kFewTiles = 200, kManyTiles = 12000;
+    // enough for their neighbours to stay in the L2, up to four times that
+    // size.  Staged / wave runs, residual and Jacobian action, us: 40^3 6.4 /
+    // 6.4 and 7.3 / 6.4; 80^3 13.4 / 11.4 and 18.9 / 16.1; 128^3 37 / 31 and 60
+    // / 44; 160^3 82 / 53 and 125 / 85; 192^3 204 / 114 and 294 / 151; 256^3 332
+    // / 274 and 397 / 343 (one thread per column, which staged planes gave way
+    // to there).  Batches of boxes up to 96 wide: 8 boxes, 1.6 M cells 28.6 /
+    // 25.3 and 40.7 / 37.5, 16, 5.2 M 78 / 87 and 122 / 121, 64, 20 M 305 / 334
+    // and 367 / 410.  Several levels, with their ghosts: 58 k cells 19.9 / 17.7
+    // and 30.1 / 27.4; 5.3 M in 24 k tiles 184 / 180 and 289 / 276; 8.5 M in 38
+    // k 285 / 291 and 451 / 444; 9.6 M in 46 k 337 / 339 and 524 / 513; 11.9 M
+    // in 61 k 420 / 432 and 653 / 663; 21.6 M in 96 k 714 / 704 and 1050 /
+    // 1067.  Both operators run one kernel, and a solve has several Jacobian
+    // actions to a residual: up to 46 k tiles those gain 2 to 5 % where the
+    // residual gains or loses 2 %.  Below about 200 tiles both take their
+    // launch: 32^3 6.0 / 6.2 and 6.4 / 6.8.
+    constexpr int64_t kFewTiles = 200, kManyTiles = 12000, kManyRefined = 50000;
     const int64_t n = plane_runs(t);
     int64_t wide = 0;
     for (const PatchInfo& p : t.patches)
         if (p.n[0] > 120) wide += p.ncell;
-    return 2 * wide > t.ncells || (n >= kFewTiles && (n <= kManyTiles || t.nlev > 1)) ? 2 : 3;
+    const int64_t most = t.nlev > 1 ? kManyRefined : kManyTiles;
+    return 2 * wide > t.ncells || (n >= kFewTiles && n <= most) ? 2 : 3;
 }
 
 int32_t default_zchunk(const Tables& t, int32_t b, int32_t variant) {

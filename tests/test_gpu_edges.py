@@ -7,7 +7,7 @@ from paper_1302_6303_amd import inputs as I
 from tests.gpu_helpers import (compact_from_native, make, native_from_compact, problem_slices,
                                rel_err)
 from tests.helpers import state, system
-from tests.test_gpu_paths import _box, _grid
+from tests.test_gpu_paths import _box, _grid, test_stencil_kernel_of_the_size_rule as _one_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -149,3 +149,12 @@ def test_ghosts_of_large_tables(precision):
     for a, b in zip(got, want):
         for p in (0, nprob - 1):
             np.testing.assert_array_equal(a.reshape(2, nprob, n)[:, p].ravel(), b)
+
+
+# 46 080 and 54 272 one-plane tiles: wave runs, staged planes
+@pytest.mark.parametrize("width", [44, 52])
+def test_stencil_kernel_of_large_refined_hierarchies(width):
+    """The default kernel on both sides of its rule for several levels against
+    one thread per cell, bounds as for the other sizes."""
+    _one_kernel([(64, 64, 64)], [((x, y, z), (x + 4, y + 4, z + 4)) for z in range(0, 128, 4)
+                                 for y in range(0, 128, 4) for x in range(0, width, 4)])
