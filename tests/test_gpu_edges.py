@@ -3,11 +3,13 @@ hundreds of problems, the tile tuner's cache."""
 import numpy as np
 import pytest
 
+from oracle import precond as pc
 from paper_1302_6303_amd import inputs as I
 from tests.gpu_helpers import (compact_from_native, make, native_from_compact, problem_slices,
                                rel_err)
 from tests.helpers import state, system
-from tests.test_gpu_paths import _box, _grid, test_stencil_kernel_of_the_size_rule as _one_kernel
+from tests.test_gpu_paths import _box, _grid, _sweep_batch
+from tests.test_gpu_paths import test_stencil_kernel_of_the_size_rule as _one_kernel
 
 pytestmark = pytest.mark.gpu
 
@@ -158,3 +160,89 @@ def test_stencil_kernel_of_large_refined_hierarchies(width):
     one thread per cell, bounds as for the other sizes."""
     _one_kernel([(64, 64, 64)], [((x, y, z), (x + 4, y + 4, z + 4)) for z in range(0, 128, 4)
                                  for y in range(0, 128, 4) for x in range(0, width, 4)])
+
+
+def _with_cycle(monkeypatch, m, n):
+    """The oracle's multigrid as V(m, n)."""
+    orig = pc.mg_vcycle
+    monkeypatch.setattr(pc, "mg_vcycle", lambda grids, beta, rhs, level=0, nu_pre=1, nu_post=1,
+                        cache=None: orig(grids, beta, rhs, level, m, n, cache))
+
+
+# grids swept one by one, in blocks and within one workgroup (none, one and
+# two of them), on colour-split storage and a base grid of two boxes
+@pytest.mark.parametrize("precision,tol", [(0, 1e-10), (1, 1e-4)])
+@pytest.mark.parametrize("nu", [(2, 1), (1, 2), (1, 0), (2, 0), (3, 2)])
+@pytest.mark.parametrize("grid", ["8", "12x12x12", "24x24x56", "64x32x32", "two boxes",
+                                  "two levels"])
+def test_precond_of_any_multigrid_cycle(monkeypatch, grid, nu, precision, tol):
+    """Preconditioner with m sweeps before and n after each coarse correction
+    against the oracle's V(m, n), tolerances as for V(1, 1)."""
+    if grid == "two levels":
+        w = I.static_amr(base=16, nlevels=2, side=(8, 16), state="front")
+    elif grid == "two boxes":
+        w = _grid([(24, 24, 24)], [])
+        w.boxes = [I.Box(0, 0, (0, 0, 0), (10, 24, 24)), I.Box(0, 0, (10, 0, 0), (24, 24, 24))]
+        w.E, w.T, w.z = ([x[0][:10], x[0][10:]] for x in (w.E, w.T, w.z))
+    else:
+        ext = tuple(int(x) for x in grid.split("x"))
+        w = _box(ext * 3 if len(ext) == 1 else ext)
+    _with_cycle(monkeypatch, *nu)
+    s = system(w)
+    H = make(w, precision=precision, gmres_restart=2, mg_nu_pre=nu[0], mg_nu_post=nu[1])
+    H.begin_step([1e-3])
+    rng = np.random.default_rng(42)
+    u = s.sync(state(s, w) * rng.uniform(0.9, 1.1, 2 * s.nc))
+    wv = rng.standard_normal(u.shape)
+    H.precond_setup(native_from_compact(H, u))
+    got = compact_from_native(H, H.precond_apply(native_from_compact(H, wv), H.native()))
+    ref = s.precond(u, 1e-3)[0](wv)
+    for f in (slice(0, s.nc), slice(s.nc, 2 * s.nc)):
+        m = s.composite[f]
+        assert rel_err(got[f][m], ref[f][m]) < tol
+
+
+@pytest.mark.parametrize("nu", [(2, 1), (1, 2)])
+def test_large_batches_of_any_multigrid_cycle(nu):
+    """A hierarchy large enough for the fused base sweeps of V(1, 1), under
+    another cycle, which they do not serve: each problem's preconditioner
+    beside the others and alone, bit for bit the same."""
+    ws, w = _sweep_batch()
+    n = [x.ncells() for x in ws]
+    us = [np.concatenate([x.compact(x.E), x.compact(x.T)]) for x in ws]
+    vs = [np.random.default_rng(60 + p).standard_normal(2 * n[p]) for p in range(len(ws))]
+
+    def apply(w, u, v):
+        H = make(w, precision=1, gmres_restart=2, mg_nu_pre=nu[0], mg_nu_post=nu[1])
+        H.begin_step([float(x) for x in w.dt])
+        H.precond_setup(native_from_compact(H, u))
+        return compact_from_native(H, H.precond_apply(native_from_compact(H, v), H.native()))
+
+    got = apply(w, np.concatenate([x[:k] for x, k in zip(us, n)] + [x[k:] for x, k in zip(us, n)]),
+                np.concatenate([x[:k] for x, k in zip(vs, n)] + [x[k:] for x, k in zip(vs, n)]))
+    at = np.concatenate([[0], np.cumsum(n)])
+    for p in range(1, len(ws)):
+        want = apply(ws[p], us[p], vs[p])
+        mine = np.concatenate([got[f + at[p]:f + at[p + 1]] for f in (0, at[-1])])
+        np.testing.assert_array_equal(mine, want, err_msg=str(p))
+
+
+# wave runs of 80^3 take two planes per tile (2000 plane runs), staged planes
+# of 7 and 11 of them eight and sixteen (14 000 and 22 000)
+@pytest.mark.parametrize("nprob,other", [(1, 4), (7, 4), (11, 8)])
+def test_every_chunk_of_the_size_rule_keeps_every_value(nprob, other):
+    """The default planes per tile give bit for bit another chunk's values."""
+    w = _grid([(80, 80, 80)] * nprob, [])
+    rng = np.random.default_rng(5)
+    n = w.ncells()
+    v = rng.standard_normal(2 * n)
+    u = np.concatenate([w.compact(w.E), w.compact(w.T)]) * rng.uniform(0.9, 1.1, 2 * n)
+    outs = []
+    for zc in (0, other):
+        H = make(w, stencil=3, zchunk=zc, gmres_restart=2)
+        H.begin_step([float(x) for x in w.dt])
+        F = H.residual(native_from_compact(H, u), H.native())
+        Jv = H.jvp(native_from_compact(H, u), native_from_compact(H, v), H.native())
+        outs.append((compact_from_native(H, F), compact_from_native(H, Jv)))
+    np.testing.assert_array_equal(outs[0][0], outs[1][0])
+    np.testing.assert_array_equal(outs[0][1], outs[1][1])
