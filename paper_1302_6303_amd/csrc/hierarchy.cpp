@@ -75,6 +75,10 @@ static int64_t plane_runs(const Tables& t) {
     return n;
 }
 
+// one-plane tiles: from the first to the second number wave runs on hierarchies
+// of one level, from the first to the third on those of several
+constexpr int64_t kFewTiles = 200, kManyTiles = 12000, kManyRefined = 50000;
+
 int32_t plane_variant(const Tables& t, int32_t variant) {
     if (variant != 3) return variant;
     // Staged planes read each value of a plane once per tile, but wait at two
@@ -98,7 +102,6 @@ int32_t plane_variant(const Tables& t, int32_t variant) {
     // actions to a residual: up to 46 k tiles those gain 2 to 5 % where the
     // residual gains or loses 2 %.  Below about 200 tiles both take their
     // launch: 32^3 6.0 / 6.2 and 6.4 / 6.8.
-    constexpr int64_t kFewTiles = 200, kManyTiles = 12000, kManyRefined = 50000;
     const int64_t n = plane_runs(t);
     int64_t wide = 0;
     for (const PatchInfo& p : t.patches)
@@ -112,19 +115,15 @@ int32_t default_zchunk(const Tables& t, int32_t b, int32_t variant) {
         // Staged planes: a tile's planes are a serial chain of about 1.8 us
         // each (stage, barrier, faces, barrier), while every tile stages its
         // first plane and evaluates its lowest z face once more than a longer
-        // one would.  So the chunk is the shortest power of two that leaves
-        // the launch at most about ten workgroups per CU (256 CUs), up to 16.
-        // Measured residual and Jacobian action at the chunk chosen and at
-        // 16, us: 16^3 6 and 28, 32^3 6 and 29; 64^3 8 and 28; six ragged
-        // boxes of 0.75 M cells (2) 16 / 23 and 32 / 40; 128^3 (4) 35 / 53
-        // and 42 / 58; 160^3 (8) 72 / 110 and 77 / 111; 51 patches of 1.1 M
-        // cells (2) 47 / 76 and 65 / 93; 20 M cells (16) 291 / 366 against
-        // 311 / 418 at 4.
-        constexpr int64_t kMostTiles = 2700;
+        // one would.  Small grids (see plane_variant) take one plane: residual
+        // of 16^3 6 us, at 16 planes 28; 32^3 6 and 29.  Large ones take enough
+        // to amortise the first plane.  Residual and Jacobian action at 4, 8
+        // and 16 planes, us: 14 000 one-plane tiles 49 / 70, 48 / 67 and 54 /
+        // 71; 20 000 72 / 104, 67 / 94 and 69 / 96; 78 000 274 / 383, 271 / 341
+        // and 279 / 329.
+        constexpr int64_t kLongTiles = 21600;
         const int64_t n = plane_runs(t);
-        int32_t kc = 1;
-        while (kc < 16 && n > kMostTiles * kc) kc *= 2;
-        return kc;
+        return n < kFewTiles ? 1 : (n <= kLongTiles ? 8 : 16);
     }
     if (variant == 2) {
         // Wave runs: the same trade with a shorter chain (0.5 us a plane, no
@@ -157,8 +156,7 @@ int32_t default_run(int32_t variant) {
 bool patch_planes(const PatchInfo& p, int32_t b, int32_t kc, int32_t run, int32_t variant,
                   std::vector<STile>& out) {
     const int32_t max_span = variant == 3 ? kStageLen : 0;
-    const int32_t plane = variant == 2 ? (p.n[0] + 1) * ((p.n[1] + kWaveRows - 1) / kWaveRows)
-                                       : p.n[0] * p.n[1];
+    const int32_t plane = (p.n[0] + (variant == 2 ? 1 : 0)) * p.n[1];
     const int32_t ch = std::max(1, kc);
     // a tile's cells are owned one per thread of a 256-thread workgroup
     if (run <= 0 || run > default_run(variant)) return false;

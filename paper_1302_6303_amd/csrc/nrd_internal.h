@@ -181,9 +181,8 @@ constexpr int32_t kBottomBand = 26;
 constexpr int32_t kStageCells = 256;
 constexpr int32_t kStageLen = 512;
 // Wave-run stencil tiles: entries of a plane (a row's cells and the ghost
-// after them, kWaveRows rows each) per tile, 63 of each wavefront.
+// after them) per tile, 63 of each wavefront.
 constexpr int32_t kWaveRun = 4 * 63;
-constexpr int32_t kWaveRows = 1;
 
 // The kernel that runs the configured stencil variant (staged planes give way
 // to wave runs by a rule on sizes).

@@ -261,17 +261,15 @@ __global__ __launch_bounds__(kBlock) void k_stencil_z(
 
 // Wave-run variant.  A tile is a run of entries of one z-plane and a range of
 // planes.  An entry is a place on a row's nx cells and the ghost after them (x
-// fastest), and R rows of it: lane l evaluates its low x faces, the high ones
-// are lane l + 1's (cross-lane shuffle; the ghost's entry only serves the last
-// cell, lane 63 only lane 62: a wavefront owns 63 entries).  Between the R rows
-// a y face serves both; the z face is carried to the next plane.  No barrier,
-// nothing staged: a wavefront waits for one round of loads per plane, all of
-// them issued before the first face.  Bound by instruction issue in the cache
-// (128^3 Jacobian action 45 us, 68% of the issue slots; staged planes 54 us) and by the second
-// reads of neighbours beyond it.  R = 2 evaluates 3.5 faces per cell instead
-// of 4 but halves the wavefronts: 128^3 52 us, 160^3 the same 85.
-template <int MODE, int R>
-__global__ __launch_bounds__(kBlock, R == 1 ? 4 : 1) void k_stencil_w(
+// fastest): lane l evaluates its low x face, the high one is lane l + 1's
+// (cross-lane shuffle; the ghost's entry only serves the last cell, lane 63
+// only lane 62: a wavefront owns 63 entries).  The z face is carried to the next
+// plane.  No barrier, nothing staged: a wavefront waits for one round of loads
+// per plane, all of them issued before the first face.  Bound by instruction
+// issue in the cache (128^3 Jacobian action 45 us, 68% of the issue slots; staged
+// planes 54 us) and by the second reads of neighbours beyond it.
+template <int MODE>
+__global__ __launch_bounds__(kBlock, 4) void k_stencil_w(
     const STile* __restrict__ tiles, int t0, const int32_t* __restrict__ map,
     const PatchInfo* __restrict__ P,
     const ProbScalars* __restrict__ ps, const int32_t* __restrict__ active,
@@ -287,9 +285,8 @@ __global__ __launch_bounds__(kBlock, R == 1 ? 4 : 1) void k_stencil_w(
     const int lane = threadIdx.x & 63;
     const int pos = (threadIdx.x >> 6) * 63 + lane;        // within the tile's run
     const int nx = p.n[0], ny = p.n[1], nz = p.n[2];
-    const int last = (nx + 1) * ((ny + R - 1) / R) - 1;    // entries beyond repeat it
-    const int lin = min(t.s0 + pos, last);
-    const int i = lin % (nx + 1), j = (lin / (nx + 1)) * R;
+    const int lin = min(t.s0 + pos, (nx + 1) * ny - 1);    // entries beyond repeat the last
+    const int i = lin % (nx + 1), j = lin / (nx + 1);
     const bool mine = lane < 63 && pos < t.cnt && i < nx;
     const int sy = p.sy, sz = p.sz;
     const bool use_ct = p.flags & PF_CTYPE;
@@ -311,11 +308,9 @@ __global__ __launch_bounds__(kBlock, R == 1 ? 4 : 1) void k_stencil_w(
     auto ld = [](const double* x, int64_t o, uint32_t e) {
         return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(x + o) + e * 8u);
     };
-    // plane offsets of the rows j - 1 .. j + R (a last odd row's group repeats
-    // the ghost row)
-    uint32_t row[R + 2];
+    uint32_t row[3];                                       // plane offsets of rows j - 1 .. j + 1
 #pragma unroll
-    for (int r = 0; r < R + 2; ++r) row[r] = (i + 1) + sy * min(j + r, ny + 1);
+    for (int r = 0; r < 3; ++r) row[r] = (i + 1) + sy * (j + r);
     auto face = [&](const double* a, const double* c, double h, double ih, double& fe,
                     double& ft) {
         if constexpr (MODE == 0)
@@ -329,113 +324,95 @@ __global__ __launch_bounds__(kBlock, R == 1 ? 4 : 1) void k_stencil_w(
                                MODE ? c[NA - 1] : 0.0);
     };
     int64_t base = p.off + (int64_t)sz * (t.k0 + 1);       // the plane's first entry
-    double own[R][NA];                                     // the entry's cells, plane k
-    double czE[R], czT[R];                                 // their low z fluxes
+    double own[NA];                                        // the entry's cell, plane k
+    double czE = 0.0, czT = 0.0;                           // its low z fluxes
     {
-        double below[R][NA];
+        double below[NA];
 #pragma unroll
-        for (int r = 0; r < R; ++r)
-#pragma unroll
-            for (int a = 0; a < NA; ++a) {
-                own[r][a] = ld(src[a], base, row[r + 1]);
-                below[r][a] = ld(src[a], base - sz, row[r + 1]);
-            }
+        for (int a = 0; a < NA; ++a) {
+            own[a] = ld(src[a], base, row[1]);
+            below[a] = ld(src[a], base - sz, row[1]);
+        }
         const bool edge = t.k0 == 0 && zlo_p;              // uniform
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            czE[r] = czT[r] = 0.0;
-            if (!edge)
-                face(below[r], own[r], hz, ihz, czE[r], czT[r]);
-            else if ((p.robin >> 4) & 1)
-                czE[r] = -robin(own[r], 4, hz);
+        face(below, own, hz, ihz, czE, czT);
+        if (edge) {
+            czE = czT = 0.0;
+            if ((p.robin >> 4) & 1) czE = -robin(own, 4, hz);
         }
     }
     for (int k = t.k0; k < t.k1; ++k, base += sz) {
         // every load of the plane first
-        double next[R][NA], west[R][NA], south[NA], north[NA], bE[R] = {}, bT[R] = {};
-        int ct[R] = {};
+        double next[NA], west[NA], south[NA], north[NA], bE = 0.0, bT = 0.0;
+        int ct = 0;
 #pragma unroll
         for (int a = 0; a < NA; ++a) {
             south[a] = ld(src[a], base, row[0]);
-            north[a] = ld(src[a], base, row[R + 1]);
-#pragma unroll
-            for (int r = 0; r < R; ++r) {
-                west[r][a] = ld(src[a], base - 1, row[r + 1]);
-                next[r][a] = ld(src[a], base + sz, row[r + 1]);
-            }
+            north[a] = ld(src[a], base, row[2]);
+            west[a] = ld(src[a], base - 1, row[1]);
+            next[a] = ld(src[a], base + sz, row[1]);
         }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (MODE == 0) {
-                bE[r] = ld(b, base, row[r + 1]);
-                bT[r] = ld(b + nl, base, row[r + 1]);
-            }
-            if (use_ct) ct[r] = ctype[base + row[r + 1]];
+        if (MODE == 0) {
+            bE = ld(b, base, row[1]);
+            bT = ld(b + nl, base, row[1]);
         }
-        // y faces: low one of the first row, between rows, high one of the last
-        double yE[R + 1], yT[R + 1];
-        face(south, own[0], hy, ihy, yE[0], yT[0]);
-#pragma unroll
-        for (int r = 1; r < R; ++r) face(own[r - 1], own[r], hy, ihy, yE[r], yT[r]);
-        face(own[R - 1], north, hy, ihy, yE[R], yT[R]);
+        if (use_ct) ct = ctype[base + row[1]];
+        double yE[2], yT[2];
+        face(south, own, hy, ihy, yE[0], yT[0]);
+        face(own, north, hy, ihy, yE[1], yT[1]);
         if (ylo_p) {
             yE[0] = yT[0] = 0.0;
-            if ((p.robin >> 2) & 1) yE[0] = -robin(own[0], 2, hy);
+            if ((p.robin >> 2) & 1) yE[0] = -robin(own, 2, hy);
+        }
+        const bool yhi_p = ((p.phys >> 3) & 1) && j == ny - 1;
+        double lxE, lxT, hzE = 0.0, hzT = 0.0;
+        face(west, own, hx, ihx, lxE, lxT);
+        face(own, next, hz, ihz, hzE, hzT);
+        if (k == nz - 1 && zhi_p) {                        // uniform
+            hzE = hzT = 0.0;
+            if ((p.robin >> 5) & 1) hzE = robin(own, 5, hz);
+        }
+        if (xlo_p) {
+            lxE = lxT = 0.0;
+            if (p.robin & 1) lxE = -robin(own, 0, hx);
+        }
+        // high x face of lane l = low x face of lane l + 1
+        double hxE = __shfl_down(lxE, 1, 64);
+        double hxT = __shfl_down(lxT, 1, 64);
+        if (xhi_p) {
+            hxE = hxT = 0.0;
+            if ((p.robin >> 1) & 1) hxE = robin(own, 1, hx);
+        }
+        double lyE = yE[0], lyT = yT[0], hyE = yE[1], hyT = yT[1];
+        if (yhi_p) {
+            hyE = hyT = 0.0;
+            if ((p.robin >> 3) & 1) hyE = robin(own, 3, hy);
+        }
+        double lzE = czE, lzT = czT;
+        czE = hzE;
+        czT = hzT;
+        if (use_ct) {                                      // uniform
+            if (ct & (1 << 1)) lxE = lxT = 0.0;
+            if (ct & (1 << 2)) hxE = hxT = 0.0;
+            if (ct & (1 << 3)) lyE = lyT = 0.0;
+            if (ct & (1 << 4)) hyE = hyT = 0.0;
+            if (ct & (1 << 5)) lzE = lzT = 0.0;
+            if (ct & (1 << 6)) hzE = hzT = 0.0;
+        }
+        const double divE = (hxE - lxE) * ihx + (hyE - lyE) * ihy + (hzE - lzE) * ihz;
+        const double divT = (hxT - lxT) * ihx + (hyT - lyT) * ihy + (hzT - lzT) * ihz;
+        double oE, oT;
+        if (MODE == 0)
+            cell_out0(q, own[0], own[1], own[2], bE, bT, divE, divT, oE, oT);
+        else
+            cell_out1(q, own[0], own[1], own[2], own[NA - 2], own[NA - 1], divE, divT, oE, oT);
+        if (mine) {
+            const int64_t c = base + row[1];
+            const bool covered = ct & CT_COVERED;
+            out[c] = covered ? 0.0 : oE;
+            out[c + nl] = covered ? 0.0 : oT;
         }
 #pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const bool yhi_p = ((p.phys >> 3) & 1) && j + r == ny - 1;
-            double lxE, lxT, hzE = 0.0, hzT = 0.0;
-            face(west[r], own[r], hx, ihx, lxE, lxT);
-            if (k == nz - 1 && zhi_p) {                    // uniform
-                if ((p.robin >> 5) & 1) hzE = robin(own[r], 5, hz);
-            } else {
-                face(own[r], next[r], hz, ihz, hzE, hzT);
-            }
-            if (xlo_p) {
-                lxE = lxT = 0.0;
-                if (p.robin & 1) lxE = -robin(own[r], 0, hx);
-            }
-            // high x face of lane l = low x face of lane l + 1
-            double hxE = __shfl_down(lxE, 1, 64);
-            double hxT = __shfl_down(lxT, 1, 64);
-            if (xhi_p) {
-                hxE = hxT = 0.0;
-                if ((p.robin >> 1) & 1) hxE = robin(own[r], 1, hx);
-            }
-            double lyE = yE[r], lyT = yT[r], hyE = yE[r + 1], hyT = yT[r + 1];
-            if (yhi_p) {
-                hyE = hyT = 0.0;
-                if ((p.robin >> 3) & 1) hyE = robin(own[r], 3, hy);
-            }
-            double lzE = czE[r], lzT = czT[r];
-            czE[r] = hzE;
-            czT[r] = hzT;
-            if (use_ct) {                                  // uniform
-                if (ct[r] & (1 << 1)) lxE = lxT = 0.0;
-                if (ct[r] & (1 << 2)) hxE = hxT = 0.0;
-                if (ct[r] & (1 << 3)) lyE = lyT = 0.0;
-                if (ct[r] & (1 << 4)) hyE = hyT = 0.0;
-                if (ct[r] & (1 << 5)) lzE = lzT = 0.0;
-                if (ct[r] & (1 << 6)) hzE = hzT = 0.0;
-            }
-            const double divE = (hxE - lxE) * ihx + (hyE - lyE) * ihy + (hzE - lzE) * ihz;
-            const double divT = (hxT - lxT) * ihx + (hyT - lyT) * ihy + (hzT - lzT) * ihz;
-            double oE, oT;
-            if (MODE == 0)
-                cell_out0(q, own[r][0], own[r][1], own[r][2], bE[r], bT[r], divE, divT, oE, oT);
-            else
-                cell_out1(q, own[r][0], own[r][1], own[r][2], own[r][NA - 2], own[r][NA - 1],
-                          divE, divT, oE, oT);
-            if (mine && j + r < ny) {
-                const int64_t c = base + row[r + 1];
-                const bool covered = ct[r] & CT_COVERED;
-                out[c] = covered ? 0.0 : oE;
-                out[c + nl] = covered ? 0.0 : oT;
-            }
-#pragma unroll
-            for (int a = 0; a < NA; ++a) own[r][a] = next[r][a];
-        }
+        for (int a = 0; a < NA; ++a) own[a] = next[a];
     }
 }
 
@@ -819,7 +796,7 @@ static void residual_launch(const Dev& D, hipStream_t s, int t0, int nt, const i
         k_stencil_z<0><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, nullptr, D.z3, b, F, D.nl);
     else if (D.bricks == 2)
-        k_stencil_w<0, kWaveRows><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
+        k_stencil_w<0><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, nullptr, D.z3, b, F, D.nl);
     else
         k_stencil_flat<0><<<nt, kBlock, 0, s>>>(D.tiles, t0, map, D.patches, D.ps, D.active,
@@ -835,7 +812,7 @@ static void jvp_launch(const Dev& D, hipStream_t s, int t0, int nt, const int32_
         k_stencil_z<1><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, v, D.z3, nullptr, Jv, D.nl);
     else if (D.bricks == 2)
-        k_stencil_w<1, kWaveRows><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
+        k_stencil_w<1><<<nt, kBlock, 0, s>>>(D.stiles, t0, map, D.patches, D.ps, D.active,
                                              D.ctype, u, v, D.z3, nullptr, Jv, D.nl);
     else
         k_stencil_flat<1><<<nt, kBlock, 0, s>>>(D.tiles, t0, map, D.patches, D.ps, D.active,
