@@ -108,7 +108,10 @@ static_assert(kSetupThreads == kTailThreads, "owners of the cells are the same t
 __device__ __forceinline__ void invert(const double* A, double (*col)[2][kBottomMax], int N,
                                        double* Xi) {
     const int ld = (N + 3) >> 2, tid = threadIdx.x;
-    if ((tid & ~63) >= ld * ld) return;              // wavefronts without a tile
+    // Wavefronts without a tile leave whole; the barriers below are passed by the
+    // others alone (s_barrier waits for the wavefronts of the workgroup that have
+    // not ended).
+    if ((tid & ~63) >= ld * ld) return;
     const int tr = tid / ld, tc = tid - tr * ld;
     const int r0 = 4 * tr, c0 = 4 * tc;
     const bool on = tr < ld;
@@ -189,9 +192,6 @@ __device__ __forceinline__ void invert(const double* A, double (*col)[2][kBottom
                 if (r0 + i < N && c0 + j < N) Xi[(r0 + i) * N + c0 + j] = -a[i][j];
 }
 
-__device__ __forceinline__ float reciprocal(float x) { return 1.0f / x; }
-__device__ __forceinline__ double reciprocal(double x) { return rcp_nr(x); }
-
 // One grid of a tail, one field, held by the workgroup: every thread owns up
 // to C cells of each colour and keeps their level operator (beta D / h^2 of
 // the six faces, 0 on physical ones; the diagonal with its Marshak terms) and
@@ -268,7 +268,7 @@ struct TailGrid {
                 }
 #pragma unroll
                 for (int f = 0; f < 6; ++f) op[(col * 7 + f) * half + q] = v[f];
-                op[(col * 7 + 6) * half + q] = reciprocal(s);
+                op[(col * 7 + 6) * half + q] = PT(1) / s;
             }
         }
     }
@@ -509,7 +509,11 @@ __global__ __launch_bounds__(kSetupThreads) void k_tail_setup(
 // and 19.3 when every cycle formed the operator from the coefficients anew, 13.9
 // and 23.1 when it also waited for each of them), of the 64 problems of an
 // ensemble 14.3 us, where the 13 launches it replaces took about 58 and 75 us
-// in float.
+// in float.  A cell is relaxed by the stored reciprocal of its diagonal: a
+// division here costs 2 us of a 96^3 preconditioner's 182 and leaves the cycle's
+// error in single precision where it is (16^3 to 64^3 against float64: 8.04e-8 to
+// 1.217e-7 either way, equal to three digits, and with one division per cell on
+// every grid and no grid in one workgroup 8.07e-8 to 1.218e-7).
 template <typename PT>
 __global__ __launch_bounds__(kTailThreads) void k_mg_tail(
     const int32_t* __restrict__ act, const TailEntry* __restrict__ tails, const TailGrids<PT> G,
