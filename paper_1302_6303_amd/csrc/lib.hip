@@ -2087,6 +2087,7 @@ nrd_status nrd_precond_setup(nrd_hierarchy* h, double* u) {
 nrd_status nrd_precond_apply(nrd_hierarchy* h, const double* w, double* y) {
     NEED_BOUND(h);
     if (!h->step_ready) return fail(NRD_ESTATE, "call nrd_begin_step first");
+    if (!w || !y) return fail(NRD_EINVAL, "NULL argument");   // (w NULL means something inside)
     h->D.active = nullptr;
     pc_apply(h, w, y, nullptr, true);
     HIPCHK(hipGetLastError());

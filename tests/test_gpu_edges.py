@@ -246,3 +246,14 @@ def test_every_chunk_of_the_size_rule_keeps_every_value(nprob, other):
         outs.append((compact_from_native(H, F), compact_from_native(H, Jv)))
     np.testing.assert_array_equal(outs[0][0], outs[1][0])
     np.testing.assert_array_equal(outs[0][1], outs[1][1])
+
+
+def test_precond_apply_needs_its_vectors():
+    """The solver's own calls leave the input in place and pass none; a caller
+    without one is refused rather than given the last call's."""
+    from paper_1302_6303_amd import nrd
+    H = make(_box((8, 8, 8)), gmres_restart=2)
+    H.begin_step([1e-3])
+    y = H.native()
+    for w, out in ((None, y.data_ptr()), (y.data_ptr(), None)):
+        assert nrd.nrd_precond_apply(H.h, w, out) == nrd.NRD_EINVAL
