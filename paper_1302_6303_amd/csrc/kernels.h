@@ -222,7 +222,6 @@ struct PutArgs {
 void put(hipStream_t s, const PutArgs<kPutSmall>& a);
 void put(hipStream_t s, const PutArgs<kPutLarge>& a);
 void fill_native(hipStream_t s, double* x, int64_t n, double v);
-void fill_native_f(hipStream_t s, float* x, int64_t n, float v);
 void pack(const Dev& D, hipStream_t s, const int64_t* coff, const double* native,
           double* compact, int nf, int64_t ncells);
 void unpack(const Dev& D, hipStream_t s, const int64_t* coff,

@@ -252,6 +252,9 @@ __device__ __forceinline__ void level_terms(const PatchInfo& p, const int id[3],
                                    : ef[SPLIT ? enb[fc] : (s ? c + st[d] : c - st[d])];
                 const bool open = !(ph[fc] || cf[fc]);
                 dg += open ? a : (cf[fc] ? PT(2.0 / 3.0) * a : PT(0));
+                // (behind a closed face en is a ghost slot that nothing writes:
+                // it holds the 0 that the workspace is cleared to.  A select
+                // of the sum itself, 185 us instead of 183 at 96^3)
                 ns = fma_t(open ? a : PT(0), en, ns);
             }
         }

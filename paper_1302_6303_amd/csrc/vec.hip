@@ -937,16 +937,17 @@ __global__ __launch_bounds__(kBlock) void k_put(const PutArgs<W> a) {
 void put(hipStream_t s, const PutArgs<kPutSmall>& a) { k_put<kPutSmall><<<1, kBlock, 0, s>>>(a); }
 void put(hipStream_t s, const PutArgs<kPutLarge>& a) { k_put<kPutLarge><<<1, kBlock, 0, s>>>(a); }
 
-template <typename T>
-__global__ __launch_bounds__(kBlock) void k_fill(T* __restrict__ x, int64_t n, T v) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = v;
+// (n may be a whole workspace: a grid holds fewer than 2^32 threads, and a
+// launch of more starts only what is left modulo 2^32, without an error)
+__global__ __launch_bounds__(kBlock) void k_fill(double* __restrict__ x, int64_t n, double v) {
+    for (int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x; i < n;
+         i += (int64_t)gridDim.x * kBlock)
+        x[i] = v;
 }
 void fill_native(hipStream_t s, double* x, int64_t n, double v) {
-    if (n > 0) k_fill<double><<<nblocks(n), kBlock, 0, s>>>(x, n, v);
-}
-void fill_native_f(hipStream_t s, float* x, int64_t n, float v) {
-    if (n > 0) k_fill<float><<<nblocks(n), kBlock, 0, s>>>(x, n, v);
+    constexpr int64_t kMostBlocks = 1 << 16;
+    const int64_t nb = (n + kBlock - 1) / kBlock;
+    if (n > 0) k_fill<<<(int)std::min(nb, kMostBlocks), kBlock, 0, s>>>(x, n, v);
 }
 
 __global__ __launch_bounds__(kBlock) void k_pack(const Tile* __restrict__ vt,

@@ -257,3 +257,42 @@ def test_precond_apply_needs_its_vectors():
     y = H.native()
     for w, out in ((None, y.data_ptr()), (y.data_ptr(), None)):
         assert nrd.nrd_precond_apply(H.h, w, out) == nrd.NRD_EINVAL
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("opt", [dict(), dict(fac_cycle=1), dict(fac_smoother=1),
+                                 dict(fac_smoother=2), dict(fac_base=1)])
+def test_workspaces_of_more_than_2_to_32_values(monkeypatch, opt, precision):
+    """A workspace of 34.4 GB full of NaN and -1 (adjoint slots of a small
+    refined hierarchy) is cleared as a small one is: ghost slots that nothing
+    fills, and the counters of the sums.  Operators, preconditioner and a
+    step, bit for bit those of a small clean workspace."""
+    import torch
+    w = I.static_amr(base=16, nlevels=3, side=(8, 16), state="front")
+    plain = torch.empty
+    rng = np.random.default_rng(5)
+    n = w.ncells()
+    v = rng.standard_normal(2 * n)
+    u = np.concatenate([w.compact(w.E), w.compact(w.T)]) * rng.uniform(0.9, 1.1, 2 * n)
+
+    def outputs(**more):
+        H = make(w, precision=precision, **opt, **more)
+        H.begin_step([1e-3])
+        un = native_from_compact(H, u)
+        out = [compact_from_native(H, H.residual(un, H.native())),
+               compact_from_native(H, H.jvp(un, native_from_compact(H, v), H.native()))]
+        H.precond_setup(un)
+        out.append(compact_from_native(H, H.precond_apply(native_from_compact(H, v), H.native())))
+        H.implicit_step([1e-4])
+        out += [x.cpu().numpy() for x in H.get_fields()]
+        return out, H.native_len, H.workspace_bytes
+
+    want, nl, small = outputs()
+    slots = -(-(8 * 2 ** 32 - small) // (16 * nl)) + 1
+    monkeypatch.setattr(torch, "empty", lambda *a, **k: plain(*a, **k).fill_(255)
+                        if k.get("dtype") == torch.uint8 else plain(*a, **k))
+    got, _, large = outputs(adjoint_slots=slots)
+    torch.cuda.empty_cache()
+    assert large > 8 * 2 ** 32
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a, b)
