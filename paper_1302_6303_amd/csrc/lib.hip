@@ -2243,6 +2243,10 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
     } else {
         for (int kc : {2, 4, 8, 16}) cand.push_back({kc, run0});
     }
+    // One and two planes are tried where the default takes fewer than four:
+    // 128^3 with three refined levels (2187 box shapes, the residual 0.75 ms)
+    // would be tuned in 36 s with them and is in 21 without, to the same time.
+    const bool thin = var >= 2 && default_zchunk(t, 0, var) < 4;
     std::map<ClassKey, std::vector<int32_t>> cls;
     for (int b = 0; b < t.nbox; ++b) {
         ClassKey k;
@@ -2334,6 +2338,7 @@ nrd_status nrd_autotune(nrd_hierarchy* h, const char* cache_path, int32_t* timed
         double best = cur_ms;
         for (auto [ckc, crun] : cand) {
             if (ckc == choice.first && crun == choice.second) continue;
+            if (var >= 2 && !thin && ckc < 4) continue;
             std::vector<int32_t> kc2 = kc, run2 = run;
             for (int b : kv.second) {
                 kc2[b] = ckc;

@@ -1,7 +1,10 @@
 """Edges of the solver's ranges: overflow and NaN, cycles other than V(1,1),
 hundreds of problems, the tile tuner's cache."""
+import time
+
 import numpy as np
 import pytest
+import torch
 
 from oracle import precond as pc
 from paper_1302_6303_amd import inputs as I
@@ -87,6 +90,34 @@ def test_tuned_shapes_are_kept_per_kernel(tmp_path):
     cache = str(tmp_path / "tiles.txt")
     few, many = _grid([(16, 16, 16)], []), _grid([(16, 16, 16)] * 13, [])
     assert [make(w).autotune(cache) for w in (few, many, few, many)] == [1, 1, 0, 0]
+
+
+def test_large_hierarchies_are_tuned_in_few_launches():
+    """Eight shapes of 96 and 128 cells (16 planes by default, so three other
+    plane counts are tried): 12 launches for each of them and the lists of their
+    tiles, together the time of 17.5; with the counts of small grids 20 and 27."""
+    exts = [(96 + 32 * (s & 1), 96 + 16 * (s & 2), 96 + 8 * (s & 4)) for s in range(8)]
+    w = _grid(exts, [])
+    H = make(w)
+    H.begin_step([1e-4] * 8)
+    u, F = native_from_compact(H, np.concatenate([np.concatenate([x.ravel(order="F") for x in f])
+                                                  for f in (w.E, w.T)])), H.native()
+    t0, t1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    with torch.cuda.stream(H.stream):
+        H.residual(u, F)
+        t0.record()
+        for _ in range(20):
+            H.residual(u, F)
+        t1.record()
+    torch.cuda.synchronize()
+    each = 1e-3 * t0.elapsed_time(t1) / 20
+    tune = []
+    for _ in range(3):
+        start = time.perf_counter()
+        assert H.autotune(None) == 8
+        tune.append(time.perf_counter() - start)
+    print(f"residual {1e6 * each:.0f} us, tuned in {1e3 * min(tune):.1f} ms")
+    assert min(tune) < 8 * 22 * each
 
 
 def test_steps_of_hundreds_of_problems():
