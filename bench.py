@@ -75,10 +75,10 @@ HBM_PEAK_GBS = 8000.0
 # the factor a plain 2 GiB copy reads in the same run, WRITE by its own
 # factor; the 20 full launches timed after the steps), valid for the stencil
 # source with this SHA-256 prefix; null otherwise.
-MEASURED_TRAFFIC = {"workload": "ensemble", "stencil_sha256": "66ce56210b6335b8",
-                    "bytes_per_cell": 63.3620,
-                    "fetch_bytes_per_cell": 46.7650,
-                    "write_bytes_per_cell": 16.5970,
+MEASURED_TRAFFIC = {"workload": "ensemble", "stencil_sha256": "9cf7c4cd43980537",
+                    "bytes_per_cell": 62.5222,
+                    "fetch_bytes_per_cell": 45.9251,
+                    "write_bytes_per_cell": 16.5971,
                     "fetch_scale": 2.0, "write_scale": 1.0}
 
 
