@@ -19,8 +19,8 @@ def _box(ext, seed=3):
     return I.Workload("box", [prob], boxes, z, E, T, np.array([1e-3]), 1)
 
 
-# plane runs of 256 cells times planes: 24, 1152 (one plane per tile),
-# 3456 (two), 8192 (four)
+# plane runs of 256 cells times planes: 24 (staged planes, one per tile), 1152
+# (wave runs, one plane), 3456 and 8192 (wave runs, four)
 @pytest.mark.parametrize("ext", [(12, 12, 24), (96, 64, 48), (96, 96, 96), (128, 128, 128)])
 def test_plane_chunk_of_the_size_rule_keeps_every_value(ext):
     """The default chunk gives bit for bit the values of 16-plane chunks."""
